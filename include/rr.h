@@ -114,11 +114,13 @@ typedef struct {
                           h = (x1-x0)/(nx+1), (y1-y0)/(ny+1))                     */
 } rr_problem;
 
-/* Tuning knobs; pass NULL to rr_factor for defaults (or the autotuner's pick). */
+/* Tuning knobs; pass NULL to rr_factor for defaults (or the autotuner's pick).
+ * The LU is taken in nested-dissection order of the grid by default; tile and
+ * grid shape only the band LU, which superblock != 0 or GMRES-IR asks for. */
 typedef struct {
   int32_t tile;          /* band tile edge T: 32 or 64 (default 64)             */
-  int32_t grid;          /* persistent workgroups of the factorisation; 0 = 2
-                            per CU (the solves use at least 2 per CU)          */
+  int32_t grid;          /* persistent workgroups of the band factorisation;
+                            0 = 2 per CU (the solves use at least 2 per CU)    */
   int32_t refine_iters;  /* mixed only: most corrections per solve (default 6,
                             at most 16).  The launches are fixed (graph-safe)
                             but skip their work on the device once every
@@ -152,18 +154,24 @@ typedef struct {
                             Each GMRES-IR correction costs gmres_restart + 1
                             FP32 solves and holds gmres_restart + 2 more
                             blocks of n_omega*k_max*n complex FP64 (not
-                            counted by rr_factor_bytes)                        */
+                            counted by rr_factor_bytes).  The FP32 LU is then
+                            the band LU: as a preconditioner at such shifts it
+                            has to be backward stable                          */
   int32_t gmres_restart; /* steps per GMRES-IR correction, 1 .. 16 (default 8) */
-  int32_t superblock;    /* block rows (tiles) a solve step takes at once: the
-                            sweeps of every solve walk superblocks of this many
-                            block rows, x_S = D_S^-1 (b_S - sum T x), with the
-                            inverses D_S^-1 of the superblocks' diagonal blocks
-                            formed after each factorisation.  1 .. 8; 0 = the
-                            default (256 rows per step, at most the half-band's
-                            tiles); negative = one block row per step (the
-                            tile-by-tile recurrence with chain tiles)          */
-  int32_t solver;        /* RR_SOLVER_BAND_LU (default): the band LU of
-                            M(omega) serves every solve (Section 3.1).
+  int32_t superblock;    /* 0 = the LU in nested-dissection order (for a
+                            GMRES-IR handle the band LU with 256 rows per
+                            step, at most the half-band's tiles).  1 .. 8 =
+                            the band LU, and block rows (tiles) a solve step
+                            takes at once: the sweeps of every solve walk
+                            superblocks of this many block rows, x_S = D_S^-1
+                            (b_S - sum T x), with the inverses D_S^-1 of the
+                            superblocks' diagonal blocks formed after each
+                            factorisation.  Negative = the band LU one block
+                            row per step (the tile-by-tile recurrence with
+                            chain tiles)                                       */
+  int32_t solver;        /* RR_SOLVER_BAND_LU (default): one LU of M(omega)
+                            (by nested dissection or of the band, see
+                            superblock) serves every solve (Section 3.1).
                             RR_SOLVER_BICGSTAB / RR_SOLVER_GMRES: no LU at
                             all; every solve of Algorithm 1 is a Krylov
                             iteration with M applied from the stencil and the
@@ -224,7 +232,8 @@ rr_status rr_apply(const rr_problem* p, const double* omega_re, const double* om
                    int32_t n_omega, int32_t k, int32_t adjoint, const double* X, double* Y,
                    void* stream);
 
-/* Factor M(omega_w) = L_w U_w (no pivoting, band kl = ku = 2*ny) for each of
+/* Factor M(omega_w) = L_w U_w (no pivoting; in nested-dissection order, or
+ * the band kl = ku = 2*ny, see rr_tuning.superblock) for each of
  * the n_omega shifts; the factors live in the returned handle, which also
  * takes private copies of coef, phi and U.  k_max bounds the sketch width of
  * later calls (workspaces are sized for it): 1 .. 32 in mixed precision,
@@ -344,12 +353,13 @@ rr_status rr_check(rr_factors* f, void* stream);
 int32_t rr_refine_count(rr_factors* f);
 
 /* Timing hook: HIP events (hipEvent_t, or NULL for none) that later calls on
- * this handle record on their stream right before and right after the band
- * factorisation kernel (rr_factor's and rr_refactor's launch of the first 64
- * shifts; not the flag fill or the superblock inverses) and the main solve
- * launch of every solve call (the first FP32 or FP64 solve of a logical
- * solve, with its two small counter fills, not the refinement corrections),
- * so that one kernel's duration can be measured inside a timed pass.  The
+ * this handle record on their stream right before and right after the
+ * factorisation (nested dissection: all its launches; the band LU: the factor
+ * kernel of rr_factor's and rr_refactor's launch of the first 64 shifts, not
+ * the flag fill or the superblock inverses) and the main solve
+ * of every solve call (the first FP32 or FP64 solve of a logical
+ * solve, with all its launches, not the refinement corrections),
+ * so that their duration can be measured inside a timed pass.  The
  * caller keeps the events alive while they are set; passing NULLs clears
  * them.  Host only; RR_ERR_INVALID for a NULL handle. */
 rr_status rr_set_timing_events(rr_factors* f, void* factor_begin, void* factor_end,
@@ -382,7 +392,8 @@ typedef void (*rr_free_fn)(void* ptr, void* ctx);
 rr_status rr_set_allocator(rr_alloc_fn alloc, rr_free_fn dealloc, void* ctx);
 
 /* Device bytes rr_factor would allocate for these sizes (with phi and U),
- * 0 for invalid sizes; tile 0 means the default.  A sweep too large for the
+ * 0 for invalid sizes; tile 0 means the default LU (nested dissection), a
+ * tile the band LU with that tile and 256 rows per solve step.  A sweep too large for the
  * device is split into chunks of shifts sized with it. */
 size_t rr_factor_bytes(int32_t nx, int32_t ny, int32_t n_omega, int32_t k_max, rr_precision prec,
                        int32_t tile);
@@ -405,10 +416,10 @@ rr_status rr_graph_capture(rr_factors* f, int32_t refactor, int32_t k, uint64_t 
 rr_status rr_graph_launch(rr_graph* g, void* stream);
 void rr_graph_free(rr_graph* g);
 
-/* Autotuner for the band tile, the persistent grid and the solve's
- * superblock: it first tries tile 64 and 32 with one and two workgroups per
- * CU (default superblock), then, for the best of those, superblocks of 2, 4
- * and 8 block rows and the tile-by-tile solve; each candidate builds a trial
+/* Autotuner: it tries the nested-dissection LU (superblock 0), then the band
+ * LU with tile 64 and 32 and one and two workgroups per CU (256 rows per
+ * solve step), then, for the best of those, superblocks of 2, 4 and 8 block
+ * rows and the tile-by-tile solve; each candidate builds a trial
  * handle for this operator and the first max_shifts shifts (all when
  * max_shifts <= 0), runs one warm-up pass and one timed pass of
  * refactorisation, sketch solve and adjoint solve, and is scored factor +
@@ -460,6 +471,18 @@ rr_status rr_precond_apply(rr_factors* f, int32_t k, int32_t adjoint, const doub
  * shift.  Returns the number of tasks (which may exceed cap), or -1 if B or
  * NB is not positive. */
 int64_t rr_factor_schedule(int32_t B, int32_t NB, int32_t* out, int64_t cap);
+
+/* Test hook for the nested-dissection LU (host only, no device call): the plan
+ * of an nx x ny grid as int64 values, written to out[0 .. cap).  what = 0: per
+ * front (the root first) p, q, P, Q, row, bor, childA, childB, baseA, baseB,
+ * urow, the offsets of A, B12, F21, the Schur complement and the temporaries,
+ * and the depth; 1: the unknown of every row (-1: padding); 2: per border
+ * entry 2 * (position in a half's border) + half, or -1; 3: per border entry
+ * its row; 4: the tasks (front, i, j, kind); 5: the totals rows, border
+ * entries, factor elements, Schur arenas (2), temporaries, update rows (2),
+ * tasks.  Returns the number of values (which may exceed cap), or -1 for bad
+ * arguments. */
+int64_t rr_nd_plan(int32_t nx, int32_t ny, int32_t what, int64_t* out, int64_t cap);
 
 #ifdef __cplusplus
 }

@@ -95,6 +95,7 @@ def lib() -> ctypes.CDLL:
         "rr_precond_apply": [vp, i32, i32, vp, vp, vp],
         "rr_factor_bytes": [i32, i32, i32, i32, ctypes.c_int, i32],
         "rr_factor_schedule": [i32, i32, vp, i64],
+        "rr_nd_plan": [i32, i32, i32, vp, i64],
         "rr_set_allocator": [ALLOC_FN, FREE_FN, vp],
         "rr_graph_capture": [vp, i32, i32, u64, i32, ctypes.c_int, vp, vp, vp, vp, vp, vp,
                              ctypes.POINTER(vp)],
@@ -114,6 +115,7 @@ def lib() -> ctypes.CDLL:
     L.rr_graph_free.restype = None
     L.rr_refine_count.restype = ctypes.c_int32
     L.rr_factor_schedule.restype = ctypes.c_int64
+    L.rr_nd_plan.restype = ctypes.c_int64
     _lib = L
     return L
 

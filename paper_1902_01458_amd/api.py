@@ -422,8 +422,8 @@ def sweep(prob: BurgersProblem, omegas, k: int, q: int = 0, seed: int = 0,
     tile = int(tune["tile"]) if tune else 0
     grid = int(tune["grid"]) if tune else 0
     sb = int(tune.get("superblock", 0)) if tune else 0
-    if chunk <= 0:
-        chunk = _chunk_size(prob, k, precision, tile, memory_fraction, om.size)
+    if chunk <= 0:  # rr_factor_bytes: tile 0 is the default LU's size, a tile the band LU's
+        chunk = _chunk_size(prob, k, precision, tile if sb else 0, memory_fraction, om.size)
     sB = torch.empty((om.size, k), dtype=torch.float64, device="cuda")
     sAV = torch.empty((om.size, k), dtype=torch.float64, device="cuda")
     redone = []

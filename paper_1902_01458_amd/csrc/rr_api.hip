@@ -81,7 +81,10 @@ void free_all(rr_factors* f) {
                 f->gm.V, f->gm.t, f->gm.H, f->gm.h, f->gm.beta, f->gm.y, f->gm.partial,
                 f->pc_dinv, f->kv[0], f->kv[1], f->kv[2], f->kv[3], f->kv[4], f->kv[5],
                 f->kv[6], f->kpart, f->kscal, f->kbnorm, f->kactive, f->small.big1,
-                f->small.big2, f->wide_tmp, f->probe_b, f->probe_x, f->probe_r, f->probe_z};
+                f->small.big2, f->wide_tmp, f->probe_b, f->probe_x, f->probe_r, f->probe_z,
+                f->ndd.fronts, f->ndd.tasks, f->ndd.pdof, f->ndd.bmap, f->ndd.grow,
+                f->ndd.factor, f->ndd.schur[0], f->ndd.schur[1], f->ndd.temp, f->ndd.w,
+                f->ndd.z, f->ndd.u[0], f->ndd.u[1]};
   for (void* p : ps) {
     if (!p) continue;
     if (f->dealloc) f->dealloc(p, f->alloc_ctx);
@@ -111,6 +114,17 @@ constexpr uint64_t kProbeSeed = 0x70726f6265ull;  // the probes' Philox key
 int probe_cols(int k, int np_max) {
   const int p = std::min(solve_np(k), np_max) - k;
   return p >= kMinProbes ? std::min(p, kMaxProbes) : 0;
+}
+
+// X = M^-1 Bm (adjoint: M^-H Bm) with the handle's LU, k <= kNarrowK columns.
+hipError_t lu_solve(rr_factors* f, int k, bool fp32, int adjoint, const double* Bm,
+                    int64_t bstride, double* X, hipStream_t s, const uint32_t* skip = nullptr) {
+  if (f->nd)
+    return launch_nd_solve(f->ndp, f->ndd, f->n, f->n_omega, k, 0, k, fp32, adjoint, Bm, bstride,
+                           X, s, skip);
+  return launch_solve(f->geom, f->n, f->n_omega, k, fp32, f->tiles, adjoint, Bm, bstride, X,
+                      f->xs, f->cbuf, f->flags, ticket_word(f), st_word(f), f->solve_grid, s,
+                      skip);
 }
 
 // The k x k steps for narrow (k <= 32: LDS-resident) or wide sketches.
@@ -156,13 +170,12 @@ hipError_t gmres_correction(rr_factors* f, int k, int adjoint, double* r, hipStr
   const uint32_t* skip = conv_word(f);
   auto V = [&](int i) { return g.V + 2 * i * vstride; };
   hipError_t e = launch_fill_u32((uint32_t*)g.H, 0u, (int64_t)n_omega * k * (m + 1) * m * 4, s);
-  // the preconditioner: the FP32 band LU (GMRES-IR), or the Krylov handle's K
+  // the preconditioner: the FP32 LU (GMRES-IR), or the Krylov handle's K
   auto solve32 = [&](const double* in, double* out) {
     if (f->solver != RR_SOLVER_BAND_LU)
       return launch_pc_apply(opdesc(f), f->precond, n_omega, k, adjoint, f->pc_dinv, in, out,
                              nullptr, skip, s);
-    return launch_solve(f->geom, f->n, n_omega, k, true, f->tiles, adjoint, in, blk, out, f->xs,
-                        f->cbuf, f->flags, ticket_word(f), st_word(f), f->solve_grid, s, skip);
+    return lu_solve(f, k, true, adjoint, in, blk, out, s, skip);
   };
   if (e == hipSuccess) e = solve32(r, V(0));
   if (e == hipSuccess)
@@ -266,8 +279,13 @@ rr_status solve_any(rr_factors* f, int k, int adjoint, const double* Bm, int64_t
     return st;
   }
   if (k > kNarrowK) {
-    // a wide block (FP64 only): the band solve takes 32 columns at a time,
-    // gathered into and scattered from two narrow blocks
+    // a wide block (FP64 only) takes 32 columns at a time: in place with the
+    // nested-dissection LU, whose solves copy into elimination order anyway;
+    // gathered into and scattered from two narrow blocks with the band LU
+    for (int c0 = 0; f->nd && c0 < k; c0 += kNarrowK)
+      RR_HIP(launch_nd_solve(f->ndp, f->ndd, f->n, f->n_omega, std::min(kNarrowK, k - c0), c0, k,
+                             false, adjoint, Bm, bstride, X, s));
+    if (f->nd) return RR_OK;
     double* nb = f->wide_tmp;
     double* nx = f->wide_tmp + 2 * (size_t)f->n_omega * kNarrowK * f->n;
     for (int c0 = 0; c0 < k; c0 += kNarrowK) {
@@ -309,8 +327,7 @@ rr_status solve_any(rr_factors* f, int k, int adjoint, const double* Bm, int64_t
     res = f->probe_r;
   }
   if (f->tev[2]) RR_HIP(hipEventRecord(f->tev[2], s));
-  RR_HIP(launch_solve(f->geom, f->n, f->n_omega, kk, mixed, f->tiles, adjoint, B1, bs1, X1,
-                      f->xs, f->cbuf, f->flags, ticket_word(f), st_word(f), f->solve_grid, s));
+  RR_HIP(lu_solve(f, kk, mixed, adjoint, B1, bs1, X1, s));
   if (f->tev[3]) RR_HIP(hipEventRecord(f->tev[3], s));
   if (!refine) return RR_OK;
   if (p > 0)
@@ -325,9 +342,7 @@ rr_status solve_any(rr_factors* f, int k, int adjoint, const double* Bm, int64_t
     if (f->gm.m > 0) {
       RR_HIP(gmres_correction(f, k, adjoint, res, s));
     } else {
-      RR_HIP(launch_solve(f->geom, f->n, f->n_omega, kk, true, f->tiles, adjoint, res, pblk, res,
-                          f->xs, f->cbuf, f->flags, ticket_word(f), st_word(f), f->solve_grid, s,
-                          conv_word(f)));
+      RR_HIP(lu_solve(f, kk, true, adjoint, res, pblk, res, s, conv_word(f)));
     }
     RR_HIP(launch_fill_u32(fail_word(f), 0u, 1, s));
     RR_HIP(launch_refine_update(f->n, f->n_omega, k, X1, res, tol, it, adjoint, f->small,
@@ -348,10 +363,15 @@ struct Plan {
   BandGeom geom;
   size_t coef, phi, U, omega, tiles, xs, cbuf, flags, ctrl, theta, vec, work3, partial, kk2, rho,
       shifted, grad, big = 0, wide = 0, probe_blk = 0, probe_z = 0;
+  NdPlan nd;  // the nested-dissection LU's (no band LU then)
+  size_t nd_fronts = 0, nd_tasks = 0, nd_rows = 0, nd_border = 0, nd_factor = 0, nd_schur[2] = {},
+         nd_temp = 0, nd_vec = 0, nd_u[2] = {};
   int nchunk, grad_nchunk, probe_np = 0, probe_p = 0;
-  size_t nflags;
+  size_t nflags = 0;
   size_t total() const {
-    return coef + phi + U + omega + tiles + xs + cbuf + flags + ctrl + theta + 2 * vec + work3 +
+    return nd_fronts + nd_tasks + nd_rows + 2 * nd_border + nd_factor + nd_schur[0] + nd_schur[1] +
+           nd_temp + 2 * nd_vec + nd_u[0] + nd_u[1] +
+           coef + phi + U + omega + tiles + xs + cbuf + flags + ctrl + theta + 2 * vec + work3 +
            partial + 5 * kk2 + rho + shifted + grad + 2 * big + wide + 3 * probe_blk + probe_z;
   }
 };
@@ -365,8 +385,19 @@ int superblock_tiles(int want, int T, int B) {
   return std::max(1, std::min(B, 256 / T));
 }
 
+// Which LU a handle takes: the nested-dissection one, unless the caller asks
+// for a superblock (or, < 0, the tile-by-tile solve), which only the band LU
+// has, or for GMRES-IR.  GMRES-IR serves shifts with kappa(M) eps_32 >> 1,
+// where the FP32 factors are only a preconditioner: there the fronts' explicit
+// inverses are too far from a backward stable LU (at 1e-7 |lambda| from an
+// eigenvalue of a 32 x 16 operator it left 7 of 8 columns unconverged after
+// six corrections; with the band LU two suffice).
+bool use_nd(bool krylov, bool gmres_ir, int superblock) {
+  return !krylov && !gmres_ir && superblock == 0;
+}
+
 Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T, bool has_phi,
-               bool has_U, int sb, bool probes) {
+               bool has_U, int sb, bool probes, bool nd, bool nd_tables) {
   Plan pl{};
   const int64_t n = 2 * (int64_t)nx * ny;
   const size_t nn = (size_t)nx * ny;
@@ -379,13 +410,33 @@ Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T,
   pl.phi = has_phi ? nn * sizeof(double) : 0;
   pl.U = has_U ? (size_t)(nx + 2) * (ny + 2) * sizeof(double) : 0;
   pl.omega = 2 * (size_t)n_omega * sizeof(double);
-  pl.tiles = (size_t)n_omega * pl.geom.tiles_per_omega() * T * T * elem;
   const int kn = std::min(k_max, kNarrowK);  // widest solve launch
-  pl.xs = (size_t)n_omega * pl.geom.NB * T * solve_np(kn) * 2 * sizeof(double);
-  pl.cbuf = (size_t)n_omega * std::max(pl.geom.P, 1) * T * solve_np(kn) * 2 * sizeof(double);
-  pl.nflags = std::max({(size_t)n_omega * pl.geom.tiles_per_omega(), (size_t)n_omega * pl.geom.NB,
-                        (size_t)ssolve_counters(pl.geom, n_omega)});
-  pl.flags = pl.nflags * sizeof(int);
+  if (nd) {
+    nd_make_plan(nx, ny, nd_tables, &pl.nd);
+    const NdPlan& d = pl.nd;
+    const size_t w = n_omega;
+    // a mixed solve runs the probes' columns too
+    const int ks = prec == RR_MIXED && probes ? kn + probe_cols(kn, solve_np(kn)) : kn;
+    pl.nd_fronts = d.fronts.size() * sizeof(NdFront);
+    pl.nd_tasks = (size_t)d.ntasks * sizeof(NdTask);
+    pl.nd_rows = (size_t)d.rows * sizeof(int);
+    pl.nd_border = (size_t)d.border * sizeof(int);
+    pl.nd_factor = w * d.factor * elem;
+    pl.nd_temp = w * d.temp * elem;
+    pl.nd_vec = w * (d.rows + 1) * ks * elem;
+    for (int i = 0; i < 2; i++) {
+      pl.nd_schur[i] = w * d.schur[i] * elem;
+      pl.nd_u[i] = w * d.urows[i] * ks * elem;
+    }
+  } else {
+    pl.tiles = (size_t)n_omega * pl.geom.tiles_per_omega() * T * T * elem;
+    pl.xs = (size_t)n_omega * pl.geom.NB * T * solve_np(kn) * 2 * sizeof(double);
+    pl.cbuf = (size_t)n_omega * std::max(pl.geom.P, 1) * T * solve_np(kn) * 2 * sizeof(double);
+    pl.nflags =
+        std::max({(size_t)n_omega * pl.geom.tiles_per_omega(), (size_t)n_omega * pl.geom.NB,
+                  (size_t)ssolve_counters(pl.geom, n_omega)});
+    pl.flags = pl.nflags * sizeof(int);
+  }
   pl.ctrl = 64 * sizeof(uint32_t);
   pl.theta = (size_t)k_max * n * 2 * sizeof(double);
   pl.vec = (size_t)n_omega * k_max * n * 2 * sizeof(double);
@@ -549,8 +600,18 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
   hipStream_t s = (hipStream_t)stream;
   const size_t nn = (size_t)p->nx * p->ny;
   const bool gmres_ir = prec == RR_MIXED && tune && tune->refine_method == RR_REFINE_GMRES;
-  const Plan pl = make_plan(p->nx, p->ny, n_omega, k_max, prec, T, p->phi != nullptr,
-                            p->U != nullptr, tune ? tune->superblock : 0, !krylov && !gmres_ir);
+  f->nd = use_nd(krylov, gmres_ir, tune ? tune->superblock : 0);
+  if (f->nd) {  // a plan is made on the host: not for what no device holds (16 entries a row at least)
+    size_t free_b = 0, total_b = 0;
+    const double need = 16.0 * n64 * n_omega * (prec == RR_MIXED ? 8 : 16);
+    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need > (double)total_b) {
+      delete f;
+      return fail(RR_ERR_NOMEM, "the LU does not fit in device memory");
+    }
+  }
+  Plan pl = make_plan(p->nx, p->ny, n_omega, k_max, prec, T, p->phi != nullptr, p->U != nullptr,
+                      tune ? tune->superblock : 0, !krylov && !gmres_ir, f->nd, true);
+  f->ndp = std::move(pl.nd);
   f->tile_bytes = pl.tiles;
   rr_status st = RR_OK;
 #define ALLOC(ptr, bytes)                      \
@@ -562,7 +623,21 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
   if (p->phi) ALLOC(f->phi, pl.phi);
   if (p->U) ALLOC(f->U, pl.U);
   ALLOC(f->omega, pl.omega);
-  if (!krylov) {  // the band LU and its dataflow state
+  if (f->nd) {  // the nested-dissection LU
+    ALLOC(f->ndd.fronts, pl.nd_fronts);
+    ALLOC(f->ndd.tasks, pl.nd_tasks);
+    ALLOC(f->ndd.pdof, pl.nd_rows);
+    ALLOC(f->ndd.bmap, pl.nd_border);
+    ALLOC(f->ndd.grow, pl.nd_border);
+    ALLOC(f->ndd.factor, pl.nd_factor);
+    ALLOC(f->ndd.schur[0], pl.nd_schur[0]);
+    ALLOC(f->ndd.schur[1], pl.nd_schur[1]);
+    ALLOC(f->ndd.temp, pl.nd_temp);
+    ALLOC(f->ndd.w, pl.nd_vec);
+    ALLOC(f->ndd.z, pl.nd_vec);
+    ALLOC(f->ndd.u[0], pl.nd_u[0]);
+    ALLOC(f->ndd.u[1], pl.nd_u[1]);
+  } else if (!krylov) {  // the band LU and its dataflow state
     ALLOC(f->tiles, pl.tiles);
     ALLOC(f->xs, pl.xs);
     ALLOC(f->cbuf, pl.cbuf);
@@ -633,6 +708,16 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     if (e == hipSuccess)
       e = hipMemcpyAsync(f->omega, f->omega_host.data(), 2 * n_omega * sizeof(double),
                          hipMemcpyHostToDevice, s);
+    auto upload = [&](void* dst, const void* src, size_t bytes) {
+      if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    };
+    if (f->nd) {  // from host vectors that the handle keeps
+      upload(f->ndd.fronts, f->ndp.fronts.data(), pl.nd_fronts);
+      upload(f->ndd.tasks, f->ndp.tasks.data(), pl.nd_tasks);
+      upload(f->ndd.pdof, f->ndp.pdof.data(), pl.nd_rows);
+      upload(f->ndd.bmap, f->ndp.bmap.data(), pl.nd_border);
+      upload(f->ndd.grow, f->ndp.grow.data(), pl.nd_border);
+    }
     if (e == hipSuccess) e = launch_fill_u32(f->ctrl, 0u, 64, s);
     // the Krylov blocks start finite (their norms are taken on every cycle,
     // also the ones that skip their other work)
@@ -654,8 +739,10 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     f->has_burgers = true;
   }
   {
-    hipError_t e = krylov ? prepare_krylov(p->ny) : prepare_factor(T, prec == RR_MIXED);
-    if (e == hipSuccess && !krylov) e = prepare_solve(T, prec == RR_MIXED);
+    hipError_t e = krylov ? prepare_krylov(p->ny)
+                   : f->nd ? nd_prepare()
+                           : prepare_factor(T, prec == RR_MIXED);
+    if (e == hipSuccess && !krylov && !f->nd) e = prepare_solve(T, prec == RR_MIXED);
     if (e != hipSuccess) {
       st = fail(RR_ERR_HIP, std::string("kernel attributes: ") + hipGetErrorString(e));
       goto fail_free;
@@ -672,9 +759,7 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     hipError_t e = launch_sketch(opdesc(f), nullptr, f->probe_p, kProbeSeed, RR_TM_GAUSSIAN, 0,
                                  f->probe_r, s);
     if (e == hipSuccess)
-      e = launch_solve(f->geom, f->n, n_omega, f->probe_p, true, f->tiles, 0, f->probe_r, 0,
-                       f->probe_z, f->xs, f->cbuf, f->flags, ticket_word(f), st_word(f),
-                       f->solve_grid, s);
+      e = lu_solve(f, f->probe_p, true, 0, f->probe_r, 0, f->probe_z, s);
     if (e != hipSuccess) {
       st = fail(RR_ERR_HIP, hipGetErrorString(e));
       goto fail_free;
@@ -704,9 +789,17 @@ rr_status rr_refactor(rr_factors* f, void* stream) {
     }
     return RR_OK;
   }
-  hipError_t e = launch_factor(opdesc(f), f->geom, f->omega, f->n_omega, f->prec == RR_MIXED,
-                               f->tiles, f->flags, factor_counters(f), st_word(f), f->grid,
-                               (hipStream_t)stream, f->tev);
+  hipError_t e;
+  if (f->nd) {
+    if (f->tev[0]) (void)hipEventRecord(f->tev[0], (hipStream_t)stream);
+    e = launch_nd_factor(opdesc(f), f->ndp, f->ndd, f->omega, f->n_omega, f->prec == RR_MIXED,
+                         st_word(f), (hipStream_t)stream);
+    if (f->tev[1]) (void)hipEventRecord(f->tev[1], (hipStream_t)stream);
+  } else {
+    e = launch_factor(opdesc(f), f->geom, f->omega, f->n_omega, f->prec == RR_MIXED, f->tiles,
+                      f->flags, factor_counters(f), st_word(f), f->grid, (hipStream_t)stream,
+                      f->tev);
+  }
   // a new factor: the refinement's measured contractions no longer hold
   if (e == hipSuccess && f->small.rho)
     e = launch_refine_reset(f->n_omega, f->small.rho, (hipStream_t)stream);
@@ -922,7 +1015,7 @@ rr_status rr_check(rr_factors* f, void* stream) {
   if (w & ST_SINGULAR)
     return fail(RR_ERR_SINGULAR, f->solver != RR_SOLVER_BAND_LU
                                      ? "singular node block in the preconditioner"
-                                     : "zero or non-finite pivot in the band LU");
+                                     : "zero or non-finite pivot in the LU");
   if (w & ST_NONFINITE) return fail(RR_ERR_NONFINITE, "non-finite values in the results");
   if (w & ST_BREAKDOWN)
     return fail(RR_ERR_BREAKDOWN, f->solver == RR_SOLVER_BICGSTAB
@@ -996,7 +1089,7 @@ size_t rr_factor_bytes(int32_t nx, int32_t ny, int32_t n_omega, int32_t k_max, r
   if (k_max > (prec == RR_FP64 ? kMaxWideK : kNarrowK)) return 0;
   const int T = tile ? tile : 64;
   if (T != 32 && T != 64) return 0;
-  return make_plan(nx, ny, n_omega, k_max, prec, T, true, true, 0, true).total();
+  return make_plan(nx, ny, n_omega, k_max, prec, T, true, true, 0, true, tile == 0, false).total();
 }
 
 // ---------------------------------------------------------------------------
@@ -1204,38 +1297,40 @@ rr_status rr_autotune(const rr_problem* p, const double* omega_re, const double*
   rr_status st = RR_OK;
   double best = -1.0;
   rr_tuning pick{};
-  // the tile and the persistent grid with the default superblock, then the
-  // superblock (and the tile-by-tile solve) for that tile and grid
-  const int tiles[2] = {64, 32};
-  const int grids[2] = {cus, 2 * cus};
-  for (int ti = 0; ti < 2 && st == RR_OK; ti++)
-    for (int gi = 0; gi < 2 && st == RR_OK; gi++) {
-      rr_tuning t{};
-      t.tile = tiles[ti];
-      t.grid = grids[gi];
-      double sc = 0;
-      st = trial(t, &sc);
-      if (st == RR_OK && sc >= 0 && (best < 0 || sc < best)) {
-        best = sc;
-        pick = t;
-      }
+  // the nested-dissection LU (superblock 0; its tile and grid are the
+  // defaults and unused); then, for the band LU, the tile and the persistent
+  // grid with 256 rows per step, and the superblock (and the tile-by-tile
+  // solve) for that tile and grid
+  rr_tuning band{};
+  double band_best = -1.0;
+  auto consider = [&](int tile, int grid, int sb, rr_tuning* to, double* score) {
+    rr_tuning t{};
+    t.tile = tile;
+    t.grid = grid;
+    t.superblock = sb;
+    double sc = 0;
+    st = trial(t, &sc);
+    if (st == RR_OK && sc >= 0 && (*score < 0 || sc < *score)) {
+      *score = sc;
+      *to = t;
     }
-  if (st == RR_OK && best >= 0) {
-    const int B = (2 * p->ny + pick.tile - 1) / pick.tile;
-    const int dflt = superblock_tiles(0, pick.tile, B);
-    const int sbs[4] = {-1, 2, 4, 8};
-    const rr_tuning base = pick;
-    for (int i = 0; i < 4 && st == RR_OK; i++) {
-      if (sbs[i] == dflt || (sbs[i] > 0 && sbs[i] > 2 * B)) continue;
-      rr_tuning t = base;
-      t.superblock = sbs[i];
-      double sc = 0;
-      st = trial(t, &sc);
-      if (st == RR_OK && sc >= 0 && sc < best) {
-        best = sc;
-        pick = t;
-      }
-    }
+  };
+  auto half_band = [&](int tile) { return (2 * p->ny + tile - 1) / tile; };
+  consider(64, 2 * cus, 0, &pick, &best);
+  for (int tile : {64, 32})
+    for (int grid : {cus, 2 * cus})
+      if (st == RR_OK)
+        consider(tile, grid, superblock_tiles(0, tile, half_band(tile)), &band, &band_best);
+  if (st == RR_OK && band_best >= 0) {
+    const int B = half_band(band.tile), dflt = superblock_tiles(0, band.tile, B);
+    const rr_tuning base = band;
+    for (int sb : {-1, 2, 4, 8})
+      if (st == RR_OK && sb != dflt && sb <= 2 * B)
+        consider(base.tile, base.grid, sb, &band, &band_best);
+  }
+  if (band_best >= 0 && (best < 0 || band_best < best)) {
+    best = band_best;
+    pick = band;
   }
   for (auto& x : ev) (void)hipEventDestroy(x);
   (void)hipFree(Q);

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/rr.h"
+#include "rr_nd.h"
 
 namespace rr {
 
@@ -350,7 +351,11 @@ struct rr_factors {
   bool has_burgers = false;
   double* omega = nullptr;            // device, 2*n_omega (re, im)
   std::vector<double> omega_host;     // 2*n_omega
-  // factors and dataflow state
+  // the LU in nested-dissection order (rr_nd.hip), when nd is set
+  bool nd = false;
+  rr::NdPlan ndp;
+  rr::NdDevice ndd;
+  // the band LU's tiles and dataflow state
   void* tiles = nullptr;
   size_t tile_bytes = 0;
   int* flags = nullptr;               // max(factor flags, solve flags)

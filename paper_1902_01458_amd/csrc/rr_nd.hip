@@ -1,0 +1,1201 @@
+// Sparse LU of M(omega) in nested-dissection order, batched over shifts, and
+// its solves (Section 3.1: one factorisation serves every solve).
+//
+// Every front (rr_ndplan.hip) is a dense block matrix over its p separator
+// unknowns (1) and its q border unknowns (2),
+//   F = [ F11 F12 ]   F11, F12, F21: the stencil's entries plus the halves'
+//       [ F21 F22 ]   Schur complements; F22: the halves' alone
+// and keeps A = F11^-1, B12 = A F12 and F21; S = F22 - F21 B12 goes to the
+// front above.  No pivoting.  Solves take products only:
+//   forward  up:  z = A b1,  u = (halves' u) - F21 z;     down: x1 = z - B12 x2
+//   adjoint  up:  z = b1,    u = (halves' u) - B12^H z;   down: x1 = A^H (z - F21^H x2)
+// with b1 the right-hand side plus the halves' updates u at the separator.
+// A and F21 are stored column-major and B12 row-major, so that every product
+// of the factorisation and of the sweeps up reads 16 consecutive elements of
+// either operand per MFMA row, and the sweeps down read 4 consecutive ones
+// per lane.
+//
+// Schur complements and updates are pulled by the front above through the
+// border tables (each border unknown belongs to at most one half), so nothing
+// is zeroed, scattered or added atomically and every result is bitwise
+// repeatable.
+//
+// Against the band LU in the natural order (half-band 2 ny): at 512 x 256 a
+// shift takes 6.9e10 real flops and 6.5e7 factor entries instead of 5.5e11 and
+// 2.7e8, and the longest chain of dependent eliminations is about 2.5e3
+// unknowns (the separators on one path of the tree) instead of 262144.
+#include <algorithm>
+#include <type_traits>
+
+#include "rr_mfma.h"
+
+namespace rr {
+namespace {
+
+typedef cplx<double> zc;
+
+template <typename R>
+struct CAcc {
+  typename Mf<R>::v4 re, im;
+};
+template <typename R>
+__device__ __forceinline__ void zero(CAcc<R>& a) {
+  a.re = typename Mf<R>::v4{0, 0, 0, 0};
+  a.im = typename Mf<R>::v4{0, 0, 0, 0};
+}
+
+// M(omega) between unknowns dr (row) and dc: i omega - L.
+template <typename R>
+__device__ __forceinline__ cplx<R> entry(const OpDesc& op, double om_r, double om_i, int dr,
+                                         int dc) {
+  cplx<R> v{(R)0, (R)0};
+  const int d = (dc >> 1) - (dr >> 1);
+  const bool same = ((dr ^ dc) & 1) == 0;
+  if (d != 0 && d != 1 && d != -1 && d != op.ny && d != -op.ny) return v;
+  if (d != 0 && !same) return v;
+  const double* cf = op.coef + 12 * (int64_t)(dr >> 1) + 6 * (dr & 1);
+  double lv = 0.0;
+  if (d == 0) lv = same ? cf[0] : cf[5];
+  else if (d == op.ny) lv = cf[1];
+  else if (d == -op.ny) lv = cf[2];
+  else {
+    const int j = (dr >> 1) % op.ny;
+    if (d == 1 && j < op.ny - 1) lv = cf[3];
+    else if (d == -1 && j > 0) lv = cf[4];
+  }
+  double re = -lv, im = 0.0;
+  if (dr == dc) { re -= om_i; im = om_r; }
+  v.re = (R)re;
+  v.im = (R)im;
+  return v;
+}
+
+template <typename R>
+__device__ __forceinline__ void add(cplx<R>& a, cplx<R> b) {
+  a.re += b.re;
+  a.im += b.im;
+}
+
+// ---------------------------------------------------------------------------
+// Inverse of a T x T tile in LDS (T a multiple of 16, at most 64), column
+// major with pitch ld, in place: Gauss-Jordan by 16-column blocks.  Per block
+// one wave inverts the 16 x 16 pivot block in registers (lane l: row l % 16,
+// columns 4 (l / 16) .. + 3; the pivot row comes by DPP row broadcasts); then
+// the block row is multiplied by it and the other block rows updated on MFMA,
+// a wave per block row.  A zero or non-finite pivot latches ST_SINGULAR and
+// is replaced by 1.
+// ---------------------------------------------------------------------------
+template <int S>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + S, 0xf, 0xf, true));
+}
+template <int S>
+__device__ __forceinline__ double row_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + S, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + S, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+template <int S, typename R>
+__device__ __forceinline__ cplx<R> row_bcast(cplx<R> v) {
+  return cplx<R>{row_bcast<S>(v.re), row_bcast<S>(v.im)};
+}
+
+template <typename R, int S>
+struct Inv16 {
+  static __device__ __forceinline__ void run(cplx<R> (&a)[4], bool& bad) {
+    if constexpr (S < 16) {
+      constexpr int G = S >> 2, C = S & 3;
+      const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+      const int src = 16 * G + i;
+      cplx<R> f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
+      cplx<R> d = row_bcast<S>(f);                             // the pivot
+      const R mag = d.re * d.re + d.im * d.im;
+      if (!(mag > (R)0) || !isfinite(mag)) {
+        bad = true;
+        d = cplx<R>{(R)1, (R)0};
+      }
+      const cplx<R> inv = cinv(d);
+      cplx<R> m = cmul(f, inv);
+      const bool piv = i == S;
+      if (piv) m = cplx<R>{-inv.re, -inv.im};
+#pragma unroll
+      for (int c = 0; c < 4; c++) {
+        const cplx<R> v = row_bcast<S>(a[c]);
+        cplx<R> b = a[c];
+        if (piv) b = cplx<R>{(R)0, (R)0};
+        b.re -= m.re * v.re - m.im * v.im;
+        b.im -= m.re * v.im + m.im * v.re;
+        a[c] = b;
+      }
+      if (g == G) a[C] = cplx<R>{-m.re, -m.im};
+      Inv16<R, S + 1>::run(a, bad);
+    }
+  }
+};
+
+constexpr int kPv = 17;  // pitch of the 16 x 16 pivot inverse
+
+template <typename R>
+__device__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pv, uint32_t* status) {
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  const int nb = T >> 4;
+  for (int kb = 0; kb < nb; kb++) {
+    if (wave == 0) {
+      cplx<R> a[4];
+#pragma unroll
+      for (int c = 0; c < 4; c++) a[c] = F[(16 * kb + 4 * g + c) * ld + 16 * kb + i];
+      bool bad = false;
+      Inv16<R, 0>::run(a, bad);
+      if (bad && l == 0) latch(status, ST_SINGULAR);
+#pragma unroll
+      for (int c = 0; c < 4; c++) pv[i * kPv + 4 * g + c] = a[c];
+    }
+    __syncthreads();
+    if (wave != kb && wave < nb) {  // block row kb: R_j = pv F(kb, j), j = wave
+      CAcc<R> acc;
+      zero(acc);
+      cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
+#pragma unroll
+      for (int s = 0; s < 4; s++)
+        cmfma<R, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
+#pragma unroll
+      for (int e = 0; e < 4; e++) col[Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
+    }
+    __syncthreads();
+    if (wave < nb) {
+      if (wave == kb) {
+#pragma unroll
+        for (int c = 0; c < 4; c++) F[(16 * kb + 4 * g + c) * ld + 16 * kb + i] = pv[i * kPv + 4 * g + c];
+      } else {
+        cplx<R> cf[4];  // C_i = F(i, kb), i = wave
+#pragma unroll
+        for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * wave + i];
+        for (int j = 0; j < nb; j++) {
+          CAcc<R> acc;
+          zero(acc);
+          cplx<R>* col = F + (16 * j + i) * ld;
+          if (j == kb) {  // -C_i pv
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+              cmfma<R, false, true>(acc.re, acc.im, cf[s], pv[(4 * s + g) * kPv + i]);
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+              const cplx<R> v = col[16 * wave + Mf<R>::row(l, e)];
+              acc.re[e] = v.re;
+              acc.im[e] = v.im;
+            }
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+              cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
+          }
+#pragma unroll
+          for (int e = 0; e < 4; e++)
+            col[16 * wave + Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Factorisation
+// ---------------------------------------------------------------------------
+template <typename R>
+struct FactorArgs {
+  OpDesc op;
+  const NdFront* fronts;
+  const NdTask* tasks;
+  const int *pdof, *bmap, *grow;
+  const double* omega;
+  cplx<R>* factor;
+  cplx<R>* schur_in;   // the arena of the halves
+  cplx<R>* schur_out;
+  cplx<R>* temp;
+  int64_t nfactor, nin, nout, ntemp;  // elements per shift
+  uint32_t* status;
+  int w0;
+};
+
+constexpr int kLd = kNdTile + 1;  // pitch of a tile in LDS
+template <typename R>
+constexpr size_t tile_lds() {
+  return (size_t)(kNdTile * kLd + 16 * kPv) * sizeof(cplx<R>);
+}
+
+// One workgroup per front with P <= 64: F11 into LDS, its inverse A, then
+// B12 = A F12 by 16-column strips (a wave each, F12 pulled straight into the
+// MFMA operand) and F21 through LDS into column-major order.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
+  extern __shared__ __align__(16) char smem_raw[];
+  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
+  cplx<R>* pv = F + kNdTile * kLd;
+  const int w = g.w0 + blockIdx.y;
+  const NdFront fr = g.fronts[g.tasks[blockIdx.x].front];
+  const double om_r = g.omega[2 * w], om_i = g.omega[2 * w + 1];
+  const int p = fr.p, P = fr.P, Q = fr.Q;
+  const int* pd = g.pdof + fr.row;
+  const int* bm = g.bmap + fr.bor;
+  const int* gr = g.grow + fr.bor;
+  const bool inner = fr.childA >= 0;
+  const cplx<R>* Sh[2] = {nullptr, nullptr};
+  int Qh[2] = {0, 0};
+  if (inner) {
+    const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
+    Qh[0] = ca.Q;
+    Qh[1] = cb.Q;
+    Sh[0] = g.schur_in + w * g.nin + ca.s;
+    Sh[1] = g.schur_in + w * g.nin + cb.s;
+  }
+  const int base[2] = {fr.baseA, fr.baseB};
+  cplx<R>* A = g.factor + w * g.nfactor + fr.a;
+  cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
+  cplx<R>* F21 = g.factor + w * g.nfactor + fr.f21;
+  for (int e = threadIdx.x; e < P * P; e += 256) {
+    const int r = e / P, c = e - r * P;
+    cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
+    if (r < p && c < p) {
+      v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
+      if (inner) {
+        add(v, Sh[0][(int64_t)(base[0] + r) * Qh[0] + base[0] + c]);
+        add(v, Sh[1][(int64_t)(base[1] + r) * Qh[1] + base[1] + c]);
+      }
+    }
+    F[c * kLd + r] = v;
+  }
+  __syncthreads();
+  invert_tile<R>(F, kLd, P, pv, g.status);
+  for (int e = threadIdx.x; e < P * P; e += 256) {
+    const int c = e / P, r = e - c * P;
+    A[e] = F[c * kLd + r];
+  }
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
+  for (int t = wave; t < Q / 16; t += 4) {
+    const int j = 16 * t + i;
+    const int m = bm[j];
+    const bool real = j < fr.q;
+    const int dj = real ? g.pdof[gr[j]] : 0;
+    const int h = m & 1;
+    const cplx<R>* src = m >= 0 ? Sh[h] + (int64_t)base[h] * Qh[h] + (m >> 1) : nullptr;
+    const int lds_ = Qh[h];
+    CAcc<R> acc[4];
+#pragma unroll
+    for (int rb = 0; rb < 4; rb++) zero(acc[rb]);
+    for (int k0 = 0; k0 < P; k0 += 16) {
+      cplx<R> b[4];
+#pragma unroll
+      for (int s = 0; s < 4; s++) {
+        const int kk = k0 + 4 * s + gq;
+        b[s] = cplx<R>{(R)0, (R)0};
+        if (real && kk < p) {
+          b[s] = entry<R>(g.op, om_r, om_i, pd[kk], dj);
+          if (m >= 0) add(b[s], src[(int64_t)kk * lds_]);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; s++)
+#pragma unroll
+        for (int rb = 0; rb < 4; rb++)
+          if (16 * rb < P)
+            cmfma<R, false, false>(acc[rb].re, acc[rb].im,
+                                   F[(k0 + 4 * s + gq) * kLd + 16 * rb + i], b[s]);
+    }
+#pragma unroll
+    for (int rb = 0; rb < 4; rb++)
+      if (16 * rb < P)
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          B12[(int64_t)(16 * rb + Mf<R>::row(l, e)) * Q + 16 * t + i] =
+              cplx<R>{acc[rb].re[e], acc[rb].im[e]};
+  }
+  __syncthreads();
+  // F21, 16 border rows a wave at a time, transposed in the wave's quarter of LDS
+  cplx<R>* tr = F + wave * 16 * kLd;  // [c][r]
+  for (int t0 = 0; t0 < Q / 16; t0 += 4) {
+    const int t = t0 + wave;
+    if (t < Q / 16) {
+      for (int c = 0; c < 16; c++) {
+        const int cc = 16 * t + c;
+        const int m = bm[cc];
+        if (l < P) {
+          cplx<R> v{(R)0, (R)0};
+          if (cc < fr.q && l < p) {
+            v = entry<R>(g.op, om_r, om_i, g.pdof[gr[cc]], pd[l]);
+            if (m >= 0) {
+              const int h = m & 1;
+              add(v, Sh[h][(int64_t)(m >> 1) * Qh[h] + base[h] + l]);
+            }
+          }
+          tr[c * kLd + l] = v;
+        }
+      }
+    }
+    __syncthreads();
+    if (t < Q / 16)
+      for (int r = gq; r < P; r += 4) F21[(int64_t)r * Q + 16 * t + i] = tr[i * kLd + r];
+    __syncthreads();
+  }
+}
+
+// Acc (+)= sum over k of X[k][m]^T Y[k][n] for a wave's 2 x 2 blocks of 16 x
+// 16: both operands K rows of consecutive m / n.  px, py: the lane's element
+// of row l / 16 of each block; four k-steps are loaded ahead.
+template <typename R, bool SUB>
+__device__ __forceinline__ void gemm32(CAcc<R> (&acc)[2][2], const cplx<R>* const (&px)[2],
+                                       int64_t ldx, const cplx<R>* const (&py)[2], int64_t ldy,
+                                       int K) {
+  cplx<R> x[2][4][2], y[2][4][2];
+  const int nc = K >> 4;
+  auto load = [&](int buf, int c) {
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        x[buf][s][b] = px[b][(16 * c + 4 * s) * ldx];
+        y[buf][s][b] = py[b][(16 * c + 4 * s) * ldy];
+      }
+  };
+  auto mul = [&](int buf) {
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int n = 0; n < 2; n++)
+          cmfma<R, false, SUB>(acc[m][n].re, acc[m][n].im, x[buf][s][m], y[buf][s][n]);
+  };
+  load(0, 0);
+  for (int c = 0; c < nc; c += 2) {
+    load(1, min(c + 1, nc - 1));
+    mul(0);
+    if (c + 1 >= nc) break;
+    load(0, min(c + 2, nc - 1));
+    mul(1);
+  }
+}
+
+// The wave's 32 x 32 quarter of a 64 x 64 tile: block indices, clamped for loads.
+struct Quarter {
+  int mb[2], nb[2];    // block row / column
+  bool mok[2], nok[2];
+  int ml[2], nl[2];    // for loads
+  __device__ __forceinline__ Quarter(int ti, int tj, int M, int N) {
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      mb[b] = 4 * ti + 2 * (wave >> 1) + b;
+      nb[b] = 4 * tj + 2 * (wave & 1) + b;
+      mok[b] = 16 * mb[b] < M;
+      nok[b] = 16 * nb[b] < N;
+      ml[b] = min(mb[b], M / 16 - 1);
+      nl[b] = min(nb[b], N / 16 - 1);
+    }
+  }
+  __device__ __forceinline__ bool any() const { return mok[0] && nok[0]; }
+};
+
+// S = (the halves' Schur complements at the border) - F21 B12, a 64 x 64 tile
+// per workgroup.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_schur(FactorArgs<R> g) {
+  const int w = g.w0 + blockIdx.y;
+  const NdTask t = g.tasks[blockIdx.x];
+  const NdFront fr = g.fronts[t.front];
+  const int P = fr.P, Q = fr.Q;
+  const Quarter q(t.i, t.j, Q, Q);
+  if (!q.any()) return;
+  const int l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
+  const int* bm = g.bmap + fr.bor;
+  const cplx<R>* F21 = g.factor + w * g.nfactor + fr.f21;
+  const cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
+  cplx<R>* S = g.schur_out + w * g.nout + fr.s;
+  CAcc<R> acc[2][2];
+#pragma unroll
+  for (int m = 0; m < 2; m++)
+#pragma unroll
+    for (int n = 0; n < 2; n++) zero(acc[m][n]);
+  if (fr.childA >= 0) {
+    const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
+    const cplx<R>* Sa = g.schur_in + w * g.nin + ca.s;
+    const cplx<R>* Sb = g.schur_in + w * g.nin + cb.s;
+#pragma unroll
+    for (int n = 0; n < 2; n++) {
+      const int mj = bm[16 * q.nl[n] + i];
+      const cplx<R>* src = (mj & 1) ? Sb : Sa;
+      const int ld = (mj & 1) ? cb.Q : ca.Q;
+#pragma unroll
+      for (int m = 0; m < 2; m++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int mi = bm[16 * q.ml[m] + Mf<R>::row(l, e)];
+          if (mi >= 0 && mj >= 0 && ((mi ^ mj) & 1) == 0) {
+            const cplx<R> v = src[(int64_t)(mi >> 1) * ld + (mj >> 1)];
+            acc[m][n].re[e] = v.re;
+            acc[m][n].im[e] = v.im;
+          }
+        }
+    }
+  }
+  const cplx<R>* const px[2] = {F21 + (int64_t)gq * Q + 16 * q.ml[0] + i,
+                                F21 + (int64_t)gq * Q + 16 * q.ml[1] + i};
+  const cplx<R>* const py[2] = {B12 + (int64_t)gq * Q + 16 * q.nl[0] + i,
+                                B12 + (int64_t)gq * Q + 16 * q.nl[1] + i};
+  gemm32<R, true>(acc, px, Q, py, Q, P);
+#pragma unroll
+  for (int m = 0; m < 2; m++)
+#pragma unroll
+    for (int n = 0; n < 2; n++)
+      if (q.mok[m] && q.nok[n])
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          S[(int64_t)(16 * q.mb[m] + Mf<R>::row(l, e)) * Q + 16 * q.nb[n] + i] =
+              cplx<R>{acc[m][n].re[e], acc[m][n].im[e]};
+}
+
+// B12 = A T12 (P > 64)
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_border(FactorArgs<R> g) {
+  const int w = g.w0 + blockIdx.y;
+  const NdTask t = g.tasks[blockIdx.x];
+  const NdFront fr = g.fronts[t.front];
+  const int P = fr.P, Q = fr.Q;
+  const Quarter q(t.i, t.j, P, Q);
+  if (!q.any()) return;
+  const int l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
+  const cplx<R>* A = g.factor + w * g.nfactor + fr.a;
+  const cplx<R>* T12 = g.temp + w * g.ntemp + fr.t;
+  cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
+  CAcc<R> acc[2][2];
+#pragma unroll
+  for (int m = 0; m < 2; m++)
+#pragma unroll
+    for (int n = 0; n < 2; n++) zero(acc[m][n]);
+  const cplx<R>* const px[2] = {A + (int64_t)gq * P + 16 * q.ml[0] + i,
+                                A + (int64_t)gq * P + 16 * q.ml[1] + i};
+  const cplx<R>* const py[2] = {T12 + (int64_t)gq * Q + 16 * q.nl[0] + i,
+                                T12 + (int64_t)gq * Q + 16 * q.nl[1] + i};
+  gemm32<R, false>(acc, px, P, py, Q, P);
+#pragma unroll
+  for (int m = 0; m < 2; m++)
+#pragma unroll
+    for (int n = 0; n < 2; n++)
+      if (q.mok[m] && q.nok[n])
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          B12[(int64_t)(16 * q.mb[m] + Mf<R>::row(l, e)) * Q + 16 * q.nb[n] + i] =
+              cplx<R>{acc[m][n].re[e], acc[m][n].im[e]};
+}
+
+// Temporaries of a front with P > 64: T12 (P x Q, row-major), the pivot
+// block's row (64 x P, row-major) and column (64 columns of P), and two
+// copies (by pivot parity) of the pivot inverse, column- and row-major.
+__device__ __forceinline__ int64_t t_row(const NdFront& f) { return f.t + (int64_t)f.P * f.Q; }
+__device__ __forceinline__ int64_t t_col(const NdFront& f) {
+  return t_row(f) + (int64_t)kNdTile * f.P;
+}
+__device__ __forceinline__ int64_t t_piv(const NdFront& f, int k, int rowmajor) {
+  return t_col(f) + (int64_t)kNdTile * f.P + (2 * (k & 1) + rowmajor) * kNdTile * kNdTile;
+}
+__device__ __forceinline__ int tile_width(int P, int k) { return min(kNdTile, P - kNdTile * k); }
+
+// Invert the T x T tile in LDS and write it as pivot inverse k.
+template <typename R>
+__device__ void pivot_out(cplx<R>* F, cplx<R>* pv, int T, const NdFront& fr, int k,
+                          cplx<R>* temp, uint32_t* status) {
+  __syncthreads();
+  invert_tile<R>(F, kLd, T, pv, status);
+  cplx<R>* pc = temp + t_piv(fr, k, 0);
+  cplx<R>* pr = temp + t_piv(fr, k, 1);
+  for (int e = threadIdx.x; e < T * T; e += 256) {
+    const int c = e / T, r = e - c * T;
+    pc[c * kNdTile + r] = F[c * kLd + r];
+    pr[c * kNdTile + r] = F[r * kLd + c];
+  }
+}
+
+// A 64 x 64 tile of F11 (kind 0, into A), F12 (1, into T12) or F21 (2).
+// F11's first tile is the first pivot: it is inverted at once.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
+  extern __shared__ __align__(16) char smem_raw[];
+  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
+  cplx<R>* pv = F + kNdTile * kLd;
+  const int w = g.w0 + blockIdx.y;
+  const NdTask t = g.tasks[blockIdx.x];
+  const NdFront fr = g.fronts[t.front];
+  const double om_r = g.omega[2 * w], om_i = g.omega[2 * w + 1];
+  const int p = fr.p, P = fr.P, Q = fr.Q;
+  const int* pd = g.pdof + fr.row;
+  const int* bm = g.bmap + fr.bor;
+  const int* gr = g.grow + fr.bor;
+  const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
+  const cplx<R>* Sh[2] = {g.schur_in + w * g.nin + ca.s, g.schur_in + w * g.nin + cb.s};
+  const int Qh[2] = {ca.Q, cb.Q};
+  const int base[2] = {fr.baseA, fr.baseB};
+  const int M = t.kind == 2 ? Q : P, N = t.kind == 1 ? Q : P;
+  const int r0 = kNdTile * t.i, c0 = kNdTile * t.j;
+  const int nr = min(kNdTile, M - r0), nc = min(kNdTile, N - c0);
+  const int cl = threadIdx.x & 63;
+  const int c = c0 + cl;
+  cplx<R>* T12 = g.temp + w * g.ntemp + fr.t;
+  const int mc = t.kind == 1 && cl < nc ? bm[c] : -1;
+  const int dc = cl >= nc ? -1 : t.kind == 1 ? (c < fr.q ? g.pdof[gr[c]] : -1) : pd[c];
+  for (int rl = threadIdx.x >> 6; rl < nr; rl += 4) {
+    const int r = r0 + rl;
+    cplx<R> v{(R)0, (R)0};
+    if (t.kind == 0) {
+      if (r < p && c < p) {
+        v = entry<R>(g.op, om_r, om_i, pd[r], dc);
+        add(v, Sh[0][(int64_t)(base[0] + r) * Qh[0] + base[0] + c]);
+        add(v, Sh[1][(int64_t)(base[1] + r) * Qh[1] + base[1] + c]);
+      } else {
+        v.re = (R)(r == c ? 1 : 0);
+      }
+    } else if (t.kind == 1) {
+      if (r < p && dc >= 0) {
+        v = entry<R>(g.op, om_r, om_i, pd[r], dc);
+        if (mc >= 0) add(v, Sh[mc & 1][(int64_t)(base[mc & 1] + r) * Qh[mc & 1] + (mc >> 1)]);
+      }
+    } else if (r < fr.q && c < p) {
+      v = entry<R>(g.op, om_r, om_i, g.pdof[gr[r]], dc);
+      const int m = bm[r];
+      if (m >= 0) add(v, Sh[m & 1][(int64_t)(m >> 1) * Qh[m & 1] + base[m & 1] + c]);
+    }
+    if (cl < nc) {
+      if (t.kind == 1) T12[(int64_t)r * Q + c] = v;
+      else F[cl * kLd + rl] = v;
+    }
+  }
+  if (t.kind == 1) return;
+  __syncthreads();
+  cplx<R>* out = g.factor + w * g.nfactor + (t.kind == 0 ? fr.a : fr.f21);
+  const int rl = threadIdx.x & 63;
+  if (rl < nr)
+    for (int k = threadIdx.x >> 6; k < nc; k += 4)
+      out[(int64_t)(c0 + k) * M + r0 + rl] = F[k * kLd + rl];
+  if (t.kind == 0 && t.i == 0 && t.j == 0)
+    pivot_out<R>(F, pv, nr, fr, 0, g.temp + w * g.ntemp, g.status);
+}
+
+// Pivot tile k's block row, R_j = F(k,k)^-1 F(k, j) (kind 0), and a copy of
+// its block column (kind 1): what the update reads while it overwrites both.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_panel(FactorArgs<R> g) {
+  extern __shared__ __align__(16) char smem_raw[];
+  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
+  const int w = g.w0 + blockIdx.y;
+  const NdTask t = g.tasks[blockIdx.x];
+  const NdFront fr = g.fronts[t.front];
+  const int P = fr.P, k = t.j;
+  const int T = tile_width(P, k), N = tile_width(P, t.i);  // pivot tile, tile t.i
+  const cplx<R>* A = g.factor + w * g.nfactor + fr.a;
+  cplx<R>* temp = g.temp + w * g.ntemp;
+  const int r = threadIdx.x & 63;
+  if (t.kind == 1) {
+    if (r < N)
+      for (int c = threadIdx.x >> 6; c < T; c += 4)
+        temp[t_col(fr) + (int64_t)c * P + kNdTile * t.i + r] =
+            A[(int64_t)(kNdTile * k + c) * P + kNdTile * t.i + r];
+    return;
+  }
+  if (r < T)
+    for (int c = threadIdx.x >> 6; c < N; c += 4)
+      F[c * kLd + r] = A[(int64_t)(kNdTile * t.i + c) * P + kNdTile * k + r];
+  __syncthreads();
+  const Quarter q(0, 0, T, N);
+  if (!q.any()) return;
+  const int l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
+  const cplx<R>* piv = temp + t_piv(fr, k, 0);
+  CAcc<R> acc[2][2];
+#pragma unroll
+  for (int m = 0; m < 2; m++)
+#pragma unroll
+    for (int n = 0; n < 2; n++) zero(acc[m][n]);
+  const cplx<R>* const px[2] = {piv + gq * kNdTile + 16 * q.ml[0] + i,
+                                piv + gq * kNdTile + 16 * q.ml[1] + i};
+  const cplx<R>* const py[2] = {F + (16 * q.nl[0] + i) * kLd + gq,
+                                F + (16 * q.nl[1] + i) * kLd + gq};
+  gemm32<R, false>(acc, px, kNdTile, py, 1, T);
+#pragma unroll
+  for (int m = 0; m < 2; m++)
+#pragma unroll
+    for (int n = 0; n < 2; n++)
+      if (q.mok[m] && q.nok[n])
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+          temp[t_row(fr) + (int64_t)(16 * q.mb[m] + Mf<R>::row(l, e)) * P + kNdTile * t.i +
+               16 * q.nb[n] + i] = cplx<R>{acc[m][n].re[e], acc[m][n].im[e]};
+}
+
+// Gauss-Jordan update of tile (i, j) of A for pivot tile k:
+//   F(i, j) -= C_i R_j;  F(i, k) = -C_i F(k,k)^-1;  F(k, j) = R_j;  F(k, k) = its inverse
+// computed transposed (rows of the product along j), so that lanes hold
+// consecutive elements of A's columns.  The next pivot tile is inverted where
+// it is updated.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_update(FactorArgs<R> g) {
+  extern __shared__ __align__(16) char smem_raw[];
+  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
+  cplx<R>* pv = F + kNdTile * kLd;
+  const int w = g.w0 + blockIdx.y;
+  const NdTask t = g.tasks[blockIdx.x];
+  const NdFront fr = g.fronts[t.front];
+  const int P = fr.P, k = t.kind;
+  const int T = tile_width(P, k), M = tile_width(P, t.j), N = tile_width(P, t.i);
+  cplx<R>* temp = g.temp + w * g.ntemp;
+  cplx<R>* A = g.factor + w * g.nfactor + fr.a + (int64_t)kNdTile * t.j * P + kNdTile * t.i;
+  if (t.i == k) {  // the pivot's block row, through LDS into column-major order
+    if (t.j == k) {
+      const cplx<R>* piv = temp + t_piv(fr, k, 0);
+      const int r = threadIdx.x & 63;
+      if (r < T)
+        for (int c = threadIdx.x >> 6; c < T; c += 4) A[(int64_t)c * P + r] = piv[c * kNdTile + r];
+      return;
+    }
+    const cplx<R>* row = temp + t_row(fr) + kNdTile * t.j;
+    const int x = threadIdx.x & 63;
+    if (x < M)
+      for (int r = threadIdx.x >> 6; r < T; r += 4) F[x * kLd + r] = row[(int64_t)r * P + x];
+    __syncthreads();
+    if (x < T)
+      for (int c = threadIdx.x >> 6; c < M; c += 4) A[(int64_t)c * P + x] = F[c * kLd + x];
+    return;
+  }
+  const bool next = t.i == k + 1 && t.j == k + 1;
+  const Quarter q(0, 0, M, N);
+  const int l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
+  if (q.any()) {
+    CAcc<R> acc[2][2];
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+      for (int n = 0; n < 2; n++) {
+        zero(acc[m][n]);
+        if (t.j != k)
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const cplx<R> v = A[(int64_t)(16 * q.ml[m] + Mf<R>::row(l, e)) * P + 16 * q.nl[n] + i];
+            acc[m][n].re[e] = v.re;
+            acc[m][n].im[e] = v.im;
+          }
+      }
+    const cplx<R>* X = t.j == k ? temp + t_piv(fr, k, 1) : temp + t_row(fr) + kNdTile * t.j;
+    const int64_t ldx = t.j == k ? kNdTile : P;
+    const cplx<R>* Y = temp + t_col(fr) + kNdTile * t.i;
+    const cplx<R>* const px[2] = {X + gq * ldx + 16 * q.ml[0] + i, X + gq * ldx + 16 * q.ml[1] + i};
+    const cplx<R>* const py[2] = {Y + (int64_t)gq * P + 16 * q.nl[0] + i,
+                                  Y + (int64_t)gq * P + 16 * q.nl[1] + i};
+    gemm32<R, true>(acc, px, ldx, py, P, T);
+#pragma unroll
+    for (int m = 0; m < 2; m++)
+#pragma unroll
+      for (int n = 0; n < 2; n++)
+        if (q.mok[m] && q.nok[n])
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const int c = 16 * q.mb[m] + Mf<R>::row(l, e), r = 16 * q.nb[n] + i;
+            const cplx<R> v{acc[m][n].re[e], acc[m][n].im[e]};
+            if (next) F[c * kLd + r] = v;
+            else A[(int64_t)c * P + r] = v;
+          }
+  }
+  if (next) pivot_out<R>(F, pv, N, fr, k + 1, temp, g.status);
+}
+
+// ---------------------------------------------------------------------------
+// Solves
+// ---------------------------------------------------------------------------
+template <typename R>
+struct SolveArgs {
+  const NdFront* fronts;
+  const NdTask* tasks;
+  const int *pdof, *bmap, *grow;
+  const cplx<R>* factor;
+  cplx<R>*w, *z;          // (shift, row, column)
+  cplx<R>*uin, *uout;     // the halves' updates, this level's
+  int64_t nfactor, nw, nuin, nuout;  // elements per shift
+  int k, adjoint, qsplit;
+  int w0;
+  const uint32_t* skip;
+};
+__device__ __forceinline__ bool skipped(const uint32_t* skip) {
+  return skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Right-hand sides into elimination order: w[row][j] = B[j][pdof[row]], zero
+// for padding and for the row after the last; back for the solution.
+constexpr int kRowTile = 32;
+template <typename R, bool OUT>
+__global__ __launch_bounds__(256) void k_nd_permute(const int* pdof, int64_t rows, int64_t n, int k,
+                                                    int64_t cstride, const double2* B,
+                                                    double2* X, cplx<R>* W, int w0,
+                                                    const uint32_t* skip) {
+  if (skipped(skip)) return;
+  __shared__ cplx<R> tile[kRowTile][33];
+  const int w = w0 + blockIdx.y;
+  const int64_t r0 = (int64_t)blockIdx.x * kRowTile;
+  const int64_t total = rows + 1;  // with the zero row
+  const int nr = (int)min((int64_t)kRowTile, total - r0);
+  cplx<R>* Wt = W + (w * total + r0) * k;
+  const int r = threadIdx.x & 31;
+  const int dof = r0 + r < rows ? pdof[r0 + r] : -1;
+  if (OUT) {
+    for (int e = threadIdx.x; e < nr * k; e += 256) tile[e / k][e % k] = Wt[e];
+    __syncthreads();
+    if (dof >= 0)
+      for (int j = threadIdx.x >> 5; j < k; j += 8) {
+        const cplx<R> v = tile[r][j];
+        X[(int64_t)w * cstride + (int64_t)j * n + dof] = make_double2(v.re, v.im);
+      }
+  } else {
+    for (int j = threadIdx.x >> 5; j < k; j += 8) {
+      cplx<R> v{(R)0, (R)0};
+      if (dof >= 0) {
+        const double2 b = B[(int64_t)w * cstride + (int64_t)j * n + dof];
+        v = cplx<R>{(R)b.x, (R)b.y};
+      }
+      tile[r][j] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < nr * k; e += 256) Wt[e] = tile[e / k][e % k];
+  }
+}
+
+// acc[cb] += X(rows of one 16-row block) * V over the k-chunks of 16 in
+// [c0, nc) by step; X element (i, kk) at i + kk * ld (KF false) or
+// i * ld + kk (KF true); V row kk's first element from `row`.  KF takes k in
+// the order 4 (l / 16) + s, so that a lane's four loads are consecutive.
+template <typename R, int NB, bool KF, bool CONJ, typename RowPtr>
+__device__ __forceinline__ void rows_mul(CAcc<R> (&acc)[NB], const cplx<R>* X, int64_t ld, int c0,
+                                         int nc, int step, const int (&col)[NB], RowPtr row) {
+  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  cplx<R> x[2][4], v[2][4][NB];
+  auto load = [&](int buf, int c) {
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+      const int kk = 16 * c + (KF ? 4 * g + s : 4 * s + g);
+      x[buf][s] = X[KF ? i * ld + kk : (int64_t)kk * ld + i];
+      const cplx<R>* vr = row(kk);
+#pragma unroll
+      for (int b = 0; b < NB; b++) v[buf][s][b] = vr[col[b]];
+    }
+  };
+  auto mul = [&](int buf) {
+#pragma unroll
+    for (int s = 0; s < 4; s++)
+#pragma unroll
+      for (int b = 0; b < NB; b++)
+        cmfma<R, CONJ, false>(acc[b].re, acc[b].im, x[buf][s], v[buf][s][b]);
+  };
+  if (c0 >= nc) return;
+  load(0, c0);
+  for (int c = c0; c < nc; c += 2 * step) {
+    load(1, c + step < nc ? c + step : c);
+    mul(0);
+    if (c + step >= nc) break;
+    load(0, c + 2 * step < nc ? c + 2 * step : c);
+    mul(1);
+  }
+}
+
+// A front with P <= 64, sweep up: one workgroup per front (and share of its
+// border rows, blockIdx.z).
+template <typename R, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
+  if (skipped(a.skip)) return;
+  extern __shared__ __align__(16) char smem_raw[];
+  constexpr int NC = 16 * NB;
+  const int w = a.w0 + blockIdx.y;
+  const NdFront fr = a.fronts[a.tasks[blockIdx.x].front];
+  const int P = fr.P, Q = fr.Q, k = a.k;
+  cplx<R>* bs = reinterpret_cast<cplx<R>*>(smem_raw);  // b1, P x NC
+  cplx<R>* zs = ADJ ? bs : bs + P * NC;                // z
+  const cplx<R>* ua = nullptr;
+  const cplx<R>* ub = nullptr;
+  if (fr.childA >= 0) {
+    ua = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childA].urow * k;
+    ub = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childB].urow * k;
+  }
+  cplx<R>* z = a.z + w * a.nw + (int64_t)fr.row * k;
+  const cplx<R>* b = a.w + w * a.nw + (int64_t)fr.row * k;
+  for (int e = threadIdx.x; e < P * NC; e += 256) {
+    const int r = e / NC, j = e % NC;
+    cplx<R> v{(R)0, (R)0};
+    if (j < k) {
+      v = b[r * k + j];
+      if (ua && r < fr.p) {
+        add(v, ua[(fr.baseA + r) * k + j]);
+        add(v, ub[(fr.baseB + r) * k + j]);
+      }
+      if (ADJ && blockIdx.z == 0) z[r * k + j] = v;
+    }
+    bs[e] = v;
+  }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15;
+  const cplx<R>* fac = a.factor + w * a.nfactor;
+  int col[NB];
+#pragma unroll
+  for (int c = 0; c < NB; c++) col[c] = 16 * c + i;
+  if (!ADJ) {
+    for (int rb = wave; rb < P / 16; rb += 4) {
+      CAcc<R> acc[NB];
+#pragma unroll
+      for (int c = 0; c < NB; c++) zero(acc[c]);
+      rows_mul<R, NB, false, false>(acc, fac + fr.a + 16 * rb, P, 0, P / 16, 1, col,
+                                    [&](int kk) { return bs + kk * NC; });
+#pragma unroll
+      for (int c = 0; c < NB; c++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int r = 16 * rb + Mf<R>::row(l, e);
+          const cplx<R> v{acc[c].re[e], acc[c].im[e]};
+          zs[r * NC + col[c]] = v;
+          if (blockIdx.z == 0 && col[c] < k) z[r * k + col[c]] = v;
+        }
+    }
+    __syncthreads();
+  }
+  const int* bm = a.bmap + fr.bor;
+  cplx<R>* uo = a.uout + w * a.nuout + (int64_t)fr.urow * k;
+  for (int rb = wave + 4 * blockIdx.z; rb < Q / 16; rb += 4 * a.qsplit) {
+    CAcc<R> acc[NB];
+#pragma unroll
+    for (int c = 0; c < NB; c++) zero(acc[c]);
+    rows_mul<R, NB, false, ADJ>(acc, fac + (ADJ ? fr.b12 : fr.f21) + 16 * rb, Q, 0, P / 16, 1, col,
+                                [&](int kk) { return zs + kk * NC; });
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int r = 16 * rb + Mf<R>::row(l, e);
+      const int m = bm[r];
+      const cplx<R>* src = (m & 1) ? ub : ua;
+#pragma unroll
+      for (int c = 0; c < NB; c++)
+        if (col[c] < k) {
+          cplx<R> v{(R)0, (R)0};
+          if (m >= 0) v = src[(m >> 1) * k + col[c]];
+          v.re -= acc[c].re[e];
+          v.im -= acc[c].im[e];
+          uo[r * k + col[c]] = v;
+        }
+    }
+  }
+}
+
+// A front with P <= 64, sweep down; the four waves split the inner dimension
+// where P leaves them idle.
+template <typename R, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R> a) {
+  if (skipped(a.skip)) return;
+  extern __shared__ __align__(16) char smem_raw[];
+  constexpr int NC = 16 * NB;
+  cplx<R>* red = reinterpret_cast<cplx<R>*>(smem_raw);  // 4 x 16 x NC: the waves' sums
+  const int w = a.w0 + blockIdx.y;
+  const NdFront fr = a.fronts[a.tasks[blockIdx.x].front];
+  const int P = fr.P, Q = fr.Q, k = a.k;
+  cplx<R>* ts = red + 4 * 16 * NC;  // P x NC (adjoint)
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15;
+  const cplx<R>* fac = a.factor + w * a.nfactor;
+  cplx<R>* W = a.w + w * a.nw;
+  const cplx<R>* z = a.z + w * a.nw + (int64_t)fr.row * k;
+  cplx<R>* x = W + (int64_t)fr.row * k;
+  const int* gr = a.grow + fr.bor;
+  const int nrb = P / 16, nsplit = 4 / nrb;  // nrb <= 4
+  const int rb = wave % nrb, ks = wave / nrb;
+  int col[NB];
+#pragma unroll
+  for (int c = 0; c < NB; c++) col[c] = min(16 * c + i, k - 1);
+  CAcc<R> acc[NB];
+#pragma unroll
+  for (int c = 0; c < NB; c++) zero(acc[c]);
+  if (ks < nsplit)
+    rows_mul<R, NB, true, ADJ>(acc, fac + (ADJ ? fr.f21 : fr.b12) + (int64_t)16 * rb * Q, Q, ks,
+                               Q / 16, nsplit, col,
+                               [&](int kk) { return W + (int64_t)gr[kk] * k; });
+#pragma unroll
+  for (int c = 0; c < NB; c++)
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      red[(wave * 16 + Mf<R>::row(l, e)) * NC + 16 * c + i] = cplx<R>{acc[c].re[e], acc[c].im[e]};
+  __syncthreads();
+  for (int e = threadIdx.x; e < P * NC; e += 256) {
+    const int r = e / NC, j = e % NC;
+    cplx<R> v{(R)0, (R)0};
+    if (j < k) {
+      v = z[r * k + j];
+      for (int s = 0; s < nsplit; s++) {
+        const cplx<R> d = red[((s * nrb + (r >> 4)) * 16 + (r & 15)) * NC + j];
+        v.re -= d.re;
+        v.im -= d.im;
+      }
+      if (!ADJ) x[r * k + j] = v;
+    }
+    if (ADJ) ts[e] = v;
+  }
+  if (!ADJ) return;
+  __syncthreads();
+  int lcol[NB];
+#pragma unroll
+  for (int c = 0; c < NB; c++) lcol[c] = 16 * c + i;
+  if (wave >= nrb) return;
+#pragma unroll
+  for (int c = 0; c < NB; c++) zero(acc[c]);
+  rows_mul<R, NB, true, true>(acc, fac + fr.a + (int64_t)16 * wave * P, P, 0, P / 16, 1, lcol,
+                              [&](int kk) { return ts + kk * NC; });
+#pragma unroll
+  for (int c = 0; c < NB; c++)
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      if (lcol[c] < k)
+        x[(16 * wave + Mf<R>::row(l, e)) * k + lcol[c]] = cplx<R>{acc[c].re[e], acc[c].im[e]};
+}
+
+// P > 64: b1 of 64 rows (into w, or z for the adjoint sweep)
+template <typename R>
+__global__ __launch_bounds__(256) void k_nd_gather(SolveArgs<R> a) {
+  if (skipped(a.skip)) return;
+  const int w = a.w0 + blockIdx.y;
+  const NdTask t = a.tasks[blockIdx.x];
+  const NdFront fr = a.fronts[t.front];
+  const int k = a.k;
+  const cplx<R>* ua = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childA].urow * k;
+  const cplx<R>* ub = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childB].urow * k;
+  const int r0 = kNdTile * t.i, nr = min(kNdTile, fr.P - r0);
+  const int64_t at = w * a.nw + (int64_t)(fr.row + r0) * k;
+  for (int e = threadIdx.x; e < nr * k; e += 256) {
+    cplx<R> v = a.w[at + e];
+    if (r0 + e / k < fr.p) {
+      add(v, ua[(fr.baseA + r0) * k + e]);
+      add(v, ub[(fr.baseB + r0) * k + e]);
+    }
+    (a.adjoint ? a.z : a.w)[at + e] = v;
+  }
+}
+
+// P > 64: 16 rows of one product, the four waves splitting its inner dimension.
+enum { ND_Z = 0,    // z = A w               (forward, up)
+       ND_U = 1,    // u = pulled - F21 z    (adjoint: B12^H z)
+       ND_X = 2,    // w = z - B12 w[border]  (adjoint: z -= F21^H w[border])
+       ND_AH = 3 }; // w = A^H z             (adjoint, down)
+template <typename R, int NB, int MODE, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R> a) {
+  if (skipped(a.skip)) return;
+  constexpr int NC = 16 * NB;
+  constexpr bool KF = MODE == ND_X || MODE == ND_AH;
+  __shared__ cplx<R> red[4 * 16 * NC];
+  const int w = a.w0 + blockIdx.y;
+  const NdTask t = a.tasks[blockIdx.x];
+  const NdFront fr = a.fronts[t.front];
+  const int P = fr.P, Q = fr.Q, k = a.k;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15;
+  cplx<R>* W = a.w + w * a.nw;
+  cplx<R>* Z = a.z + w * a.nw;
+  const int* gr = a.grow + fr.bor;
+  const int64_t off = MODE == ND_Z || MODE == ND_AH ? fr.a
+                      : (MODE == ND_U) != ADJ        ? fr.f21
+                                                     : fr.b12;
+  const int64_t ld = MODE == ND_U || MODE == ND_X ? Q : P;
+  const int K = MODE == ND_X ? Q : P;
+  const cplx<R>* X = a.factor + w * a.nfactor + off + (KF ? 16 * t.i * ld : 16 * t.i);
+  int col[NB];
+#pragma unroll
+  for (int c = 0; c < NB; c++) col[c] = min(16 * c + i, k - 1);
+  CAcc<R> acc[NB];
+#pragma unroll
+  for (int c = 0; c < NB; c++) zero(acc[c]);
+  const cplx<R>* V = (MODE == ND_Z ? W : Z) + (int64_t)fr.row * k;
+  rows_mul<R, NB, KF, ADJ>(acc, X, ld, wave, K / 16, 4, col, [&](int kk) {
+    return MODE == ND_X ? W + (int64_t)gr[kk] * k : V + (int64_t)kk * k;
+  });
+#pragma unroll
+  for (int c = 0; c < NB; c++)
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      red[(wave * 16 + Mf<R>::row(l, e)) * NC + 16 * c + i] = cplx<R>{acc[c].re[e], acc[c].im[e]};
+  __syncthreads();
+  for (int e = threadIdx.x; e < 16 * NC; e += 256) {
+    const int r = 16 * t.i + e / NC, j = e % NC;
+    if (j >= k) continue;
+    cplx<R> v = red[e];
+#pragma unroll
+    for (int s = 1; s < 4; s++) add(v, red[s * 16 * NC + e]);
+    const int64_t at = (int64_t)(fr.row + r) * k + j;
+    if (MODE == ND_Z) {
+      Z[at] = v;
+    } else if (MODE == ND_AH) {
+      W[at] = v;
+    } else if (MODE == ND_X) {
+      const cplx<R> z = Z[at];
+      (ADJ ? Z : W)[at] = cplx<R>{z.re - v.re, z.im - v.im};
+    } else {
+      const int m = a.bmap[fr.bor + r];
+      cplx<R> u{(R)0, (R)0};
+      if (m >= 0) {
+        const int half = (m & 1) ? fr.childB : fr.childA;
+        u = a.uin[w * a.nuin + (int64_t)(a.fronts[half].urow + (m >> 1)) * k + j];
+      }
+      a.uout[w * a.nuout + (int64_t)(fr.urow + r) * k + j] = cplx<R>{u.re - v.re, u.im - v.im};
+    }
+  }
+}
+
+constexpr int kMaxY = 32768;  // shifts per launch (grid y)
+
+template <typename R>
+hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, const double* omega,
+                      int n_omega, uint32_t* status, hipStream_t s) {
+  FactorArgs<R> a{};
+  a.op = op;
+  a.fronts = d.fronts;
+  a.pdof = d.pdof;
+  a.bmap = d.bmap;
+  a.grow = d.grow;
+  a.omega = omega;
+  a.factor = (cplx<R>*)d.factor;
+  a.temp = (cplx<R>*)d.temp;
+  a.nfactor = pl.factor;
+  a.ntemp = pl.temp;
+  a.status = status;
+  const size_t lds = tile_lds<R>();
+  for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
+    const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
+    a.w0 = w0;
+    auto run = [&](auto kernel, const NdSpan& sp, size_t shm) {
+      if (!sp.count) return;
+      a.tasks = d.tasks + sp.first;
+      hipLaunchKernelGGL(kernel, dim3(sp.count, nw), dim3(256), shm, s, a);
+    };
+    for (int dep = (int)pl.levels.size() - 1; dep >= 0; dep--) {
+      const NdLevel& lv = pl.levels[dep];
+      a.schur_out = (cplx<R>*)d.schur[dep & 1];
+      a.schur_in = (cplx<R>*)d.schur[~dep & 1];
+      a.nout = pl.schur[dep & 1];
+      a.nin = pl.schur[~dep & 1];
+      run(k_nd_front<R>, lv.small, lds);
+      run(k_nd_assemble<R>, lv.assemble, lds);
+      for (size_t k = 0; k < lv.panel.size(); k++) {
+        run(k_nd_panel<R>, lv.panel[k], lds);
+        run(k_nd_update<R>, lv.update[k], lds);
+      }
+      run(k_nd_border<R>, lv.border, 0);
+      run(k_nd_schur<R>, lv.schur, 0);
+    }
+  }
+  return hipGetLastError();
+}
+
+template <typename R, int NB, bool ADJ>
+hipError_t solve_run(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k, int c0,
+                     int ktot, const double* Bm, int64_t bstride, double* X, hipStream_t s,
+                     const uint32_t* skip) {
+  constexpr int NC = 16 * NB;
+  SolveArgs<R> a{};
+  a.fronts = d.fronts;
+  a.pdof = d.pdof;
+  a.bmap = d.bmap;
+  a.grow = d.grow;
+  a.factor = (const cplx<R>*)d.factor;
+  a.w = (cplx<R>*)d.w;
+  a.z = (cplx<R>*)d.z;
+  a.nfactor = pl.factor;
+  a.nw = (pl.rows + 1) * k;
+  a.k = k;
+  a.adjoint = ADJ;
+  a.skip = skip;
+  const unsigned rb = (unsigned)((pl.rows + 1 + kRowTile - 1) / kRowTile);
+  const double2* B = (const double2*)Bm + (int64_t)c0 * n;
+  double2* Xo = (double2*)X + (int64_t)c0 * n;
+  for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
+    const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
+    a.w0 = w0;
+    auto run = [&](auto kernel, const NdSpan& sp, size_t shm, int zs = 1) {
+      if (!sp.count) return;
+      a.tasks = d.tasks + sp.first;
+      a.qsplit = zs;
+      hipLaunchKernelGGL(kernel, dim3(sp.count, nw, zs), dim3(256), shm, s, a);
+    };
+    auto level = [&](int dep) -> const NdLevel& {
+      a.uout = (cplx<R>*)d.u[dep & 1];
+      a.uin = (cplx<R>*)d.u[~dep & 1];
+      a.nuout = pl.urows[dep & 1] * k;
+      a.nuin = pl.urows[~dep & 1] * k;
+      return pl.levels[dep];
+    };
+    hipLaunchKernelGGL((k_nd_permute<R, false>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n,
+                       k, bstride, B, (double2*)nullptr, a.w, w0, skip);
+    for (int dep = (int)pl.levels.size() - 1; dep >= 0; dep--) {
+      const NdLevel& lv = level(dep);
+      if (lv.small.count) {
+        // border rows over several workgroups where the fronts leave CUs idle
+        const int64_t wgs = (int64_t)lv.small.count * nw;
+        const int zs = (int)std::max<int64_t>(
+            1, std::min<int64_t>((lv.maxQ + 63) / 64, 512 / std::max<int64_t>(wgs, 1)));
+        run(k_nd_up<R, NB, ADJ>, lv.small, (size_t)lv.maxP * NC * (ADJ ? 1 : 2) * sizeof(cplx<R>),
+            zs);
+      }
+      run(k_nd_gather<R>, lv.gather, 0);
+      if (!ADJ) run(k_nd_rows<R, NB, ND_Z, ADJ>, lv.rowsP, 0);
+      run(k_nd_rows<R, NB, ND_U, ADJ>, lv.rowsQ, 0);
+    }
+    for (int dep = 0; dep < (int)pl.levels.size(); dep++) {
+      const NdLevel& lv = level(dep);
+      run(k_nd_down<R, NB, ADJ>, lv.small,
+          (size_t)(64 + (ADJ ? lv.maxP : 0)) * NC * sizeof(cplx<R>));
+      run(k_nd_rows<R, NB, ND_X, ADJ>, lv.rowsP, 0);
+      if (ADJ) run(k_nd_rows<R, NB, ND_AH, ADJ>, lv.rowsP, 0);
+    }
+    hipLaunchKernelGGL((k_nd_permute<R, true>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n, k,
+                       (int64_t)ktot * n, (const double2*)nullptr, Xo, a.w, w0, skip);
+  }
+  return hipGetLastError();
+}
+
+template <typename R>
+hipError_t prepare_r() {
+  hipError_t e = hipSuccess;
+  auto lds = [&](const void* fn, size_t bytes) {
+    if (e == hipSuccess && bytes > 64 * 1024)
+      e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  lds((const void*)k_nd_front<R>, tile_lds<R>());
+  lds((const void*)k_nd_assemble<R>, tile_lds<R>());
+  lds((const void*)k_nd_panel<R>, tile_lds<R>());
+  lds((const void*)k_nd_update<R>, tile_lds<R>());
+  return e;
+}
+
+}  // namespace
+
+hipError_t nd_prepare() {
+  const hipError_t e = prepare_r<double>();
+  return e != hipSuccess ? e : prepare_r<float>();
+}
+
+hipError_t launch_nd_factor(const OpDesc& op, const NdPlan& pl, const NdDevice& d,
+                            const double* omega, int n_omega, bool fp32, uint32_t* status,
+                            hipStream_t s) {
+  return fp32 ? factor_run<float>(op, pl, d, omega, n_omega, status, s)
+              : factor_run<double>(op, pl, d, omega, n_omega, status, s);
+}
+
+hipError_t launch_nd_solve(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
+                           int c0, int ktot, bool fp32, int adjoint, const double* Bm,
+                           int64_t bstride, double* X, hipStream_t s, const uint32_t* skip) {
+  auto go = [&](auto r, auto nb, auto adj) {
+    return solve_run<decltype(r), decltype(nb)::value, decltype(adj)::value>(
+        pl, d, n, n_omega, k, c0, ktot, Bm, bstride, X, s, skip);
+  };
+  auto by_adj = [&](auto r, auto nb) {
+    return adjoint ? go(r, nb, std::true_type{}) : go(r, nb, std::false_type{});
+  };
+  auto by_nb = [&](auto r) {
+    return k <= 16 ? by_adj(r, std::integral_constant<int, 1>{})
+                   : by_adj(r, std::integral_constant<int, 2>{});
+  };
+  return fp32 ? by_nb(0.0f) : by_nb(0.0);
+}
+
+}  // namespace rr
