@@ -477,8 +477,10 @@ int64_t rr_factor_schedule(int32_t B, int32_t NB, int32_t* out, int64_t cap);
  * front (the root first) p, q, P, Q, row, bor, childA, childB, baseA, baseB,
  * urow, the offsets of A, B12, F21, the Schur complement and the temporaries,
  * and the depth; 1: the unknown of every row (-1: padding); 2: per border
- * entry 2 * (position in a half's border) + half, or -1; 3: per border entry
- * its row; 4: the tasks (front, i, j, kind); 5: the totals rows, border
+ * entry 2 * (position in a half's border) + half, or -1 (a leaf's: the
+ * position of its neighbour among the leaf's unknowns); 3: per border entry
+ * its row; 4: the tasks (front, i, j, kind); 5: the totals separator rows
+ * (also the zero row, which padding of 3 names), all rows, border
  * entries, factor elements, Schur arenas (2), temporaries, update rows (2),
  * tasks.  Returns the number of values (which may exceed cap), or -1 for bad
  * arguments. */

@@ -120,7 +120,7 @@ int probe_cols(int k, int np_max) {
 hipError_t lu_solve(rr_factors* f, int k, bool fp32, int adjoint, const double* Bm,
                     int64_t bstride, double* X, hipStream_t s, const uint32_t* skip = nullptr) {
   if (f->nd)
-    return launch_nd_solve(f->ndp, f->ndd, f->n, f->n_omega, k, 0, k, fp32, adjoint, Bm, bstride,
+    return launch_nd_solve(opdesc(f), f->ndp, f->ndd, f->n, f->n_omega, k, 0, k, fp32, adjoint, Bm, bstride,
                            X, s, skip);
   return launch_solve(f->geom, f->n, f->n_omega, k, fp32, f->tiles, adjoint, Bm, bstride, X,
                       f->xs, f->cbuf, f->flags, ticket_word(f), st_word(f), f->solve_grid, s,
@@ -283,7 +283,7 @@ rr_status solve_any(rr_factors* f, int k, int adjoint, const double* Bm, int64_t
     // nested-dissection LU, whose solves copy into elimination order anyway;
     // gathered into and scattered from two narrow blocks with the band LU
     for (int c0 = 0; f->nd && c0 < k; c0 += kNarrowK)
-      RR_HIP(launch_nd_solve(f->ndp, f->ndd, f->n, f->n_omega, std::min(kNarrowK, k - c0), c0, k,
+      RR_HIP(launch_nd_solve(opdesc(f), f->ndp, f->ndd, f->n, f->n_omega, std::min(kNarrowK, k - c0), c0, k,
                              false, adjoint, Bm, bstride, X, s));
     if (f->nd) return RR_OK;
     double* nb = f->wide_tmp;
@@ -419,7 +419,7 @@ Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T,
     const int ks = prec == RR_MIXED && probes ? kn + probe_cols(kn, solve_np(kn)) : kn;
     pl.nd_fronts = d.fronts.size() * sizeof(NdFront);
     pl.nd_tasks = (size_t)d.ntasks * sizeof(NdTask);
-    pl.nd_rows = (size_t)d.rows * sizeof(int);
+    pl.nd_rows = (size_t)d.allrows * sizeof(int);
     pl.nd_border = (size_t)d.border * sizeof(int);
     pl.nd_factor = w * d.factor * elem;
     pl.nd_temp = w * d.temp * elem;

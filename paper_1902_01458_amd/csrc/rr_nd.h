@@ -14,14 +14,17 @@ struct OpDesc;
 // leaf block of them), whose p unknowns are eliminated, and the q unknowns of
 // the separators around its block.  P and Q are p and q rounded up to 16 (the
 // MFMA block edge); padding carries the identity in A and zeros elsewhere.
+// Rows number the unknowns, separators first: the solves' workspaces hold
+// only those.
 struct NdFront {
   int p, q, P, Q;
-  int row;             // its unknowns' first row in elimination order
+  int row;             // its unknowns' first row
   int bor;             // its border's first entry in the border tables
   int childA, childB;  // fronts of the two halves, -1 for a leaf
   int baseA, baseB;    // the separator's first position in the halves' borders
   int urow;            // first row of its update in the level's update arena
-  int64_t a, b12, f21;  // offsets in one shift's factors
+  int side[5];         // border offsets: left, right, low, high, end
+  int64_t a, b12, f21;  // offsets in one shift's factors (a leaf keeps A alone)
   int64_t s;           // offset of its Schur complement in the level's arena
   int64_t t;           // offset of its temporaries (P > kNdTile only)
 };
@@ -32,13 +35,15 @@ struct NdTask { int front, i, j, kind; };
 struct NdSpan { int first = 0, count = 0; };  // a range of the task list
 
 struct NdLevel {  // fronts at one depth of the tree
-  NdSpan small;      // one task a front, P <= kNdTile
+  NdSpan leaf;       // one task a leaf
+  NdSpan small;      // one task a front with halves, P <= kNdTile
   NdSpan assemble;   // P > kNdTile: tiles of A, T12 and F21
   std::vector<NdSpan> panel, update;  // per pivot tile
   NdSpan border;     // tiles of B12
-  NdSpan schur;      // tiles of S, every front
+  NdSpan schur;      // tiles of S, every front with halves
   NdSpan gather, rowsP, rowsQ;  // solves, P > kNdTile: 64 rows; 16 rows of P; of Q
   int maxP = 0, maxQ = 0;  // over the small fronts
+  int leafP = 0;           // largest P of the leaves
   int front = 0;           // the level's first front
 };
 
@@ -48,9 +53,12 @@ struct NdPlan {
   std::vector<NdLevel> levels;  // [depth]
   std::vector<NdTask> tasks;
   std::vector<int> pdof;   // row -> unknown, -1: padding
-  std::vector<int> bmap;   // border entry -> 2 * (position in a half's border) + half, -1: none
+  // border entry -> 2 * (position in a half's border) + half, -1: none; a
+  // leaf's: the position of its one neighbour among the leaf's unknowns
+  std::vector<int> bmap;
   std::vector<int> grow;   // border entry -> row (padding: the zero row)
-  int64_t rows = 0;        // rows of all fronts; row `rows` is zero
+  int64_t rows = 0;        // rows of the separators; row `rows` of the workspaces is zero
+  int64_t allrows = 0;     // with the leaves'
   int64_t border = 0;
   int64_t factor = 0;      // complex elements of one shift: factors,
   int64_t schur[2] = {};   // Schur arenas of even and odd depths,
@@ -68,7 +76,8 @@ struct NdDevice {  // device pointers of a handle
   void* factor = nullptr;
   void* schur[2] = {};
   void* temp = nullptr;
-  void *w = nullptr, *z = nullptr;  // n_omega * (rows + 1) * k: right-hand sides, solutions
+  void *w = nullptr, *z = nullptr;  // n_omega * (rows + 1) * k: separators' right-hand
+                                    // sides, then solutions; A b1 or b1
   void* u[2] = {};                  // n_omega * urows * k: updates
 };
 
@@ -79,7 +88,7 @@ hipError_t launch_nd_factor(const OpDesc& op, const NdPlan& pl, const NdDevice& 
 // X = M^-1 Bm (M^-H Bm) for columns [c0, c0 + k) of blocks with ktot columns
 // per shift, k <= 32; Bm's blocks are bstride complex elements apart (0:
 // shared) and may be X's.
-hipError_t launch_nd_solve(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
+hipError_t launch_nd_solve(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
                            int c0, int ktot, bool fp32, int adjoint, const double* Bm,
                            int64_t bstride, double* X, hipStream_t s,
                            const uint32_t* skip = nullptr);

@@ -10,6 +10,13 @@
 //   forward  up:  z = A b1,  u = (halves' u) - F21 z;     down: x1 = z - B12 x2
 //   adjoint  up:  z = b1,    u = (halves' u) - B12^H z;   down: x1 = A^H (z - F21^H x2)
 // with b1 the right-hand side plus the halves' updates u at the separator.
+// A leaf (a block of grid nodes, no halves) keeps A alone: each of its border
+// unknowns has one neighbour in it, so F12 and F21 have one real entry per
+// border unknown, S = -F21 A F12 takes no product, and its sweeps apply F12 and
+// F21 entry by entry (up z = A b, u = -F21 z, or z = A^H b, u = -F12^H z; down
+// x = A (b - F12 x2) or A^H (b - F21^H x2)), straight from and to the caller's
+// blocks.
+//
 // A and F21 are stored column-major and B12 row-major, so that every product
 // of the factorisation and of the sweeps up reads 16 consecutive elements of
 // either operand per MFMA row, and the sweeps down read 4 consecutive ones
@@ -224,32 +231,85 @@ template <typename R>
 constexpr size_t tile_lds() {
   return (size_t)(kNdTile * kLd + 16 * kPv) * sizeof(cplx<R>);
 }
+template <typename R>
+size_t front_lds(int P, bool leaf) {  // k_nd_front keeps 4 x 16 rows of P + 1 for F21
+  return (size_t)((leaf ? P : kNdTile) * (P + 1) + 16 * kPv) * sizeof(cplx<R>);
+}
 
-// One workgroup per front with P <= 64: F11 into LDS, its inverse A, then
+// A leaf's border: its unknowns' positions in the leaf and their real
+// couplings.  At most 32 nodes have at most 66 neighbours around them.
+constexpr int kLeafQ = 144;
+template <typename R>
+struct LeafBorder {
+  R f12[kLeafQ], f21[kLeafQ];
+  int at[kLeafQ];
+};
+template <typename R>
+__device__ __forceinline__ void leaf_border(LeafBorder<R>& lb, const OpDesc& op, const NdFront& fr,
+                                            const int* pdof, const int* bmap, const int* grow) {
+  for (int c = threadIdx.x; c < fr.Q; c += 256) {
+    const int at = bmap[fr.bor + c];
+    const bool real = c < fr.q;
+    lb.at[c] = real ? at : 0;
+    const int dp = real ? pdof[fr.row + at] : 0, db = real ? pdof[grow[fr.bor + c]] : 0;
+    lb.f12[c] = real ? entry<R>(op, 0.0, 0.0, dp, db).re : (R)0;
+    lb.f21[c] = real ? entry<R>(op, 0.0, 0.0, db, dp).re : (R)0;
+  }
+}
+
+// One workgroup per leaf: F11 from the stencil into LDS, its inverse A, and S.
+template <typename R>
+__global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
+  extern __shared__ __align__(16) char smem_raw[];
+  __shared__ LeafBorder<R> lb;
+  const int w = g.w0 + blockIdx.y;
+  const NdFront fr = g.fronts[g.tasks[blockIdx.x].front];
+  const double om_r = g.omega[2 * w], om_i = g.omega[2 * w + 1];
+  const int p = fr.p, P = fr.P, Q = fr.Q, ld = P + 1;
+  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
+  cplx<R>* pv = F + P * ld;
+  const int* pd = g.pdof + fr.row;
+  leaf_border<R>(lb, g.op, fr, g.pdof, g.bmap, g.grow);
+  for (int e = threadIdx.x; e < P * P; e += 256) {
+    const int c = e / P, r = e - c * P;
+    cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
+    if (r < p && c < p) v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
+    F[c * ld + r] = v;
+  }
+  __syncthreads();
+  invert_tile<R>(F, ld, P, pv, g.status);
+  cplx<R>* A = g.factor + w * g.nfactor + fr.a;
+  for (int e = threadIdx.x; e < P * P; e += 256) {
+    const int c = e / P, r = e - c * P;
+    A[e] = F[c * ld + r];
+  }
+  cplx<R>* S = g.schur_out + w * g.nout + fr.s;
+  for (int e = threadIdx.x; e < Q * Q; e += 256) {
+    const int r = e / Q, c = e - r * Q;
+    const cplx<R> v = F[lb.at[c] * ld + lb.at[r]];
+    const R f = -lb.f21[r], h = lb.f12[c];
+    S[e] = cplx<R>{f * v.re * h, f * v.im * h};
+  }
+}
+
+// One workgroup per front with halves and P <= 64: F11 into LDS, its inverse A, then
 // B12 = A F12 by 16-column strips (a wave each, F12 pulled straight into the
 // MFMA operand) and F21 through LDS into column-major order.
 template <typename R>
 __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
   cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
-  cplx<R>* pv = F + kNdTile * kLd;
   const int w = g.w0 + blockIdx.y;
   const NdFront fr = g.fronts[g.tasks[blockIdx.x].front];
   const double om_r = g.omega[2 * w], om_i = g.omega[2 * w + 1];
-  const int p = fr.p, P = fr.P, Q = fr.Q;
+  const int p = fr.p, P = fr.P, Q = fr.Q, ld = P + 1;
+  cplx<R>* pv = F + kNdTile * ld;
   const int* pd = g.pdof + fr.row;
   const int* bm = g.bmap + fr.bor;
   const int* gr = g.grow + fr.bor;
-  const bool inner = fr.childA >= 0;
-  const cplx<R>* Sh[2] = {nullptr, nullptr};
-  int Qh[2] = {0, 0};
-  if (inner) {
-    const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
-    Qh[0] = ca.Q;
-    Qh[1] = cb.Q;
-    Sh[0] = g.schur_in + w * g.nin + ca.s;
-    Sh[1] = g.schur_in + w * g.nin + cb.s;
-  }
+  const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
+  const cplx<R>* Sh[2] = {g.schur_in + w * g.nin + ca.s, g.schur_in + w * g.nin + cb.s};
+  const int Qh[2] = {ca.Q, cb.Q};
   const int base[2] = {fr.baseA, fr.baseB};
   cplx<R>* A = g.factor + w * g.nfactor + fr.a;
   cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
@@ -259,18 +319,16 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
     cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
     if (r < p && c < p) {
       v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
-      if (inner) {
-        add(v, Sh[0][(int64_t)(base[0] + r) * Qh[0] + base[0] + c]);
-        add(v, Sh[1][(int64_t)(base[1] + r) * Qh[1] + base[1] + c]);
-      }
+      add(v, Sh[0][(int64_t)(base[0] + r) * Qh[0] + base[0] + c]);
+      add(v, Sh[1][(int64_t)(base[1] + r) * Qh[1] + base[1] + c]);
     }
-    F[c * kLd + r] = v;
+    F[c * ld + r] = v;
   }
   __syncthreads();
-  invert_tile<R>(F, kLd, P, pv, g.status);
+  invert_tile<R>(F, ld, P, pv, g.status);
   for (int e = threadIdx.x; e < P * P; e += 256) {
     const int c = e / P, r = e - c * P;
-    A[e] = F[c * kLd + r];
+    A[e] = F[c * ld + r];
   }
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
   for (int t = wave; t < Q / 16; t += 4) {
@@ -301,7 +359,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
         for (int rb = 0; rb < 4; rb++)
           if (16 * rb < P)
             cmfma<R, false, false>(acc[rb].re, acc[rb].im,
-                                   F[(k0 + 4 * s + gq) * kLd + 16 * rb + i], b[s]);
+                                   F[(k0 + 4 * s + gq) * ld + 16 * rb + i], b[s]);
     }
 #pragma unroll
     for (int rb = 0; rb < 4; rb++)
@@ -313,7 +371,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
   }
   __syncthreads();
   // F21, 16 border rows a wave at a time, transposed in the wave's quarter of LDS
-  cplx<R>* tr = F + wave * 16 * kLd;  // [c][r]
+  cplx<R>* tr = F + wave * 16 * ld;  // [c][r]
   for (int t0 = 0; t0 < Q / 16; t0 += 4) {
     const int t = t0 + wave;
     if (t < Q / 16) {
@@ -329,13 +387,13 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
               add(v, Sh[h][(int64_t)(m >> 1) * Qh[h] + base[h] + l]);
             }
           }
-          tr[c * kLd + l] = v;
+          tr[c * ld + l] = v;
         }
       }
     }
     __syncthreads();
     if (t < Q / 16)
-      for (int r = gq; r < P; r += 4) F21[(int64_t)r * Q + 16 * t + i] = tr[i * kLd + r];
+      for (int r = gq; r < P; r += 4) F21[(int64_t)r * Q + 16 * t + i] = tr[i * ld + r];
     __syncthreads();
   }
 }
@@ -417,7 +475,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_schur(FactorArgs<R> g) {
   for (int m = 0; m < 2; m++)
 #pragma unroll
     for (int n = 0; n < 2; n++) zero(acc[m][n]);
-  if (fr.childA >= 0) {
+  {
     const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
     const cplx<R>* Sa = g.schur_in + w * g.nin + ca.s;
     const cplx<R>* Sb = g.schur_in + w * g.nin + cb.s;
@@ -717,6 +775,10 @@ struct SolveArgs {
   cplx<R>*w, *z;          // (shift, row, column)
   cplx<R>*uin, *uout;     // the halves' updates, this level's
   int64_t nfactor, nw, nuin, nuout;  // elements per shift
+  OpDesc op;
+  const double2* B;       // the caller's right-hand sides and solutions (their first column)
+  double2* X;
+  int64_t n, bstride, xstride;
   int k, adjoint, qsplit;
   int w0;
   const uint32_t* skip;
@@ -725,7 +787,7 @@ __device__ __forceinline__ bool skipped(const uint32_t* skip) {
   return skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Right-hand sides into elimination order: w[row][j] = B[j][pdof[row]], zero
+// The separators' right-hand sides by rows: w[row][j] = B[j][pdof[row]], zero
 // for padding and for the row after the last; back for the solution.
 constexpr int kRowTile = 32;
 template <typename R, bool OUT>
@@ -764,41 +826,188 @@ __global__ __launch_bounds__(256) void k_nd_permute(const int* pdof, int64_t row
   }
 }
 
-// acc[cb] += X(rows of one 16-row block) * V over the k-chunks of 16 in
+// Columns go through the matrix cores eight at a time in real form: MFMA
+// column c < 8 holds the real part of a block's column c and column c + 8 the
+// imaginary part, so that a complex product is two real MFMAs,
+//   [Yr | Yi] += Xr [Vr | Vi] + Xi [-Vi | Vr],
+// and a block of k columns takes 2 ceil(k / 8) of them per 16 rows and 4 inner
+// elements instead of 4 ceil(k / 16) (k = 20: 6 instead of 8).
+template <typename R>
+using v4 = typename Mf<R>::v4;
+
+// acc[b] += X(rows of one 16-row block) * V over the k-chunks of 16 in
 // [c0, nc) by step; X element (i, kk) at i + kk * ld (KF false) or
-// i * ld + kk (KF true); V row kk's first element from `row`.  KF takes k in
-// the order 4 (l / 16) + s, so that a lane's four loads are consecutive.
-template <typename R, int NB, bool KF, bool CONJ, typename RowPtr>
-__device__ __forceinline__ void rows_mul(CAcc<R> (&acc)[NB], const cplx<R>* X, int64_t ld, int c0,
+// i * ld + kk (KF true); row(kk): V's row, col[b] the lane's column in it.
+// KF takes k in the order 4 (l / 16) + s, so that a lane's four loads are
+// consecutive.  LDS: V is in LDS and read when it is used.
+template <typename R, int NB, bool KF, bool CONJ, bool LDS, typename RowPtr>
+__device__ __forceinline__ void rows_mul(v4<R> (&acc)[NB], const cplx<R>* X, int64_t ld, int c0,
                                          int nc, int step, const int (&col)[NB], RowPtr row) {
   const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
-  cplx<R> x[2][4], v[2][4][NB];
+  const bool hi = i >= 8;
+  cplx<R> x[2][4], v[2][4][LDS ? 1 : NB];
+  auto at = [&](int c, int s) { return 16 * c + (KF ? 4 * g + s : 4 * s + g); };
   auto load = [&](int buf, int c) {
 #pragma unroll
     for (int s = 0; s < 4; s++) {
-      const int kk = 16 * c + (KF ? 4 * g + s : 4 * s + g);
+      const int kk = at(c, s);
       x[buf][s] = X[KF ? i * ld + kk : (int64_t)kk * ld + i];
-      const cplx<R>* vr = row(kk);
+      if constexpr (!LDS) {
+        const cplx<R>* vr = row(kk);
 #pragma unroll
-      for (int b = 0; b < NB; b++) v[buf][s][b] = vr[col[b]];
+        for (int b = 0; b < NB; b++) v[buf][s][b] = vr[col[b]];
+      }
     }
   };
-  auto mul = [&](int buf) {
+  auto mul = [&](int buf, int c) {
 #pragma unroll
-    for (int s = 0; s < 4; s++)
+    for (int s = 0; s < 4; s++) {
+      const R xi = CONJ ? -x[buf][s].im : x[buf][s].im;
 #pragma unroll
-      for (int b = 0; b < NB; b++)
-        cmfma<R, CONJ, false>(acc[b].re, acc[b].im, x[buf][s], v[buf][s][b]);
+      for (int b = 0; b < NB; b++) {
+        cplx<R> y;
+        if constexpr (LDS) y = row(at(c, s))[col[b]];
+        else y = v[buf][s][b];
+        acc[b] = Mf<R>::op(x[buf][s].re, hi ? y.im : y.re, acc[b]);
+        acc[b] = Mf<R>::op(xi, hi ? y.re : -y.im, acc[b]);
+      }
+    }
   };
   if (c0 >= nc) return;
   load(0, c0);
   for (int c = c0; c < nc; c += 2 * step) {
     load(1, c + step < nc ? c + step : c);
-    mul(0);
+    mul(0, c);
     if (c + step >= nc) break;
     load(0, c + 2 * step < nc ? c + 2 * step : c);
-    mul(1);
+    mul(1, c + step);
   }
+}
+template <typename R, int NB>
+__device__ __forceinline__ void zero(v4<R> (&acc)[NB]) {
+#pragma unroll
+  for (int b = 0; b < NB; b++) acc[b] = v4<R>{0, 0, 0, 0};
+}
+// the lane's part of element (row(l, e), block b) of a rows x pitch array
+template <typename R>
+__device__ __forceinline__ R& part(cplx<R>* a, int64_t pitch, int r, int b) {
+  const int i = threadIdx.x & 15;
+  return reinterpret_cast<R*>(a + r * pitch + 8 * b + (i & 7))[i >> 3];
+}
+
+// A leaf, sweep up: z = A b (A^H b) in LDS, u = -F21 z (-F12^H z).
+template <typename R, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_leaf_up(SolveArgs<R> a) {
+  if (skipped(a.skip)) return;
+  extern __shared__ __align__(16) char smem_raw[];
+  __shared__ LeafBorder<R> lb;
+  constexpr int NC = 8 * NB + 1;  // pitch: columns of one row, and a bank of its own
+  const int w = a.w0 + blockIdx.y;
+  const NdFront fr = a.fronts[a.tasks[blockIdx.x].front];
+  const int P = fr.P, k = a.k;
+  cplx<R>* bs = reinterpret_cast<cplx<R>*>(smem_raw);  // P x NC
+  leaf_border<R>(lb, a.op, fr, a.pdof, a.bmap, a.grow);
+  const int r = threadIdx.x & 63;
+  const int dof = r < P ? a.pdof[fr.row + r] : -1;
+  const double2* B = a.B + (int64_t)w * a.bstride;
+  if (r < P)
+    for (int j = threadIdx.x >> 6; j < 8 * NB; j += 4) {
+      cplx<R> v{(R)0, (R)0};
+      if (dof >= 0 && j < k) {
+        const double2 b = B[j * a.n + dof];
+        v = cplx<R>{(R)b.x, (R)b.y};
+      }
+      bs[r * NC + j] = v;
+    }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  int col[NB];
+#pragma unroll
+  for (int b = 0; b < NB; b++) col[b] = 8 * b + (l & 7);
+  v4<R> acc[NB];
+  zero<R, NB>(acc);
+  const cplx<R>* A = a.factor + w * a.nfactor + fr.a;
+  if (16 * wave < P)
+    rows_mul<R, NB, ADJ, ADJ, true>(acc, A + (ADJ ? 16 * wave * P : 16 * wave), P, 0, P / 16, 1, col,
+                                    [&](int kk) { return bs + kk * NC; });
+  __syncthreads();
+  if (16 * wave < P)
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) part(bs, NC, 16 * wave + Mf<R>::row(l, e), b) = acc[b][e];
+  __syncthreads();
+  cplx<R>* u = a.uout + w * a.nuout + (int64_t)fr.urow * k;
+  for (int e = threadIdx.x; e < fr.Q * k; e += 256) {
+    const int c = e / k, j = e - c * k;
+    const R f = ADJ ? -lb.f12[c] : -lb.f21[c];
+    const cplx<R> z = bs[lb.at[c] * NC + j];
+    u[e] = cplx<R>{f * z.re, f * z.im};
+  }
+}
+
+// A leaf, sweep down: x = A (b - F12 x2) (A^H (b - F21^H x2)) into X.
+template <typename R, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_leaf_down(SolveArgs<R> a) {
+  if (skipped(a.skip)) return;
+  extern __shared__ __align__(16) char smem_raw[];
+  __shared__ LeafBorder<R> lb;
+  constexpr int NC = 8 * NB + 1;
+  const int w = a.w0 + blockIdx.y;
+  const NdFront fr = a.fronts[a.tasks[blockIdx.x].front];
+  const int P = fr.P, k = a.k;
+  cplx<R>* bs = reinterpret_cast<cplx<R>*>(smem_raw);
+  leaf_border<R>(lb, a.op, fr, a.pdof, a.bmap, a.grow);
+  const int r = threadIdx.x & 63;
+  const int dof = r < P ? a.pdof[fr.row + r] : -1;
+  const double2* B = a.B + (int64_t)w * a.bstride;
+  if (r < P)
+    for (int j = threadIdx.x >> 6; j < 8 * NB; j += 4) {
+      cplx<R> v{(R)0, (R)0};
+      if (dof >= 0 && j < k) {
+        const double2 b = B[j * a.n + dof];
+        v = cplx<R>{(R)b.x, (R)b.y};
+      }
+      bs[r * NC + j] = v;
+    }
+  const cplx<R>* W = a.w + w * a.nw;
+  const int* gr = a.grow + fr.bor;
+#pragma unroll
+  for (int side = 0; side < 4; side++) {  // a leaf unknown has one neighbour a side at most
+    __syncthreads();
+    const int s0 = fr.side[side], len = fr.side[side + 1] - s0;
+    for (int e = threadIdx.x; e < len * k; e += 256) {
+      const int c = s0 + e / k, j = e % k;
+      const cplx<R> x = W[(int64_t)gr[c] * k + j];
+      const R f = ADJ ? lb.f21[c] : lb.f12[c];
+      cplx<R>& t = bs[lb.at[c] * NC + j];
+      t.re -= f * x.re;
+      t.im -= f * x.im;
+    }
+  }
+  __syncthreads();
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  int col[NB];
+#pragma unroll
+  for (int b = 0; b < NB; b++) col[b] = 8 * b + (l & 7);
+  v4<R> acc[NB];
+  zero<R, NB>(acc);
+  const cplx<R>* A = a.factor + w * a.nfactor + fr.a;
+  if (16 * wave < P)
+    rows_mul<R, NB, ADJ, ADJ, true>(acc, A + (ADJ ? 16 * wave * P : 16 * wave), P, 0, P / 16, 1, col,
+                                    [&](int kk) { return bs + kk * NC; });
+  __syncthreads();
+  if (16 * wave < P)
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) part(bs, NC, 16 * wave + Mf<R>::row(l, e), b) = acc[b][e];
+  __syncthreads();
+  if (dof >= 0)
+    for (int j = threadIdx.x >> 6; j < k; j += 4) {
+      const cplx<R> v = bs[r * NC + j];
+      a.X[(int64_t)w * a.xstride + j * a.n + dof] = make_double2(v.re, v.im);
+    }
 }
 
 // A front with P <= 64, sweep up: one workgroup per front (and share of its
@@ -807,18 +1016,14 @@ template <typename R, int NB, bool ADJ>
 __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
-  constexpr int NC = 16 * NB;
+  constexpr int NC = 8 * NB;
   const int w = a.w0 + blockIdx.y;
   const NdFront fr = a.fronts[a.tasks[blockIdx.x].front];
   const int P = fr.P, Q = fr.Q, k = a.k;
   cplx<R>* bs = reinterpret_cast<cplx<R>*>(smem_raw);  // b1, P x NC
   cplx<R>* zs = ADJ ? bs : bs + P * NC;                // z
-  const cplx<R>* ua = nullptr;
-  const cplx<R>* ub = nullptr;
-  if (fr.childA >= 0) {
-    ua = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childA].urow * k;
-    ub = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childB].urow * k;
-  }
+  const cplx<R>* ua = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childA].urow * k;
+  const cplx<R>* ub = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childB].urow * k;
   cplx<R>* z = a.z + w * a.nw + (int64_t)fr.row * k;
   const cplx<R>* b = a.w + w * a.nw + (int64_t)fr.row * k;
   for (int e = threadIdx.x; e < P * NC; e += 256) {
@@ -826,7 +1031,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
     cplx<R> v{(R)0, (R)0};
     if (j < k) {
       v = b[r * k + j];
-      if (ua && r < fr.p) {
+      if (r < fr.p) {
         add(v, ua[(fr.baseA + r) * k + j]);
         add(v, ub[(fr.baseB + r) * k + j]);
       }
@@ -835,26 +1040,25 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
     bs[e] = v;
   }
   __syncthreads();
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int hi = (l >> 3) & 1;
   const cplx<R>* fac = a.factor + w * a.nfactor;
   int col[NB];
 #pragma unroll
-  for (int c = 0; c < NB; c++) col[c] = 16 * c + i;
+  for (int c = 0; c < NB; c++) col[c] = 8 * c + (l & 7);
+  v4<R> acc[NB];
   if (!ADJ) {
-    for (int rb = wave; rb < P / 16; rb += 4) {
-      CAcc<R> acc[NB];
-#pragma unroll
-      for (int c = 0; c < NB; c++) zero(acc[c]);
-      rows_mul<R, NB, false, false>(acc, fac + fr.a + 16 * rb, P, 0, P / 16, 1, col,
-                                    [&](int kk) { return bs + kk * NC; });
+    if (16 * wave < P) {
+      zero<R, NB>(acc);
+      rows_mul<R, NB, false, false, true>(acc, fac + fr.a + 16 * wave, P, 0, P / 16, 1, col,
+                                          [&](int kk) { return bs + kk * NC; });
 #pragma unroll
       for (int c = 0; c < NB; c++)
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-          const int r = 16 * rb + Mf<R>::row(l, e);
-          const cplx<R> v{acc[c].re[e], acc[c].im[e]};
-          zs[r * NC + col[c]] = v;
-          if (blockIdx.z == 0 && col[c] < k) z[r * k + col[c]] = v;
+          const int r = 16 * wave + Mf<R>::row(l, e);
+          part(zs, NC, r, c) = acc[c][e];
+          if (blockIdx.z == 0 && col[c] < k) part(z, k, r, c) = acc[c][e];
         }
     }
     __syncthreads();
@@ -862,11 +1066,9 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
   const int* bm = a.bmap + fr.bor;
   cplx<R>* uo = a.uout + w * a.nuout + (int64_t)fr.urow * k;
   for (int rb = wave + 4 * blockIdx.z; rb < Q / 16; rb += 4 * a.qsplit) {
-    CAcc<R> acc[NB];
-#pragma unroll
-    for (int c = 0; c < NB; c++) zero(acc[c]);
-    rows_mul<R, NB, false, ADJ>(acc, fac + (ADJ ? fr.b12 : fr.f21) + 16 * rb, Q, 0, P / 16, 1, col,
-                                [&](int kk) { return zs + kk * NC; });
+    zero<R, NB>(acc);
+    rows_mul<R, NB, false, ADJ, true>(acc, fac + (ADJ ? fr.b12 : fr.f21) + 16 * rb, Q, 0, P / 16, 1,
+                                      col, [&](int kk) { return zs + kk * NC; });
 #pragma unroll
     for (int e = 0; e < 4; e++) {
       const int r = 16 * rb + Mf<R>::row(l, e);
@@ -875,11 +1077,8 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
 #pragma unroll
       for (int c = 0; c < NB; c++)
         if (col[c] < k) {
-          cplx<R> v{(R)0, (R)0};
-          if (m >= 0) v = src[(m >> 1) * k + col[c]];
-          v.re -= acc[c].re[e];
-          v.im -= acc[c].im[e];
-          uo[r * k + col[c]] = v;
+          const R v = m >= 0 ? reinterpret_cast<const R*>(src + (m >> 1) * k + col[c])[hi] : (R)0;
+          part(uo, k, r, c) = v - acc[c][e];
         }
     }
   }
@@ -891,13 +1090,13 @@ template <typename R, int NB, bool ADJ>
 __global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
-  constexpr int NC = 16 * NB;
+  constexpr int NC = 8 * NB;
   cplx<R>* red = reinterpret_cast<cplx<R>*>(smem_raw);  // 4 x 16 x NC: the waves' sums
   const int w = a.w0 + blockIdx.y;
   const NdFront fr = a.fronts[a.tasks[blockIdx.x].front];
   const int P = fr.P, Q = fr.Q, k = a.k;
   cplx<R>* ts = red + 4 * 16 * NC;  // P x NC (adjoint)
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
   const cplx<R>* fac = a.factor + w * a.nfactor;
   cplx<R>* W = a.w + w * a.nw;
   const cplx<R>* z = a.z + w * a.nw + (int64_t)fr.row * k;
@@ -907,19 +1106,17 @@ __global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R> a) {
   const int rb = wave % nrb, ks = wave / nrb;
   int col[NB];
 #pragma unroll
-  for (int c = 0; c < NB; c++) col[c] = min(16 * c + i, k - 1);
-  CAcc<R> acc[NB];
-#pragma unroll
-  for (int c = 0; c < NB; c++) zero(acc[c]);
+  for (int c = 0; c < NB; c++) col[c] = min(8 * c + (l & 7), k - 1);
+  v4<R> acc[NB];
+  zero<R, NB>(acc);
   if (ks < nsplit)
-    rows_mul<R, NB, true, ADJ>(acc, fac + (ADJ ? fr.f21 : fr.b12) + (int64_t)16 * rb * Q, Q, ks,
-                               Q / 16, nsplit, col,
-                               [&](int kk) { return W + (int64_t)gr[kk] * k; });
+    rows_mul<R, NB, true, ADJ, false>(acc, fac + (ADJ ? fr.f21 : fr.b12) + (int64_t)16 * rb * Q, Q,
+                                      ks, Q / 16, nsplit, col,
+                                      [&](int kk) { return W + (int64_t)gr[kk] * k; });
 #pragma unroll
   for (int c = 0; c < NB; c++)
 #pragma unroll
-    for (int e = 0; e < 4; e++)
-      red[(wave * 16 + Mf<R>::row(l, e)) * NC + 16 * c + i] = cplx<R>{acc[c].re[e], acc[c].im[e]};
+    for (int e = 0; e < 4; e++) part(red, NC, wave * 16 + Mf<R>::row(l, e), c) = acc[c][e];
   __syncthreads();
   for (int e = threadIdx.x; e < P * NC; e += 256) {
     const int r = e / NC, j = e % NC;
@@ -937,20 +1134,17 @@ __global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R> a) {
   }
   if (!ADJ) return;
   __syncthreads();
-  int lcol[NB];
-#pragma unroll
-  for (int c = 0; c < NB; c++) lcol[c] = 16 * c + i;
   if (wave >= nrb) return;
 #pragma unroll
-  for (int c = 0; c < NB; c++) zero(acc[c]);
-  rows_mul<R, NB, true, true>(acc, fac + fr.a + (int64_t)16 * wave * P, P, 0, P / 16, 1, lcol,
-                              [&](int kk) { return ts + kk * NC; });
+  for (int c = 0; c < NB; c++) col[c] = 8 * c + (l & 7);
+  zero<R, NB>(acc);
+  rows_mul<R, NB, true, true, true>(acc, fac + fr.a + (int64_t)16 * wave * P, P, 0, P / 16, 1, col,
+                                    [&](int kk) { return ts + kk * NC; });
 #pragma unroll
   for (int c = 0; c < NB; c++)
 #pragma unroll
     for (int e = 0; e < 4; e++)
-      if (lcol[c] < k)
-        x[(16 * wave + Mf<R>::row(l, e)) * k + lcol[c]] = cplx<R>{acc[c].re[e], acc[c].im[e]};
+      if (col[c] < k) part(x, k, 16 * wave + Mf<R>::row(l, e), c) = acc[c][e];
 }
 
 // P > 64: b1 of 64 rows (into w, or z for the adjoint sweep)
@@ -983,14 +1177,14 @@ enum { ND_Z = 0,    // z = A w               (forward, up)
 template <typename R, int NB, int MODE, bool ADJ>
 __global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R> a) {
   if (skipped(a.skip)) return;
-  constexpr int NC = 16 * NB;
+  constexpr int NC = 8 * NB;
   constexpr bool KF = MODE == ND_X || MODE == ND_AH;
   __shared__ cplx<R> red[4 * 16 * NC];
   const int w = a.w0 + blockIdx.y;
   const NdTask t = a.tasks[blockIdx.x];
   const NdFront fr = a.fronts[t.front];
   const int P = fr.P, Q = fr.Q, k = a.k;
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15;
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
   cplx<R>* W = a.w + w * a.nw;
   cplx<R>* Z = a.z + w * a.nw;
   const int* gr = a.grow + fr.bor;
@@ -1002,19 +1196,17 @@ __global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R> a) {
   const cplx<R>* X = a.factor + w * a.nfactor + off + (KF ? 16 * t.i * ld : 16 * t.i);
   int col[NB];
 #pragma unroll
-  for (int c = 0; c < NB; c++) col[c] = min(16 * c + i, k - 1);
-  CAcc<R> acc[NB];
-#pragma unroll
-  for (int c = 0; c < NB; c++) zero(acc[c]);
+  for (int c = 0; c < NB; c++) col[c] = min(8 * c + (l & 7), k - 1);
+  v4<R> acc[NB];
+  zero<R, NB>(acc);
   const cplx<R>* V = (MODE == ND_Z ? W : Z) + (int64_t)fr.row * k;
-  rows_mul<R, NB, KF, ADJ>(acc, X, ld, wave, K / 16, 4, col, [&](int kk) {
+  rows_mul<R, NB, KF, ADJ, false>(acc, X, ld, wave, K / 16, 4, col, [&](int kk) {
     return MODE == ND_X ? W + (int64_t)gr[kk] * k : V + (int64_t)kk * k;
   });
 #pragma unroll
   for (int c = 0; c < NB; c++)
 #pragma unroll
-    for (int e = 0; e < 4; e++)
-      red[(wave * 16 + Mf<R>::row(l, e)) * NC + 16 * c + i] = cplx<R>{acc[c].re[e], acc[c].im[e]};
+    for (int e = 0; e < 4; e++) part(red, NC, wave * 16 + Mf<R>::row(l, e), c) = acc[c][e];
   __syncthreads();
   for (int e = threadIdx.x; e < 16 * NC; e += 256) {
     const int r = 16 * t.i + e / NC, j = e % NC;
@@ -1074,7 +1266,8 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
       a.schur_in = (cplx<R>*)d.schur[~dep & 1];
       a.nout = pl.schur[dep & 1];
       a.nin = pl.schur[~dep & 1];
-      run(k_nd_front<R>, lv.small, lds);
+      run(k_nd_leaf<R>, lv.leaf, front_lds<R>(lv.leafP, true));
+      run(k_nd_front<R>, lv.small, front_lds<R>(lv.maxP, false));
       run(k_nd_assemble<R>, lv.assemble, lds);
       for (size_t k = 0; k < lv.panel.size(); k++) {
         run(k_nd_panel<R>, lv.panel[k], lds);
@@ -1088,11 +1281,12 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
 }
 
 template <typename R, int NB, bool ADJ>
-hipError_t solve_run(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k, int c0,
+hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k, int c0,
                      int ktot, const double* Bm, int64_t bstride, double* X, hipStream_t s,
                      const uint32_t* skip) {
-  constexpr int NC = 16 * NB;
+  constexpr int NC = 8 * NB;
   SolveArgs<R> a{};
+  a.op = op;
   a.fronts = d.fronts;
   a.pdof = d.pdof;
   a.bmap = d.bmap;
@@ -1108,6 +1302,11 @@ hipError_t solve_run(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega
   const unsigned rb = (unsigned)((pl.rows + 1 + kRowTile - 1) / kRowTile);
   const double2* B = (const double2*)Bm + (int64_t)c0 * n;
   double2* Xo = (double2*)X + (int64_t)c0 * n;
+  a.B = B;
+  a.X = Xo;
+  a.n = n;
+  a.bstride = bstride;
+  a.xstride = (int64_t)ktot * n;
   for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
     const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
     a.w0 = w0;
@@ -1128,6 +1327,7 @@ hipError_t solve_run(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega
                        k, bstride, B, (double2*)nullptr, a.w, w0, skip);
     for (int dep = (int)pl.levels.size() - 1; dep >= 0; dep--) {
       const NdLevel& lv = level(dep);
+      run(k_nd_leaf_up<R, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
       if (lv.small.count) {
         // border rows over several workgroups where the fronts leave CUs idle
         const int64_t wgs = (int64_t)lv.small.count * nw;
@@ -1146,6 +1346,7 @@ hipError_t solve_run(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega
           (size_t)(64 + (ADJ ? lv.maxP : 0)) * NC * sizeof(cplx<R>));
       run(k_nd_rows<R, NB, ND_X, ADJ>, lv.rowsP, 0);
       if (ADJ) run(k_nd_rows<R, NB, ND_AH, ADJ>, lv.rowsP, 0);
+      run(k_nd_leaf_down<R, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
     }
     hipLaunchKernelGGL((k_nd_permute<R, true>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n, k,
                        (int64_t)ktot * n, (const double2*)nullptr, Xo, a.w, w0, skip);
@@ -1160,6 +1361,7 @@ hipError_t prepare_r() {
     if (e == hipSuccess && bytes > 64 * 1024)
       e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   };
+  lds((const void*)k_nd_leaf<R>, tile_lds<R>());
   lds((const void*)k_nd_front<R>, tile_lds<R>());
   lds((const void*)k_nd_assemble<R>, tile_lds<R>());
   lds((const void*)k_nd_panel<R>, tile_lds<R>());
@@ -1181,19 +1383,21 @@ hipError_t launch_nd_factor(const OpDesc& op, const NdPlan& pl, const NdDevice& 
               : factor_run<double>(op, pl, d, omega, n_omega, status, s);
 }
 
-hipError_t launch_nd_solve(const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
+hipError_t launch_nd_solve(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
                            int c0, int ktot, bool fp32, int adjoint, const double* Bm,
                            int64_t bstride, double* X, hipStream_t s, const uint32_t* skip) {
   auto go = [&](auto r, auto nb, auto adj) {
     return solve_run<decltype(r), decltype(nb)::value, decltype(adj)::value>(
-        pl, d, n, n_omega, k, c0, ktot, Bm, bstride, X, s, skip);
+        op, pl, d, n, n_omega, k, c0, ktot, Bm, bstride, X, s, skip);
   };
   auto by_adj = [&](auto r, auto nb) {
     return adjoint ? go(r, nb, std::true_type{}) : go(r, nb, std::false_type{});
   };
   auto by_nb = [&](auto r) {
-    return k <= 16 ? by_adj(r, std::integral_constant<int, 1>{})
-                   : by_adj(r, std::integral_constant<int, 2>{});
+    return k <= 8    ? by_adj(r, std::integral_constant<int, 1>{})
+           : k <= 16 ? by_adj(r, std::integral_constant<int, 2>{})
+           : k <= 24 ? by_adj(r, std::integral_constant<int, 3>{})
+                     : by_adj(r, std::integral_constant<int, 4>{});
   };
   return fp32 ? by_nb(0.0f) : by_nb(0.0);
 }

@@ -91,14 +91,17 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     for (int f = first[d]; f < first[d + 1]; f++) {
       NdFront& fr = pl.fronts[f];
       const int64_t P = fr.P, Q = fr.Q;
-      fr.row = (int)pl.rows;
-      pl.rows += P;
+      const bool leaf = fr.childA < 0;
+      if (!leaf) {
+        fr.row = (int)pl.rows;
+        pl.rows += P;
+      }
       fr.bor = (int)pl.border;
       pl.border += Q;
       fr.a = pl.factor;
       fr.b12 = fr.a + P * P;
-      fr.f21 = fr.b12 + P * Q;
-      pl.factor = fr.f21 + P * Q;
+      fr.f21 = fr.b12 + (leaf ? 0 : P * Q);
+      pl.factor = fr.f21 + (leaf ? 0 : P * Q);
       fr.s = s;
       s += Q * Q;
       fr.urow = (int)u;
@@ -112,9 +115,19 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     pl.urows[d & 1] = std::max(pl.urows[d & 1], u);
     pl.temp = std::max(pl.temp, t);
   }
+  pl.allrows = pl.rows;
+  for (NdFront& fr : pl.fronts)
+    if (fr.childA < 0) {
+      fr.row = (int)pl.allrows;
+      pl.allrows += fr.P;
+    }
   auto tiles = [](int v) { return (v + kNdTile - 1) / kNdTile; };
   for (const NdFront& fr : pl.fronts) {
     const int64_t np = tiles(fr.P), nq = tiles(fr.Q);
+    if (fr.childA < 0) {
+      pl.ntasks++;
+      continue;
+    }
     pl.ntasks += nq * nq;  // schur
     if (fr.P <= kNdTile) {
       pl.ntasks++;
@@ -126,7 +139,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
   if (!tables) return;
 
   std::vector<int> row_of((size_t)nx * ny);
-  pl.pdof.assign(pl.rows, -1);
+  pl.pdof.assign(pl.allrows, -1);
   for (size_t f = 0; f < blocks.size(); f++) {
     const Block& b = blocks[f];
     const int i0 = !b.leaf && b.across_x ? b.mid : b.i0, i1 = !b.leaf && b.across_x ? b.mid + 1 : b.i1;
@@ -153,6 +166,8 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
       fr.baseA = h[0]->off[b.across_x ? 1 : 3];  // A's right / high side is the separator
       fr.baseB = h[1]->off[b.across_x ? 0 : 2];  // B's left / low side
     }
+    std::copy(b.off, b.off + 5, fr.side);
+    const int across = b.j1 - b.j0;  // a leaf's unknowns: i, then j, then u and v
     for (int side = 0; side < 4; side++) {
       const bool along_y = side < 2;  // left and right run along y
       const int c0 = along_y ? b.j0 : b.i0;
@@ -175,6 +190,11 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
           const int at = fr.bor + b.off[side] + 2 * e + u;
           pl.grow[at] = row_of[node] + u;
           if (half >= 0) pl.bmap[at] = 2 * (h[half]->off[side] + 2 * pos + u) + half;
+          if (b.leaf) {
+            const int i = along_y ? (side == 0 ? 0 : b.i1 - b.i0 - 1) : e;
+            const int j = along_y ? e : (side == 2 ? 0 : across - 1);
+            pl.bmap[at] = 2 * (i * across + j) + u;
+          }
         }
       }
     }
@@ -186,11 +206,19 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     NdLevel& lv = pl.levels[d];
     const int f0 = first[d], f1 = first[d + 1];
     lv.front = f0;
+    open(lv.leaf);
+    for (int f = f0; f < f1; f++)
+      if (pl.fronts[f].childA < 0) {
+        pl.tasks.push_back({f, 0, 0, 0});
+        lv.leafP = std::max(lv.leafP, pl.fronts[f].P);
+      }
+    close(lv.leaf);
     // calls emit(front) for the fronts of one kind, collecting a span
     auto each = [&](NdSpan& sp, bool small, bool large, auto emit) {
       open(sp);
       for (int f = f0; f < f1; f++)
-        if (pl.fronts[f].P <= kNdTile ? small : large) emit(f, pl.fronts[f]);
+        if (pl.fronts[f].childA >= 0 && (pl.fronts[f].P <= kNdTile ? small : large))
+          emit(f, pl.fronts[f]);
       close(sp);
     };
     each(lv.small, true, false, [&](int f, const NdFront& fr) {
@@ -279,7 +307,7 @@ extern "C" int64_t rr_nd_plan(int32_t nx, int32_t ny, int32_t what, int64_t* out
     for (const rr::NdTask& t : pl.tasks)
       for (int v : {t.front, t.i, t.j, t.kind}) put(v);
   } else if (what == 5) {
-    for (int64_t v : {pl.rows, pl.border, pl.factor, pl.schur[0], pl.schur[1], pl.temp,
+    for (int64_t v : {pl.rows, pl.allrows, pl.border, pl.factor, pl.schur[0], pl.schur[1], pl.temp,
                       pl.urows[0], pl.urows[1], pl.ntasks})
       put(v);
   } else {

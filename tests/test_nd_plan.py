@@ -43,8 +43,8 @@ def test_plan_carries_a_multifrontal_elimination(nx, ny):
     coef[..., 0] -= 8.0
     coef[..., 6] -= 8.0
     M = op.shifted(op.assemble(coef), 0.7 - 0.1j).tocsr()
-    n, rows = 2 * nx * ny, int(totals[0])
-    assert sorted(pdof[pdof >= 0]) == list(range(n)) and len(pdof) == rows
+    n, rows, allrows = 2 * nx * ny, int(totals[0]), int(totals[1])
+    assert sorted(pdof[pdof >= 0]) == list(range(n)) and len(pdof) == allrows
     assert grow.max(initial=rows) == rows
     F = {}
     for f in range(len(fronts) - 1, -1, -1):
@@ -58,6 +58,13 @@ def test_plan_carries_a_multifrontal_elimination(nx, ny):
         both = np.concatenate([piv, bor])
         D[:] = M[both][:, both].toarray()
         D[p:, p:] = 0.0
+        if x["childA"] < 0:  # a border unknown has one neighbour in a leaf
+            at = bmap[x["bor"]:x["bor"] + q]
+            only = np.zeros((p, q), dtype=bool)
+            only[at, np.arange(q)] = True
+            assert (D[:p, p:][~only] == 0).all() and (D[p:, :p][~only.T] == 0).all()
+        else:
+            assert x["row"] + x["P"] <= rows
         for half, name in enumerate("AB"):
             c = x["child" + name]
             if c < 0:
@@ -77,9 +84,9 @@ def test_plan_carries_a_multifrontal_elimination(nx, ny):
         F[f] = {"A": A, "B12": B12, "F21": D[p:, :p], "S": D[p:, p:] - D[p:, :p] @ B12}
     b = rng.standard_normal(n) + 1j * rng.standard_normal(n)
     for adjoint in (False, True):
-        rhs = np.zeros(rows + 1, dtype=complex)
-        rhs[:rows][pdof >= 0] = b[pdof[pdof >= 0]]
-        u, z, sol = {}, {}, np.zeros(rows + 1, dtype=complex)
+        rhs = np.zeros(allrows, dtype=complex)
+        rhs[pdof >= 0] = b[pdof[pdof >= 0]]
+        u, z, sol, X = {}, {}, np.zeros(rows + 1, dtype=complex), np.zeros(n, dtype=complex)
         for f in range(len(fronts) - 1, -1, -1):
             x, g = fronts[f], F[f]
             b1 = rhs[x["row"]:x["row"] + x["p"]].copy()
@@ -96,11 +103,11 @@ def test_plan_carries_a_multifrontal_elimination(nx, ny):
         for f, x in enumerate(fronts):
             x2 = sol[grow[x["bor"]:x["bor"] + x["q"]]]
             g = F[f]
-            sol[x["row"]:x["row"] + x["p"]] = (
-                g["A"].conj().T @ (z[f] - g["F21"].conj().T @ x2) if adjoint
-                else z[f] - g["B12"] @ x2)
-        X = np.zeros(n, dtype=complex)
-        X[pdof[pdof >= 0]] = sol[:rows][pdof >= 0]
+            x1 = (g["A"].conj().T @ (z[f] - g["F21"].conj().T @ x2) if adjoint
+                  else z[f] - g["B12"] @ x2)
+            if x["childA"] >= 0:
+                sol[x["row"]:x["row"] + x["p"]] = x1
+            X[pdof[x["row"]:x["row"] + x["p"]]] = x1
         K = (M.conj().T if adjoint else M)
         assert np.linalg.norm(K @ X - b) <= 1e-11 * np.linalg.norm(b)
 
@@ -108,7 +115,7 @@ def test_plan_carries_a_multifrontal_elimination(nx, ny):
 @pytest.mark.parametrize("nx,ny", GRIDS + [(300, 200), (20, 400)])
 def test_plan_arenas_and_tasks(nx, ny):
     fronts, pdof, bmap, grow, tasks, totals = plan(nx, ny)
-    rows, border, factor, s0, s1, temp, u0, u1, ntasks = map(int, totals)
+    rows, allrows, border, factor, s0, s1, temp, u0, u1, ntasks = map(int, totals)
     assert len(tasks) == ntasks and len(bmap) == len(grow) == border
 
     def disjoint(spans, size):
@@ -118,10 +125,11 @@ def test_plan_arenas_and_tasks(nx, ny):
             end = lo + n
         assert end <= size
 
-    disjoint([(x["row"], x["P"]) for x in fronts], rows)
+    disjoint([(x["row"], x["P"]) for x in fronts], allrows)
     disjoint([(x["bor"], x["Q"]) for x in fronts], border)
     disjoint([(x[o], n) for x in fronts for o, n in (("a", x["P"] ** 2), ("b12", x["P"] * x["Q"]),
-                                                      ("f21", x["P"] * x["Q"])) if n], factor)
+                                                      ("f21", x["P"] * x["Q"]))
+              if o == "a" or x["childA"] >= 0], factor)
     want = {}
 
     def expect(f, key, n=1):
@@ -133,9 +141,13 @@ def test_plan_arenas_and_tasks(nx, ny):
         disjoint([(x["urow"], x["Q"]) for _, x in level], (u0, u1)[d % 2])
         disjoint([(x["t"], x["P"] * x["Q"] + 2 * TILE * x["P"] + 4 * TILE * TILE)
                   for _, x in level if x["P"] > TILE], temp)
+        assert all(x["P"] <= TILE for _, x in level if x["childA"] < 0)
     for f, x in enumerate(fronts):
         np_, nq = -(-x["P"] // TILE), -(-x["Q"] // TILE)
         T = [(i, j) for i in range(np_) for j in range(np_)]
+        if x["childA"] < 0:
+            expect(f, (0, 0, 0))
+            continue
         for i in range(nq):
             for j in range(nq):
                 expect(f, (i, j, 0))  # S
