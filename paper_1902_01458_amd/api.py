@@ -386,18 +386,30 @@ def autotune(prob: BurgersProblem, omegas, k: int, precision: str = "fp64",
     return {"tile": t.tile, "grid": t.grid, "superblock": t.superblock, "ms": ms.value}
 
 
+# Device memory of one of the sweep's handles: the shifts of a chunk are taken a
+# few at a time in the same memory (freed handles keep up to 9 GB of blocks for
+# the next), and 8 GiB hold enough of them to fill the GPU (7 at 512 x 256)
+_SWEEP_BYTES = 8 << 30
+
+
 def _sweep_chunk(prob, om, k, seed, q, precision, tile, grid, superblock=0):
-    f = factor(prob, om, precision, k_max=k, tile=tile, grid=grid, superblock=superblock)
-    g = None
-    try:
-        g = capture(f, k, seed, q, "av", refactor=False)
-        out = g.launch()
-        f.check()
-        return out["sigma_B"].clone(), out["sigma_AV"].clone()
-    finally:
-        if g is not None:
-            g.free()
-        f.free()
+    per = factor_bytes(prob.nx, prob.ny, 1, k, precision, tile if superblock else 0)
+    parts = max(1, min(om.size, -(-om.size * per // _SWEEP_BYTES)))
+    sB, sAV = [], []
+    for part in np.array_split(om, parts):
+        f = factor(prob, part, precision, k_max=k, tile=tile, grid=grid, superblock=superblock)
+        g = None
+        try:
+            g = capture(f, k, seed, q, "av", refactor=False)
+            out = g.launch()
+            f.check()
+            sB.append(out["sigma_B"])
+            sAV.append(out["sigma_AV"])
+        finally:
+            if g is not None:
+                g.free()
+            f.free()
+    return torch.cat(sB), torch.cat(sAV)
 
 
 def _chunk_size(prob, k, precision, tile, memory_fraction, n_omega):

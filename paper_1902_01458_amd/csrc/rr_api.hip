@@ -55,40 +55,116 @@ rr_alloc_fn g_alloc = nullptr;
 rr_free_fn g_dealloc = nullptr;
 void* g_alloc_ctx = nullptr;
 
+// Blocks of freed handles (default allocator, 1 MiB and more), kept for the
+// next handle.  Freshly mapped device memory has to be cleared by the driver:
+// a program that makes and frees a 23 GB handle per sweep of 64 shifts at 256
+// x 128 spent 600 ms a sweep waiting for that once the card's cleared memory
+// was used up, against 56 ms of work.  Bounded at 1/32 of the device's memory
+// (9 GB); a block that eight further handles did not use is given back, and
+// all of a device's are when an allocation fails or the allocator changes.
+// Blocks enter idle (the device is synchronised first), so any stream may
+// take one.
+class BlockPool {
+ public:
+  static constexpr size_t kMin = size_t(1) << 20;
+  void* take(size_t bytes, size_t* got) {
+    std::lock_guard<std::mutex> lock(mu_);
+    const int dev = device();
+    size_t best = blocks_.size();
+    for (size_t i = 0; i < blocks_.size(); i++)
+      if (blocks_[i].dev == dev && blocks_[i].bytes >= bytes &&
+          blocks_[i].bytes <= bytes + bytes / 8 &&
+          (best == blocks_.size() || blocks_[i].bytes < blocks_[best].bytes))
+        best = i;
+    if (best == blocks_.size()) return nullptr;
+    void* p = blocks_[best].p;
+    *got = blocks_[best].bytes;
+    blocks_.erase(blocks_.begin() + best);
+    return p;
+  }
+  // false: not kept, the caller frees it
+  bool give(int dev, void* p, size_t bytes) {
+    if (bytes < kMin) return false;
+    std::lock_guard<std::mutex> lock(mu_);
+    size_t held = bytes;
+    for (const Block& b : blocks_)
+      if (b.dev == dev) held += b.bytes;
+    if (total_.size() <= (size_t)dev) total_.resize(dev + 1, 0);
+    size_t avail = 0;
+    if (!total_[dev] && hipMemGetInfo(&avail, &total_[dev]) != hipSuccess) return false;
+    if (held > total_[dev] / 32) return false;
+    blocks_.push_back({dev, p, bytes, age_});
+    return true;
+  }
+  void new_handle() {  // gives back what eight handles did not use
+    std::lock_guard<std::mutex> lock(mu_);
+    age_++;
+    drop([&](const Block& b) { return age_ - b.age > 8; });
+  }
+  void trim() {
+    std::lock_guard<std::mutex> lock(mu_);
+    drop([](const Block&) { return true; });
+  }
+
+ private:
+  struct Block {
+    int dev;
+    void* p;
+    size_t bytes;
+    uint64_t age;
+  };
+  static int device() {
+    int d = 0;
+    return hipGetDevice(&d) == hipSuccess ? d : 0;
+  }
+  template <typename Pred>
+  void drop(Pred pred) {
+    for (size_t i = blocks_.size(); i-- > 0;)
+      if (pred(blocks_[i])) {
+        (void)hipFree(blocks_[i].p);
+        blocks_.erase(blocks_.begin() + i);
+      }
+  }
+  std::mutex mu_;
+  std::vector<Block> blocks_;
+  std::vector<size_t> total_;  // memory per device
+  uint64_t age_ = 0;
+};
+BlockPool& pool() {  // never destroyed: the runtime may be gone at process exit
+  static BlockPool* p = new BlockPool();
+  return *p;
+}
+
 template <typename T>
 rr_status dalloc(rr_factors* f, T** p, size_t bytes) {
   if (bytes == 0) bytes = 256;
+  size_t got = bytes;
   if (f->alloc) {
     *p = (T*)f->alloc(bytes, f->alloc_stream, f->alloc_ctx);
     if (!*p) return fail(RR_ERR_NOMEM, "allocator returned NULL for " + std::to_string(bytes));
-  } else {
+  } else if (bytes < BlockPool::kMin || !(*p = (T*)pool().take(bytes, &got))) {
     hipError_t e = hipMalloc((void**)p, bytes);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      pool().trim();
+      e = hipMalloc((void**)p, bytes);
+    }
     if (e != hipSuccess) {
       (void)hipGetLastError();
       *p = nullptr;
       return fail(RR_ERR_NOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
     }
   }
+  f->blocks.push_back({*p, got});
   f->bytes += bytes;
   return RR_OK;
 }
 
+// The handle's device is idle.
 void free_all(rr_factors* f) {
-  void* ps[] = {f->coef, f->phi, f->U, f->omega, f->tiles, f->xs, f->cbuf, f->flags, f->ctrl,
-                f->theta,
-                f->work1, f->work2, f->work3, f->small.partial, f->small.G, f->small.R,
-                f->small.Rinv, f->small.W, f->small.Ut, f->small.rho, f->small.shifted, f->grad_partial,
-                f->gm.V, f->gm.t, f->gm.H, f->gm.h, f->gm.beta, f->gm.y, f->gm.partial,
-                f->pc_dinv, f->kv[0], f->kv[1], f->kv[2], f->kv[3], f->kv[4], f->kv[5],
-                f->kv[6], f->kpart, f->kscal, f->kbnorm, f->kactive, f->small.big1,
-                f->small.big2, f->wide_tmp, f->probe_b, f->probe_x, f->probe_r, f->probe_z,
-                f->ndd.fronts, f->ndd.tasks, f->ndd.pdof, f->ndd.bmap, f->ndd.grow,
-                f->ndd.factor, f->ndd.schur[0], f->ndd.schur[1], f->ndd.temp, f->ndd.w,
-                f->ndd.z, f->ndd.u[0], f->ndd.u[1]};
-  for (void* p : ps) {
-    if (!p) continue;
-    if (f->dealloc) f->dealloc(p, f->alloc_ctx);
-    else (void)hipFree(p);
+  for (const auto& b : f->blocks) {
+    if (f->dealloc) f->dealloc(b.first, f->alloc_ctx);
+    else if (!pool().give(f->device, b.first, b.second)) (void)hipFree(b.first);
   }
 }
 
@@ -564,6 +640,8 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     return fail(RR_ERR_INVALID, "coef/phi/U must be device pointers");
 
   rr_factors* f = new rr_factors();
+  (void)hipGetDevice(&f->device);
+  pool().new_handle();
   f->alloc = g_alloc;
   f->dealloc = g_dealloc;
   f->alloc_ctx = g_alloc_ctx;
@@ -1069,14 +1147,19 @@ size_t rr_bytes(const rr_factors* f) { return f ? f->bytes : 0; }
 
 void rr_factors_free(rr_factors* f) {
   if (!f) return;
+  int dev = f->device;
+  (void)hipGetDevice(&dev);
+  if (dev != f->device) (void)hipSetDevice(f->device);
   (void)hipDeviceSynchronize();
   free_all(f);
+  if (dev != f->device) (void)hipSetDevice(dev);
   delete f;
 }
 
 rr_status rr_set_allocator(rr_alloc_fn alloc, rr_free_fn dealloc, void* ctx) {
   if ((alloc == nullptr) != (dealloc == nullptr))
     return fail(RR_ERR_INVALID, "alloc and dealloc must both be set or both be NULL");
+  pool().trim();
   g_alloc = alloc;
   g_dealloc = dealloc;
   g_alloc_ctx = ctx;

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/rr.h"
@@ -381,6 +382,8 @@ struct rr_factors {
   double* grad_partial = nullptr;
   int grad_nchunk = 0;
   size_t bytes = 0;
+  std::vector<std::pair<void*, size_t>> blocks;  // everything it allocated
+  int device = 0;
   // allocator the handle was created with (NULL: hipMalloc / hipFree)
   rr_alloc_fn alloc = nullptr;
   rr_free_fn dealloc = nullptr;
