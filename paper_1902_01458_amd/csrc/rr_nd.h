@@ -24,6 +24,7 @@ struct NdFront {
   int baseA, baseB;    // the separator's first position in the halves' borders
   int urow;            // first row of its update in the level's update arena
   int side[5];         // border offsets: left, right, low, high, end
+  int across;          // a leaf's nodes along y
   int64_t a, b12, f21;  // offsets in one shift's factors (a leaf keeps A alone)
   int64_t s;           // offset of its Schur complement in the level's arena
   int64_t t;           // offset of its temporaries (P > kNdTile only)

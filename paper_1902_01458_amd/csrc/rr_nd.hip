@@ -89,8 +89,11 @@ __device__ __forceinline__ void add(cplx<R>& a, cplx<R> b) {
 // one wave inverts the 16 x 16 pivot block in registers (lane l: row l % 16,
 // columns 4 (l / 16) .. + 3; the pivot row comes by DPP row broadcasts); then
 // the block row is multiplied by it and the other block rows updated on MFMA,
-// a wave per block row.  A zero or non-finite pivot latches ST_SINGULAR and
-// is replaced by 1.
+// a wave per block row.  Bound by its serial chain, so the next pivot block
+// is updated and inverted first, by a wave of its own, while the other waves
+// update the rest (the pivot row's wave, which has no row to update, takes
+// that wave's row).  A zero or non-finite pivot latches ST_SINGULAR and is
+// replaced by 1.
 // ---------------------------------------------------------------------------
 template <int S>
 __device__ __forceinline__ float row_bcast(float v) {
@@ -107,6 +110,22 @@ template <int S, typename R>
 __device__ __forceinline__ cplx<R> row_bcast(cplx<R> v) {
   return cplx<R>{row_bcast<S>(v.re), row_bcast<S>(v.im)};
 }
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// 1 / x: the hardware reciprocal and two Newton steps (the division's length
+// is on the chain), the division itself near the ends of the range
+__device__ __forceinline__ double recip(double x) {
+  if (!(x > 1e-290 && x < 1e290)) return 1.0 / x;
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ __forceinline__ float recip(float x) { return 1.0f / x; }
 
 template <typename R, int S>
 struct Inv16 {
@@ -115,14 +134,16 @@ struct Inv16 {
       constexpr int G = S >> 2, C = S & 3;
       const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
       const int src = 16 * G + i;
-      cplx<R> f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
-      cplx<R> d = row_bcast<S>(f);                             // the pivot
+      const cplx<R> f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
+      cplx<R> d{lane_value(a[C].re, 16 * G + S), lane_value(a[C].im, 16 * G + S)};
       const R mag = d.re * d.re + d.im * d.im;
+      R rm = recip(mag);
       if (!(mag > (R)0) || !isfinite(mag)) {
         bad = true;
         d = cplx<R>{(R)1, (R)0};
+        rm = (R)1;
       }
-      const cplx<R> inv = cinv(d);
+      const cplx<R> inv{d.re * rm, -d.im * rm};
       cplx<R> m = cmul(f, inv);
       const bool piv = i == S;
       if (piv) m = cplx<R>{-inv.re, -inv.im};
@@ -141,70 +162,86 @@ struct Inv16 {
   }
 };
 
-constexpr int kPv = 17;  // pitch of the 16 x 16 pivot inverse
+constexpr int kPv = 17;             // pitch of the 16 x 16 pivot inverses
+constexpr int kPvSize = 2 * 16 * kPv;  // two of them, by pivot parity
 
 template <typename R>
-__device__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pv, uint32_t* status) {
+__device__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pvs, uint32_t* status) {
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
   const int nb = T >> 4;
+  // invert pivot block kb from LDS into its pv
+  auto pivot = [&](int kb) {
+    cplx<R> a[4];
+#pragma unroll
+    for (int c = 0; c < 4; c++) a[c] = F[(16 * kb + 4 * g + c) * ld + 16 * kb + i];
+    bool bad = false;
+    Inv16<R, 0>::run(a, bad);
+    if (bad && l == 0) latch(status, ST_SINGULAR);
+#pragma unroll
+    for (int c = 0; c < 4; c++) pvs[(kb & 1) * 16 * kPv + i * kPv + 4 * g + c] = a[c];
+  };
+  auto put = [&](int rb, int j, const CAcc<R>& acc) {
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+      F[(16 * j + i) * ld + 16 * rb + Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
+  };
+  if (wave == 0) pivot(0);
+  __syncthreads();
   for (int kb = 0; kb < nb; kb++) {
-    if (wave == 0) {
-      cplx<R> a[4];
-#pragma unroll
-      for (int c = 0; c < 4; c++) a[c] = F[(16 * kb + 4 * g + c) * ld + 16 * kb + i];
-      bool bad = false;
-      Inv16<R, 0>::run(a, bad);
-      if (bad && l == 0) latch(status, ST_SINGULAR);
-#pragma unroll
-      for (int c = 0; c < 4; c++) pv[i * kPv + 4 * g + c] = a[c];
-    }
-    __syncthreads();
+    const cplx<R>* pv = pvs + (kb & 1) * 16 * kPv;
+    const int nx = kb + 1;
     if (wave != kb && wave < nb) {  // block row kb: R_j = pv F(kb, j), j = wave
       CAcc<R> acc;
       zero(acc);
-      cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
+      const cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
 #pragma unroll
       for (int s = 0; s < 4; s++)
         cmfma<R, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
-#pragma unroll
-      for (int e = 0; e < 4; e++) col[Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
+      put(kb, wave, acc);
     }
     __syncthreads();
-    if (wave < nb) {
-      if (wave == kb) {
+    // block row `rb` of the update: F(rb, j) -= C R_j and, held back until
+    // every reader of C = F(rb, kb) is done, F(rb, kb) = -C pv
+    CAcc<R> held;
+    int rb = wave;
+    if (wave == kb) rb = nx;         // (nx < nb) the next pivot's row, for its wave
+    const bool rows = wave < nb && rb < nb && (wave == kb || wave != nx);
+    if (wave < nb && (rows || wave == nx)) {
+      cplx<R> cf[4];
 #pragma unroll
-        for (int c = 0; c < 4; c++) F[(16 * kb + 4 * g + c) * ld + 16 * kb + i] = pv[i * kPv + 4 * g + c];
-      } else {
-        cplx<R> cf[4];  // C_i = F(i, kb), i = wave
+      for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * rb + i];
+      for (int j = 0; j < nb; j++) {
+        if (j == kb || (wave == nx ? j != nx : (rb == nx && j == nx))) continue;
+        CAcc<R> acc;
+        const cplx<R>* col = F + (16 * j + i) * ld;
 #pragma unroll
-        for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * wave + i];
-        for (int j = 0; j < nb; j++) {
-          CAcc<R> acc;
-          zero(acc);
-          cplx<R>* col = F + (16 * j + i) * ld;
-          if (j == kb) {  // -C_i pv
-#pragma unroll
-            for (int s = 0; s < 4; s++)
-              cmfma<R, false, true>(acc.re, acc.im, cf[s], pv[(4 * s + g) * kPv + i]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const cplx<R> v = col[16 * wave + Mf<R>::row(l, e)];
-              acc.re[e] = v.re;
-              acc.im[e] = v.im;
-            }
-#pragma unroll
-            for (int s = 0; s < 4; s++)
-              cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
-          }
-#pragma unroll
-          for (int e = 0; e < 4; e++)
-            col[16 * wave + Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
+        for (int e = 0; e < 4; e++) {
+          const cplx<R> v = col[16 * rb + Mf<R>::row(l, e)];
+          acc.re[e] = v.re;
+          acc.im[e] = v.im;
         }
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+          cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
+        put(rb, j, acc);
+      }
+      if (rows) {
+        zero(held);
+#pragma unroll
+        for (int s = 0; s < 4; s++)
+          cmfma<R, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
+      } else {
+        pivot(nx);
       }
     }
     __syncthreads();
+    if (rows) put(rb, kb, held);
+    if (wave == kb)
+#pragma unroll
+      for (int c = 0; c < 4; c++)
+        F[(16 * kb + 4 * g + c) * ld + 16 * kb + i] = pv[i * kPv + 4 * g + c];
   }
+  __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -229,11 +266,11 @@ struct FactorArgs {
 constexpr int kLd = kNdTile + 1;  // pitch of a tile in LDS
 template <typename R>
 constexpr size_t tile_lds() {
-  return (size_t)(kNdTile * kLd + 16 * kPv) * sizeof(cplx<R>);
+  return (size_t)(kNdTile * kLd + kPvSize) * sizeof(cplx<R>);
 }
 template <typename R>
 size_t front_lds(int P, bool leaf) {  // k_nd_front keeps 4 x 16 rows of P + 1 for F21
-  return (size_t)((leaf ? P : kNdTile) * (P + 1) + 16 * kPv) * sizeof(cplx<R>);
+  return (size_t)((leaf ? P : kNdTile) * (P + 1) + kPvSize) * sizeof(cplx<R>);
 }
 
 // A leaf's border: its unknowns' positions in the leaf and their real
@@ -270,11 +307,22 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
   cplx<R>* pv = F + P * ld;
   const int* pd = g.pdof + fr.row;
   leaf_border<R>(lb, g.op, fr, g.pdof, g.bmap, g.grow);
-  for (int e = threadIdx.x; e < P * P; e += 256) {
-    const int c = e / P, r = e - c * P;
-    cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
-    if (r < p && c < p) v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
-    F[c * ld + r] = v;
+  for (int e = threadIdx.x; e < P * ld; e += 256) F[e] = cplx<R>{(R)0, (R)0};
+  __syncthreads();
+  if (threadIdx.x < P) {  // one thread a row: its at most six entries in the leaf
+    const int r = threadIdx.x;
+    if (r < p) {
+      const int dof = pd[r], across = fr.across, m = (r >> 1) % across;
+      const double* cf = g.op.coef + 12 * (int64_t)(dof >> 1) + 6 * (r & 1);
+      F[r * ld + r] = cplx<R>{(R)(-cf[0] - om_i), (R)om_r};
+      F[(r ^ 1) * ld + r] = cplx<R>{(R)-cf[5], (R)0};
+      if (r + 2 * across < p) F[(r + 2 * across) * ld + r] = cplx<R>{(R)-cf[1], (R)0};
+      if (r - 2 * across >= 0) F[(r - 2 * across) * ld + r] = cplx<R>{(R)-cf[2], (R)0};
+      if (m < across - 1) F[(r + 2) * ld + r] = cplx<R>{(R)-cf[3], (R)0};
+      if (m > 0) F[(r - 2) * ld + r] = cplx<R>{(R)-cf[4], (R)0};
+    } else {
+      F[r * ld + r] = cplx<R>{(R)1, (R)0};
+    }
   }
   __syncthreads();
   invert_tile<R>(F, ld, P, pv, g.status);
@@ -292,9 +340,12 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
   }
 }
 
-// One workgroup per front with halves and P <= 64: F11 into LDS, its inverse A, then
-// B12 = A F12 by 16-column strips (a wave each, F12 pulled straight into the
-// MFMA operand) and F21 through LDS into column-major order.
+// A front with halves and P <= 64, one workgroup (blockIdx.z > 0: further ones
+// for shares of its border, which invert F11 again): F11 into LDS, its inverse
+// A, then B12 = A F12 by 16-column strips (a wave each, F12 pulled straight
+// into the MFMA operand) and F21 through LDS into column-major order.  Only a
+// border unknown that neither half has (m < 0) can be the stencil's neighbour
+// of the separator.
 template <typename R>
 __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
@@ -314,52 +365,68 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
   cplx<R>* A = g.factor + w * g.nfactor + fr.a;
   cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
   cplx<R>* F21 = g.factor + w * g.nfactor + fr.f21;
-  for (int e = threadIdx.x; e < P * P; e += 256) {
-    const int r = e / P, c = e - r * P;
-    cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
-    if (r < p && c < p) {
-      v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
-      add(v, Sh[0][(int64_t)(base[0] + r) * Qh[0] + base[0] + c]);
-      add(v, Sh[1][(int64_t)(base[1] + r) * Qh[1] + base[1] + c]);
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
+  {  // rows by waves, columns by lanes (P <= 64); four rows' loads at a time
+    const int c = l, cc = min(c, p - 1);
+    const cplx<R>* s0 = Sh[0] + (int64_t)base[0] * Qh[0] + base[0] + cc;
+    const cplx<R>* s1 = Sh[1] + (int64_t)base[1] * Qh[1] + base[1] + cc;
+    for (int r0 = wave; r0 < P; r0 += 16) {
+      cplx<R> x[4], y[4];
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int rr = min(r0 + 4 * u, p - 1);
+        x[u] = s0[(int64_t)rr * Qh[0]];
+        y[u] = s1[(int64_t)rr * Qh[1]];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        const int r = r0 + 4 * u;
+        if (r >= P || c >= P) continue;
+        cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
+        if (r < p && c < p) {
+          v = cplx<R>{(R)0, (R)0};
+          const int d = (r >> 1) - (c >> 1);
+          if (d >= -1 && d <= 1) v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
+          add(v, x[u]);
+          add(v, y[u]);
+        }
+        F[c * ld + r] = v;
+      }
     }
-    F[c * ld + r] = v;
   }
   __syncthreads();
   invert_tile<R>(F, ld, P, pv, g.status);
-  for (int e = threadIdx.x; e < P * P; e += 256) {
-    const int c = e / P, r = e - c * P;
-    A[e] = F[c * ld + r];
-  }
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
-  for (int t = wave; t < Q / 16; t += 4) {
+  if (blockIdx.z == 0)
+    for (int e = threadIdx.x; e < P * P; e += 256) {
+      const int c = e / P, r = e - c * P;
+      A[e] = F[c * ld + r];
+    }
+  const int step = 4 * gridDim.z;
+  for (int t = wave + 4 * blockIdx.z; t < Q / 16; t += step) {
     const int j = 16 * t + i;
     const int m = bm[j];
     const bool real = j < fr.q;
-    const int dj = real ? g.pdof[gr[j]] : 0;
     const int h = m & 1;
-    const cplx<R>* src = m >= 0 ? Sh[h] + (int64_t)base[h] * Qh[h] + (m >> 1) : nullptr;
-    const int lds_ = Qh[h];
+    // (a column without a source reads the first half's corner and drops it)
+    const cplx<R>* src = m >= 0 ? Sh[h] + (int64_t)base[h] * Qh[h] + (m >> 1) : Sh[0];
+    const int lds_ = m >= 0 ? Qh[h] : 0;
+    cplx<R> b[16];
+#pragma unroll
+    for (int s = 0; s < 16; s++)
+      if (4 * s < P) b[s] = src[(int64_t)min(4 * s + gq, p - 1) * lds_];
     CAcc<R> acc[4];
 #pragma unroll
     for (int rb = 0; rb < 4; rb++) zero(acc[rb]);
-    for (int k0 = 0; k0 < P; k0 += 16) {
-      cplx<R> b[4];
 #pragma unroll
-      for (int s = 0; s < 4; s++) {
-        const int kk = k0 + 4 * s + gq;
-        b[s] = cplx<R>{(R)0, (R)0};
-        if (real && kk < p) {
-          b[s] = entry<R>(g.op, om_r, om_i, pd[kk], dj);
-          if (m >= 0) add(b[s], src[(int64_t)kk * lds_]);
-        }
-      }
+    for (int s = 0; s < 16; s++) {
+      if (4 * s >= P) continue;
+      const int kk = 4 * s + gq;
+      if (m < 0 || kk >= p) b[s] = cplx<R>{(R)0, (R)0};
+      if (m < 0 && real && kk < p) b[s] = entry<R>(g.op, om_r, om_i, pd[kk], g.pdof[gr[j]]);
 #pragma unroll
-      for (int s = 0; s < 4; s++)
-#pragma unroll
-        for (int rb = 0; rb < 4; rb++)
-          if (16 * rb < P)
-            cmfma<R, false, false>(acc[rb].re, acc[rb].im,
-                                   F[(k0 + 4 * s + gq) * ld + 16 * rb + i], b[s]);
+      for (int rb = 0; rb < 4; rb++)
+        if (16 * rb < P)
+          cmfma<R, false, false>(acc[rb].re, acc[rb].im, F[kk * ld + 16 * rb + i], b[s]);
     }
 #pragma unroll
     for (int rb = 0; rb < 4; rb++)
@@ -372,23 +439,23 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
   __syncthreads();
   // F21, 16 border rows a wave at a time, transposed in the wave's quarter of LDS
   cplx<R>* tr = F + wave * 16 * ld;  // [c][r]
-  for (int t0 = 0; t0 < Q / 16; t0 += 4) {
+  for (int t0 = 4 * blockIdx.z; t0 < Q / 16; t0 += step) {
     const int t = t0 + wave;
-    if (t < Q / 16) {
+    if (t < Q / 16 && l < P) {
+      const int lr = min(l, p - 1);
+      cplx<R> v[16];
+#pragma unroll
       for (int c = 0; c < 16; c++) {
-        const int cc = 16 * t + c;
-        const int m = bm[cc];
-        if (l < P) {
-          cplx<R> v{(R)0, (R)0};
-          if (cc < fr.q && l < p) {
-            v = entry<R>(g.op, om_r, om_i, g.pdof[gr[cc]], pd[l]);
-            if (m >= 0) {
-              const int h = m & 1;
-              add(v, Sh[h][(int64_t)(m >> 1) * Qh[h] + base[h] + l]);
-            }
-          }
-          tr[c * ld + l] = v;
-        }
+        const int m = bm[16 * t + c], h = m & 1;
+        v[c] = (m >= 0 ? Sh[h] + (int64_t)(m >> 1) * Qh[h] + base[h] : Sh[0])[lr];
+      }
+#pragma unroll
+      for (int c = 0; c < 16; c++) {
+        const int cc = 16 * t + c, m = bm[cc];
+        if (m < 0 || l >= p) v[c] = cplx<R>{(R)0, (R)0};
+        if (m < 0 && cc < fr.q && l < p)
+          v[c] = entry<R>(g.op, om_r, om_i, g.pdof[gr[cc]], pd[l]);
+        tr[c * ld + l] = v[c];
       }
     }
     __syncthreads();
@@ -599,30 +666,59 @@ __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
   const int cl = threadIdx.x & 63;
   const int c = c0 + cl;
   cplx<R>* T12 = g.temp + w * g.ntemp + fr.t;
+  // Four rows' loads at a time, from valid places also where there is none;
+  // the stencil couples a separator's unknowns along its line, and with a
+  // border unknown only if neither half has it (m < 0).
+  const int cc = min(c, (t.kind == 1 ? fr.q : p) - 1);
   const int mc = t.kind == 1 && cl < nc ? bm[c] : -1;
   const int dc = cl >= nc ? -1 : t.kind == 1 ? (c < fr.q ? g.pdof[gr[c]] : -1) : pd[c];
-  for (int rl = threadIdx.x >> 6; rl < nr; rl += 4) {
-    const int r = r0 + rl;
-    cplx<R> v{(R)0, (R)0};
-    if (t.kind == 0) {
-      if (r < p && c < p) {
-        v = entry<R>(g.op, om_r, om_i, pd[r], dc);
-        add(v, Sh[0][(int64_t)(base[0] + r) * Qh[0] + base[0] + c]);
-        add(v, Sh[1][(int64_t)(base[1] + r) * Qh[1] + base[1] + c]);
+  const cplx<R>* q0 = Sh[0];
+  const cplx<R>* q1 = Sh[1];
+  int64_t l0 = 0, l1 = 0;
+  if (t.kind == 0) {
+    q0 += (int64_t)base[0] * Qh[0] + base[0] + cc;
+    q1 += (int64_t)base[1] * Qh[1] + base[1] + cc;
+    l0 = Qh[0];
+    l1 = Qh[1];
+  } else if (t.kind == 1 && mc >= 0) {
+    q0 = Sh[mc & 1] + (int64_t)base[mc & 1] * Qh[mc & 1] + (mc >> 1);
+    l0 = Qh[mc & 1];
+  }
+  for (int b0 = threadIdx.x >> 6; b0 < nr; b0 += 16) {
+    cplx<R> x[4], y[4];
+    int mr[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int r = min(r0 + b0 + 4 * u, (t.kind == 2 ? fr.q : p) - 1);
+      mr[u] = t.kind == 2 ? bm[r] : 0;
+      y[u] = cplx<R>{(R)0, (R)0};
+      if (t.kind == 2) {
+        const int h = mr[u] & 1;
+        x[u] = (mr[u] >= 0 ? Sh[h] + (int64_t)(mr[u] >> 1) * Qh[h] + base[h] : Sh[0])[cc];
       } else {
-        v.re = (R)(r == c ? 1 : 0);
+        x[u] = q0[r * l0];
+        if (t.kind == 0) y[u] = q1[r * l1];
       }
-    } else if (t.kind == 1) {
-      if (r < p && dc >= 0) {
-        v = entry<R>(g.op, om_r, om_i, pd[r], dc);
-        if (mc >= 0) add(v, Sh[mc & 1][(int64_t)(base[mc & 1] + r) * Qh[mc & 1] + (mc >> 1)]);
-      }
-    } else if (r < fr.q && c < p) {
-      v = entry<R>(g.op, om_r, om_i, g.pdof[gr[r]], dc);
-      const int m = bm[r];
-      if (m >= 0) add(v, Sh[m & 1][(int64_t)(m >> 1) * Qh[m & 1] + base[m & 1] + c]);
     }
-    if (cl < nc) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int rl = b0 + 4 * u, r = r0 + rl;
+      if (rl >= nr || cl >= nc) continue;
+      cplx<R> v{(R)0, (R)0};
+      if (t.kind == 0) {
+        if (r < p && c < p) {
+          const int d = (r >> 1) - (c >> 1);
+          if (d >= -1 && d <= 1) v = entry<R>(g.op, om_r, om_i, pd[r], dc);
+          add(v, x[u]);
+          add(v, y[u]);
+        } else {
+          v.re = (R)(r == c ? 1 : 0);
+        }
+      } else if (t.kind == 1) {
+        if (r < p && dc >= 0) v = mc >= 0 ? x[u] : entry<R>(g.op, om_r, om_i, pd[r], dc);
+      } else if (r < fr.q && c < p) {
+        v = mr[u] >= 0 ? x[u] : entry<R>(g.op, om_r, om_i, g.pdof[gr[r]], dc);
+      }
       if (t.kind == 1) T12[(int64_t)r * Q + c] = v;
       else F[cl * kLd + rl] = v;
     }
@@ -1236,6 +1332,14 @@ __global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R> a) {
 
 constexpr int kMaxY = 32768;  // shifts per launch (grid y)
 
+// Workgroups per small front: its border (64 rows or columns a share at
+// least) over several where the level's fronts leave CUs idle (two
+// workgroups each on 256 CUs).
+int shares(const NdLevel& lv, int64_t nw) {
+  const int64_t wgs = std::max<int64_t>(1, lv.small.count * nw);
+  return (int)std::max<int64_t>(1, std::min<int64_t>((lv.maxQ + 63) / 64, 512 / wgs));
+}
+
 template <typename R>
 hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, const double* omega,
                       int n_omega, uint32_t* status, hipStream_t s) {
@@ -1255,10 +1359,10 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
   for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
     const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
     a.w0 = w0;
-    auto run = [&](auto kernel, const NdSpan& sp, size_t shm) {
+    auto run = [&](auto kernel, const NdSpan& sp, size_t shm, int zs = 1) {
       if (!sp.count) return;
       a.tasks = d.tasks + sp.first;
-      hipLaunchKernelGGL(kernel, dim3(sp.count, nw), dim3(256), shm, s, a);
+      hipLaunchKernelGGL(kernel, dim3(sp.count, nw, zs), dim3(256), shm, s, a);
     };
     for (int dep = (int)pl.levels.size() - 1; dep >= 0; dep--) {
       const NdLevel& lv = pl.levels[dep];
@@ -1267,7 +1371,7 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
       a.nout = pl.schur[dep & 1];
       a.nin = pl.schur[~dep & 1];
       run(k_nd_leaf<R>, lv.leaf, front_lds<R>(lv.leafP, true));
-      run(k_nd_front<R>, lv.small, front_lds<R>(lv.maxP, false));
+      run(k_nd_front<R>, lv.small, front_lds<R>(lv.maxP, false), shares(lv, nw));
       run(k_nd_assemble<R>, lv.assemble, lds);
       for (size_t k = 0; k < lv.panel.size(); k++) {
         run(k_nd_panel<R>, lv.panel[k], lds);
@@ -1329,12 +1433,8 @@ hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int6
       const NdLevel& lv = level(dep);
       run(k_nd_leaf_up<R, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
       if (lv.small.count) {
-        // border rows over several workgroups where the fronts leave CUs idle
-        const int64_t wgs = (int64_t)lv.small.count * nw;
-        const int zs = (int)std::max<int64_t>(
-            1, std::min<int64_t>((lv.maxQ + 63) / 64, 512 / std::max<int64_t>(wgs, 1)));
         run(k_nd_up<R, NB, ADJ>, lv.small, (size_t)lv.maxP * NC * (ADJ ? 1 : 2) * sizeof(cplx<R>),
-            zs);
+            shares(lv, nw));
       }
       run(k_nd_gather<R>, lv.gather, 0);
       if (!ADJ) run(k_nd_rows<R, NB, ND_Z, ADJ>, lv.rowsP, 0);

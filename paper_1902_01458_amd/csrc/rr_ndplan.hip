@@ -168,6 +168,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     }
     std::copy(b.off, b.off + 5, fr.side);
     const int across = b.j1 - b.j0;  // a leaf's unknowns: i, then j, then u and v
+    fr.across = b.leaf ? across : 0;
     for (int side = 0; side < 4; side++) {
       const bool along_y = side < 2;  // left and right run along y
       const int c0 = along_y ? b.j0 : b.i0;
