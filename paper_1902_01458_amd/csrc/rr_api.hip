@@ -520,9 +520,11 @@ Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T,
   pl.nchunk = (int)((n + 2047) / 2048);
   const size_t kk = (size_t)std::max(k_max * k_max, 64);
   const size_t kkn = (size_t)std::max(kn * kn, 64);
-  // (at least 96 complex per chunk: the refinement's three partial rows of 64)
-  pl.partial = (size_t)n_omega * std::max<size_t>(pl.nchunk * std::max<size_t>(kkn, 96),
-                                                  k_max > kNarrowK ? gramb_chunks(n) * kk : 0) *
+  // the norms' partial rows (the refinement has three of 64 doubles per
+  // chunk), the narrow Gram matrices (rr_small.hip) or the wide ones
+  pl.partial = (size_t)n_omega *
+               std::max({(size_t)pl.nchunk * 96, (size_t)gram_chunks(n) * kkn,
+                         k_max > kNarrowK ? (size_t)gramb_chunks(n) * kk : (size_t)0}) *
                2 * sizeof(double);
   if (k_max > kNarrowK) {  // the wide k x k steps' scratch and one wide block
     pl.big = (size_t)n_omega * (k_max + 1) * (k_max + 1) * 2 * sizeof(double);

@@ -179,7 +179,7 @@ hipError_t prepare_ssolve(int T, bool fp32);
 // Small dense / tall-skinny kernels (rr_small.hip)
 constexpr int kJacobiSweeps = 40;  // one-sided Jacobi: sweeps before non-convergence
 struct SmallWs {   // workspace for tall-skinny reductions
-  double* partial;     // n_omega * nchunk * kmax*kmax complex
+  double* partial;     // n_omega * max(nchunk * 96, gram_chunks(n) * k * k, k <= 32) complex
   double* G;           // n_omega * kmax*kmax complex
   double* R;           // n_omega * kmax*kmax complex (upper triangular factor)
   double* Rinv;        // n_omega * kmax*kmax complex (applied matrix)
@@ -194,6 +194,7 @@ struct SmallWs {   // workspace for tall-skinny reductions
   double* big1 = nullptr;  // wide sketches (k > 32): n_omega * (kmax+1)^2 complex each
   double* big2 = nullptr;
 };
+int gram_chunks(int64_t n);  // chunks of the Gram kernel's partial sums
 // CholQR2 in place: Y <- Q = Y R^-1 with R upper, real positive diagonal.
 // A shift whose Gram matrix is not numerically positive definite takes
 // shifted CholeskyQR3 instead (three passes, the first with a diagonal shift).

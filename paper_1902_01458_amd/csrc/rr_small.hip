@@ -6,12 +6,14 @@
 //
 // Reductions over n use a fixed chunking and a fixed summation order, so the
 // results are bitwise reproducible from run to run.
-#include "rr_internal.h"
+#include <algorithm>
+#include <type_traits>
+
+#include "rr_mfma.h"
 
 namespace rr {
 
-constexpr int kChunkRows = 2048;  // rows per partial-sum chunk
-constexpr int kSub = 64;          // rows staged in LDS at a time
+constexpr int kChunkRows = 2048;  // rows per partial-sum chunk (norms)
 constexpr int KM = 32;            // largest sketch width the k x k kernels take
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
@@ -22,132 +24,169 @@ __device__ __forceinline__ double2 cmulc(double2 a, double2 b) {  // conj(a) * b
 }
 
 // partial[w][chunk] = (Y_c T)^H (Y_c T) over the chunk's rows, where T is the
-// k x k matrix Tm[w] (identity when Tm == NULL).  Y: (n_omega, k, n).  The
-// output is cut into 2 x 2 groups on and above the diagonal (the Cholesky
-// reads the upper triangle only); each group is accumulated by S = 256 /
-// groups threads that take every S-th row of a staged sub-block, and their S
-// sums are added in a fixed order at the end, so results are bitwise
-// reproducible.  With Tm, each staged sub-block is first multiplied by T in
-// LDS, every thread taking one row and every fourth column.  The sketch width
-// is at most KM = 32: at most 136 groups, so S >= 1.
+// k x k matrix Tm[w] (MUL; identity otherwise).  Y: (n_omega, k, n).
+//
+// In real form on the FP64 matrix cores: with the 2k real columns [re im] of
+// every column of Y, H = Yr^T Yr holds all four real products of each complex
+// one, and only its 16 x 16 blocks on and above the diagonal are formed (6 at
+// k = 20, i.e. 6 MFMAs per 4 rows).  For a Gram matrix both MFMA operands have
+// the same lane layout, so each element is loaded once.  With MUL a wave first
+// multiplies its 16 rows by T, whose operand stays in registers; the product's
+// accumulator layout is the Gram product's operand layout, so nothing moves.
+// Each wave takes every fourth group of 16 rows; the waves' sums are added in
+// order, so results are bitwise reproducible, and the chunks depend on n
+// alone, so a shift's result does not depend on the batch.
+// Bound by HBM (one read of Y per pass) once there are enough rows: at n =
+// 262144, k = 20 one shift / 16 shifts took 111 / 466 us a pass on the vector
+// units with 2048 rows a workgroup.
 // With only_if != NULL a shift whose only_if[w] is zero is skipped.
-__device__ __forceinline__ void upper_group(int g, int ng, int& gi, int& gj) {
-  int rem = g;
-  gi = 0;
-  while (rem >= ng - gi) { rem -= ng - gi; gi++; }
-  gj = gi + rem;
+static int gram_rows(int64_t n) {  // rows per chunk: at most 512 chunks
+  return (int)std::max<int64_t>(256, ((n + 511) / 512 + 63) / 64 * 64);
 }
+int gram_chunks(int64_t n) { return (int)((n + gram_rows(n) - 1) / gram_rows(n)); }
 
-__global__ __launch_bounds__(256) void k_gram_partial(int64_t n, int k, const double2* __restrict__ Y,
-                                                      const double2* __restrict__ Tm, int kmax,
-                                                      int nchunk, double2* __restrict__ partial,
-                                                      const uint32_t* __restrict__ only_if) {
-  __shared__ double2 ys[kSub][KM + 1];
-  __shared__ double2 tm[KM][KM];
+template <int NB, bool MUL>  // NB blocks of 16 real columns
+__global__ __launch_bounds__(256) void k_gram(int64_t n, int k, const double* __restrict__ Y,
+                                              const double2* __restrict__ Tm, int kmax, int rows,
+                                              double2* __restrict__ partial,
+                                              const uint32_t* __restrict__ only_if) {
+  typedef Mf<double>::v4 v4;
+  constexpr int NU = NB * (NB + 1) / 2, NH = 16 * NB;
+  __shared__ double hs[NH][NH + 1];
   const int w = blockIdx.y, chunk = blockIdx.x;
   if (only_if && only_if[w] == 0) return;
-  const double2* Yw = Y + (int64_t)w * k * n;
-  if (Tm) {
-    for (int idx = threadIdx.x; idx < k * k; idx += 256)
-      tm[idx / k][idx % k] = Tm[(int64_t)w * kmax * kmax + idx];  // tm[i][j] = T[i][j]
-  }
-  const int ng = (k + 1) / 2, nup = ng * (ng + 1) / 2, S = 256 / nup;
-  const int t = threadIdx.x;
-  const bool act = t < nup * S;
-  const int g = t % nup, slice = t / nup;
-  int gi, gj;
-  upper_group(g, ng, gi, gj);
-  const int i0 = 2 * gi, j0 = 2 * gj;
-  double2 acc[2][2];
+  const double* Yw = Y + 2 * (int64_t)w * k * n;
+  const int64_t r0 = (int64_t)chunk * rows, r1 = min(n, r0 + rows);
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  v4 h[NU];
 #pragma unroll
-  for (int a = 0; a < 2; a++)
+  for (int u = 0; u < NU; u++) h[u] = v4{0, 0, 0, 0};
+  auto accumulate = [&](const double (&z)[NB]) {
+    int u = 0;
 #pragma unroll
-    for (int c = 0; c < 2; c++) acc[a][c] = make_double2(0, 0);
-  int64_t r0 = (int64_t)chunk * kChunkRows, r1 = min(n, r0 + kChunkRows);
-  // each stage's rows are loaded into registers during the previous stage's
-  // products, then staged in LDS
-  constexpr int NST = kSub * KM / 256;
-  double2 pf[NST];
-  auto fetch = [&](int64_t rb) {
-    const int64_t rows = min((int64_t)kSub, r1 - rb);
+    for (int a = 0; a < NB; a++)
 #pragma unroll
-    for (int q = 0; q < NST; q++) {
-      const int idx = threadIdx.x + 256 * q, j = idx / kSub, rr = idx % kSub;
-      pf[q] = (rr < rows && j < k) ? Yw[(int64_t)j * n + rb + rr] : make_double2(0, 0);
-    }
+      for (int b = a; b < NB; b++, u++) h[u] = Mf<double>::op(z[a], z[b], h[u]);
   };
-  fetch(r0);
-  for (int64_t rb = r0; rb < r1; rb += kSub) {
-    int rows = (int)min((int64_t)kSub, r1 - rb);
-    __syncthreads();
+  if constexpr (!MUL) {
+    // lane: real column 16 b + i, rows 4 g + s of the group
+    double y[2][4][NB];
+    auto load = [&](int buf, int64_t rg) {
 #pragma unroll
-    for (int q = 0; q < NST; q++) {
-      const int idx = threadIdx.x + 256 * q;
-      ys[idx % kSub][idx / kSub] = pf[q];
-    }
-    __syncthreads();
-    fetch(rb + kSub);  // past the chunk: no rows, no loads
-    if (Tm) {  // ys <- ys * T: thread (row rr, columns cg + 4 c)
-      const int rr = t % kSub, cg = t / kSub;
-      double2 o[KM / 4];
+      for (int s = 0; s < 4; s++) {
+        const int64_t r = rg + 4 * g + s;
 #pragma unroll
-      for (int c = 0; c < KM / 4; c++) o[c] = make_double2(0, 0);
-      for (int i = 0; i < k; i++) {
-        const double2 a = ys[rr][i];
-#pragma unroll
-        for (int c = 0; c < KM / 4; c++) {
-          const int j = cg + 4 * c;
-          if (j < k) {
-            const double2 p = cmul(a, tm[i][j]);
-            o[c].x += p.x; o[c].y += p.y;
-          }
+        for (int b = 0; b < NB; b++) {
+          const int c = 16 * b + i;
+          y[buf][s][b] = r < r1 && c < 2 * k ? Yw[2 * ((int64_t)(c >> 1) * n + r) + (c & 1)] : 0.0;
         }
       }
-      __syncthreads();
+    };
+    int64_t rg = r0 + 16 * wave;
+    load(0, rg);
+    for (; rg < r1; rg += 128) {
+      load(1, rg + 64);  // past the chunk: zeros
 #pragma unroll
-      for (int c = 0; c < KM / 4; c++)
-        if (cg + 4 * c < k) ys[rr][cg + 4 * c] = o[c];
-      __syncthreads();
+      for (int s = 0; s < 4; s++) accumulate(y[0][s]);
+      load(0, rg + 128);
+#pragma unroll
+      for (int s = 0; s < 4; s++) accumulate(y[1][s]);
     }
-    if (act) {
-      for (int rr = slice; rr < rows; rr += S) {
-        const double2 a0 = ys[rr][i0], a1 = ys[rr][i0 + 1];
-        const double2 b0 = ys[rr][j0], b1 = ys[rr][j0 + 1];
-        double2 p;
-        p = cmulc(a0, b0); acc[0][0].x += p.x; acc[0][0].y += p.y;
-        p = cmulc(a0, b1); acc[0][1].x += p.x; acc[0][1].y += p.y;
-        p = cmulc(a1, b0); acc[1][0].x += p.x; acc[1][0].y += p.y;
-        p = cmulc(a1, b1); acc[1][1].x += p.x; acc[1][1].y += p.y;
+  } else {
+    // T in real form, [[tr, ti], [-ti, tr]] per entry: element (4 s + g, 16 b + i)
+    double t[4 * NB][NB];
+#pragma unroll
+    for (int s = 0; s < 4 * NB; s++)
+#pragma unroll
+      for (int b = 0; b < NB; b++) {
+        const int c = 4 * s + g, d = 16 * b + i;
+        t[s][b] = 0.0;
+        if (c < 2 * k && d < 2 * k) {
+          const double2 v = Tm[(int64_t)w * kmax * kmax + (c >> 1) * k + (d >> 1)];
+          t[s][b] = (c & 1) == (d & 1) ? v.x : (c & 1) ? -v.y : v.y;
+        }
+      }
+    for (int64_t rg = r0 + 16 * wave; rg < r1; rg += 64) {
+      double x[4 * NB];  // row i, real column 4 s + g
+#pragma unroll
+      for (int s = 0; s < 4 * NB; s++) {
+        const int c = 4 * s + g;
+        x[s] = rg + i < r1 && c < 2 * k ? Yw[2 * ((int64_t)(c >> 1) * n + rg + i) + (c & 1)] : 0.0;
+      }
+      v4 z[NB];
+#pragma unroll
+      for (int b = 0; b < NB; b++) z[b] = v4{0, 0, 0, 0};
+#pragma unroll
+      for (int s = 0; s < 4 * NB; s++)
+#pragma unroll
+        for (int b = 0; b < NB; b++) z[b] = Mf<double>::op(x[s], t[s][b], z[b]);
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        double zb[NB];
+#pragma unroll
+        for (int b = 0; b < NB; b++) zb[b] = z[b][e];
+        accumulate(zb);
       }
     }
   }
-  // the S slice sums of every group, added in slice order (S * groups * 4 <=
-  // 1024 entries, staged in ys)
-  __syncthreads();
-  double2* red = &ys[0][0];
-  if (act) {
+  for (int v = 0; v < 4; v++) {  // the waves' sums, in order
+    if (wave == v) {
+      int u = 0;
 #pragma unroll
-    for (int a = 0; a < 2; a++)
+      for (int a = 0; a < NB; a++)
 #pragma unroll
-      for (int c = 0; c < 2; c++) red[(slice * nup + g) * 4 + a * 2 + c] = acc[a][c];
-  }
-  __syncthreads();
-  for (int e = t; e < nup * 4; e += 256) {
-    const int gg = e / 4, a = (e % 4) / 2, c = e % 2;
-    double2 sum = make_double2(0, 0);
-    for (int sl = 0; sl < S; sl++) {
-      const double2 v = red[(sl * nup + gg) * 4 + e % 4];
-      sum.x += v.x; sum.y += v.y;
+        for (int b = a; b < NB; b++, u++)
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            double& d = hs[16 * a + Mf<double>::row(l, e)][16 * b + i];
+            d = v ? d + h[u][e] : h[u][e];
+          }
     }
-    int hi, hj;
-    upper_group(gg, ng, hi, hj);
-    const int ii = 2 * hi + a, jj = 2 * hj + c;
-    if (ii < k && jj < k)
-      partial[((int64_t)w * nchunk + chunk) * kmax * kmax + ii * k + jj] = sum;
+    __syncthreads();
+  }
+  double2* out = partial + ((int64_t)w * gridDim.x + chunk) * k * k;
+  for (int e = threadIdx.x; e < k * k; e += 256) {
+    const int a = e / k, b = e - a * k;
+    if (b >= a)
+      out[e] = make_double2(hs[2 * a][2 * b] + hs[2 * a + 1][2 * b + 1],
+                            hs[2 * a][2 * b + 1] - hs[2 * a + 1][2 * b]);
   }
 }
 
-// Sum the partials (fixed order), Cholesky G = R^H R (R upper, real positive
+// G[w] = sum of the chunks' partials (upper triangle), 16 slices of the chunks
+// per entry, added in order.
+__global__ __launch_bounds__(256) void k_gram_sum(int k, int kmax, int nchunk,
+                                                  const double2* __restrict__ partial,
+                                                  double2* __restrict__ G,
+                                                  const uint32_t* __restrict__ only_if) {
+  __shared__ double2 red[16][17];
+  const int w = blockIdx.y;
+  if (only_if && only_if[w] == 0) return;
+  const int e = threadIdx.x & 15, slice = threadIdx.x >> 4;
+  const int idx = blockIdx.x * 16 + e;
+  double2 s = make_double2(0, 0);
+  if (idx < k * k && idx % k >= idx / k) {
+    const double2* p = partial + (int64_t)w * nchunk * k * k + idx;
+#pragma unroll 4
+    for (int c = slice; c < nchunk; c += 16) {
+      const double2 v = p[(int64_t)c * k * k];
+      s.x += v.x;
+      s.y += v.y;
+    }
+  }
+  red[slice][e] = s;
+  __syncthreads();
+  if (slice == 0 && idx < k * k) {
+    s = red[0][e];
+    for (int c = 1; c < 16; c++) {
+      s.x += red[c][e].x;
+      s.y += red[c][e].y;
+    }
+    G[(int64_t)w * kmax * kmax + idx] = s;
+  }
+}
+
+// Cholesky G = R^H R (R upper, real positive
 // diagonal), Rinv = R^-1.  Passes 1 and 2 compose: R <- Rnew Rold,
 // Rinv <- Rinv_old Rinv_new.
 //
@@ -160,117 +199,134 @@ __global__ __launch_bounds__(256) void k_gram_partial(int64_t n, int k, const do
 // then has a condition number near (u m k)^-1/2, which the two passes that
 // follow make orthonormal.  Pass 2 runs only for shifts with shifted[w] set.
 // A breakdown that remains latches ST_BREAKDOWN (the pivot is replaced by 1).
-__global__ __launch_bounds__(256) void k_chol(int k, int kmax, int nchunk, int64_t m,
-                                              const double2* __restrict__ partial,
+//
+// Bound by latency (k dependent steps, one workgroup per shift): one barrier
+// per step of the factorisation, which leaves the rows' scaling by the roots
+// of the pivots to the end, and one per row of the inverse, eight threads
+// sharing each of its elements' sums.
+__global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
+                                              const double2* __restrict__ Gg,
                                               double2* __restrict__ Rg, double2* __restrict__ Rinvg,
                                               int pass, uint32_t* __restrict__ shifted,
                                               uint32_t* status) {
   __shared__ double2 G[KM][KM + 1];
-  __shared__ double2 Rn[KM][KM + 1];
   __shared__ double2 Ri[KM][KM + 1];
-  __shared__ int bad;
-  __shared__ double shift;
-  const int w = blockIdx.x;
+  __shared__ double2 Ro[KM][KM + 1];
+  const int w = blockIdx.x, t = threadIdx.x;
   if (pass == 2 && shifted[w] == 0) return;
+  const int64_t at = (int64_t)w * kmax * kmax;
+  double2* Rw = Rg + at;
+  double2* Riw = Rinvg + at;
+  bool bad = false;
   int attempt = 0;
+  double shift = 0.0;
   for (;; attempt++) {
-    for (int pr = threadIdx.x; pr < k * k; pr += 256) {  // upper triangle (all that is used)
-      double2 s = make_double2(0, 0);
-      if (pr % k >= pr / k) {
-        for (int c = 0; c < nchunk; c++) {
-          double2 v = partial[((int64_t)w * nchunk + c) * kmax * kmax + pr];
-          s.x += v.x; s.y += v.y;
-        }
-        if (attempt && pr % k == pr / k) s.x += shift;
-      }
-      G[pr / k][pr % k] = s;
+    for (int e = t; e < k * k; e += 256) {
+      const int a = e / k, c = e % k;
+      double2 v = c >= a ? Gg[at + e] : make_double2(0, 0);
+      if (a == c) v.x += shift;
+      G[a][c] = v;
+      if (pass > 0) Ro[a][c] = Rw[e];
     }
-    if (threadIdx.x == 0) bad = 0;
     __syncthreads();
-    if (attempt == 0 && threadIdx.x == 0) {
+    if (attempt == 0) {
       double tr = 0;
       for (int j = 0; j < k; j++) tr += G[j][j].x;
       shift = 11.0 * ((double)(m + 2) * k + (double)k * (k + 1)) * 0x1p-53 * tr;
     }
-    // right-looking Cholesky on the upper triangle: G = R^H R
-    for (int j = 0; j < k; j++) {
-      if (threadIdx.x == 0) {
-        double d = G[j][j].x;
-        if (!(d > 0.0) || !isfinite(d)) { bad = 1; d = 1.0; }
-        G[j][j] = make_double2(sqrt(d), 0.0);
-      }
-      __syncthreads();
-      double rjj = G[j][j].x;
-      for (int c = j + 1 + threadIdx.x; c < k; c += 256) {
-        G[j][c].x /= rjj; G[j][c].y /= rjj;
-      }
-      __syncthreads();
-      int wd = k - 1 - j;
-      for (int idx = threadIdx.x; idx < wd * wd; idx += 256) {
-        int a = j + 1 + idx / wd, c = j + 1 + idx % wd;
+    bad = false;
+    for (int j = 0; j < k; j++) {  // rows j of sqrt(pivot) R; `bad` is block-uniform
+      const double d = G[j][j].x;
+      const bool no = !(d > 0.0) || !isfinite(d);
+      bad |= no;
+      const double rd = no ? 1.0 : 1.0 / d;
+      const int wd = k - 1 - j;
+      for (int e = t; e < wd * wd; e += 256) {
+        const int a = j + 1 + e / wd, c = j + 1 + e % wd;
         if (c < a) continue;
-        double2 p = cmulc(G[j][a], G[j][c]);  // R[j][a]^* R[j][c]
-        G[a][c].x -= p.x; G[a][c].y -= p.y;
+        const double2 p = cmulc(G[j][a], G[j][c]);
+        G[a][c].x -= p.x * rd;
+        G[a][c].y -= p.y * rd;
       }
       __syncthreads();
     }
-    if (!(bad && pass == 0 && attempt == 0)) break;  // bad is block-uniform here
-    __syncthreads();
+    if (!(bad && pass == 0 && attempt == 0)) break;
   }
-  if (pass == 0 && threadIdx.x == 0) shifted[w] = attempt;
-  const int compose = pass > 0;
-  for (int idx = threadIdx.x; idx < k * k; idx += 256) {
-    int a = idx / k, c = idx % k;
-    Rn[a][c] = c >= a ? G[a][c] : make_double2(0, 0);
-    Ri[a][c] = make_double2(a == c ? 1.0 : 0.0, 0.0);
-  }
-  __syncthreads();
-  // Rinv: solve R X = I by back substitution, one column per thread
-  for (int c = threadIdx.x; c < k; c += 256) {
-    for (int a = c; a >= 0; a--) {
-      double2 s = make_double2(a == c ? 1.0 : 0.0, 0.0);
-      for (int t = a + 1; t <= c; t++) {
-        double2 p = cmul(Rn[a][t], Ri[t][c]);
-        s.x -= p.x; s.y -= p.y;
-      }
-      double d = Rn[a][a].x;
-      Ri[a][c] = make_double2(s.x / d, s.y / d);
-    }
+  if (pass == 0 && t == 0) shifted[w] = attempt;
+  double2 v[4];
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int e = t + 256 * q;
+    if (e >= k * k) break;
+    const int a = e / k, c = e % k;
+    const double d = G[a][a].x;
+    const double r = !(d > 0.0) || !isfinite(d) ? 1.0 : sqrt(d);
+    v[q] = c > a ? make_double2(G[a][c].x / r, G[a][c].y / r) : make_double2(c == a ? r : 0.0, 0.0);
   }
   __syncthreads();
-  double2* Rw = Rg + (int64_t)w * kmax * kmax;
-  double2* Riw = Rinvg + (int64_t)w * kmax * kmax;
-  if (compose) {
-    // R <- Rn * Rold ; Rinv <- Riold * Ri  (Rold, Riold are the global inputs)
-    double2 nr[4], ni[4];
-    for (int q = 0; q < 4; q++) {
-      int idx = threadIdx.x + 256 * q;
-      if (idx >= k * k) break;
-      int a = idx / k, c = idx % k;
-      double2 s = make_double2(0, 0), t2 = make_double2(0, 0);
-      for (int t = 0; t < k; t++) {
-        double2 p = cmul(Rn[a][t], Rw[t * k + c]);
-        s.x += p.x; s.y += p.y;
-        double2 q2 = cmul(Riw[a * k + t], Ri[t][c]);
-        t2.x += q2.x; t2.y += q2.y;
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int e = t + 256 * q;
+    if (e < k * k) G[e / k][e % k] = v[q];  // R
+  }
+  __syncthreads();
+  {  // R X = I from the last row up: eight threads per column
+    const int c = t >> 3, sub = t & 7;
+    for (int a = k - 1; a >= 0; a--) {
+      double2 s = make_double2(0, 0);
+      if (c < k)
+        for (int x = a + 1 + sub; x <= c; x += 8) {
+          const double2 p = cmul(G[a][x], Ri[x][c]);
+          s.x -= p.x;
+          s.y -= p.y;
+        }
+      for (int o = 1; o < 8; o <<= 1) {
+        s.x += __shfl_xor(s.x, o, 8);
+        s.y += __shfl_xor(s.y, o, 8);
       }
-      nr[q] = s;
-      ni[q] = t2;
+      if (c < k && sub == 0) {
+        if (a == c) s.x += 1.0;
+        const double d = G[a][a].x;
+        Ri[a][c] = c >= a ? make_double2(s.x / d, s.y / d) : make_double2(0, 0);
+      }
+      __syncthreads();
+    }
+  }
+  if (pass > 0) {
+    // R <- R Rold ; Rinv <- Riold Ri
+    double2 ni[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int e = t + 256 * q;
+      if (e >= k * k) break;
+      const int a = e / k, c = e % k;
+      double2 s = make_double2(0, 0), u = make_double2(0, 0);
+      for (int x = 0; x < k; x++) {
+        const double2 p = cmul(G[a][x], Ro[x][c]);
+        s.x += p.x;
+        s.y += p.y;
+        const double2 z = cmul(Riw[a * k + x], Ri[x][c]);
+        u.x += z.x;
+        u.y += z.y;
+      }
+      v[q] = s;
+      ni[q] = u;
     }
     __syncthreads();
+#pragma unroll
     for (int q = 0; q < 4; q++) {
-      int idx = threadIdx.x + 256 * q;
-      if (idx >= k * k) break;
-      Rw[idx] = nr[q];
-      Riw[idx] = ni[q];
+      const int e = t + 256 * q;
+      if (e >= k * k) break;
+      Rw[e] = v[q];
+      Riw[e] = ni[q];
     }
   } else {
-    for (int idx = threadIdx.x; idx < k * k; idx += 256) {
-      Rw[idx] = Rn[idx / k][idx % k];
-      Riw[idx] = Ri[idx / k][idx % k];
+    for (int e = t; e < k * k; e += 256) {
+      Rw[e] = G[e / k][e % k];
+      Riw[e] = Ri[e / k][e % k];
     }
   }
-  if (threadIdx.x == 0 && bad) latch(status, ST_BREAKDOWN);
+  if (t == 0 && bad) latch(status, ST_BREAKDOWN);
 }
 
 // Out = Y * Tm[w]  (n x k times k x k), one row per thread (held in registers);
@@ -328,15 +384,29 @@ static int nchunks(int64_t n) { return (int)((n + kChunkRows - 1) / kChunkRows);
 // R is the composed factor (Y = Q R) either way.
 static void chol_passes(int n, int n_omega, int k, double* Y, bool explicit_q, SmallWs& ws,
                         uint32_t* status, hipStream_t s) {
-  const int nc = nchunks(n);
+  const int rows = gram_rows(n), nc = gram_chunks(n);
   const dim3 g(nc, n_omega);
   double2* part = (double2*)ws.partial;
   for (int pass = 0; pass < 3; pass++) {
-    hipLaunchKernelGGL(k_gram_partial, g, dim3(256), 0, s, (int64_t)n, k, (const double2*)Y,
-                       pass ? (const double2*)ws.Rinv : (const double2*)nullptr, ws.kmax, nc,
-                       part, pass == 2 ? (const uint32_t*)ws.shifted : (const uint32_t*)nullptr);
-    hipLaunchKernelGGL(k_chol, dim3(n_omega), dim3(256), 0, s, k, ws.kmax, nc, (int64_t)n, part,
-                       (double2*)ws.R, (double2*)ws.Rinv, pass, ws.shifted, status);
+    const uint32_t* only = pass == 2 ? ws.shifted : nullptr;
+    auto gram = [&](auto nb) {
+      constexpr int NB = decltype(nb)::value;
+      if (pass)
+        hipLaunchKernelGGL((k_gram<NB, true>), g, dim3(256), 0, s, (int64_t)n, k, Y,
+                           (const double2*)ws.Rinv, ws.kmax, rows, part, only);
+      else
+        hipLaunchKernelGGL((k_gram<NB, false>), g, dim3(256), 0, s, (int64_t)n, k, Y,
+                           (const double2*)nullptr, ws.kmax, rows, part, only);
+    };
+    if (k <= 8) gram(std::integral_constant<int, 1>{});
+    else if (k <= 16) gram(std::integral_constant<int, 2>{});
+    else if (k <= 24) gram(std::integral_constant<int, 3>{});
+    else gram(std::integral_constant<int, 4>{});
+    hipLaunchKernelGGL(k_gram_sum, dim3((k * k + 15) / 16, n_omega), dim3(256), 0, s, k, ws.kmax,
+                       nc, (const double2*)part, (double2*)ws.G, only);
+    hipLaunchKernelGGL(k_chol, dim3(n_omega), dim3(256), 0, s, k, ws.kmax, (int64_t)n,
+                       (const double2*)ws.G, (double2*)ws.R, (double2*)ws.Rinv, pass, ws.shifted,
+                       status);
     if (pass == 0 && explicit_q) {
       hipLaunchKernelGGL(k_apply_small, dim3((n + 255) / 256, n_omega), dim3(256), 0, s,
                          (int64_t)n, k, (const double2*)Y, (const double2*)ws.Rinv, ws.kmax,
