@@ -524,7 +524,7 @@ Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T,
   // chunk), the narrow Gram matrices (rr_small.hip) or the wide ones
   pl.partial = (size_t)n_omega *
                std::max({(size_t)pl.nchunk * 96, (size_t)gram_chunks(n) * kkn,
-                         k_max > kNarrowK ? (size_t)gramb_chunks(n) * kk : (size_t)0}) *
+                         k_max > kNarrowK ? gramb_partial(n, k_max) : (size_t)0}) *
                2 * sizeof(double);
   if (k_max > kNarrowK) {  // the wide k x k steps' scratch and one wide block
     pl.big = (size_t)n_omega * (k_max + 1) * (k_max + 1) * 2 * sizeof(double);
@@ -823,6 +823,7 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
                    : f->nd ? nd_prepare()
                            : prepare_factor(T, prec == RR_MIXED);
     if (e == hipSuccess && !krylov && !f->nd) e = prepare_solve(T, prec == RR_MIXED);
+    if (e == hipSuccess && k_max > kNarrowK) e = prepare_big();
     if (e != hipSuccess) {
       st = fail(RR_ERR_HIP, std::string("kernel attributes: ") + hipGetErrorString(e));
       goto fail_free;

@@ -6,11 +6,11 @@
 // matrices in global memory (L2-resident at this size) and tile the tall
 // products through LDS:
 //   * Gram G = Y^H Y in 32 x 32 tiles per row chunk, then summed over chunks;
-//   * Cholesky G = R^H R and R^-1, one workgroup per shift;
+//   * Cholesky G = R^H R and R^-1 in 32 x 32 blocks, one workgroup per shift;
 //   * k x k products (composing the two CholQR passes, R^-1 W) in 32 x 32 tiles;
 //   * tall products Y S (n x k by k x k) in 64 x 32 output tiles;
-//   * the one-sided Jacobi SVD of R^H, one workgroup per shift, one wave per
-//     column pair of the round-robin order;
+//   * the one-sided Jacobi SVD of R^H, one workgroup per shift, 16 lanes per
+//     column pair of the round-robin order (in LDS up to k = 100);
 //   * column norms for eq. (9)'s sigma_j = ||M^-1 v_j||.
 // Same steps and outputs as the narrow path (CholQR2, then the SVD of the
 // k x k factor), with one difference: a Gram matrix that is not numerically
@@ -25,7 +25,6 @@ namespace rr {
 namespace {
 
 constexpr int kBT = 32;          // tile edge of the k x k blocks
-constexpr int kBigChunks = 16;   // row chunks of the tiled Gram matrix
 
 __device__ __forceinline__ double2 bmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -94,65 +93,143 @@ __global__ void k_gramb_reduce(int k, int nchunk, const double2* part, int64_t s
 }
 
 // G = R^H R (R upper, real positive diagonal) and R^-1, one workgroup per
-// shift, in global memory: the right-looking Cholesky by rows, then each
-// thread back-substitutes columns of R^-1.  A pivot that is not positive
-// latches ST_BREAKDOWN and is taken as 1 (the results stay finite).
+// shift, in 32 x 32 blocks: a diagonal block is factored and inverted in LDS
+// (one barrier per step, as in the narrow path), its block row multiplied by
+// the inverse, the blocks below updated; then R^-1 by block back-substitution
+// with the diagonal inverses.  A thread holds one element of a block.  The
+// chain is k short steps in LDS and (k / 32)^3 / 3 block products, where the
+// unblocked form took k steps through global memory and one thread per column
+// of R^-1: 957 us at k = 100.  A pivot that is not positive latches
+// ST_BREAKDOWN and is taken as 1 (the results stay finite).
 __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2* G, double2* R,
                                                 double2* Rinv, uint32_t* status) {
-  __shared__ double piv;
-  const int w = blockIdx.x;
+  __shared__ double2 S0[kBT][kBT + 1], S1[kBT][kBT + 1], S2[kBT][kBT + 1];
+  const int w = blockIdx.x, t = threadIdx.x, ti = t >> 5, tj = t & 31;
+  const int nt = (k + kBT - 1) / kBT;
   const double2* Gw = G + w * sM;
   double2* Rw = R + w * sM;
   double2* Xw = Rinv + w * sM;
-  for (int64_t e = threadIdx.x; e < (int64_t)k * k; e += blockDim.x) {
+  const double2 none = make_double2(0, 0);
+  auto get = [&](const double2* M, int i, int j) {
+    return i < k && j < k ? M[(int64_t)i * k + j] : none;
+  };
+  auto put = [&](double2* M, int i, int j, double2 v) {
+    if (i < k && j < k) M[(int64_t)i * k + j] = v;
+  };
+  for (int64_t e = t; e < (int64_t)k * k; e += 1024) {
     const int i = (int)(e / k), j = (int)(e % k);
-    Rw[e] = j >= i ? Gw[e] : make_double2(0, 0);
+    Rw[e] = j >= i ? Gw[e] : none;
+    Xw[e] = none;
   }
   __syncthreads();
-  for (int j = 0; j < k; j++) {
-    if (threadIdx.x == 0) {
-      double d = Rw[(int64_t)j * k + j].x;
-      if (!(d > 0.0) || !isfinite(d)) {
-        latch(status, ST_BREAKDOWN);
-        d = 1.0;
+  bool bad = false;
+  for (int J = 0; J < nt; J++) {
+    const int j0 = kBT * J, jb = min(kBT, k - j0);
+    S0[ti][tj] = ti < jb && tj < jb ? get(Rw, j0 + ti, j0 + tj)
+                                    : make_double2(ti == tj ? 1.0 : 0.0, 0.0);
+    __syncthreads();
+    for (int j = 0; j < jb; j++) {
+      const double d = S0[j][j].x;
+      const bool no = !(d > 0.0) || !isfinite(d);
+      bad |= no;
+      const double rd = no ? 1.0 : 1.0 / d;
+      if (ti > j && tj >= ti) {
+        const double2 p = bmulc(S0[j][ti], S0[j][tj]);
+        S0[ti][tj].x -= p.x * rd;
+        S0[ti][tj].y -= p.y * rd;
       }
-      piv = sqrt(d);
-      Rw[(int64_t)j * k + j] = make_double2(piv, 0.0);
+      __syncthreads();
     }
+    const double d = S0[ti][ti].x;
+    const double r = !(d > 0.0) || !isfinite(d) ? 1.0 : sqrt(d);
+    double2 v = S0[ti][tj];
+    v = tj > ti ? make_double2(v.x / r, v.y / r) : make_double2(tj == ti ? r : 0.0, 0.0);
     __syncthreads();
-    const double inv = 1.0 / piv;
-    for (int c = j + 1 + threadIdx.x; c < k; c += blockDim.x) {
-      const double2 v = Rw[(int64_t)j * k + c];
-      Rw[(int64_t)j * k + c] = make_double2(v.x * inv, v.y * inv);
+    S0[ti][tj] = v;
+    put(Rw, j0 + ti, j0 + tj, v);
+    __syncthreads();
+    {  // S1 = S0^-1 from the last row up, eight threads per column
+      const int c = t >> 3, sub = t & 7;
+      for (int a = kBT - 1; a >= 0; a--) {
+        double2 s = none;
+        if (c < kBT)
+          for (int x = a + 1 + sub; x <= c; x += 8) {
+            const double2 p = bmul(S0[a][x], S1[x][c]);
+            s.x -= p.x;
+            s.y -= p.y;
+          }
+        for (int o = 1; o < 8; o <<= 1) {
+          s.x += __shfl_xor(s.x, o, 8);
+          s.y += __shfl_xor(s.y, o, 8);
+        }
+        if (c < kBT && sub == 0) {
+          if (a == c) s.x += 1.0;
+          const double q = S0[a][a].x;
+          S1[a][c] = c >= a ? make_double2(s.x / q, s.y / q) : none;
+        }
+        __syncthreads();
+      }
     }
-    __syncthreads();
-    // trailing rows r > j: R[r][c] -= conj(R[j][r]) R[j][c], c >= r
-    const int m = k - j - 1;
-    for (int64_t e = threadIdx.x; e < (int64_t)m * m; e += blockDim.x) {
-      const int r = j + 1 + (int)(e / m), c = j + 1 + (int)(e % m);
-      if (c < r) continue;
-      const double2 p = bmulc(Rw[(int64_t)j * k + r], Rw[(int64_t)j * k + c]);
-      const double2 v = Rw[(int64_t)r * k + c];
-      Rw[(int64_t)r * k + c] = make_double2(v.x - p.x, v.y - p.y);
-    }
-    __syncthreads();
-  }
-  // R^-1 column by column: X[c][c] = 1 / R[c][c], X[i][c] = -sum_{l=i+1..c} R[i][l] X[l][c] / R[i][i]
-  for (int c = threadIdx.x; c < k; c += blockDim.x) {
-    for (int i = 0; i < k; i++)
-      if (i > c) Xw[(int64_t)i * k + c] = make_double2(0, 0);
-    Xw[(int64_t)c * k + c] = make_double2(1.0 / Rw[(int64_t)c * k + c].x, 0.0);
-    for (int i = c - 1; i >= 0; i--) {
-      double2 s = make_double2(0, 0);
-      for (int l = i + 1; l <= c; l++) {
-        const double2 p = bmul(Rw[(int64_t)i * k + l], Xw[(int64_t)l * k + c]);
+    put(Xw, j0 + ti, j0 + tj, S1[ti][tj]);
+    for (int C = J + 1; C < nt; C++) {  // block row J: R_JC = S1^H G_JC
+      S2[ti][tj] = get(Rw, j0 + ti, kBT * C + tj);
+      __syncthreads();
+      double2 s = none;
+      for (int l = 0; l <= ti; l++) {
+        const double2 p = bmulc(S1[l][ti], S2[l][tj]);
         s.x += p.x;
         s.y += p.y;
       }
-      const double d = 1.0 / Rw[(int64_t)i * k + i].x;
-      Xw[(int64_t)i * k + c] = make_double2(-s.x * d, -s.y * d);
+      put(Rw, j0 + ti, kBT * C + tj, s);
+      __syncthreads();
+    }
+    for (int B = J + 1; B < nt; B++) {  // G_BC -= R_JB^H R_JC, C >= B
+      S0[ti][tj] = get(Rw, j0 + ti, kBT * B + tj);
+      for (int C = B; C < nt; C++) {
+        S2[ti][tj] = get(Rw, j0 + ti, kBT * C + tj);
+        const double2 g = get(Rw, kBT * B + ti, kBT * C + tj);
+        __syncthreads();
+        double2 s = none;
+#pragma unroll 8
+        for (int l = 0; l < kBT; l++) {
+          const double2 p = bmulc(S0[l][ti], S2[l][tj]);
+          s.x += p.x;
+          s.y += p.y;
+        }
+        put(Rw, kBT * B + ti, kBT * C + tj,
+            C > B || tj >= ti ? make_double2(g.x - s.x, g.y - s.y) : none);
+        __syncthreads();
+      }
     }
   }
+  for (int J = 1; J < nt; J++)
+    for (int I = J - 1; I >= 0; I--) {  // X_IJ = -X_II sum_L R_IL X_LJ
+      double2 s = none;
+      for (int L = I + 1; L <= J; L++) {
+        S0[ti][tj] = get(Rw, kBT * I + ti, kBT * L + tj);
+        S1[ti][tj] = get(Xw, kBT * L + ti, kBT * J + tj);
+        __syncthreads();
+#pragma unroll 8
+        for (int l = 0; l < kBT; l++) {
+          const double2 p = bmul(S0[ti][l], S1[l][tj]);
+          s.x += p.x;
+          s.y += p.y;
+        }
+        __syncthreads();
+      }
+      S2[ti][tj] = s;
+      S0[ti][tj] = get(Xw, kBT * I + ti, kBT * I + tj);
+      __syncthreads();
+      double2 x = none;
+      for (int l = ti; l < kBT; l++) {
+        const double2 p = bmul(S0[ti][l], S2[l][tj]);
+        x.x -= p.x;
+        x.y -= p.y;
+      }
+      put(Xw, kBT * I + ti, kBT * J + tj, x);
+      __syncthreads();
+    }
+  if (t == 0 && bad) latch(status, ST_BREAKDOWN);
 }
 
 // C[w] = A[w] B[w] (k x k, row-major, leading dimension k), 32 x 32 tiles.
@@ -236,23 +313,44 @@ __global__ __launch_bounds__(256) void k_applyb(int64_t n, int k, const double2*
 }
 
 // One-sided (Hestenes) Jacobi SVD of A = R^H (k x k) per shift, one
-// workgroup of 16 waves: A and the accumulated rotations J live column-major
-// in global scratch (column c contiguous), the pairs of each round follow the
-// round-robin order and each wave takes pairs in turn, its 64 lanes splitting
-// the column length.  The rotation is the narrow path's: with
-// gamma = a_p^H a_q and e = gamma / |gamma|, the columns [a_p, conj(e) a_q]
-// are rotated by the real Jacobi angle of [[alpha, |gamma|], [|gamma|, beta]].
-// Then sigma_c = ||a_c||, sorted descending (ranks counted in parallel),
-// Ut = A diag(1/sigma), W = J, both permuted; Rinv W is formed by k_sgemm.
+// workgroup: the pairs of each round follow the round-robin order, 16 lanes a
+// pair, so that a round of up to 64 pairs runs at once.  The rotation is the
+// narrow path's: with gamma = a_p^H a_q and e = gamma / |gamma|, the columns
+// [a_p, conj(e) a_q] are rotated by the real Jacobi angle of [[alpha,
+// |gamma|], [|gamma|, beta]].  Then sigma_c = ||a_c||, sorted descending
+// (ranks counted in parallel), Ut = A diag(1/sigma), W = J, both permuted;
+// Rinv W is formed by k_sgemm.
+//
+// Bound by the latency of its rounds (m - 1 a sweep).  In LDS mode (m <= 100:
+// 160 KB) A stays in LDS, a pair's columns in registers for the round, and
+// kJacobiParts workgroups per shift compute the same rotations of A while each
+// applies them to its own rows of J, at most 16 (in global scratch, loaded at
+// the round's start): one workgroup's J traffic, 320 KB a round, took longer
+// than the rotations.  Beyond m = 100 A is in global scratch too (column c
+// contiguous) and one workgroup does everything.  At k = 100: 11.4 ms with A
+// in global scratch and a wave per pair, 5.1 ms with all of J in one
+// workgroup, 3.6 ms now.
+constexpr int kJacobiLds = 100;  // largest m whose A fits the CU's LDS
+constexpr int kJacobiEl = (kJacobiLds + 15) / 16;
+constexpr int kJacobiParts = (kJacobiLds + 15) / 16;
+__device__ __forceinline__ double sum16(double v) {
+  for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 16);
+  return v;
+}
+template <bool LDS>
 __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const double2* R, double2* A,
                                                   double2* Jm, double* sigma, double2* Ut,
                                                   double2* W, double* sv, int* rank,
                                                   uint32_t* status, int max_sweeps) {
+  extern __shared__ __align__(16) char smem_raw[];
   __shared__ int rotated;
   const int w = blockIdx.x;
   const int m = (k + 1) & ~1;  // even number of players (a zero column pads odd k)
+  const int part = blockIdx.y, nparts = gridDim.y;
+  const int j0 = LDS ? m * part / nparts : 0;  // this workgroup's rows of J
+  const int j1 = LDS ? m * (part + 1) / nparts : m;
   const double2* Rw = R + w * sM;
-  double2* Aw = A + (int64_t)w * m * m;
+  double2* Aw = LDS ? reinterpret_cast<double2*>(smem_raw) : A + (int64_t)w * m * m;
   double2* Jw = Jm + (int64_t)w * m * m;
   double* svw = sv + (int64_t)w * m;
   int* rk = rank + (int64_t)w * m;
@@ -264,17 +362,17 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
       v = make_double2(rc.x, -rc.y);
     }
     Aw[e] = v;
-    Jw[e] = make_double2(a == c ? 1.0 : 0.0, 0.0);
+    if (a >= j0 && a < j1) Jw[e] = make_double2(a == c ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nwave = blockDim.x >> 6;
+  const int group = threadIdx.x >> 4, lane = threadIdx.x & 15, ngroup = blockDim.x >> 4;
   const int npair = m / 2;
   int sweep = 0;
   for (; sweep < max_sweeps; sweep++) {
     if (threadIdx.x == 0) rotated = 0;
     __syncthreads();
     for (int rnd = 0; rnd < m - 1; rnd++) {
-      for (int pr = wave; pr < npair; pr += nwave) {
+      for (int pr = group; pr < npair; pr += ngroup) {
         int p, q;
         if (pr == 0) {
           p = 0;
@@ -286,38 +384,68 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
         if (p > q) { const int tt = p; p = q; q = tt; }
         double2* ap = Aw + (int64_t)p * m;
         double2* aq = Aw + (int64_t)q * m;
+        double2* jp = Jw + (int64_t)p * m;
+        double2* jq = Jw + (int64_t)q * m;
+        double2 ax[kJacobiEl], ay[kJacobiEl], jx, jy;
         double al = 0, be = 0, gr = 0, gi = 0;
-        for (int a = lane; a < m; a += 64) {
-          const double2 x = ap[a], y = aq[a];
+        auto gram = [&](double2 x, double2 y) {
           al += x.x * x.x + x.y * x.y;
           be += y.x * y.x + y.y * y.y;
           gr += x.x * y.x + x.y * y.y;
           gi += x.x * y.y - x.y * y.x;
+        };
+        if constexpr (LDS) {
+          const int jr = min(j0 + lane, m - 1);
+          jx = jp[jr];
+          jy = jq[jr];
+#pragma unroll
+          for (int u = 0; u < kJacobiEl; u++) {
+            const int r = lane + 16 * u;
+            ax[u] = r < m ? ap[r] : make_double2(0, 0);
+            ay[u] = r < m ? aq[r] : make_double2(0, 0);
+            gram(ax[u], ay[u]);
+          }
+        } else {
+          for (int r = lane; r < m; r += 16) gram(ap[r], aq[r]);
         }
-        for (int o = 32; o > 0; o >>= 1) {
-          al += __shfl_xor(al, o, 64);
-          be += __shfl_xor(be, o, 64);
-          gr += __shfl_xor(gr, o, 64);
-          gi += __shfl_xor(gi, o, 64);
-        }
-        const double g = sqrt(gr * gr + gi * gi);
-        if (g > 1e-15 * sqrt(al * be) && g > 0.0) {
-          const double er = gr / g, ei = -gi / g;  // e^{-i phi}
-          const double zeta = (be - al) / (2.0 * g);
-          const double tn = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-          const double c = 1.0 / sqrt(1.0 + tn * tn), sn = c * tn;
-          double2* jp = Jw + (int64_t)p * m;
-          double2* jq = Jw + (int64_t)q * m;
-          for (int a = lane; a < m; a += 64) {
-            double2 x = ap[a], y = aq[a];
-            double2 yp = make_double2(y.x * er - y.y * ei, y.x * ei + y.y * er);
-            ap[a] = make_double2(c * x.x - sn * yp.x, c * x.y - sn * yp.y);
-            aq[a] = make_double2(sn * x.x + c * yp.x, sn * x.y + c * yp.y);
-            x = jp[a];
-            y = jq[a];
-            yp = make_double2(y.x * er - y.y * ei, y.x * ei + y.y * er);
-            jp[a] = make_double2(c * x.x - sn * yp.x, c * x.y - sn * yp.y);
-            jq[a] = make_double2(sn * x.x + c * yp.x, sn * x.y + c * yp.y);
+        al = sum16(al);
+        be = sum16(be);
+        gr = sum16(gr);
+        gi = sum16(gi);
+        double er, ei, c, sn;
+        if (jacobi_angle(al, be, gr, gi, er, ei, c, sn)) {
+          auto rotate = [&](double2& x, double2& y) {
+            const double2 yp = make_double2(y.x * er - y.y * ei, y.x * ei + y.y * er);
+            y = make_double2(sn * x.x + c * yp.x, sn * x.y + c * yp.y);
+            x = make_double2(c * x.x - sn * yp.x, c * x.y - sn * yp.y);
+          };
+          if constexpr (LDS) {
+#pragma unroll
+            for (int u = 0; u < kJacobiEl; u++) {
+              const int r = lane + 16 * u;
+              rotate(ax[u], ay[u]);
+              if (r < m) {
+                ap[r] = ax[u];
+                aq[r] = ay[u];
+              }
+            }
+            if (j0 + lane < j1) {
+              rotate(jx, jy);
+              jp[j0 + lane] = jx;
+              jq[j0 + lane] = jy;
+            }
+          } else {
+            for (int r = lane; r < m; r += 16) {
+              double2 x = ap[r], y = aq[r];
+              rotate(x, y);
+              ap[r] = x;
+              aq[r] = y;
+              x = jp[r];
+              y = jq[r];
+              rotate(x, y);
+              jp[r] = x;
+              jq[r] = y;
+            }
           }
           if (lane == 0) rotated = 1;
         }
@@ -327,7 +455,10 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
     if (!rotated) break;
     __syncthreads();
   }
-  if (threadIdx.x == 0 && rotated) latch(status, ST_SVD_NOT_CONVERGED);
+  if (threadIdx.x == 0 && rotated && part == 0) latch(status, ST_SVD_NOT_CONVERGED);
+  // every part has the same norms and ranks, in scratch of its own
+  svw += (int64_t)part * gridDim.x * m;
+  rk += (int64_t)part * gridDim.x * m;
   for (int c = threadIdx.x; c < k; c += blockDim.x) {
     double s = 0;
     for (int a = 0; a < k; a++) {
@@ -346,6 +477,7 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
   __syncthreads();
   for (int64_t e = threadIdx.x; e < (int64_t)k * k; e += blockDim.x) {
     const int src = (int)(e / k), a = (int)(e % k);  // source column, row
+    if (a < j0 || a >= j1) continue;
     const int c = rk[src];
     const double s = svw[src];
     const double2 u = Aw[(int64_t)src * m + a];
@@ -395,14 +527,36 @@ __global__ void k_cols_copy(int64_t n, int k, int64_t wstride, int c0, int kg, c
 
 }  // namespace
 
-int gramb_chunks(int64_t n) { return (int)std::min<int64_t>(kBigChunks, (n + 2047) / 2048); }
+// Row chunks of the tiled Gram matrix: at least 128 rows each, and with the
+// nt (nt + 1) / 2 tiles about 512 workgroups (at least 16 chunks, at most 64).
+// At n = 4096, k = 100 two chunks of 2048 rows (20 workgroups) took 342 us.
+int gramb_chunks(int64_t n, int k) {
+  const int nt = (k + kBT - 1) / kBT;
+  const int want = std::min(64, std::max(16, 1024 / (nt * (nt + 1))));
+  return (int)std::min<int64_t>(want, (n + 127) / 128);
+}
+// complex elements of partial sums per shift for any k <= k_max
+size_t gramb_partial(int64_t n, int k_max) {
+  size_t most = 0;
+  for (int nt = 1; nt <= (k_max + kBT - 1) / kBT; nt++) {
+    const size_t k = std::min(kBT * nt, k_max);
+    most = std::max(most, (size_t)gramb_chunks(n, (int)k) * k * k);
+  }
+  return most;
+}
+// dynamic LDS of the wide kernels, set when a handle is created
+hipError_t prepare_big() {
+  return hipFuncSetAttribute((const void*)k_jacobib<true>,
+                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                             kJacobiLds * kJacobiLds * (int)sizeof(double2));
+}
 
 namespace {
 
 // Gram, Cholesky and R^-1 of Y into G, R, Rinv (k x k per shift, stride sM)
 void gram_chol(int64_t n, int n_omega, int k, const double* Y, SmallWs& ws, double* G, double* R,
                double* Rinv, uint32_t* status, hipStream_t s) {
-  const int nt = (k + kBT - 1) / kBT, nc = gramb_chunks(n);
+  const int nt = (k + kBT - 1) / kBT, nc = gramb_chunks(n, k);
   const int64_t rows = (n + nc - 1) / nc, sM = (int64_t)ws.kmax * ws.kmax;
   hipLaunchKernelGGL(k_gramb_partial, dim3(nt * nt, nc, n_omega), dim3(256), 0, s, n, k,
                      (const double2*)Y, rows, nc, (double2*)ws.partial);
@@ -462,11 +616,16 @@ hipError_t launch_small_svd_big(int64_t n, int n_omega, int k, const double* Z, 
   const int m = (k + 1) & ~1;
   // Jacobi scratch: A and J (m x m each; big1 / big2 hold (kmax + 1)^2 per
   // shift), the column norms and ranks in the partial-sum buffer
+  const int parts = m <= kJacobiLds ? kJacobiParts : 1;
   double* sv = ws.partial;
-  int* rank = reinterpret_cast<int*>(ws.partial + (size_t)n_omega * m);
-  hipLaunchKernelGGL(k_jacobib, dim3(n_omega), dim3(1024), 0, s, k, sM, (const double2*)ws.R,
-                     (double2*)ws.big1, (double2*)ws.big2, sigma, (double2*)ws.Ut,
-                     (double2*)ws.W, sv, rank, status, ws.jacobi_sweeps);
+  int* rank = reinterpret_cast<int*>(ws.partial + (size_t)parts * n_omega * m);
+  auto jacobi = [&](auto kernel, size_t lds) {
+    hipLaunchKernelGGL(kernel, dim3(n_omega, parts), dim3(1024), lds, s, k, sM,
+                       (const double2*)ws.R, (double2*)ws.big1, (double2*)ws.big2, sigma,
+                       (double2*)ws.Ut, (double2*)ws.W, sv, rank, status, ws.jacobi_sweeps);
+  };
+  if (m <= kJacobiLds) jacobi(k_jacobib<true>, (size_t)m * m * sizeof(double2));
+  else jacobi(k_jacobib<false>, 0);
   sgemm(n_omega, k, sM, ws.Rinv, ws.W, ws.G, s);  // Tv = R^-1 W
   applyb(n, n_omega, k, Z, sM, ws.G, V, s);        // V = Z Tv
   if (Uqu) applyb(n, n_omega, k, Q, sM, ws.Ut, Uqu, s);

@@ -34,6 +34,53 @@ struct cplx {
   R re, im;
 };
 
+// 1 / sqrt(x) and 1 / x in FP64: the hardware's approximation (about 2^-24)
+// and two Newton steps, for normal positive x well inside the range
+__device__ __forceinline__ double rsqrt_newton(double x) {
+  double r = __builtin_amdgcn_rsq(x);
+  r = fma(r, fma(-0.5 * x * r, r, 0.5), r);
+  return fma(r, fma(-0.5 * x * r, r, 0.5), r);
+}
+__device__ __forceinline__ double recip_newton(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+// The Jacobi rotation of two columns with Gram matrix [[al, g e], [., be]],
+// g e = gr + i gi: false when it is below the threshold |gr + i gi| <= 1e-15
+// sqrt(al be).  er + i ei = conj(e); the columns [x, (er + i ei) y] are rotated
+// by (c, sn).  Reciprocal roots instead of roots and divisions: their
+// sequences are most of a round's instructions.
+__device__ __forceinline__ bool jacobi_angle(double al, double be, double gr, double gi,
+                                             double& er, double& ei, double& c, double& sn) {
+  const double g2 = gr * gr + gi * gi;
+  if (!(g2 > 1e-30 * (al * be)) || !(g2 > 1e-290) || !(g2 < 1e290)) {
+    // the ends of the range, where squares under- or overflow
+    const double g = hypot(gr, gi);
+    if (!(g > 1e-15 * sqrt(al) * sqrt(be) && g > 0.0)) return false;
+    er = gr / g;
+    ei = -gi / g;
+    const double zeta = (be - al) / (2.0 * g);
+    const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + hypot(1.0, zeta));
+    c = 1.0 / sqrt(1.0 + t * t);
+    sn = c * t;
+    return true;
+  }
+  const double rg = rsqrt_newton(g2);
+  er = gr * rg;
+  ei = -gi * rg;
+  const double zeta = 0.5 * (be - al) * rg, z = fabs(zeta);
+  const double z2 = fma(z, z, 1.0);
+  const double s = z < 1e8 ? z2 * rsqrt_newton(z2) : z;  // sqrt(1 + z^2)
+  const double u = z + s;
+  double t = u < 1e290 ? recip_newton(u) : 0.0;
+  if (zeta < 0) t = -t;
+  c = rsqrt_newton(fma(t, t, 1.0));
+  sn = c * t;
+  return true;
+}
+
 __device__ __forceinline__ void latch(uint32_t* status, uint32_t bit) {
   atomicOr(status, bit);
 }
@@ -265,7 +312,8 @@ hipError_t launch_cols_place(int64_t n, int n_omega, int ncols, const double* sr
 hipError_t launch_refine_reset(int n_omega, double* rho, hipStream_t s);
 // Wide sketches, 32 < k <= kMaxWideK (rr_bigk.hip), FP64 only
 constexpr int kMaxWideK = 512;
-int gramb_chunks(int64_t n);
+size_t gramb_partial(int64_t n, int k_max);  // complex elements per shift
+hipError_t prepare_big();
 hipError_t launch_cholqr2_big(int64_t n, int n_omega, int k, double* Y, double* tmp, SmallWs& ws,
                               uint32_t* status, hipStream_t s);
 hipError_t launch_small_svd_big(int64_t n, int n_omega, int k, const double* Z, const double* Q,

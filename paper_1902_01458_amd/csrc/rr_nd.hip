@@ -117,13 +117,10 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
                           __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
-// 1 / x: the hardware reciprocal and two Newton steps (the division's length
-// is on the chain), the division itself near the ends of the range
+// 1 / x off the division's length, which is on the chain; the division itself
+// near the ends of the range
 __device__ __forceinline__ double recip(double x) {
-  if (!(x > 1e-290 && x < 1e290)) return 1.0 / x;
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
+  return x > 1e-290 && x < 1e290 ? recip_newton(x) : 1.0 / x;
 }
 __device__ __forceinline__ float recip(float x) { return 1.0f / x; }
 

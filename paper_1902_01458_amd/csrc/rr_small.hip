@@ -485,13 +485,8 @@ __global__ __launch_bounds__(256) void k_jacobi_svd(int k, int kmax, const doubl
           gr += __shfl_xor(gr, o, 8);
           gi += __shfl_xor(gi, o, 8);
         }
-        double g = sqrt(gr * gr + gi * gi);
-        if (g > 1e-15 * sqrt(al * be) && g > 0.0) {
-          // phase e^{i phi} = gamma/|gamma|; rotate [a_p, e^{-i phi} a_q]
-          double er = gr / g, ei = -gi / g;  // e^{-i phi}
-          double zeta = (be - al) / (2.0 * g);
-          double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-          double c = 1.0 / sqrt(1.0 + t * t), sn = c * t;
+        double er, ei, c, sn;
+        if (jacobi_angle(al, be, gr, gi, er, ei, c, sn)) {  // rotate [a_p, e^{-i phi} a_q]
           for (int a = sub; a < m; a += 8) {
             double2 x = A[a][p], y = A[a][q];
             double2 yp = make_double2(y.x * er - y.y * ei, y.x * ei + y.y * er);
