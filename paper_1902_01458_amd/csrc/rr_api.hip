@@ -196,8 +196,8 @@ int probe_cols(int k, int np_max) {
 hipError_t lu_solve(rr_factors* f, int k, bool fp32, int adjoint, const double* Bm,
                     int64_t bstride, double* X, hipStream_t s, const uint32_t* skip = nullptr) {
   if (f->nd)
-    return launch_nd_solve(opdesc(f), f->ndp, f->ndd, f->n, f->n_omega, k, 0, k, fp32, adjoint, Bm, bstride,
-                           X, s, skip);
+    return launch_nd_solve(opdesc(f), f->ndp, f->ndd, f->n, f->n_omega, k, 0, k, fp32, false,
+                           adjoint, Bm, bstride, X, s, skip);
   return launch_solve(f->geom, f->n, f->n_omega, k, fp32, f->tiles, adjoint, Bm, bstride, X,
                       f->xs, f->cbuf, f->flags, ticket_word(f), st_word(f), f->solve_grid, s,
                       skip);
@@ -360,7 +360,7 @@ rr_status solve_any(rr_factors* f, int k, int adjoint, const double* Bm, int64_t
     // gathered into and scattered from two narrow blocks with the band LU
     for (int c0 = 0; f->nd && c0 < k; c0 += kNarrowK)
       RR_HIP(launch_nd_solve(opdesc(f), f->ndp, f->ndd, f->n, f->n_omega, std::min(kNarrowK, k - c0), c0, k,
-                             false, adjoint, Bm, bstride, X, s));
+                             false, false, adjoint, Bm, bstride, X, s));
     if (f->nd) return RR_OK;
     double* nb = f->wide_tmp;
     double* nx = f->wide_tmp + 2 * (size_t)f->n_omega * kNarrowK * f->n;
@@ -412,16 +412,25 @@ rr_status solve_any(rr_factors* f, int k, int adjoint, const double* Bm, int64_t
   RR_HIP(launch_fill_u32(conv_word(f), 0u, 1, s));
   for (int it = 0; it < f->refine_iters; it++) {
     // res = Bm - M X in FP64 from the stencil, then res <- M32^-1 res (or the
-    // GMRES-IR correction), X += res
-    RR_HIP(launch_apply(opdesc(f), f->omega, f->n_omega, kk, adjoint, X1, B1, bs1, res, s,
-                        conv_word(f)));
-    if (f->gm.m > 0) {
-      RR_HIP(gmres_correction(f, k, adjoint, res, s));
+    // GMRES-IR correction), X += res.  Between FP32 factors the residual and
+    // the correction are FP32 values, and stored as such where the solve
+    // takes them (the band LU's and GMRES-IR take FP64 blocks).
+    const bool r32 = f->nd && f->gm.m == 0;
+    if (r32) {
+      RR_HIP(launch_residual32(opdesc(f), f->omega, f->n_omega, kk, adjoint, X1, B1, bs1,
+                               (float*)res, s, conv_word(f)));
+      RR_HIP(launch_nd_solve(opdesc(f), f->ndp, f->ndd, n, f->n_omega, kk, 0, kk, true, true,
+                             adjoint, res, pblk, res, s, conv_word(f)));
     } else {
-      RR_HIP(lu_solve(f, kk, true, adjoint, res, pblk, res, s, conv_word(f)));
+      RR_HIP(launch_apply(opdesc(f), f->omega, f->n_omega, kk, adjoint, X1, B1, bs1, res, s,
+                          conv_word(f)));
+      if (f->gm.m > 0)
+        RR_HIP(gmres_correction(f, k, adjoint, res, s));
+      else
+        RR_HIP(lu_solve(f, kk, true, adjoint, res, pblk, res, s, conv_word(f)));
     }
     RR_HIP(launch_fill_u32(fail_word(f), 0u, 1, s));
-    RR_HIP(launch_refine_update(f->n, f->n_omega, k, X1, res, tol, it, adjoint, f->small,
+    RR_HIP(launch_refine_update(f->n, f->n_omega, k, X1, res, r32, tol, it, adjoint, f->small,
                                 st_word(f), fail_word(f), s, conv_word(f), kk, p, f->probe_z));
     hipLaunchKernelGGL(k_refine_step, dim3(1), dim3(64), 0, s, (const uint32_t*)fail_word(f),
                        f->ctrl + 4 + it, conv_word(f));

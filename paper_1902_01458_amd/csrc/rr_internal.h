@@ -183,6 +183,10 @@ hipError_t launch_burgers_coeffs(int nx, int ny, const double* U, double hx, dou
 hipError_t launch_apply(const OpDesc& op, const double* omega /*dev 2*n_omega*/, int n_omega,
                         int k, int adjoint, const double* X, const double* Bm, int64_t bstride,
                         double* Y, hipStream_t s, const uint32_t* skip = nullptr);
+// The residual b - M X (b - M^H X) rounded to FP32.
+hipError_t launch_residual32(const OpDesc& op, const double* omega, int n_omega, int k, int adjoint,
+                             const double* X, const double* Bm, int64_t bstride, float* Y,
+                             hipStream_t s, const uint32_t* skip);
 // Theta (k, n) of step 1 for an elementwise kind (RR_TM_ORTHONORMAL: the
 // unweighted Gaussian matrix, to be orthonormalised and weighted by the
 // caller); zeta: nonzeros per row of RR_TM_SPARSE, already in [1, k].
@@ -295,7 +299,8 @@ constexpr int kProbeSlot = 32;  // [32, 32 + p): the probe columns' errors befor
 // first k; with probes (p > 0: columns k .. k+p-1 solve M x = M z for the
 // known z of Z, p blocks of n per shift) the first correction (it = 0) also
 // measures the contraction on them.
-hipError_t launch_refine_update(int n, int n_omega, int k, double* X, const double* D,
+// d32: D is in FP32.
+hipError_t launch_refine_update(int n, int n_omega, int k, double* X, const void* D, bool d32,
                                 double tol, int it, int adjoint, SmallWs& ws, uint32_t* status,
                                 uint32_t* fail_count, hipStream_t s,
                                 const uint32_t* skip = nullptr, int kk = 0, int p = 0,

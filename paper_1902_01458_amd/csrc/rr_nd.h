@@ -88,10 +88,10 @@ hipError_t launch_nd_factor(const OpDesc& op, const NdPlan& pl, const NdDevice& 
                             hipStream_t s);
 // X = M^-1 Bm (M^-H Bm) for columns [c0, c0 + k) of blocks with ktot columns
 // per shift, k <= 32; Bm's blocks are bstride complex elements apart (0:
-// shared) and may be X's.
-hipError_t launch_nd_solve(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
-                           int c0, int ktot, bool fp32, int adjoint, const double* Bm,
-                           int64_t bstride, double* X, hipStream_t s,
+// shared) and may be X's.  io32 (FP32 factors only): Bm and X are FP32.
+hipError_t launch_nd_solve(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n,
+                           int n_omega, int k, int c0, int ktot, bool fp32, bool io32, int adjoint,
+                           const void* Bm, int64_t bstride, void* X, hipStream_t s,
                            const uint32_t* skip = nullptr);
 
 }  // namespace rr

@@ -859,7 +859,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_update(FactorArgs<R> g) {
 // ---------------------------------------------------------------------------
 // Solves
 // ---------------------------------------------------------------------------
-template <typename R>
+template <typename R, typename IO>
 struct SolveArgs {
   const NdFront* fronts;
   const NdTask* tasks;
@@ -869,8 +869,8 @@ struct SolveArgs {
   cplx<R>*uin, *uout;     // the halves' updates, this level's
   int64_t nfactor, nw, nuin, nuout;  // elements per shift
   OpDesc op;
-  const double2* B;       // the caller's right-hand sides and solutions (their first column)
-  double2* X;
+  const cplx<IO>* B;      // the caller's right-hand sides and solutions (their first column)
+  cplx<IO>* X;
   int64_t n, bstride, xstride;
   int k, adjoint, qsplit;
   int w0;
@@ -883,10 +883,10 @@ __device__ __forceinline__ bool skipped(const uint32_t* skip) {
 // The separators' right-hand sides by rows: w[row][j] = B[j][pdof[row]], zero
 // for padding and for the row after the last; back for the solution.
 constexpr int kRowTile = 32;
-template <typename R, bool OUT>
+template <typename R, typename IO, bool OUT>
 __global__ __launch_bounds__(256) void k_nd_permute(const int* pdof, int64_t rows, int64_t n, int k,
-                                                    int64_t cstride, const double2* B,
-                                                    double2* X, cplx<R>* W, int w0,
+                                                    int64_t cstride, const cplx<IO>* B,
+                                                    cplx<IO>* X, cplx<R>* W, int w0,
                                                     const uint32_t* skip) {
   if (skipped(skip)) return;
   __shared__ cplx<R> tile[kRowTile][33];
@@ -903,14 +903,14 @@ __global__ __launch_bounds__(256) void k_nd_permute(const int* pdof, int64_t row
     if (dof >= 0)
       for (int j = threadIdx.x >> 5; j < k; j += 8) {
         const cplx<R> v = tile[r][j];
-        X[(int64_t)w * cstride + (int64_t)j * n + dof] = make_double2(v.re, v.im);
+        X[(int64_t)w * cstride + (int64_t)j * n + dof] = cplx<IO>{(IO)v.re, (IO)v.im};
       }
   } else {
     for (int j = threadIdx.x >> 5; j < k; j += 8) {
       cplx<R> v{(R)0, (R)0};
       if (dof >= 0) {
-        const double2 b = B[(int64_t)w * cstride + (int64_t)j * n + dof];
-        v = cplx<R>{(R)b.x, (R)b.y};
+        const cplx<IO> b = B[(int64_t)w * cstride + (int64_t)j * n + dof];
+        v = cplx<R>{(R)b.re, (R)b.im};
       }
       tile[r][j] = v;
     }
@@ -989,8 +989,8 @@ __device__ __forceinline__ R& part(cplx<R>* a, int64_t pitch, int r, int b) {
 }
 
 // A leaf, sweep up: z = A b (A^H b) in LDS, u = -F21 z (-F12^H z).
-template <typename R, int NB, bool ADJ>
-__global__ __launch_bounds__(256, 2) void k_nd_leaf_up(SolveArgs<R> a) {
+template <typename R, typename IO, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_leaf_up(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ LeafBorder<R> lb;
@@ -1002,13 +1002,13 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf_up(SolveArgs<R> a) {
   leaf_border<R>(lb, a.op, fr, a.pdof, a.bmap, a.grow);
   const int r = threadIdx.x & 63;
   const int dof = r < P ? a.pdof[fr.row + r] : -1;
-  const double2* B = a.B + (int64_t)w * a.bstride;
+  const cplx<IO>* B = a.B + (int64_t)w * a.bstride;
   if (r < P)
     for (int j = threadIdx.x >> 6; j < 8 * NB; j += 4) {
       cplx<R> v{(R)0, (R)0};
       if (dof >= 0 && j < k) {
-        const double2 b = B[j * a.n + dof];
-        v = cplx<R>{(R)b.x, (R)b.y};
+        const cplx<IO> b = B[j * a.n + dof];
+        v = cplx<R>{(R)b.re, (R)b.im};
       }
       bs[r * NC + j] = v;
     }
@@ -1040,8 +1040,8 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf_up(SolveArgs<R> a) {
 }
 
 // A leaf, sweep down: x = A (b - F12 x2) (A^H (b - F21^H x2)) into X.
-template <typename R, int NB, bool ADJ>
-__global__ __launch_bounds__(256, 2) void k_nd_leaf_down(SolveArgs<R> a) {
+template <typename R, typename IO, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_leaf_down(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
   __shared__ LeafBorder<R> lb;
@@ -1053,13 +1053,13 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf_down(SolveArgs<R> a) {
   leaf_border<R>(lb, a.op, fr, a.pdof, a.bmap, a.grow);
   const int r = threadIdx.x & 63;
   const int dof = r < P ? a.pdof[fr.row + r] : -1;
-  const double2* B = a.B + (int64_t)w * a.bstride;
+  const cplx<IO>* B = a.B + (int64_t)w * a.bstride;
   if (r < P)
     for (int j = threadIdx.x >> 6; j < 8 * NB; j += 4) {
       cplx<R> v{(R)0, (R)0};
       if (dof >= 0 && j < k) {
-        const double2 b = B[j * a.n + dof];
-        v = cplx<R>{(R)b.x, (R)b.y};
+        const cplx<IO> b = B[j * a.n + dof];
+        v = cplx<R>{(R)b.re, (R)b.im};
       }
       bs[r * NC + j] = v;
     }
@@ -1099,14 +1099,14 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf_down(SolveArgs<R> a) {
   if (dof >= 0)
     for (int j = threadIdx.x >> 6; j < k; j += 4) {
       const cplx<R> v = bs[r * NC + j];
-      a.X[(int64_t)w * a.xstride + j * a.n + dof] = make_double2(v.re, v.im);
+      a.X[(int64_t)w * a.xstride + j * a.n + dof] = cplx<IO>{(IO)v.re, (IO)v.im};
     }
 }
 
 // A front with P <= 64, sweep up: one workgroup per front (and share of its
 // border rows, blockIdx.z).
-template <typename R, int NB, bool ADJ>
-__global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
+template <typename R, typename IO, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
   constexpr int NC = 8 * NB;
@@ -1179,8 +1179,8 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R> a) {
 
 // A front with P <= 64, sweep down; the four waves split the inner dimension
 // where P leaves them idle.
-template <typename R, int NB, bool ADJ>
-__global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R> a) {
+template <typename R, typename IO, int NB, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
   constexpr int NC = 8 * NB;
@@ -1241,8 +1241,8 @@ __global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R> a) {
 }
 
 // P > 64: b1 of 64 rows (into w, or z for the adjoint sweep)
-template <typename R>
-__global__ __launch_bounds__(256) void k_nd_gather(SolveArgs<R> a) {
+template <typename R, typename IO>
+__global__ __launch_bounds__(256) void k_nd_gather(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   const int w = a.w0 + blockIdx.y;
   const NdTask t = a.tasks[blockIdx.x];
@@ -1267,8 +1267,8 @@ enum { ND_Z = 0,    // z = A w               (forward, up)
        ND_U = 1,    // u = pulled - F21 z    (adjoint: B12^H z)
        ND_X = 2,    // w = z - B12 w[border]  (adjoint: z -= F21^H w[border])
        ND_AH = 3 }; // w = A^H z             (adjoint, down)
-template <typename R, int NB, int MODE, bool ADJ>
-__global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R> a) {
+template <typename R, typename IO, int NB, int MODE, bool ADJ>
+__global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   constexpr int NC = 8 * NB;
   constexpr bool KF = MODE == ND_X || MODE == ND_AH;
@@ -1381,12 +1381,12 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
   return hipGetLastError();
 }
 
-template <typename R, int NB, bool ADJ>
-hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k, int c0,
-                     int ktot, const double* Bm, int64_t bstride, double* X, hipStream_t s,
-                     const uint32_t* skip) {
+template <typename R, typename IO, int NB, bool ADJ>
+hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega,
+                     int k, int c0, int ktot, const void* Bm, int64_t bstride, void* X,
+                     hipStream_t s, const uint32_t* skip) {
   constexpr int NC = 8 * NB;
-  SolveArgs<R> a{};
+  SolveArgs<R, IO> a{};
   a.op = op;
   a.fronts = d.fronts;
   a.pdof = d.pdof;
@@ -1401,8 +1401,8 @@ hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int6
   a.adjoint = ADJ;
   a.skip = skip;
   const unsigned rb = (unsigned)((pl.rows + 1 + kRowTile - 1) / kRowTile);
-  const double2* B = (const double2*)Bm + (int64_t)c0 * n;
-  double2* Xo = (double2*)X + (int64_t)c0 * n;
+  const cplx<IO>* B = (const cplx<IO>*)Bm + (int64_t)c0 * n;
+  cplx<IO>* Xo = (cplx<IO>*)X + (int64_t)c0 * n;
   a.B = B;
   a.X = Xo;
   a.n = n;
@@ -1424,29 +1424,29 @@ hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int6
       a.nuin = pl.urows[~dep & 1] * k;
       return pl.levels[dep];
     };
-    hipLaunchKernelGGL((k_nd_permute<R, false>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n,
-                       k, bstride, B, (double2*)nullptr, a.w, w0, skip);
+    hipLaunchKernelGGL((k_nd_permute<R, IO, false>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n,
+                       k, bstride, B, (cplx<IO>*)nullptr, a.w, w0, skip);
     for (int dep = (int)pl.levels.size() - 1; dep >= 0; dep--) {
       const NdLevel& lv = level(dep);
-      run(k_nd_leaf_up<R, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
+      run(k_nd_leaf_up<R, IO, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
       if (lv.small.count) {
-        run(k_nd_up<R, NB, ADJ>, lv.small, (size_t)lv.maxP * NC * (ADJ ? 1 : 2) * sizeof(cplx<R>),
+        run(k_nd_up<R, IO, NB, ADJ>, lv.small, (size_t)lv.maxP * NC * (ADJ ? 1 : 2) * sizeof(cplx<R>),
             shares(lv, nw));
       }
-      run(k_nd_gather<R>, lv.gather, 0);
-      if (!ADJ) run(k_nd_rows<R, NB, ND_Z, ADJ>, lv.rowsP, 0);
-      run(k_nd_rows<R, NB, ND_U, ADJ>, lv.rowsQ, 0);
+      run(k_nd_gather<R, IO>, lv.gather, 0);
+      if (!ADJ) run(k_nd_rows<R, IO, NB, ND_Z, ADJ>, lv.rowsP, 0);
+      run(k_nd_rows<R, IO, NB, ND_U, ADJ>, lv.rowsQ, 0);
     }
     for (int dep = 0; dep < (int)pl.levels.size(); dep++) {
       const NdLevel& lv = level(dep);
-      run(k_nd_down<R, NB, ADJ>, lv.small,
+      run(k_nd_down<R, IO, NB, ADJ>, lv.small,
           (size_t)(64 + (ADJ ? lv.maxP : 0)) * NC * sizeof(cplx<R>));
-      run(k_nd_rows<R, NB, ND_X, ADJ>, lv.rowsP, 0);
-      if (ADJ) run(k_nd_rows<R, NB, ND_AH, ADJ>, lv.rowsP, 0);
-      run(k_nd_leaf_down<R, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
+      run(k_nd_rows<R, IO, NB, ND_X, ADJ>, lv.rowsP, 0);
+      if (ADJ) run(k_nd_rows<R, IO, NB, ND_AH, ADJ>, lv.rowsP, 0);
+      run(k_nd_leaf_down<R, IO, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
     }
-    hipLaunchKernelGGL((k_nd_permute<R, true>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n, k,
-                       (int64_t)ktot * n, (const double2*)nullptr, Xo, a.w, w0, skip);
+    hipLaunchKernelGGL((k_nd_permute<R, IO, true>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n, k,
+                       (int64_t)ktot * n, (const cplx<IO>*)nullptr, Xo, a.w, w0, skip);
   }
   return hipGetLastError();
 }
@@ -1480,23 +1480,24 @@ hipError_t launch_nd_factor(const OpDesc& op, const NdPlan& pl, const NdDevice& 
               : factor_run<double>(op, pl, d, omega, n_omega, status, s);
 }
 
-hipError_t launch_nd_solve(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n, int n_omega, int k,
-                           int c0, int ktot, bool fp32, int adjoint, const double* Bm,
-                           int64_t bstride, double* X, hipStream_t s, const uint32_t* skip) {
-  auto go = [&](auto r, auto nb, auto adj) {
-    return solve_run<decltype(r), decltype(nb)::value, decltype(adj)::value>(
+hipError_t launch_nd_solve(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int64_t n,
+                           int n_omega, int k, int c0, int ktot, bool fp32, bool io32, int adjoint,
+                           const void* Bm, int64_t bstride, void* X, hipStream_t s,
+                           const uint32_t* skip) {
+  auto go = [&](auto r, auto io, auto nb, auto adj) {
+    return solve_run<decltype(r), decltype(io), decltype(nb)::value, decltype(adj)::value>(
         op, pl, d, n, n_omega, k, c0, ktot, Bm, bstride, X, s, skip);
   };
-  auto by_adj = [&](auto r, auto nb) {
-    return adjoint ? go(r, nb, std::true_type{}) : go(r, nb, std::false_type{});
+  auto by_adj = [&](auto r, auto io, auto nb) {
+    return adjoint ? go(r, io, nb, std::true_type{}) : go(r, io, nb, std::false_type{});
   };
-  auto by_nb = [&](auto r) {
-    return k <= 8    ? by_adj(r, std::integral_constant<int, 1>{})
-           : k <= 16 ? by_adj(r, std::integral_constant<int, 2>{})
-           : k <= 24 ? by_adj(r, std::integral_constant<int, 3>{})
-                     : by_adj(r, std::integral_constant<int, 4>{});
+  auto by_nb = [&](auto r, auto io) {
+    return k <= 8    ? by_adj(r, io, std::integral_constant<int, 1>{})
+           : k <= 16 ? by_adj(r, io, std::integral_constant<int, 2>{})
+           : k <= 24 ? by_adj(r, io, std::integral_constant<int, 3>{})
+                     : by_adj(r, io, std::integral_constant<int, 4>{});
   };
-  return fp32 ? by_nb(0.0f) : by_nb(0.0);
+  return !fp32 ? by_nb(0.0, 0.0) : io32 ? by_nb(0.0f, 0.0f) : by_nb(0.0f, 0.0);
 }
 
 }  // namespace rr

@@ -575,8 +575,9 @@ hipError_t launch_small_svd(int n, int n_omega, int k, const double* Z, const do
 // all of a column's loads before it adds them up (in i order), so a column
 // costs one memory round trip.
 constexpr int kColGroup = 4;
+template <typename RD>
 __global__ __launch_bounds__(256) void k_colnorm_partial(int64_t n, int k, double2* X,
-                                                         const double2* __restrict__ D,
+                                                         const cplx<RD>* __restrict__ D,
                                                          int nchunk, double* partial,
                                                          double* partial2, const uint32_t* skip) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
@@ -587,13 +588,17 @@ __global__ __launch_bounds__(256) void k_colnorm_partial(int64_t n, int k, doubl
   const int j1 = min(k, kColGroup * ((int)blockIdx.z + 1));
   for (int j = kColGroup * blockIdx.z; j < j1; j++) {
     double2* x = X + ((int64_t)w * k + j) * n;
-    const double2* d = D ? D + ((int64_t)w * k + j) * n : nullptr;
+    const cplx<RD>* d = D ? D + ((int64_t)w * k + j) * n : nullptr;
     double2 xv[RPT], dv[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; i++) {
       const int64_t r = r0 + threadIdx.x + 256 * i;
       xv[i] = r < r1 ? x[r] : make_double2(0, 0);
-      dv[i] = d && r < r1 ? d[r] : make_double2(0, 0);
+      dv[i] = make_double2(0, 0);
+      if (d && r < r1) {
+        const cplx<RD> q = d[r];
+        dv[i] = make_double2(q.re, q.im);
+      }
     }
     double sx = 0, sd = 0;
 #pragma unroll
@@ -680,10 +685,9 @@ hipError_t launch_colnorm_scale(int n, int n_omega, int k, const double* W, doub
   int nc = nchunks(n);
   if (nc > ws.nchunk || k > KM) return hipErrorInvalidValue;
   double* part = ws.partial;
-  hipLaunchKernelGGL(k_colnorm_partial, colnorm_grid(nc, n_omega, k), dim3(256), 0, s,
-                     (int64_t)n, k,
-                     (double2*)W, (const double2*)nullptr, nc, part, (double*)nullptr,
-                     (const uint32_t*)nullptr);
+  hipLaunchKernelGGL((k_colnorm_partial<double>), colnorm_grid(nc, n_omega, k), dim3(256), 0, s,
+                     (int64_t)n, k, (double2*)W, (const cplx<double>*)nullptr, nc, part,
+                     (double*)nullptr, (const uint32_t*)nullptr);
   hipLaunchKernelGGL(k_colnorm_final, dim3(n_omega), dim3(64), 0, s, k, nc, part, sigma, status);
   if (U)
     hipLaunchKernelGGL(k_scale_cols, scale_grid(n, k, n_omega), dim3(256), 0, s,
@@ -872,8 +876,8 @@ hipError_t launch_refine_reset(int n_omega, double* rho, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_refine_update(int n, int n_omega, int k, double* X, const double* D, double tol,
-                                int it, int adjoint, SmallWs& ws, uint32_t* status,
+hipError_t launch_refine_update(int n, int n_omega, int k, double* X, const void* D, bool d32,
+                                double tol, int it, int adjoint, SmallWs& ws, uint32_t* status,
                                 uint32_t* fail_count, hipStream_t s, const uint32_t* skip, int kk,
                                 int p, const double* Z) {
   int nc = nchunks(n);
@@ -881,9 +885,12 @@ hipError_t launch_refine_update(int n, int n_omega, int k, double* X, const doub
   if (nc > ws.nchunk || kk > KM || (p > 0 && (!Z || k + p > kk))) return hipErrorInvalidValue;
   double* px = ws.partial;
   double* pd = ws.partial + (size_t)n_omega * nc * 64;
-  hipLaunchKernelGGL(k_colnorm_partial, colnorm_grid(nc, n_omega, kk), dim3(256), 0, s,
-                     (int64_t)n, kk,
-                     (double2*)X, (const double2*)D, nc, px, pd, skip);
+  if (d32)
+    hipLaunchKernelGGL((k_colnorm_partial<float>), colnorm_grid(nc, n_omega, kk), dim3(256), 0, s,
+                       (int64_t)n, kk, (double2*)X, (const cplx<float>*)D, nc, px, pd, skip);
+  else
+    hipLaunchKernelGGL((k_colnorm_partial<double>), colnorm_grid(nc, n_omega, kk), dim3(256), 0, s,
+                       (int64_t)n, kk, (double2*)X, (const cplx<double>*)D, nc, px, pd, skip);
   if (p > 0 && it == 0) {  // the probes' errors after the first correction: rho
     double* pz = ws.partial + 2 * (size_t)n_omega * nc * 64;
     hipLaunchKernelGGL(k_probe_partial, dim3(nc, n_omega), dim3(256), 0, s, (int64_t)n, kk, k, p,
