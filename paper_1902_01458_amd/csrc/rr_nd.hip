@@ -182,61 +182,66 @@ __device__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pvs, uint32_t* s
     for (int e = 0; e < 4; e++)
       F[(16 * j + i) * ld + 16 * rb + Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
   };
-  if (wave == 0) pivot(0);
-  __syncthreads();
-  for (int kb = 0; kb < nb; kb++) {
+  // (one place calls pivot: a second would make it a function, its operands in
+  // scratch memory)
+  for (int kb = -1;; kb++) {
     const cplx<R>* pv = pvs + (kb & 1) * 16 * kPv;
     const int nx = kb + 1;
-    if (wave != kb && wave < nb) {  // block row kb: R_j = pv F(kb, j), j = wave
-      CAcc<R> acc;
-      zero(acc);
-      const cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
-#pragma unroll
-      for (int s = 0; s < 4; s++)
-        cmfma<R, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
-      put(kb, wave, acc);
-    }
-    __syncthreads();
-    // block row `rb` of the update: F(rb, j) -= C R_j and, held back until
-    // every reader of C = F(rb, kb) is done, F(rb, kb) = -C pv
     CAcc<R> held;
     int rb = wave;
-    if (wave == kb) rb = nx;         // (nx < nb) the next pivot's row, for its wave
-    const bool rows = wave < nb && rb < nb && (wave == kb || wave != nx);
-    if (wave < nb && (rows || wave == nx)) {
-      cplx<R> cf[4];
-#pragma unroll
-      for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * rb + i];
-      for (int j = 0; j < nb; j++) {
-        if (j == kb || (wave == nx ? j != nx : (rb == nx && j == nx))) continue;
+    bool rows = false;
+    if (kb >= 0) {
+      if (wave != kb && wave < nb) {  // block row kb: R_j = pv F(kb, j), j = wave
         CAcc<R> acc;
-        const cplx<R>* col = F + (16 * j + i) * ld;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const cplx<R> v = col[16 * rb + Mf<R>::row(l, e)];
-          acc.re[e] = v.re;
-          acc.im[e] = v.im;
-        }
+        zero(acc);
+        const cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
 #pragma unroll
         for (int s = 0; s < 4; s++)
-          cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
-        put(rb, j, acc);
+          cmfma<R, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
+        put(kb, wave, acc);
       }
-      if (rows) {
-        zero(held);
+      __syncthreads();
+      // block row `rb` of the update: F(rb, j) -= C R_j and, held back until
+      // every reader of C = F(rb, kb) is done, F(rb, kb) = -C pv
+      if (wave == kb) rb = nx;         // (nx < nb) the next pivot's row, for its wave
+      rows = wave < nb && rb < nb && (wave == kb || wave != nx);
+      if (wave < nb && (rows || wave == nx)) {
+        cplx<R> cf[4];
 #pragma unroll
-        for (int s = 0; s < 4; s++)
-          cmfma<R, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
-      } else {
-        pivot(nx);
+        for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * rb + i];
+        for (int j = 0; j < nb; j++) {
+          if (j == kb || (wave == nx ? j != nx : (rb == nx && j == nx))) continue;
+          CAcc<R> acc;
+          const cplx<R>* col = F + (16 * j + i) * ld;
+#pragma unroll
+          for (int e = 0; e < 4; e++) {
+            const cplx<R> v = col[16 * rb + Mf<R>::row(l, e)];
+            acc.re[e] = v.re;
+            acc.im[e] = v.im;
+          }
+#pragma unroll
+          for (int s = 0; s < 4; s++)
+            cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
+          put(rb, j, acc);
+        }
+        if (rows) {
+          zero(held);
+#pragma unroll
+          for (int s = 0; s < 4; s++)
+            cmfma<R, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
+        }
       }
     }
+    if (nx < nb && wave == nx) pivot(nx);
     __syncthreads();
-    if (rows) put(rb, kb, held);
-    if (wave == kb)
+    if (kb >= 0) {
+      if (rows) put(rb, kb, held);
+      if (wave == kb)
 #pragma unroll
-      for (int c = 0; c < 4; c++)
-        F[(16 * kb + 4 * g + c) * ld + 16 * kb + i] = pv[i * kPv + 4 * g + c];
+        for (int c = 0; c < 4; c++)
+          F[(16 * kb + 4 * g + c) * ld + 16 * kb + i] = pv[i * kPv + 4 * g + c];
+    }
+    if (nx >= nb) break;
   }
   __syncthreads();
 }
@@ -343,8 +348,12 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
 // into the MFMA operand) and F21 through LDS into column-major order.  Only a
 // border unknown that neither half has (m < 0) can be the stencil's neighbour
 // of the separator.
-template <typename R>
-__global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
+//
+// Bound by latency (a chain of loads, the inverse and the products per
+// workgroup), so the registers a wave holds, which set how many workgroups a CU
+// runs, follow the level's largest P (PM = 16, 32 or 64).
+template <typename R, int PM>
+__global__ __launch_bounds__(256, PM <= 16 ? 4 : PM <= 32 ? 3 : 2) void k_nd_front(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
   cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
   const int w = g.w0 + blockIdx.y;
@@ -356,24 +365,26 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
   const int* bm = g.bmap + fr.bor;
   const int* gr = g.grow + fr.bor;
   const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
-  const cplx<R>* Sh[2] = {g.schur_in + w * g.nin + ca.s, g.schur_in + w * g.nin + cb.s};
-  const int Qh[2] = {ca.Q, cb.Q};
-  const int base[2] = {fr.baseA, fr.baseB};
+  const cplx<R>* const sa = g.schur_in + w * g.nin + ca.s;
+  const cplx<R>* const sb = g.schur_in + w * g.nin + cb.s;
+  auto Sh = [&](int h) { return h ? sb : sa; };
+  auto Qh = [&](int h) { return h ? cb.Q : ca.Q; };
+  auto base = [&](int h) { return h ? fr.baseB : fr.baseA; };
   cplx<R>* A = g.factor + w * g.nfactor + fr.a;
   cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
   cplx<R>* F21 = g.factor + w * g.nfactor + fr.f21;
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, gq = l >> 4;
   {  // rows by waves, columns by lanes (P <= 64); four rows' loads at a time
     const int c = l, cc = min(c, p - 1);
-    const cplx<R>* s0 = Sh[0] + (int64_t)base[0] * Qh[0] + base[0] + cc;
-    const cplx<R>* s1 = Sh[1] + (int64_t)base[1] * Qh[1] + base[1] + cc;
+    const cplx<R>* s0 = sa + (int64_t)base(0) * Qh(0) + base(0) + cc;
+    const cplx<R>* s1 = sb + (int64_t)base(1) * Qh(1) + base(1) + cc;
     for (int r0 = wave; r0 < P; r0 += 16) {
       cplx<R> x[4], y[4];
 #pragma unroll
       for (int u = 0; u < 4; u++) {
         const int rr = min(r0 + 4 * u, p - 1);
-        x[u] = s0[(int64_t)rr * Qh[0]];
-        y[u] = s1[(int64_t)rr * Qh[1]];
+        x[u] = s0[(int64_t)rr * Qh(0)];
+        y[u] = s1[(int64_t)rr * Qh(1)];
       }
 #pragma unroll
       for (int u = 0; u < 4; u++) {
@@ -405,28 +416,28 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
     const bool real = j < fr.q;
     const int h = m & 1;
     // (a column without a source reads the first half's corner and drops it)
-    const cplx<R>* src = m >= 0 ? Sh[h] + (int64_t)base[h] * Qh[h] + (m >> 1) : Sh[0];
-    const int lds_ = m >= 0 ? Qh[h] : 0;
-    cplx<R> b[16];
+    const cplx<R>* src = m >= 0 ? Sh(h) + (int64_t)base(h) * Qh(h) + (m >> 1) : Sh(0);
+    const int lds_ = m >= 0 ? Qh(h) : 0;
+    cplx<R> b[PM / 4];
 #pragma unroll
-    for (int s = 0; s < 16; s++)
+    for (int s = 0; s < PM / 4; s++)
       if (4 * s < P) b[s] = src[(int64_t)min(4 * s + gq, p - 1) * lds_];
-    CAcc<R> acc[4];
+    CAcc<R> acc[PM / 16];
 #pragma unroll
-    for (int rb = 0; rb < 4; rb++) zero(acc[rb]);
+    for (int rb = 0; rb < PM / 16; rb++) zero(acc[rb]);
 #pragma unroll
-    for (int s = 0; s < 16; s++) {
+    for (int s = 0; s < PM / 4; s++) {
       if (4 * s >= P) continue;
       const int kk = 4 * s + gq;
       if (m < 0 || kk >= p) b[s] = cplx<R>{(R)0, (R)0};
       if (m < 0 && real && kk < p) b[s] = entry<R>(g.op, om_r, om_i, pd[kk], g.pdof[gr[j]]);
 #pragma unroll
-      for (int rb = 0; rb < 4; rb++)
+      for (int rb = 0; rb < PM / 16; rb++)
         if (16 * rb < P)
           cmfma<R, false, false>(acc[rb].re, acc[rb].im, F[kk * ld + 16 * rb + i], b[s]);
     }
 #pragma unroll
-    for (int rb = 0; rb < 4; rb++)
+    for (int rb = 0; rb < PM / 16; rb++)
       if (16 * rb < P)
 #pragma unroll
         for (int e = 0; e < 4; e++)
@@ -444,7 +455,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_front(FactorArgs<R> g) {
 #pragma unroll
       for (int c = 0; c < 16; c++) {
         const int m = bm[16 * t + c], h = m & 1;
-        v[c] = (m >= 0 ? Sh[h] + (int64_t)(m >> 1) * Qh[h] + base[h] : Sh[0])[lr];
+        v[c] = (m >= 0 ? Sh(h) + (int64_t)(m >> 1) * Qh(h) + base(h) : Sh(0))[lr];
       }
 #pragma unroll
       for (int c = 0; c < 16; c++) {
@@ -654,9 +665,11 @@ __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
   const int* bm = g.bmap + fr.bor;
   const int* gr = g.grow + fr.bor;
   const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
-  const cplx<R>* Sh[2] = {g.schur_in + w * g.nin + ca.s, g.schur_in + w * g.nin + cb.s};
-  const int Qh[2] = {ca.Q, cb.Q};
-  const int base[2] = {fr.baseA, fr.baseB};
+  const cplx<R>* const sa = g.schur_in + w * g.nin + ca.s;
+  const cplx<R>* const sb = g.schur_in + w * g.nin + cb.s;
+  auto Sh = [&](int h) { return h ? sb : sa; };
+  auto Qh = [&](int h) { return h ? cb.Q : ca.Q; };
+  auto base = [&](int h) { return h ? fr.baseB : fr.baseA; };
   const int M = t.kind == 2 ? Q : P, N = t.kind == 1 ? Q : P;
   const int r0 = kNdTile * t.i, c0 = kNdTile * t.j;
   const int nr = min(kNdTile, M - r0), nc = min(kNdTile, N - c0);
@@ -669,17 +682,17 @@ __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
   const int cc = min(c, (t.kind == 1 ? fr.q : p) - 1);
   const int mc = t.kind == 1 && cl < nc ? bm[c] : -1;
   const int dc = cl >= nc ? -1 : t.kind == 1 ? (c < fr.q ? g.pdof[gr[c]] : -1) : pd[c];
-  const cplx<R>* q0 = Sh[0];
-  const cplx<R>* q1 = Sh[1];
+  const cplx<R>* q0 = Sh(0);
+  const cplx<R>* q1 = Sh(1);
   int64_t l0 = 0, l1 = 0;
   if (t.kind == 0) {
-    q0 += (int64_t)base[0] * Qh[0] + base[0] + cc;
-    q1 += (int64_t)base[1] * Qh[1] + base[1] + cc;
-    l0 = Qh[0];
-    l1 = Qh[1];
+    q0 += (int64_t)base(0) * Qh(0) + base(0) + cc;
+    q1 += (int64_t)base(1) * Qh(1) + base(1) + cc;
+    l0 = Qh(0);
+    l1 = Qh(1);
   } else if (t.kind == 1 && mc >= 0) {
-    q0 = Sh[mc & 1] + (int64_t)base[mc & 1] * Qh[mc & 1] + (mc >> 1);
-    l0 = Qh[mc & 1];
+    q0 = Sh(mc & 1) + (int64_t)base(mc & 1) * Qh(mc & 1) + (mc >> 1);
+    l0 = Qh(mc & 1);
   }
   for (int b0 = threadIdx.x >> 6; b0 < nr; b0 += 16) {
     cplx<R> x[4], y[4];
@@ -691,7 +704,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
       y[u] = cplx<R>{(R)0, (R)0};
       if (t.kind == 2) {
         const int h = mr[u] & 1;
-        x[u] = (mr[u] >= 0 ? Sh[h] + (int64_t)(mr[u] >> 1) * Qh[h] + base[h] : Sh[0])[cc];
+        x[u] = (mr[u] >= 0 ? Sh(h) + (int64_t)(mr[u] >> 1) * Qh(h) + base(h) : Sh(0))[cc];
       } else {
         x[u] = q0[r * l0];
         if (t.kind == 0) y[u] = q1[r * l1];
@@ -1368,7 +1381,10 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
       a.nout = pl.schur[dep & 1];
       a.nin = pl.schur[~dep & 1];
       run(k_nd_leaf<R>, lv.leaf, front_lds<R>(lv.leafP, true));
-      run(k_nd_front<R>, lv.small, front_lds<R>(lv.maxP, false), shares(lv, nw));
+      const size_t fl = front_lds<R>(lv.maxP, false);
+      if (lv.maxP <= 16) run(k_nd_front<R, 16>, lv.small, fl, shares(lv, nw));
+      else if (lv.maxP <= 32) run(k_nd_front<R, 32>, lv.small, fl, shares(lv, nw));
+      else run(k_nd_front<R, 64>, lv.small, fl, shares(lv, nw));
       run(k_nd_assemble<R>, lv.assemble, lds);
       for (size_t k = 0; k < lv.panel.size(); k++) {
         run(k_nd_panel<R>, lv.panel[k], lds);
@@ -1459,7 +1475,7 @@ hipError_t prepare_r() {
       e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   };
   lds((const void*)k_nd_leaf<R>, tile_lds<R>());
-  lds((const void*)k_nd_front<R>, tile_lds<R>());
+  lds((const void*)k_nd_front<R, 64>, tile_lds<R>());
   lds((const void*)k_nd_assemble<R>, tile_lds<R>());
   lds((const void*)k_nd_panel<R>, tile_lds<R>());
   lds((const void*)k_nd_update<R>, tile_lds<R>());
