@@ -162,12 +162,14 @@ struct Inv16 {
 constexpr int kPv = 17;             // pitch of the 16 x 16 pivot inverses
 constexpr int kPvSize = 2 * 16 * kPv;  // two of them, by pivot parity
 
+// (inlined: as a function it would take its LDS operands through generic
+// pointers, i.e. flat instead of LDS instructions)
 template <typename R>
-__device__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pvs, uint32_t* status) {
+__device__ __forceinline__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pvs, uint32_t* status) {
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
   const int nb = T >> 4;
   // invert pivot block kb from LDS into its pv
-  auto pivot = [&](int kb) {
+  auto pivot = [&](int kb) __attribute__((always_inline)) {
     cplx<R> a[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) a[c] = F[(16 * kb + 4 * g + c) * ld + 16 * kb + i];
@@ -636,7 +638,7 @@ __device__ __forceinline__ int tile_width(int P, int k) { return min(kNdTile, P 
 
 // Invert the T x T tile in LDS and write it as pivot inverse k.
 template <typename R>
-__device__ void pivot_out(cplx<R>* F, cplx<R>* pv, int T, const NdFront& fr, int k,
+__device__ __forceinline__ void pivot_out(cplx<R>* F, cplx<R>* pv, int T, const NdFront& fr, int k,
                           cplx<R>* temp, uint32_t* status) {
   __syncthreads();
   invert_tile<R>(F, kLd, T, pv, status);
