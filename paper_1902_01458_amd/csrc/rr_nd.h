@@ -28,8 +28,16 @@ struct NdFront {
   int64_t a, b12, f21;  // offsets in one shift's factors (a leaf keeps A alone)
   int64_t s;           // offset of its Schur complement in the level's arena
   int64_t t;           // offset of its temporaries (P > kNdTile only)
+  // the halves' Q, s and urow, so that a kernel reads one front
+  int QA, QB, uA, uB;
+  int64_t sA, sB;
 };
 constexpr int kNdTile = 64;       // product tile edge, and the widest one-launch inverse
+// Fronts up to this P take their sweep down in one workgroup; wider ones 16
+// rows a workgroup, whose waves then share the border instead of one wave
+// walking all of it (P = 64, Q = 376: 48 / 79 us forward / adjoint a level for
+// one shift against 20 / 28; level by level about equal for 16).
+constexpr int kNdDownP = 32;
 constexpr int kNdLeafNodes = 32;  // blocks of at most this many nodes are leaves
 
 struct NdTask { int front, i, j, kind; };
@@ -43,7 +51,11 @@ struct NdLevel {  // fronts at one depth of the tree
   NdSpan border;     // tiles of B12
   NdSpan schur;      // tiles of S, every front with halves
   NdSpan gather, rowsP, rowsQ;  // solves, P > kNdTile: 64 rows; 16 rows of P; of Q
+  NdSpan down;       // solves, down: one task a front with halves, P <= kNdDownP
+  NdSpan rowsX;      // ... and 16 rows of the wider ones
   int maxP = 0, maxQ = 0;  // over the small fronts
+  int downP = 0;           // largest P of the fronts in `down`
+  int largeP = 0;          // largest P of the fronts past kNdTile
   int leafP = 0;           // largest P of the leaves
   int front = 0;           // the level's first front
 };

@@ -366,11 +366,10 @@ __global__ __launch_bounds__(256, PM <= 16 ? 4 : PM <= 32 ? 3 : 2) void k_nd_fro
   const int* pd = g.pdof + fr.row;
   const int* bm = g.bmap + fr.bor;
   const int* gr = g.grow + fr.bor;
-  const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
-  const cplx<R>* const sa = g.schur_in + w * g.nin + ca.s;
-  const cplx<R>* const sb = g.schur_in + w * g.nin + cb.s;
+  const cplx<R>* const sa = g.schur_in + w * g.nin + fr.sA;
+  const cplx<R>* const sb = g.schur_in + w * g.nin + fr.sB;
   auto Sh = [&](int h) { return h ? sb : sa; };
-  auto Qh = [&](int h) { return h ? cb.Q : ca.Q; };
+  auto Qh = [&](int h) { return h ? fr.QB : fr.QA; };
   auto base = [&](int h) { return h ? fr.baseB : fr.baseA; };
   cplx<R>* A = g.factor + w * g.nfactor + fr.a;
   cplx<R>* B12 = g.factor + w * g.nfactor + fr.b12;
@@ -553,14 +552,13 @@ __global__ __launch_bounds__(256, 2) void k_nd_schur(FactorArgs<R> g) {
 #pragma unroll
     for (int n = 0; n < 2; n++) zero(acc[m][n]);
   {
-    const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
-    const cplx<R>* Sa = g.schur_in + w * g.nin + ca.s;
-    const cplx<R>* Sb = g.schur_in + w * g.nin + cb.s;
+    const cplx<R>* Sa = g.schur_in + w * g.nin + fr.sA;
+    const cplx<R>* Sb = g.schur_in + w * g.nin + fr.sB;
 #pragma unroll
     for (int n = 0; n < 2; n++) {
       const int mj = bm[16 * q.nl[n] + i];
       const cplx<R>* src = (mj & 1) ? Sb : Sa;
-      const int ld = (mj & 1) ? cb.Q : ca.Q;
+      const int ld = (mj & 1) ? fr.QB : fr.QA;
 #pragma unroll
       for (int m = 0; m < 2; m++)
 #pragma unroll
@@ -666,11 +664,10 @@ __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
   const int* pd = g.pdof + fr.row;
   const int* bm = g.bmap + fr.bor;
   const int* gr = g.grow + fr.bor;
-  const NdFront ca = g.fronts[fr.childA], cb = g.fronts[fr.childB];
-  const cplx<R>* const sa = g.schur_in + w * g.nin + ca.s;
-  const cplx<R>* const sb = g.schur_in + w * g.nin + cb.s;
+  const cplx<R>* const sa = g.schur_in + w * g.nin + fr.sA;
+  const cplx<R>* const sb = g.schur_in + w * g.nin + fr.sB;
   auto Sh = [&](int h) { return h ? sb : sa; };
-  auto Qh = [&](int h) { return h ? cb.Q : ca.Q; };
+  auto Qh = [&](int h) { return h ? fr.QB : fr.QA; };
   auto base = [&](int h) { return h ? fr.baseB : fr.baseA; };
   const int M = t.kind == 2 ? Q : P, N = t.kind == 1 ? Q : P;
   const int r0 = kNdTile * t.i, c0 = kNdTile * t.j;
@@ -1118,9 +1115,44 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf_down(SolveArgs<R, IO> a) {
     }
 }
 
+// A 16-row operand block of P <= PM inner elements, all its loads issued at
+// once (i + kk * ld, kk = 4 s + l / 16), and its product with V in LDS.
+template <typename R, int PM>
+struct OperandBlock {
+  cplx<R> v[PM / 4];
+};
+template <typename R, int PM>
+__device__ __forceinline__ void load_block(OperandBlock<R, PM>& x, const cplx<R>* X, int64_t ld,
+                                           int P) {
+  const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+#pragma unroll
+  for (int s = 0; s < PM / 4; s++)
+    if (4 * s < P) x.v[s] = X[(int64_t)(4 * s + g) * ld + i];
+}
+template <typename R, int PM, int NB, bool CONJ>
+__device__ __forceinline__ void block_mul(v4<R> (&acc)[NB], const OperandBlock<R, PM>& x, int P,
+                                          const int (&col)[NB], const cplx<R>* V, int pitch) {
+  const int l = threadIdx.x & 63, g = l >> 4;
+  const bool hi = (l & 15) >= 8;
+#pragma unroll
+  for (int s = 0; s < PM / 4; s++) {
+    if (4 * s >= P) continue;
+    const R xi = CONJ ? -x.v[s].im : x.v[s].im;
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+      const cplx<R> y = V[(4 * s + g) * pitch + col[b]];
+      acc[b] = Mf<R>::op(x.v[s].re, hi ? y.im : y.re, acc[b]);
+      acc[b] = Mf<R>::op(xi, hi ? y.re : -y.im, acc[b]);
+    }
+  }
+}
+
 // A front with P <= 64, sweep up: one workgroup per front (and share of its
-// border rows, blockIdx.z).
-template <typename R, typename IO, int NB, bool ADJ>
+// border rows, blockIdx.z).  A chain of short products: each one's operands are
+// on their way before the one ahead of it is done, and the halves' updates
+// while it runs (8 shifts, the 2048 x 1024 grid's solve 4.14 -> 4.00 ms).
+// PM: the level's largest P, 16, 32 or 64 (the operands held in registers)
+template <typename R, typename IO, int NB, bool ADJ, int PM>
 __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   extern __shared__ __align__(16) char smem_raw[];
@@ -1130,36 +1162,58 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R, IO> a) {
   const int P = fr.P, Q = fr.Q, k = a.k;
   cplx<R>* bs = reinterpret_cast<cplx<R>*>(smem_raw);  // b1, P x NC
   cplx<R>* zs = ADJ ? bs : bs + P * NC;                // z
-  const cplx<R>* ua = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childA].urow * k;
-  const cplx<R>* ub = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childB].urow * k;
+  const cplx<R>* ua = a.uin + w * a.nuin + (int64_t)fr.uA * k;
+  const cplx<R>* ub = a.uin + w * a.nuin + (int64_t)fr.uB * k;
   cplx<R>* z = a.z + w * a.nw + (int64_t)fr.row * k;
   const cplx<R>* b = a.w + w * a.nw + (int64_t)fr.row * k;
-  for (int e = threadIdx.x; e < P * NC; e += 256) {
-    const int r = e / NC, j = e % NC;
-    cplx<R> v{(R)0, (R)0};
-    if (j < k) {
-      v = b[r * k + j];
-      if (r < fr.p) {
-        add(v, ua[(fr.baseA + r) * k + j]);
-        add(v, ub[(fr.baseB + r) * k + j]);
-      }
-      if (ADJ && blockIdx.z == 0) z[r * k + j] = v;
-    }
-    bs[e] = v;
-  }
-  __syncthreads();
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int hi = (l >> 3) & 1;
   const cplx<R>* fac = a.factor + w * a.nfactor;
+  // the first product's operands, which wait on nothing, before b1's loads
+  const int first = ADJ ? wave + 4 * (int)blockIdx.z : wave;
+  const bool live = 16 * first < (ADJ ? Q : P);
+  const int64_t xld = ADJ ? Q : P;
+  const cplx<R>* xp = fac + (ADJ ? fr.b12 : fr.a) + 16 * (live ? first : 0);
+  OperandBlock<R, PM> x;
+  if (!ADJ || Q > 0) load_block<R, PM>(x, xp, xld, P);
+  for (int e0 = threadIdx.x; e0 < P * NC; e0 += 1024) {  // four elements' loads at a time
+    cplx<R> v[4], p[4], q[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int e = min(e0 + 256 * u, P * NC - 1);
+      const int r = e / NC, j = min(e % NC, k - 1), rr = min(r, fr.p - 1);
+      v[u] = b[r * k + j];
+      p[u] = ua[(fr.baseA + rr) * k + j];
+      q[u] = ub[(fr.baseB + rr) * k + j];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int e = e0 + 256 * u;
+      if (e >= P * NC) continue;
+      const int r = e / NC, j = e % NC;
+      if (r < fr.p) {
+        add(v[u], p[u]);
+        add(v[u], q[u]);
+      }
+      if (j >= k) v[u] = cplx<R>{(R)0, (R)0};
+      else if (ADJ && blockIdx.z == 0) z[r * k + j] = v[u];
+      bs[e] = v[u];
+    }
+  }
+  __syncthreads();
   int col[NB];
 #pragma unroll
   for (int c = 0; c < NB; c++) col[c] = 8 * c + (l & 7);
   v4<R> acc[NB];
   if (!ADJ) {
-    if (16 * wave < P) {
+    if (live) {
       zero<R, NB>(acc);
-      rows_mul<R, NB, false, false, true>(acc, fac + fr.a + 16 * wave, P, 0, P / 16, 1, col,
-                                          [&](int kk) { return bs + kk * NC; });
+      block_mul<R, PM, NB, false>(acc, x, P, col, bs, NC);
+    }
+    // F21's first rows, while z is written and read back
+    if (Q > 0)
+      load_block<R, PM>(x, fac + fr.f21 + 16 * min(wave + 4 * (int)blockIdx.z, Q / 16 - 1), Q, P);
+    if (live)
 #pragma unroll
       for (int c = 0; c < NB; c++)
 #pragma unroll
@@ -1168,32 +1222,37 @@ __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R, IO> a) {
           part(zs, NC, r, c) = acc[c][e];
           if (blockIdx.z == 0 && col[c] < k) part(z, k, r, c) = acc[c][e];
         }
-    }
     __syncthreads();
   }
   const int* bm = a.bmap + fr.bor;
   cplx<R>* uo = a.uout + w * a.nuout + (int64_t)fr.urow * k;
   for (int rb = wave + 4 * blockIdx.z; rb < Q / 16; rb += 4 * a.qsplit) {
-    zero<R, NB>(acc);
-    rows_mul<R, NB, false, ADJ, true>(acc, fac + (ADJ ? fr.b12 : fr.f21) + 16 * rb, Q, 0, P / 16, 1,
-                                      col, [&](int kk) { return zs + kk * NC; });
+    R pulled[4][NB];  // the halves' updates, loaded while the product runs
 #pragma unroll
     for (int e = 0; e < 4; e++) {
-      const int r = 16 * rb + Mf<R>::row(l, e);
-      const int m = bm[r];
-      const cplx<R>* src = (m & 1) ? ub : ua;
+      const int m = bm[16 * rb + Mf<R>::row(l, e)];
+      const cplx<R>* src = m < 0 ? ua : ((m & 1) ? ub : ua) + (m >> 1) * k;
+#pragma unroll
+      for (int c = 0; c < NB; c++) {
+        const R v = reinterpret_cast<const R*>(src + min(col[c], k - 1))[hi];
+        pulled[e][c] = m >= 0 ? v : (R)0;
+      }
+    }
+    zero<R, NB>(acc);
+    block_mul<R, PM, NB, ADJ>(acc, x, P, col, zs, NC);
+    const int nx = rb + 4 * a.qsplit;
+    if (nx < Q / 16) load_block<R, PM>(x, fac + (ADJ ? fr.b12 : fr.f21) + 16 * nx, Q, P);
+#pragma unroll
+    for (int e = 0; e < 4; e++)
 #pragma unroll
       for (int c = 0; c < NB; c++)
-        if (col[c] < k) {
-          const R v = m >= 0 ? reinterpret_cast<const R*>(src + (m >> 1) * k + col[c])[hi] : (R)0;
-          part(uo, k, r, c) = v - acc[c][e];
-        }
-    }
+        if (col[c] < k)
+          part(uo, k, 16 * rb + Mf<R>::row(l, e), c) = pulled[e][c] - acc[c][e];
   }
 }
 
-// A front with P <= 64, sweep down; the four waves split the inner dimension
-// where P leaves them idle.
+// A front with P <= kNdDownP, sweep down; the four waves split the inner
+// dimension where P leaves them idle.
 template <typename R, typename IO, int NB, bool ADJ>
 __global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
@@ -1263,8 +1322,8 @@ __global__ __launch_bounds__(256) void k_nd_gather(SolveArgs<R, IO> a) {
   const NdTask t = a.tasks[blockIdx.x];
   const NdFront fr = a.fronts[t.front];
   const int k = a.k;
-  const cplx<R>* ua = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childA].urow * k;
-  const cplx<R>* ub = a.uin + w * a.nuin + (int64_t)a.fronts[fr.childB].urow * k;
+  const cplx<R>* ua = a.uin + w * a.nuin + (int64_t)fr.uA * k;
+  const cplx<R>* ub = a.uin + w * a.nuin + (int64_t)fr.uB * k;
   const int r0 = kNdTile * t.i, nr = min(kNdTile, fr.P - r0);
   const int64_t at = w * a.nw + (int64_t)(fr.row + r0) * k;
   for (int e = threadIdx.x; e < nr * k; e += 256) {
@@ -1277,17 +1336,20 @@ __global__ __launch_bounds__(256) void k_nd_gather(SolveArgs<R, IO> a) {
   }
 }
 
-// P > 64: 16 rows of one product, the four waves splitting its inner dimension.
+// 16 rows of one product, the workgroup's NW waves splitting its inner dimension.
+// Eight where it is long (the border, or P > 256): with four, one shift's
+// product over 1024 border rows took 34 us against 27.  Four where it is 256 or
+// less, two chunks or so a wave (8 shifts, P = 128: 90 us against 137).
 enum { ND_Z = 0,    // z = A w               (forward, up)
        ND_U = 1,    // u = pulled - F21 z    (adjoint: B12^H z)
        ND_X = 2,    // w = z - B12 w[border]  (adjoint: z -= F21^H w[border])
        ND_AH = 3 }; // w = A^H z             (adjoint, down)
-template <typename R, typename IO, int NB, int MODE, bool ADJ>
-__global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R, IO> a) {
+template <typename R, typename IO, int NB, int MODE, bool ADJ, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_nd_rows(SolveArgs<R, IO> a) {
   if (skipped(a.skip)) return;
   constexpr int NC = 8 * NB;
   constexpr bool KF = MODE == ND_X || MODE == ND_AH;
-  __shared__ cplx<R> red[4 * 16 * NC];
+  __shared__ cplx<R> red[NW * 16 * NC];
   const int w = a.w0 + blockIdx.y;
   const NdTask t = a.tasks[blockIdx.x];
   const NdFront fr = a.fronts[t.front];
@@ -1308,7 +1370,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R, IO> a) {
   v4<R> acc[NB];
   zero<R, NB>(acc);
   const cplx<R>* V = (MODE == ND_Z ? W : Z) + (int64_t)fr.row * k;
-  rows_mul<R, NB, KF, ADJ, false>(acc, X, ld, wave, K / 16, 4, col, [&](int kk) {
+  rows_mul<R, NB, KF, ADJ, false>(acc, X, ld, wave, K / 16, NW, col, [&](int kk) {
     return MODE == ND_X ? W + (int64_t)gr[kk] * k : V + (int64_t)kk * k;
   });
 #pragma unroll
@@ -1316,12 +1378,12 @@ __global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R, IO> a) {
 #pragma unroll
     for (int e = 0; e < 4; e++) part(red, NC, wave * 16 + Mf<R>::row(l, e), c) = acc[c][e];
   __syncthreads();
-  for (int e = threadIdx.x; e < 16 * NC; e += 256) {
+  for (int e = threadIdx.x; e < 16 * NC; e += 64 * NW) {
     const int r = 16 * t.i + e / NC, j = e % NC;
     if (j >= k) continue;
     cplx<R> v = red[e];
 #pragma unroll
-    for (int s = 1; s < 4; s++) add(v, red[s * 16 * NC + e]);
+    for (int s = 1; s < NW; s++) add(v, red[s * 16 * NC + e]);
     const int64_t at = (int64_t)(fr.row + r) * k + j;
     if (MODE == ND_Z) {
       Z[at] = v;
@@ -1334,8 +1396,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_rows(SolveArgs<R, IO> a) {
       const int m = a.bmap[fr.bor + r];
       cplx<R> u{(R)0, (R)0};
       if (m >= 0) {
-        const int half = (m & 1) ? fr.childB : fr.childA;
-        u = a.uin[w * a.nuin + (int64_t)(a.fronts[half].urow + (m >> 1)) * k + j];
+        u = a.uin[w * a.nuin + (int64_t)(((m & 1) ? fr.uB : fr.uA) + (m >> 1)) * k + j];
       }
       a.uout[w * a.nuout + (int64_t)(fr.urow + r) * k + j] = cplx<R>{u.re - v.re, u.im - v.im};
     }
@@ -1429,12 +1490,13 @@ hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int6
   for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
     const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
     a.w0 = w0;
-    auto run = [&](auto kernel, const NdSpan& sp, size_t shm, int zs = 1) {
+    auto run = [&](auto kernel, const NdSpan& sp, size_t shm, int zs = 1, int threads = 256) {
       if (!sp.count) return;
       a.tasks = d.tasks + sp.first;
       a.qsplit = zs;
-      hipLaunchKernelGGL(kernel, dim3(sp.count, nw, zs), dim3(256), shm, s, a);
+      hipLaunchKernelGGL(kernel, dim3(sp.count, nw, zs), dim3(threads), shm, s, a);
     };
+    auto rows = [&](auto kernel, const NdSpan& sp, int waves) { run(kernel, sp, 0, 1, 64 * waves); };
     auto level = [&](int dep) -> const NdLevel& {
       a.uout = (cplx<R>*)d.u[dep & 1];
       a.uin = (cplx<R>*)d.u[~dep & 1];
@@ -1448,19 +1510,27 @@ hipError_t solve_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, int6
       const NdLevel& lv = level(dep);
       run(k_nd_leaf_up<R, IO, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
       if (lv.small.count) {
-        run(k_nd_up<R, IO, NB, ADJ>, lv.small, (size_t)lv.maxP * NC * (ADJ ? 1 : 2) * sizeof(cplx<R>),
-            shares(lv, nw));
+        const size_t lds = (size_t)lv.maxP * NC * (ADJ ? 1 : 2) * sizeof(cplx<R>);
+        if (lv.maxP <= 16) run(k_nd_up<R, IO, NB, ADJ, 16>, lv.small, lds, shares(lv, nw));
+        else if (lv.maxP <= 32) run(k_nd_up<R, IO, NB, ADJ, 32>, lv.small, lds, shares(lv, nw));
+        else run(k_nd_up<R, IO, NB, ADJ, 64>, lv.small, lds, shares(lv, nw));
       }
       run(k_nd_gather<R, IO>, lv.gather, 0);
-      if (!ADJ) run(k_nd_rows<R, IO, NB, ND_Z, ADJ>, lv.rowsP, 0);
-      run(k_nd_rows<R, IO, NB, ND_U, ADJ>, lv.rowsQ, 0);
+      if (lv.largeP <= 256) {
+        if (!ADJ) rows(k_nd_rows<R, IO, NB, ND_Z, ADJ, 4>, lv.rowsP, 4);
+        rows(k_nd_rows<R, IO, NB, ND_U, ADJ, 4>, lv.rowsQ, 4);
+      } else {
+        if (!ADJ) rows(k_nd_rows<R, IO, NB, ND_Z, ADJ, 8>, lv.rowsP, 8);
+        rows(k_nd_rows<R, IO, NB, ND_U, ADJ, 8>, lv.rowsQ, 8);
+      }
     }
     for (int dep = 0; dep < (int)pl.levels.size(); dep++) {
       const NdLevel& lv = level(dep);
-      run(k_nd_down<R, IO, NB, ADJ>, lv.small,
-          (size_t)(64 + (ADJ ? lv.maxP : 0)) * NC * sizeof(cplx<R>));
-      run(k_nd_rows<R, IO, NB, ND_X, ADJ>, lv.rowsP, 0);
-      if (ADJ) run(k_nd_rows<R, IO, NB, ND_AH, ADJ>, lv.rowsP, 0);
+      run(k_nd_down<R, IO, NB, ADJ>, lv.down,
+          (size_t)(64 + (ADJ ? lv.downP : 0)) * NC * sizeof(cplx<R>));
+      rows(k_nd_rows<R, IO, NB, ND_X, ADJ, 8>, lv.rowsX, 8);
+      if (ADJ && lv.largeP <= 256) rows(k_nd_rows<R, IO, NB, ND_AH, ADJ, 4>, lv.rowsX, 4);
+      if (ADJ && lv.largeP > 256) rows(k_nd_rows<R, IO, NB, ND_AH, ADJ, 8>, lv.rowsX, 8);
       run(k_nd_leaf_down<R, IO, NB, ADJ>, lv.leaf, (size_t)lv.leafP * (NC + 1) * sizeof(cplx<R>));
     }
     hipLaunchKernelGGL((k_nd_permute<R, IO, true>), dim3(rb, nw), dim3(256), 0, s, d.pdof, pl.rows, n, k,

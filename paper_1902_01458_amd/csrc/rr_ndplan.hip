@@ -129,6 +129,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
       continue;
     }
     pl.ntasks += nq * nq;  // schur
+    pl.ntasks += fr.P <= kNdDownP ? 1 : fr.P / 16;  // down, rowsX
     if (fr.P <= kNdTile) {
       pl.ntasks++;
     } else {  // assemble, panel, update, border, gather, rowsP, rowsQ
@@ -165,6 +166,15 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
       h[1] = &blocks[fr.childB];
       fr.baseA = h[0]->off[b.across_x ? 1 : 3];  // A's right / high side is the separator
       fr.baseB = h[1]->off[b.across_x ? 0 : 2];  // B's left / low side
+    }
+    if (!b.leaf) {
+      const NdFront &ca = pl.fronts[fr.childA], &cb = pl.fronts[fr.childB];
+      fr.QA = ca.Q;
+      fr.QB = cb.Q;
+      fr.uA = ca.urow;
+      fr.uB = cb.urow;
+      fr.sA = ca.s;
+      fr.sB = cb.s;
     }
     std::copy(b.off, b.off + 5, fr.side);
     const int across = b.j1 - b.j0;  // a leaf's unknowns: i, then j, then u and v
@@ -230,6 +240,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     int steps = 0;
     each(lv.assemble, false, true, [&](int f, const NdFront& fr) {
       const int np = tiles(fr.P), nq = tiles(fr.Q);
+      lv.largeP = std::max(lv.largeP, fr.P);
       steps = std::max(steps, np);
       for (int i = 0; i < np; i++)
         for (int j = 0; j < np; j++) pl.tasks.push_back({f, i, j, 0});
@@ -272,6 +283,14 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     });
     each(lv.rowsP, false, true, [&](int f, const NdFront& fr) {
       for (int i = 0; i < fr.P / 16; i++) pl.tasks.push_back({f, i, 0, 0});
+    });
+    each(lv.down, true, false, [&](int f, const NdFront& fr) {
+      if (fr.P > kNdDownP) return;
+      pl.tasks.push_back({f, 0, 0, 0});
+      lv.downP = std::max(lv.downP, fr.P);
+    });
+    each(lv.rowsX, true, true, [&](int f, const NdFront& fr) {
+      for (int i = 0; i < fr.P / 16 && fr.P > kNdDownP; i++) pl.tasks.push_back({f, i, 0, 0});
     });
     each(lv.rowsQ, false, true, [&](int f, const NdFront& fr) {
       for (int i = 0; i < fr.Q / 16; i++) pl.tasks.push_back({f, i, 0, 0});

@@ -151,6 +151,8 @@ def test_plan_arenas_and_tasks(nx, ny):
         for i in range(nq):
             for j in range(nq):
                 expect(f, (i, j, 0))  # S
+        for i in range(1 if x["P"] <= 32 else x["P"] // 16):
+            expect(f, (i, 0, 0))  # down
         if x["P"] <= TILE:
             expect(f, (0, 0, 0))
             continue
