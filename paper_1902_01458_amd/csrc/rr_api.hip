@@ -176,6 +176,8 @@ uint32_t* fail_word(rr_factors* f) { return f->ctrl + 2; }
 uint32_t* conv_word(rr_factors* f) { return f->ctrl + 3; }
 // ctrl[20], ctrl[21]: the factorisation's task tickets and diagonal-worker roles
 uint32_t* factor_counters(rr_factors* f) { return f->ctrl + 20; }
+// live systems of a Krylov solve
+uint32_t* live_word(rr_factors* f) { return f->ctrl + 22; }
 // ctrl[4 + it]: unconverged columns after correction it (mixed solves)
 constexpr int kMaxRefine = 16;
 // Sketch widths above this take the wide k x k kernels (rr_bigk.hip) and
@@ -289,53 +291,53 @@ rr_status krylov_solve(rr_factors* f, int k, int adjoint, const double* Bm, int6
   RR_HIP(launch_fill_u32((uint32_t*)X, 0u, total * 4, s));  // x = 0
   // r = b - M 0 = b (the apply also spreads a right-hand side shared by the shifts)
   RR_HIP(launch_apply(op, f->omega, nw, k, adjoint, X, Bm, bstride, r, s));
-  RR_HIP(launch_kdot(n, nw, k, 1, r, r, nullptr, nullptr, f->kpart, nullptr, nullptr, s));
-  RR_HIP(launch_bicg_scalars(N, n, 0, 0, tol, f->kpart, f->kscal, f->kbnorm, act, conv, st,
-                             nullptr, s));
+  double* part = f->kpart;  // <r, r> and <rhat, r>; the applies' beside them
+  double* apart = part + (int64_t)N * krylov_nchunk(n) * 4;
+  RR_HIP(launch_kdot(n, nw, k, r, r, part, nullptr, nullptr, s));
+  RR_HIP(launch_krylov_scalars(N, n, 0, tol, part, f->kscal, f->kbnorm, act, live_word(f), conv, st,
+                               nullptr, s));
   if (f->solver == RR_SOLVER_BICGSTAB) {
     double *rh = f->kv[1], *p = f->kv[2], *v = f->kv[3], *y = f->kv[4], *z = f->kv[5],
            *t = f->kv[6];
+    BicgStep b{part, krylov_nchunk(n), 0, tol * tol, f->kscal, f->kbnorm, act, live_word(f), conv,
+               st, r, v};
+    BicgStep a = b;  // with the applies' partial sums
+    a.part = apart;
+    a.nparts = apply_chunks(f->nx, f->ny);
     RR_HIP(launch_kcopy(total, r, rh, s));
-    RR_HIP(launch_fill_u32((uint32_t*)p, 0u, total * 4, s));
-    RR_HIP(launch_fill_u32((uint32_t*)v, 0u, total * 4, s));
+    RR_HIP(launch_kcopy(total, r, p, s));
+    // Five launches an iteration (15 with the dot products, their scalars and
+    // the vector updates apart): each kernel totals the partial sums that the
+    // one before it left and takes the scalar step itself.
     for (int it = 0; it < f->krylov_maxit; it++) {
-      // rho = <rhat, r>, beta; p = r + beta (p - omega v); y = K^-1 p; v = M y
-      RR_HIP(launch_kdot(n, nw, k, 1, rh, r, nullptr, nullptr, f->kpart, act, conv, s));
-      RR_HIP(launch_bicg_scalars(N, n, 1, it, tol, f->kpart, f->kscal, f->kbnorm, act, conv, st,
-                                 conv, s));
-      RR_HIP(launch_bicg_vec(0, n, nw, k, f->kscal, r, v, nullptr, nullptr, p, act, conv, s));
-      RR_HIP(launch_pc_apply(op, f->precond, nw, k, adjoint, f->pc_dinv, p, y, act, conv, s));
-      RR_HIP(launch_apply(op, f->omega, nw, k, adjoint, y, nullptr, 0, v, s, conv));
-      // alpha = rho / <rhat, v>; s = r - alpha v (kept in r)
-      RR_HIP(launch_kdot(n, nw, k, 1, rh, v, nullptr, nullptr, f->kpart, act, conv, s));
-      RR_HIP(launch_bicg_scalars(N, n, 2, it, tol, f->kpart, f->kscal, f->kbnorm, act, conv, st,
-                                 conv, s));
-      RR_HIP(launch_bicg_vec(1, n, nw, k, f->kscal, nullptr, v, nullptr, nullptr, r, act, conv, s));
-      // z = K^-1 s; t = M z; omega = <t, s> / <t, t>
-      RR_HIP(launch_pc_apply(op, f->precond, nw, k, adjoint, f->pc_dinv, r, z, act, conv, s));
-      RR_HIP(launch_apply(op, f->omega, nw, k, adjoint, z, nullptr, 0, t, s, conv));
-      RR_HIP(launch_kdot(n, nw, k, 2, t, r, t, t, f->kpart, act, conv, s));
-      RR_HIP(launch_bicg_scalars(N, n, 3, it, tol, f->kpart, f->kscal, f->kbnorm, act, conv, st,
-                                 conv, s));
-      // x += alpha y + omega z; r = s - omega t; then the convergence test
-      RR_HIP(launch_bicg_vec(2, n, nw, k, f->kscal, y, z, t, X, r, act, conv, s));
-      RR_HIP(launch_kdot(n, nw, k, 1, r, r, nullptr, nullptr, f->kpart, act, conv, s));
-      RR_HIP(launch_bicg_scalars(N, n, 4, it, tol, f->kpart, f->kscal, f->kbnorm, act, conv, st,
-                                 conv, s));
+      a.it = b.it = it;
+      // the convergence test, rho and beta; p = r + beta (p - omega v); y = K^-1 p
+      if (it == 0)
+        RR_HIP(launch_pc_apply(op, f->precond, nw, k, adjoint, f->pc_dinv, p, y, act, conv, s));
+      else
+        RR_HIP(launch_bicg_p(op, f->precond, nw, k, adjoint, f->pc_dinv, p, y, b, s));
+      // v = M y, <rhat, v>; alpha = rho / <rhat, v>; s = r - alpha v (kept in r); z = K^-1 s
+      RR_HIP(launch_apply_dots(op, f->omega, nw, k, adjoint, y, v, rh, false, apart, s, conv));
+      RR_HIP(launch_bicg_s(op, f->precond, nw, k, adjoint, f->pc_dinv, r, z, a, s));
+      // t = M z; omega = <t, s> / <t, t>; x += alpha y + omega z; r = s - omega t
+      RR_HIP(launch_apply_dots(op, f->omega, nw, k, adjoint, z, t, r, true, apart, s, conv));
+      RR_HIP(launch_bicg_xr(n, nw, k, y, z, t, rh, X, r, part, a, s));
     }
+    RR_HIP(launch_krylov_scalars(N, n, 1, tol, part, f->kscal, f->kbnorm, act, live_word(f), conv,
+                                 st, conv, s));
   } else {
     const int m = f->gm.m;
     const int cycles = (f->krylov_maxit + m - 1) / m;
     for (int c = 0; c <= cycles; c++) {
       if (c > 0) {  // r = b - M x and the convergence test
         RR_HIP(launch_apply(op, f->omega, nw, k, adjoint, X, Bm, bstride, r, s, conv));
-        RR_HIP(launch_kdot(n, nw, k, 1, r, r, nullptr, nullptr, f->kpart, act, conv, s));
-        RR_HIP(launch_bicg_scalars(N, n, 4, c, tol, f->kpart, f->kscal, f->kbnorm, act, conv, st,
-                                   conv, s));
+        RR_HIP(launch_kdot(n, nw, k, r, r, part, act, conv, s));
+        RR_HIP(launch_krylov_scalars(N, n, 1, tol, part, f->kscal, f->kbnorm, act, live_word(f),
+                                     conv, st, conv, s));
       }
       if (c == cycles) break;
       RR_HIP(gmres_correction(f, k, adjoint, r, s));  // r <- m steps of GMRES on K^-1 M d = K^-1 r
-      RR_HIP(launch_bicg_vec(3, n, nw, k, nullptr, r, nullptr, nullptr, X, nullptr, act, conv, s));
+      RR_HIP(launch_kaxpy(n, nw, k, r, X, act, conv, s));
     }
   }
   RR_HIP(launch_latch_live(N, act, st, ST_NOT_CONVERGED, s));
@@ -737,7 +739,7 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     ALLOC(f->pc_dinv, pc_bytes(f->precond, p->nx, p->ny, n_omega));
     const int nvec = solver == RR_SOLVER_BICGSTAB ? 7 : 1;
     for (int v = 0; v < nvec; v++) ALLOC(f->kv[v], pl.vec);
-    ALLOC(f->kpart, cols * krylov_nchunk(n64) * 2 * cplx);
+    ALLOC(f->kpart, cols * (krylov_nchunk(n64) + apply_chunks(p->nx, p->ny)) * 2 * cplx);
     ALLOC(f->kscal, cols * 4 * cplx);
     ALLOC(f->kbnorm, cols * sizeof(double));
     ALLOC(f->kactive, cols * sizeof(uint32_t));

@@ -183,6 +183,12 @@ hipError_t launch_burgers_coeffs(int nx, int ny, const double* U, double hx, dou
 hipError_t launch_apply(const OpDesc& op, const double* omega /*dev 2*n_omega*/, int n_omega,
                         int k, int adjoint, const double* X, const double* Bm, int64_t bstride,
                         double* Y, hipStream_t s, const uint32_t* skip = nullptr);
+// Y = M X (M^H X) and per system the partial sums of <D, Y>, and with `norm`
+// of <Y, D>, <Y, Y> instead (apply_chunks(op) pairs): a step of BiCGStab.
+int apply_chunks(int nx, int ny);
+hipError_t launch_apply_dots(const OpDesc& op, const double* omega, int n_omega, int k, int adjoint,
+                             const double* X, double* Y, const double* D, bool norm,
+                             double* partial, hipStream_t s, const uint32_t* skip);
 // The residual b - M X (b - M^H X) rounded to FP32.
 hipError_t launch_residual32(const OpDesc& op, const double* omega, int n_omega, int k, int adjoint,
                              const double* X, const double* Bm, int64_t bstride, float* Y,
@@ -344,22 +350,42 @@ hipError_t launch_pc_setup(const OpDesc& op, int precond, const double* omega, i
 hipError_t launch_pc_apply(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
                            const double* Dinv, const double* X, double* Y,
                            const uint32_t* active, const uint32_t* skip, hipStream_t s);
-// partial sums of <A_e, B_e> per system (npair 1 or 2)
-hipError_t launch_kdot(int64_t n, int n_omega, int k, int npair, const double* A0,
-                       const double* B0, const double* A1, const double* B1, double* partial,
-                       const uint32_t* active, const uint32_t* skip, hipStream_t s);
-// the scalar steps of BiCGStab (mode 0 start, 1 rho / beta, 2 alpha, 3 omega,
-// 4 convergence check), ks: 4 complex per system
-hipError_t launch_bicg_scalars(int N, int64_t n, int mode, int it, double tol,
-                               const double* partial, double* ks, double* bnorm2,
-                               uint32_t* active, uint32_t* conv, uint32_t* status,
-                               const uint32_t* skip, hipStream_t s);
-// vector steps: 0 p = r + beta (p - omega v); 1 r -= alpha v;
-// 2 x += alpha y + omega z, r -= omega t; 3 x += d
-hipError_t launch_bicg_vec(int which, int64_t n, int n_omega, int k, const double* ks,
-                           const double* a, const double* b, const double* c, double* x,
-                           double* y, const uint32_t* active, const uint32_t* skip,
-                           hipStream_t s);
+// What a fused BiCGStab kernel needs for its scalars: the partial sums it
+// totals (nparts pairs per system), the per-system scalars and state, and the
+// vectors of its update.
+struct BicgStep {
+  const double* part;
+  int nparts, it;
+  double tol2;
+  double* ks;             // 4 complex per system
+  const double* bnorm2;
+  uint32_t *active, *live, *conv, *status;
+  const double *r, *v;
+};
+// p <- r + beta (p - omega v), y = K^-1 p; the convergence test on the way
+hipError_t launch_bicg_p(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
+                         const double* Dinv, double* p, double* y, const BicgStep& b,
+                         hipStream_t s);
+// r <- r - alpha v, z = K^-1 r
+hipError_t launch_bicg_s(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
+                         const double* Dinv, double* r, double* z, const BicgStep& b,
+                         hipStream_t s);
+// x += alpha y + omega z, r -= omega t, partial sums of <r, r>, <rh, r>
+hipError_t launch_bicg_xr(int64_t n, int n_omega, int k, const double* y, const double* z,
+                          const double* t, const double* rh, double* x, double* r,
+                          double* part_out, const BicgStep& b, hipStream_t s);
+// partial sums of <A, B> per system
+hipError_t launch_kdot(int64_t n, int n_omega, int k, const double* A, const double* B,
+                       double* partial, const uint32_t* active, const uint32_t* skip,
+                       hipStream_t s);
+// the scalar steps at a solve's ends (mode 0 start, 1 convergence check)
+hipError_t launch_krylov_scalars(int N, int64_t n, int mode, double tol, const double* partial,
+                                 double* ks, double* bnorm2, uint32_t* active, uint32_t* live,
+                                 uint32_t* conv, uint32_t* status, const uint32_t* skip,
+                                 hipStream_t s);
+// x += d for live systems
+hipError_t launch_kaxpy(int64_t n, int n_omega, int k, const double* d, double* x,
+                        const uint32_t* active, const uint32_t* skip, hipStream_t s);
 hipError_t launch_kcopy(int64_t count, const double* a, double* b, hipStream_t s);
 hipError_t launch_latch_live(int N, const uint32_t* active, uint32_t* status, uint32_t bit,
                              hipStream_t s);

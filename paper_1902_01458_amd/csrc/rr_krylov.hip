@@ -21,11 +21,13 @@
 // same component of a neighbour), with entries -c from the stencil row.
 #include "rr_internal.h"
 
+#include <type_traits>
+
 namespace rr {
 
 namespace {
 
-constexpr int kKChunk = 2048;  // rows per partial sum of the batched dot products
+constexpr int kKChunk = 1024;  // rows per partial sum of the batched dot products
 constexpr int kKThreads = 256;
 
 __device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
@@ -109,7 +111,7 @@ __global__ void k_pc_jacobi(int nn, const double* __restrict__ coef,
 }
 
 // Block ILU(0) data of a shift, stored by anti-diagonal: slot (d, j) = d ny +
-// j holds node (i, j) = (d - j, j) (slots with i outside 0 .. nx-1 unused),
+// j holds node (i, j) = (d - j, j) (slots with i outside 0 .. nx-1 hold zeros),
 // as kIluFields arrays of slots double2 (structure of arrays), so that the
 // sweeps, whose threads take consecutive j on one anti-diagonal, read
 // consecutive words:
@@ -145,6 +147,10 @@ __global__ __launch_bounds__(kKThreads) void k_pc_ilu0(int nx, int ny,
     C2* cur = ring + (d & 1) * ny;
     const C2* prev = ring + ((d + 1) & 1) * ny;
     const int j0 = max(0, d - nx + 1), j1 = min(ny - 1, d);
+    for (int j = threadIdx.x; j < ny; j += blockDim.x) {  // unused slots: zeros
+      if (j < j0 || j > j1)
+        for (int e = 0; e < kIluFields; e++) Fw[e * ns + (int64_t)d * ny + j] = make_double2(0, 0);
+    }
     for (int j = j0 + threadIdx.x; j <= j1; j += blockDim.x) {
       const int i = d - j, p = j + ny * i;
       const double* c = coef + 12 * (int64_t)p;
@@ -195,19 +201,157 @@ __global__ __launch_bounds__(kKThreads) void k_pc_ilu0(int nx, int ny,
   }
 }
 
+// Sums of s0, s1 over the workgroup's waves, left in red (two per wave).
+__device__ __forceinline__ void block_pair_sum(double2 s0, double2 s1, double2* red) {
+  for (int o = 32; o > 0; o >>= 1) {
+    s0.x += __shfl_down(s0.x, o, 64);
+    s0.y += __shfl_down(s0.y, o, 64);
+    s1.x += __shfl_down(s1.x, o, 64);
+    s1.y += __shfl_down(s1.y, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[2 * (threadIdx.x >> 6)] = s0;
+    red[2 * (threadIdx.x >> 6) + 1] = s1;
+  }
+  __syncthreads();
+}
+
+// Thread e < 2: the workgroup's sum of s_e, after block_pair_sum.
+__device__ __forceinline__ double2 pair_total(const double2* red) {
+  double2 t = make_double2(0, 0);
+  for (int v = 0; v < (int)(blockDim.x >> 6); v++) t = cadd(t, red[2 * v + threadIdx.x]);
+  return t;
+}
+
+// The sum over a system's partial sums (pairs of complex) by the whole
+// workgroup, the same for every thread and in every workgroup of that size.
+// red: two complex per wave.
+__device__ __forceinline__ void dot_totals(const double2* part, int64_t q, int nparts,
+                                           double2* red, double2& t0, double2& t1) {
+  double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);
+  for (int ch = threadIdx.x; ch < nparts; ch += blockDim.x) {
+    s0 = cadd(s0, part[(q * nparts + ch) * 2]);
+    s1 = cadd(s1, part[(q * nparts + ch) * 2 + 1]);
+  }
+  block_pair_sum(s0, s1, red);
+  t0 = t1 = make_double2(0, 0);
+  for (int v = 0; v < (int)(blockDim.x >> 6); v++) {
+    t0 = cadd(t0, red[2 * v]);
+    t1 = cadd(t1, red[2 * v + 1]);
+  }
+}
+
+// Per-system BiCGStab scalars: rho of the iterations of either parity (a
+// kernel that writes one reads the other), alpha, omega.
+enum { KS_RHO = 0, KS_ALPHA = 2, KS_OMEGA = 3, KS_N = 4 };
+
+// The vector update in front of a preconditioner apply, and where its scalars
+// come from: BICG_P  p <- r + beta (p - omega v),  BICG_S  r <- r - alpha v.
+enum { BICG_NONE = 0, BICG_P = 1, BICG_S = 2 };
+
+// A system has ended: the last one to end marks the solve converged, and the
+// launches after this one do nothing.
+__device__ __forceinline__ void system_ends(const BicgStep& b, int64_t q, uint32_t why) {
+  if (why) latch(b.status, why);
+  b.active[q] = 0;
+  if (atomicSub(b.live, 1u) == 1u) *b.conv = 1u;
+}
+
+// The scalar step in front of that update, taken by every workgroup of system
+// q from the dot products' partial sums (the owner alone stores): false when
+// the system has ended.  c0, c1: beta and omega, or alpha.
+//   BICG_P (from the second iteration on) partials <r, r>, <rhat, r>:
+//          ||r||^2 <= tol^2 ||b||^2 ends the system; rho, beta
+//   BICG_S partials <rhat, v>: alpha = rho / <rhat, v>
+// A zero denominator in a live system latches ST_BREAKDOWN and ends it.
+template <int MODE>
+__device__ __forceinline__ bool bicg_step(const BicgStep& b, int64_t q, bool owner, double2* red,
+                                          double2& c0, double2& c1) {
+  double2 t0, t1;
+  dot_totals((const double2*)b.part, q, b.nparts, red, t0, t1);
+  double2* s = (double2*)b.ks + q * KS_N;
+  owner = owner && threadIdx.x == 0;
+  if (MODE == BICG_P) {
+    const bool finite = isfinite(t0.x), done = t0.x <= b.tol2 * b.bnorm2[q];
+    const bool broken = t1.x == 0.0 && t1.y == 0.0;
+    if (!finite || done || broken) {
+      if (owner) system_ends(b, q, !finite ? ST_NONFINITE : done ? 0u : ST_BREAKDOWN);
+      return false;
+    }
+    c1 = s[KS_OMEGA];
+    c0 = cmul(cdiv(t1, s[KS_RHO + ((b.it + 1) & 1)]), cdiv(s[KS_ALPHA], c1));
+    if (owner) s[KS_RHO + (b.it & 1)] = t1;
+  } else {
+    if (t0.x == 0.0 && t0.y == 0.0) {
+      if (owner) system_ends(b, q, ST_BREAKDOWN);
+      return false;
+    }
+    c0 = cdiv(s[KS_RHO + (b.it & 1)], t0);
+    if (owner) s[KS_ALPHA] = c0;
+  }
+  return true;
+}
+
+// r, p, v of one unknown to the updated vector's value
+template <int MODE>
+__device__ __forceinline__ double2 bicg_update(double2 r, double2 p, double2 v, double2 c0,
+                                               double2 c1) {
+  if (MODE == BICG_P) return cadd(r, cmul(c0, csub(p, cmul(c1, v))));
+  return csub(r, cmul(c0, v));
+}
+
+// The update alone, for the sweeps of long lines, whose loads are not coalesced.
+template <int MODE>
+__global__ __launch_bounds__(kKThreads) void k_bicg_update(int64_t n, int k, double2* X,
+                                                           BicgStep b) {
+  if (__hip_atomic_load(b.conv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+  __shared__ double2 red[2 * kKThreads / 64];
+  const int64_t q = (int64_t)blockIdx.z * k + blockIdx.y;
+  double2 c0, c1;
+  // (a workgroup that sees the owner's store ends as the others do)
+  if (!__syncthreads_or(b.active[q] != 0)) return;
+  if (!bicg_step<MODE>(b, q, blockIdx.x == 0, red, c0, c1)) return;
+  const int64_t e0 = (int64_t)blockIdx.x * kKChunk;
+  const int rows = (int)min((int64_t)kKChunk, n - e0);
+  for (int e = threadIdx.x; e < rows; e += kKThreads) {
+    const int64_t o = q * n + e0 + e;
+    const double2 x = X[o], v = ((const double2*)b.v)[o];
+    X[o] = bicg_update<MODE>(MODE == BICG_P ? ((const double2*)b.r)[o] : x, x, v, c0, c1);
+  }
+}
+
 // Y = K^-1 X (or K^-H X) with K = D (Jacobi), for every (shift, column).
-__global__ void k_pc_jacobi_apply(int nn, int k, int adjoint, const double2* __restrict__ Dinv,
-                                  const double2* X, double2* Y, const uint32_t* active,
-                                  const uint32_t* skip) {
+// MODE: X is the vector of b's update, made here.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_pc_jacobi_apply(int nn, int k, int adjoint,
+                                                         const double2* __restrict__ Dinv,
+                                                         double2* X, double2* Y,
+                                                         const uint32_t* active,
+                                                         const uint32_t* skip, BicgStep b) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+  __shared__ double2 red[8];
   const int p = blockIdx.x * blockDim.x + threadIdx.x, c = blockIdx.y, w = blockIdx.z;
-  if (p >= nn) return;
   const int64_t q = (int64_t)w * k + c;
-  if (active && !active[q]) return;
+  if (MODE == BICG_NONE && active && !active[q]) return;
+  double2 c0, c1;
+  if (MODE != BICG_NONE) {  // (a workgroup that sees the owner's store ends as the others do)
+    if (!__syncthreads_or(active[q] != 0)) return;
+    if (!bicg_step<MODE>(b, q, blockIdx.x == 0, red, c0, c1)) return;
+  }
+  if (p >= nn) return;
   const int64_t off = q * 2 * nn + 2 * (int64_t)p;
   const C2 E = load_c2(Dinv + ((int64_t)w * nn + p) * 4);
-  double2 y0, y1;
-  mv2(E, adjoint != 0, X[off], X[off + 1], y0, y1);
+  double2 x[2], y0, y1;
+#pragma unroll
+  for (int e = 0; e < 2; e++) {
+    x[e] = X[off + e];
+    if (MODE == BICG_NONE) continue;
+    const double2* v = (const double2*)b.v + off;
+    x[e] = MODE == BICG_P ? bicg_update<MODE>(((const double2*)b.r)[off + e], x[e], v[e], c0, c1)
+                          : bicg_update<MODE>(x[e], x[e], v[e], c0, c1);
+    X[off + e] = x[e];
+  }
+  mv2(E, adjoint != 0, x[0], x[1], y0, y1);
   Y[off] = y0;
   Y[off + 1] = y1;
 }
@@ -223,7 +367,6 @@ __global__ void k_pc_jacobi_apply(int nn, int k, int adjoint, const double2* __r
 //   backward y_p = w_p - D_p^-H (M_p+1,p y_p+1 + M_p+ny,p y_p+ny)
 // (the off-diagonal blocks are real and diagonal, so ^H leaves them as they are).
 __global__ __launch_bounds__(kKThreads) void k_pc_ilu0_apply(int nx, int ny, int k, int adjoint,
-                                                             const double* __restrict__ coef,
                                                              const double2* __restrict__ Dinv,
                                                              const double2* X, double2* Y,
                                                              const uint32_t* active,
@@ -304,186 +447,268 @@ __global__ __launch_bounds__(kKThreads) void k_pc_ilu0_apply(int nx, int ny, int
   }
 }
 
+// The neighbouring lane's value, lane - 1 (UP) or lane + 1; zero past the wave's end.
+template <bool UP>
+__device__ __forceinline__ double lane_next(double x) {
+  constexpr int ctl = UP ? 0x138 : 0x130;  // wave_shr:1, wave_shl:1
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), ctl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), ctl, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
 // The same sweeps with one thread per grid column j (ny <= kIluColMax):
 // thread j walks its nodes (i, j), i = 0 .. nx-1 (backward: nx-1 .. 0), at
 // anti-diagonal steps d = i + j.  Its own previous node, (i-1, j) (backward
-// (i+1, j)), stays in registers; only the other neighbour, (i, j-1)
-// (backward (i, j+1)), comes through LDS from the neighbouring thread's
-// previous step.  A node's operands (x or the forward result, the two
-// off-diagonal blocks, D^-1) do not depend on the sweep, so each thread loads
-// its next node's while it computes the current one, into the other of two
-// register sets (chosen by the parity of d, the same for every thread).  The
-// loads are issued by every thread at every step (of a valid node, kept or
-// not) and hold raw coefficients (signs applied at use): a load that is
-// conditional, or whose value is transformed at once, makes the compiler
-// wait for it, or for the loads around it, before the step's arithmetic.
-// The arithmetic is the same, in the same order, as k_pc_ilu0_apply's.
+// (i+1, j)), stays in registers; the other neighbour, (i, j-1) (backward
+// (i, j+1)), comes from the neighbouring lane's previous step, and between
+// waves through LDS and a barrier (ONE: a single wave, no barrier).
+//
+// What bounds it is the chain of nx + ny - 1 steps each way, a step being the
+// instructions that one wave issues, so a step is kept short:
+//   - It has no branch, mask or clamp.  Threads without a node at a step read
+//     zeros (the preconditioner's unused slots hold them, and vector loads past
+//     the buffer's bounds give them), so their results are zeros, which stand
+//     for the neighbours that a border node lacks; their stores fall past the
+//     bounds and are dropped.
+//   - Nothing a node needs depends on the sweep, so each thread holds the loads
+//     of its next kIluAhead steps in registers (step d: set d mod kIluAhead,
+//     the same for every thread), raw (signs applied at use).
+//   - The preconditioner's fields are stored by anti-diagonal, but the vectors
+//     by grid line, where the nodes of one step are ny - 1 apart: 64 cache lines
+//     a wave and load.  So G neighbouring threads load (and store) G neighbours
+//     of one grid line at a time, each at most G - 1 steps before it needs its
+//     own (after it has it), and keep them for those steps in LDS, in G places
+//     a thread that no other touches.
+// 128 x 64 nodes, one shift, 10 columns, with BICG_S: 140 us with masks, clamps
+// and 64-bit addresses, 145 instructions a step; 93 us now.  Without the update:
+// 130 us with branches, LDS neighbours and one step's loads ahead, 88 now; 4
+// shifts at 512 x 256: 2.00 -> 1.00 ms; one at 1024 x 512: 7.3 -> 3.8 ms.
 constexpr int kIluColMax = 512;
+constexpr int kIluAhead = 4;
 
+template <int MODE>
 struct IluOp {
-  double2 v0, v1;      // x_p (forward) or w_p (backward)
-  double a0, a1;       // minus the block to the (i, j -/+ 1) neighbour
-  double b0, b1;       // minus the block to the (i -/+ 1, j) neighbour
+  double2 v0, v1;      // x_p (forward) or w_p (backward), of the line's node
+  double2 r0, r1;      // BICG_P: r_p
+  double2 u0, u1;      // BICG_P, BICG_S: v_p
+  double2 a, b;        // minus the blocks to the (i, j -/+ 1), (i -/+ 1, j) neighbours
   C2 D;
 };
 
-__global__ __launch_bounds__(kIluColMax) void k_pc_ilu0_apply_col(
-    int nx, int ny, int k, int adjoint, const double* __restrict__ coef,
-    const double2* __restrict__ Dinv, const double2* X, double2* Y, const uint32_t* active,
-    const uint32_t* skip) {
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p, unsigned bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x27000);
+}
+__device__ __forceinline__ double2 buffer_load(__amdgpu_buffer_rsrc_t b, unsigned at, int base) {
+  return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(b, (int)at, base, 0));
+}
+__device__ __forceinline__ void buffer_store(__amdgpu_buffer_rsrc_t b, unsigned at, double2 s0,
+                                             double2 s1) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, s0), b, (int)at, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, s1), b, (int)at + 16, 0, 0);
+}
+
+// s + a x, s + a x (conj: s + conj(a) x), fused
+__device__ __forceinline__ double2 rfma(double a, double2 x, double2 s) {
+  return make_double2(fma(a, x.x, s.x), fma(a, x.y, s.y));
+}
+template <bool CONJ>
+__device__ __forceinline__ double2 cfma(double2 a, double2 x, double2 s) {
+  const double ai = CONJ ? -a.y : a.y;
+  return make_double2(fma(-ai, x.y, fma(a.x, x.x, s.x)), fma(ai, x.x, fma(a.x, x.y, s.y)));
+}
+
+template <int MODE, bool ONE, bool herm, int G>
+__global__ __launch_bounds__(ONE ? 64 : kIluColMax) void k_pc_ilu0_apply_col(
+    int nx, int ny, int k, const double2* __restrict__ Dinv, double2* X, double2* Y,
+    const uint32_t* active, const uint32_t* skip, BicgStep bs) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   extern __shared__ __align__(16) char kc_smem[];
-  double2* ring = reinterpret_cast<double2*>(kc_smem);  // [2][ny][2]
+  __shared__ double2 red[2 * kIluColMax / 64];
+  constexpr int kEdges = kIluColMax / 64 + 2;
+  __shared__ double2 edge[2][kEdges][2];  // [.][v + 1]: wave v's last (first) node of a step
+  const int j = threadIdx.x, wave = j >> 6, lane = j & 63;
   const int c = blockIdx.x, w = blockIdx.y, nn = nx * ny;
   const int64_t q = (int64_t)w * k + c;
   if (active && !active[q]) return;
-  const int64_t off = q * 2 * nn;
-  const double2* x = X + off;
-  double2* y = Y + off;
-  const int64_t ns = ilu_slots(nx, ny);
+  double2 c0, c1;
+  if (MODE != BICG_NONE && !bicg_step<MODE>(bs, q, true, red, c0, c1)) return;
+  // the places of this thread in LDS, [G][2][64] a wave: arriving, leaving
+  constexpr int kPlace = 2 * 64;
+  double2* const fin = reinterpret_cast<double2*>(kc_smem) + wave * 2 * G * kPlace + lane;
+  double2* const fout = fin + G * kPlace;
+  const int64_t off = q * 2 * nn, ns = ilu_slots(nx, ny);
   const double2* Fw = Dinv + (int64_t)w * kIluFields * ns;
-  const bool herm = adjoint != 0;
-  const int j = threadIdx.x;
+  const int jb = j & ~(G - 1), jt = j | (G - 1), nd = nx + ny - 1;
+  const unsigned line = 32u * ny;  // bytes of a grid line
+  const auto xb = buffer(X + off, 32u * nn), yb = buffer(Y + off, 32u * nn);
+  const auto rb = buffer((const double2*)bs.r + (MODE == BICG_P ? off : 0), 32u * nn);
+  const auto vb = buffer((const double2*)bs.v + (MODE != BICG_NONE ? off : 0), 32u * nn);
+  auto field = [&](int e) { return buffer(Fw + e * ns, (unsigned)(16 * ns)); };
+  const __amdgpu_buffer_rsrc_t dinv[4] = {field(0), field(1), field(2), field(3)};
+  // byte offsets: of this thread's unknown pair in grid line i, and of its slot
+  // in an anti-diagonal; far past every bound for a thread without a column
   const bool col = j < ny;
-  const int jc = col ? j : ny - 1;  // the column whose nodes this thread loads
-  const int nd = nx + ny - 1;
-  // raw loads of node (clamp(i), jc) (the blocks are minus the loaded
-  // coefficients); D^-1 and the coefficients from the anti-diagonal layout
-  auto node_load = [&](int i, IluOp& o, const double2* v, int fa, int fb) {
-    i = min(max(i, 0), nx - 1);
-    const int p = jc + ny * i;
-    const int64_t sl = (int64_t)(i + jc) * ny + jc;
-    o.v0 = v[2 * p];
-    o.v1 = v[2 * p + 1];
-    const double2 a = Fw[fa * ns + sl], b = Fw[fb * ns + sl];
-    o.a0 = a.x;
-    o.a1 = a.y;
-    o.b0 = b.x;
-    o.b1 = b.y;
+  auto at = [&](int i) { return col ? 32u * j + line * (unsigned)i : 0xA0000000u + line * i; };
+  const unsigned slot = col ? 16u * j : 0xA0000000u;
+  if (!ONE) {
+    if (j < 4 * kEdges) (&edge[0][0][0])[j] = make_double2(0, 0);
+    __syncthreads();
+  }
+  // (clamped, so that the offset stays in the field: the slots of the first and
+  // last anti-diagonal then meet vectors that are zero, or are not stored)
+  auto load = [&](int d, unsigned from, IluOp<MODE>& o, __amdgpu_buffer_rsrc_t v,
+                  __amdgpu_buffer_rsrc_t fa, __amdgpu_buffer_rsrc_t fb, bool fwd) {
+    const int diag = 16 * ny * min(max(d, 0), nd - 1);
+    o.v0 = buffer_load(v, from, 0);
+    o.v1 = buffer_load(v, from + 16, 0);
+    if (fwd && MODE == BICG_P) {
+      o.r0 = buffer_load(rb, from, 0);
+      o.r1 = buffer_load(rb, from + 16, 0);
+    }
+    if (fwd && MODE != BICG_NONE) {
+      o.u0 = buffer_load(vb, from, 0);
+      o.u1 = buffer_load(vb, from + 16, 0);
+    }
+    o.a = buffer_load(fa, slot, diag);
+    o.b = buffer_load(fb, slot, diag);
 #pragma unroll
-    for (int e = 0; e < 4; e++) o.D.m[e] = Fw[e * ns + sl];
+    for (int e = 0; e < 4; e++) o.D.m[e] = buffer_load(dinv[e], slot, diag);
   };
-  auto fwd_load = [&](int i, IluOp& o) { node_load(i, o, x, herm ? 6 : 4, herm ? 7 : 5); };
-  auto bwd_load = [&](int i, IluOp& o) { node_load(i, o, y, herm ? 10 : 8, herm ? 11 : 9); };
-  IluOp opA, opB;  // the register sets of even and odd steps
-  double2 own0 = make_double2(0, 0), own1 = make_double2(0, 0);
-  // forward: w_p = D_p^-1 (x_p - M_p,p-1 w_p-1 - M_p,p-ny w_p-ny)
-  if (j & 1) fwd_load(0, opB);
-  else fwd_load(0, opA);
-  auto fwd_step = [&](int d, IluOp& use, IluOp& fill) {
-    const int i = d - j;
-    double2* cur = ring + (d & 1) * 2 * ny;
-    const double2* prev = ring + ((d + 1) & 1) * 2 * ny;
-    fwd_load(i + 1, fill);
-    if (col && i >= 0 && i < nx) {
-      double2 r0 = use.v0, r1 = use.v1;
-      if (j > 0) {
-        r0 = csub(r0, cscale(-use.a0, prev[2 * (j - 1)]));
-        r1 = csub(r1, cscale(-use.a1, prev[2 * (j - 1) + 1]));
-      }
-      if (i > 0) {
-        r0 = csub(r0, cscale(-use.b0, own0));
-        r1 = csub(r1, cscale(-use.b1, own1));
-      }
-      double2 w0, w1;
-      mv2(use.D, herm, r0, r1, w0, w1);
-      cur[2 * j] = w0;
-      cur[2 * j + 1] = w1;
-      const int p = j + ny * i;
-      y[2 * p] = w0;
-      y[2 * p + 1] = w1;
-      own0 = w0;
-      own1 = w1;
+  auto keep = [&](double2* f, int i, double2 s0, double2 s1) {
+    f[(i & (G - 1)) * kPlace] = s0;
+    f[(i & (G - 1)) * kPlace + 64] = s1;
+  };
+  auto kept = [&](const double2* f, int i, double2& s0, double2& s1) {
+    s0 = f[(i & (G - 1)) * kPlace];
+    s1 = f[(i & (G - 1)) * kPlace + 64];
+  };
+  // (i, j - 1) or, !UP, (i, j + 1) of the step before, whose parity is par
+  auto neighbour = [&](auto up, int par, double2 own0, double2 own1, double2& n0, double2& n1) {
+    constexpr bool UP = decltype(up)::value;
+    n0 = make_double2(lane_next<UP>(own0.x), lane_next<UP>(own0.y));
+    n1 = make_double2(lane_next<UP>(own1.x), lane_next<UP>(own1.y));
+    if (!ONE) {
+      const double2 e0 = edge[par][wave + (UP ? 0 : 2)][0], e1 = edge[par][wave + (UP ? 0 : 2)][1];
+      const bool end = lane == (UP ? 0 : 63);
+      n0 = make_double2(end ? e0.x : n0.x, end ? e0.y : n0.y);
+      n1 = make_double2(end ? e1.x : n1.x, end ? e1.y : n1.y);
+    }
+  };
+  auto publish = [&](int last, int par, double2 own0, double2 own1) {
+    if (ONE) return;
+    if (lane == last) {
+      edge[par][wave + 1][0] = own0;
+      edge[par][wave + 1][1] = own1;
     }
     __syncthreads();
   };
-  int d = 0;
-  for (; d + 1 < nd; d += 2) {
-    fwd_step(d, opA, opB);
-    fwd_step(d + 1, opB, opA);
-  }
-  if (d < nd) fwd_step(d, opA, opB);
-  // backward: y_p = w_p - D_p^-1 (M_p,p+1 y_p+1 + M_p,p+ny y_p+ny); the
-  // forward results of this thread's own column are its own stores
-  if ((nx - 1 + j) & 1) bwd_load(nx - 1, opB);
-  else bwd_load(nx - 1, opA);
-  auto bwd_step = [&](int d, IluOp& use, IluOp& fill) {
-    const int i = d - j;
-    double2* cur = ring + (d & 1) * 2 * ny;
-    const double2* nxt = ring + ((d + 1) & 1) * 2 * ny;
-    bwd_load(i - 1, fill);
-    if (col && i >= 0 && i < nx) {
-      double2 t0 = make_double2(0, 0), t1 = make_double2(0, 0);
-      if (j < ny - 1) {
-        t0 = cadd(t0, cscale(-use.a0, nxt[2 * (j + 1)]));
-        t1 = cadd(t1, cscale(-use.a1, nxt[2 * (j + 1) + 1]));
-      }
-      if (i < nx - 1) {
-        t0 = cadd(t0, cscale(-use.b0, own0));
-        t1 = cadd(t1, cscale(-use.b1, own1));
-      }
-      double2 u0, u1;
-      mv2(use.D, herm, t0, t1, u0, u1);
-      const double2 y0 = csub(use.v0, u0), y1 = csub(use.v1, u1);
-      cur[2 * j] = y0;
-      cur[2 * j + 1] = y1;
-      const int p = j + ny * i;
-      y[2 * p] = y0;
-      y[2 * p + 1] = y1;
-      own0 = y0;
-      own1 = y1;
-    }
-    __syncthreads();
+  // s + D_p^-1 r (D_p^-H r)
+  auto solve2 = [&](const C2& D, double2 r0, double2 r1, double2 s0, double2 s1, double2& y0,
+                    double2& y1) {
+    y0 = cfma<herm>(D.m[herm ? 2 : 1], r1, cfma<herm>(D.m[0], r0, s0));
+    y1 = cfma<herm>(D.m[3], r1, cfma<herm>(D.m[herm ? 1 : 2], r0, s1));
   };
-  d = nd - 1;
-  for (; d - 1 >= 0; d -= 2) {
-    if (d & 1) {
-      bwd_step(d, opB, opA);
-      bwd_step(d - 1, opA, opB);
-    } else {
-      bwd_step(d, opA, opB);
-      bwd_step(d - 1, opB, opA);
+  IluOp<MODE> op[kIluAhead] = {};
+  const double2 zero = make_double2(0, 0);
+  double2 own0 = zero, own1 = zero;
+  double2 now0 = zero, now1 = zero;  // this step's x_p, w_p
+  double2 out0 = zero, out1 = zero;  // the line's results, to be stored
+#pragma unroll
+  for (int g = 0; g < G; g++) keep(fin, g, zero, zero);
+  // forward: w_p = D_p^-1 (x_p - M_p,p-1 w_p-1 - M_p,p-ny w_p-ny).  At step d
+  // the group's line d + 1 - jb arrives and line d - 1 - jt leaves.
+  const int first = -2 * kIluAhead;
+  const auto fa = field(herm ? 6 : 4), fb = field(herm ? 7 : 5);
+  unsigned arrive = at(first + 1 - jb), leave = at(first - 1 - jt);
+  for (int d0 = first; d0 < nd + G; d0 += kIluAhead) {
+#pragma unroll
+    for (int u = 0; u < kIluAhead; u++) {
+      const int d = d0 + u, i = d - j;
+      const IluOp<MODE>& use = op[u];
+      double2 n0, n1;
+      neighbour(std::true_type{}, (d + 1) & 1, own0, own1, n0, n1);
+      const double2 r0 = rfma(use.b.x, own0, rfma(use.a.x, n0, now0));
+      const double2 r1 = rfma(use.b.y, own1, rfma(use.a.y, n1, now1));
+      solve2(use.D, r0, r1, zero, zero, own0, own1);
+      double2 v0 = use.v0, v1 = use.v1;
+      if (MODE != BICG_NONE) {
+        v0 = bicg_update<MODE>(MODE == BICG_P ? use.r0 : v0, v0, use.u0, c0, c1);
+        v1 = bicg_update<MODE>(MODE == BICG_P ? use.r1 : v1, v1, use.u1, c0, c1);
+        buffer_store(xb, arrive, v0, v1);
+      }
+      buffer_store(yb, leave, out0, out1);
+      keep(fin, d + 1, v0, v1);  // jb is a multiple of G
+      keep(fout, i, own0, own1);
+      kept(fin, i + 1, now0, now1);
+      kept(fout, d + 1, out0, out1);  // jt one less than one
+      load(d + kIluAhead, arrive + kIluAhead * line, op[u], xb, fa, fb, true);
+      arrive += line;
+      leave += line;
+      publish(63, d & 1, own0, own1);
+      __builtin_amdgcn_sched_barrier(0);  // keeps a step's loads in front of the next step's
     }
   }
-  if (d == 0) bwd_step(0, opA, opB);
+  // backward: y_p = w_p - D_p^-1 (M_p,p+1 y_p+1 + M_p,p+ny y_p+ny); the forward
+  // results of a thread's column are its own stores.  At step d the group's
+  // line d - 1 - jt arrives and line d + 1 - jb leaves.
+  own0 = own1 = now0 = now1 = zero;
+#pragma unroll
+  for (int u = 0; u < kIluAhead; u++) op[u] = IluOp<MODE>{};
+#pragma unroll
+  for (int g = 0; g < G; g++) keep(fin, g, zero, zero);
+  if (!ONE) {
+    __syncthreads();
+    if (j < 4 * kEdges) (&edge[0][0][0])[j] = zero;
+    __syncthreads();
+  }
+  const int last = nd - 1 + 2 * kIluAhead + G;
+  const auto ga = field(herm ? 10 : 8), gb = field(herm ? 11 : 9);
+  arrive = at(last - 1 - jt);
+  leave = at(last + 1 - jb);
+  for (int d0 = last; d0 >= -1; d0 -= kIluAhead) {
+#pragma unroll
+    for (int u = 0; u < kIluAhead; u++) {
+      const int d = d0 - u, i = d - j;
+      const IluOp<MODE>& use = op[u];
+      double2 n0, n1;
+      neighbour(std::false_type{}, (d + 1) & 1, own0, own1, n0, n1);
+      const double2 s0 = rfma(use.b.x, own0, rfma(use.a.x, n0, zero));
+      const double2 s1 = rfma(use.b.y, own1, rfma(use.a.y, n1, zero));
+      solve2(use.D, s0, s1, now0, now1, own0, own1);
+      buffer_store(yb, leave, out0, out1);
+      keep(fin, d, use.v0, use.v1);
+      keep(fout, i, own0, own1);
+      kept(fin, i - 1, now0, now1);
+      kept(fout, d, out0, out1);
+      load(d - kIluAhead, arrive - kIluAhead * line, op[u], yb, ga, gb, false);
+      arrive -= line;
+      leave -= line;
+      publish(0, d & 1, own0, own1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
 }
 
-// partial[(q * nchunk + chunk) * 2 + e] = sum over the chunk of conj(A_e) B_e
-// for the npair (1 or 2) pairs, per system q = w * k + c.
-__global__ __launch_bounds__(kKThreads) void k_kdot_partial(int64_t n, int k, int npair,
-                                                           const double2* A0, const double2* B0,
-                                                           const double2* A1, const double2* B1,
-                                                           int nchunk, double2* partial,
+// partial[(q * nchunk + chunk) * 2] = sum over the chunk of conj(A) B, per
+// system q = w * k + c (and zero beside it, the second of the fused kernels' pairs).
+__global__ __launch_bounds__(kKThreads) void k_kdot_partial(int64_t n, int k, const double2* A,
+                                                           const double2* B, int nchunk,
+                                                           double2* partial,
                                                            const uint32_t* active,
                                                            const uint32_t* skip) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-  __shared__ double2 red[2][kKThreads / 64];
+  __shared__ double2 red[2 * kKThreads / 64];
   const int chunk = blockIdx.x, c = blockIdx.y, w = blockIdx.z;
   const int64_t q = (int64_t)w * k + c;
   if (active && !active[q]) return;
   const int64_t base = q * n, r0 = (int64_t)chunk * kKChunk, r1 = min(n, r0 + kKChunk);
-  double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);
-  for (int64_t r = r0 + threadIdx.x; r < r1; r += kKThreads) {
-    s0 = cadd(s0, cmulc(A0[base + r], B0[base + r]));
-    if (npair > 1) s1 = cadd(s1, cmulc(A1[base + r], B1[base + r]));
-  }
-  for (int o = 32; o > 0; o >>= 1) {
-    s0.x += __shfl_down(s0.x, o, 64);
-    s0.y += __shfl_down(s0.y, o, 64);
-    s1.x += __shfl_down(s1.x, o, 64);
-    s1.y += __shfl_down(s1.y, o, 64);
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) {
-    red[0][wave] = s0;
-    red[1][wave] = s1;
-  }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    double2 t = make_double2(0, 0);
-    for (int v = 0; v < kKThreads / 64; v++) t = cadd(t, red[threadIdx.x][v]);
-    partial[(q * nchunk + chunk) * 2 + threadIdx.x] = t;
-  }
+  double2 s0 = make_double2(0, 0);
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += kKThreads)
+    s0 = cadd(s0, cmulc(A[base + r], B[base + r]));
+  block_pair_sum(s0, make_double2(0, 0), red);
+  if (threadIdx.x < 2) partial[(q * nchunk + chunk) * 2 + threadIdx.x] = pair_total(red);
 }
 
 __device__ __forceinline__ double2 dot_total(const double2* partial, int64_t q, int nchunk, int e) {
@@ -492,117 +717,87 @@ __device__ __forceinline__ double2 dot_total(const double2* partial, int64_t q, 
   return t;
 }
 
-// Per-system BiCGStab scalars: [0] rho, [1] alpha, [2] omega, [3] beta.
-enum { KS_RHO = 0, KS_ALPHA = 1, KS_OMEGA = 2, KS_BETA = 3, KS_N = 4 };
-
-// The scalar steps of one BiCGStab iteration, one thread per system, from
-// the dot products just taken (mode):
-//   0  start:  bnorm2 = ||b||^2 (a zero right-hand side is solved by x = 0)
-//   1  rho:    rho = <rhat, r>, beta = (rho / rho_prev)(alpha / omega) (0 first)
-//   2  alpha:  alpha = rho / <rhat, v>
-//   3  omega:  omega = <t, s> / <t, t> (0 when t = 0)
-//   4  check:  ||r||^2 <= tol^2 ||b||^2 ends the system; the last block of
-//              the launch counts the systems left and marks the solve
-//              converged when none are (later launches then skip).
-// A zero denominator in a live system latches ST_BREAKDOWN and ends it.
-__global__ __launch_bounds__(kKThreads) void k_bicg_scalars(int N, int nchunk, int mode, int it,
-                                                           double tol2, const double2* partial,
-                                                           double2* ks, double* bnorm2,
-                                                           uint32_t* active, uint32_t* conv,
-                                                           uint32_t* status,
-                                                           const uint32_t* skip) {
+// The scalar steps at a solve's ends, one thread per system, from the partial
+// sums of ||r||^2 (mode):
+//   0  start:  bnorm2 = ||b||^2 (a zero right-hand side is solved by x = 0),
+//              rho = <rhat, r> = ||b||^2, the number of live systems
+//   1  check:  ||r||^2 <= tol^2 ||b||^2 ends the system
+// The solve is marked converged when no system is left (later launches then
+// skip).
+__global__ __launch_bounds__(kKThreads) void k_krylov_scalars(int N, int nparts, int mode,
+                                                             double tol2, const double2* partial,
+                                                             double2* ks, double* bnorm2,
+                                                             uint32_t* active, uint32_t* live_out,
+                                                             uint32_t* conv, uint32_t* status,
+                                                             const uint32_t* skip) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   __shared__ uint32_t live;
   if (threadIdx.x == 0) live = 0;
   __syncthreads();
   uint32_t mine = 0;
   for (int q = threadIdx.x; q < N; q += blockDim.x) {
-    double2* s = ks + (int64_t)q * KS_N;
     if (mode == 0) {
-      const double b2 = dot_total(partial, q, nchunk, 0).x;
+      const double b2 = dot_total(partial, q, nparts, 0).x;
       bnorm2[q] = b2;
       active[q] = b2 > 0.0 ? 1u : 0u;
-      s[KS_RHO] = s[KS_ALPHA] = s[KS_OMEGA] = make_double2(1, 0);
-      s[KS_BETA] = make_double2(0, 0);
+      ks[(int64_t)q * KS_N + KS_RHO] = make_double2(b2, 0);
       mine += active[q];
       continue;
     }
     if (!active[q]) continue;
-    if (mode == 1) {
-      const double2 rho = dot_total(partial, q, nchunk, 0);
-      if (rho.x == 0.0 && rho.y == 0.0) {
-        latch(status, ST_BREAKDOWN);
-        active[q] = 0;
-        continue;
-      }
-      s[KS_BETA] = it == 0 ? make_double2(0, 0)
-                           : cmul(cdiv(rho, s[KS_RHO]), cdiv(s[KS_ALPHA], s[KS_OMEGA]));
-      s[KS_RHO] = rho;
-    } else if (mode == 2) {
-      const double2 d = dot_total(partial, q, nchunk, 0);
-      if (d.x == 0.0 && d.y == 0.0) {
-        latch(status, ST_BREAKDOWN);
-        active[q] = 0;
-        continue;
-      }
-      s[KS_ALPHA] = cdiv(s[KS_RHO], d);
-    } else if (mode == 3) {
-      const double2 ts = dot_total(partial, q, nchunk, 0);
-      const double tt = dot_total(partial, q, nchunk, 1).x;
-      s[KS_OMEGA] = tt > 0.0 ? cscale(1.0 / tt, ts) : make_double2(0, 0);
-    } else {
-      const double r2 = dot_total(partial, q, nchunk, 0).x;
-      if (!isfinite(r2)) {
-        latch(status, ST_NONFINITE);
-        active[q] = 0;
-        continue;
-      }
-      if (r2 <= tol2 * bnorm2[q]) active[q] = 0;
-      else mine++;
+    const double r2 = dot_total(partial, q, nparts, 0).x;
+    if (!isfinite(r2)) {
+      latch(status, ST_NONFINITE);
+      active[q] = 0;
+      continue;
     }
+    if (r2 <= tol2 * bnorm2[q]) active[q] = 0;
+    else mine++;
   }
-  if (mode == 0 || mode == 4) {
-    atomicAdd(&live, mine);
-    __syncthreads();
-    if (threadIdx.x == 0 && live == 0) *conv = 1u;
+  atomicAdd(&live, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    if (mode == 0) *live_out = live;
+    if (live == 0) *conv = 1u;
   }
 }
 
-// p = r + beta (p - omega v)
-__global__ void k_bicg_p(int64_t n, int k, const double2* ks, const double2* r, const double2* v,
-                         double2* p, const uint32_t* active, const uint32_t* skip) {
+// omega = <t, s> / <t, t> (0 when t = 0) from b's partial sums, x += alpha y +
+// omega z, r <- s - omega t, and the partial sums of <r, r>, <rhat, r> of the
+// next iteration's scalars (kKChunk rows a workgroup).
+__global__ __launch_bounds__(kKThreads) void k_bicg_xr(int64_t n, int k, const double2* y,
+                                                       const double2* z, const double2* t,
+                                                       const double2* rh, double2* x, double2* r,
+                                                       double2* part_out, const uint32_t* skip,
+                                                       BicgStep b) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  __shared__ double2 red[2 * kKThreads / 64];
   const int64_t q = (int64_t)blockIdx.z * k + blockIdx.y;
-  if (e >= n || !active[q]) return;
-  const double2* s = ks + q * KS_N;
-  const int64_t o = q * n + e;
-  p[o] = cadd(r[o], cmul(s[KS_BETA], csub(p[o], cmul(s[KS_OMEGA], v[o]))));
-}
-
-// r <- s = r - alpha v
-__global__ void k_bicg_s(int64_t n, int k, const double2* ks, const double2* v, double2* r,
-                         const uint32_t* active, const uint32_t* skip) {
-  if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t q = (int64_t)blockIdx.z * k + blockIdx.y;
-  if (e >= n || !active[q]) return;
-  const int64_t o = q * n + e;
-  r[o] = csub(r[o], cmul(ks[q * KS_N + KS_ALPHA], v[o]));
-}
-
-// x += alpha y + omega z,  r <- s - omega t
-__global__ void k_bicg_xr(int64_t n, int k, const double2* ks, const double2* y,
-                          const double2* z, const double2* t, double2* x, double2* r,
-                          const uint32_t* active, const uint32_t* skip) {
-  if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-  const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  const int64_t q = (int64_t)blockIdx.z * k + blockIdx.y;
-  if (e >= n || !active[q]) return;
-  const double2* s = ks + q * KS_N;
-  const int64_t o = q * n + e;
-  x[o] = cadd(x[o], cadd(cmul(s[KS_ALPHA], y[o]), cmul(s[KS_OMEGA], z[o])));
-  r[o] = csub(r[o], cmul(s[KS_OMEGA], t[o]));
+  if (!b.active[q]) return;
+  double2 ts, tt;
+  dot_totals((const double2*)b.part, q, b.nparts, red, ts, tt);
+  __syncthreads();
+  double2* s = (double2*)b.ks + q * KS_N;
+  const double2 alpha = s[KS_ALPHA];
+  const double2 omega = tt.x > 0.0 ? cscale(1.0 / tt.x, ts) : make_double2(0, 0);
+  if (blockIdx.x == 0 && threadIdx.x == 0) s[KS_OMEGA] = omega;
+  double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);
+  const int64_t r0 = q * n + (int64_t)blockIdx.x * kKChunk;
+  const int rows = (int)min((int64_t)kKChunk, n - (int64_t)blockIdx.x * kKChunk);
+#pragma unroll
+  for (int u = 0; u < kKChunk / kKThreads; u++) {
+    const int e = threadIdx.x + u * kKThreads;
+    if (e >= rows) break;
+    const int64_t o = r0 + e;
+    x[o] = cadd(x[o], cadd(cmul(alpha, y[o]), cmul(omega, z[o])));
+    const double2 rn = csub(r[o], cmul(omega, t[o]));
+    r[o] = rn;
+    s0 = cadd(s0, cmulc(rn, rn));
+    s1 = cadd(s1, cmulc(rh[o], rn));
+  }
+  block_pair_sum(s0, s1, red);
+  if (threadIdx.x < 2)
+    part_out[(q * gridDim.x + blockIdx.x) * 2 + threadIdx.x] = pair_total(red);
 }
 
 // x += d for live systems
@@ -641,6 +836,23 @@ size_t pc_bytes(int precond, int nx, int ny, int n_omega) {
 }
 size_t ilu0_apply_lds(int ny) { return (size_t)2 * ny * 2 * sizeof(double2); }
 
+size_t ilu0_col_lds(int G, int threads) { return (size_t)4 * G * threads * sizeof(double2); }
+
+template <int MODE>
+static hipError_t prepare_ilu0_col() {
+  auto lds = [](const void* fn, size_t bytes) {
+    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  };
+  hipError_t e = hipSuccess;
+  for (const void* fn : {(const void*)k_pc_ilu0_apply_col<MODE, false, true, 8>,
+                         (const void*)k_pc_ilu0_apply_col<MODE, false, false, 8>})
+    if (e == hipSuccess) e = lds(fn, ilu0_col_lds(8, 256));
+  for (const void* fn : {(const void*)k_pc_ilu0_apply_col<MODE, false, true, 4>,
+                         (const void*)k_pc_ilu0_apply_col<MODE, false, false, 4>})
+    if (e == hipSuccess) e = lds(fn, ilu0_col_lds(4, kIluColMax));
+  return e;
+}
+
 hipError_t prepare_krylov(int ny) {
   hipError_t e = hipFuncSetAttribute((const void*)k_pc_ilu0,
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -648,9 +860,9 @@ hipError_t prepare_krylov(int ny) {
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void*)k_pc_ilu0_apply,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)ilu0_apply_lds(ny));
-  if (e == hipSuccess && ny <= kIluColMax)
-    e = hipFuncSetAttribute((const void*)k_pc_ilu0_apply_col,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)ilu0_apply_lds(ny));
+  if (e == hipSuccess) e = prepare_ilu0_col<BICG_NONE>();
+  if (e == hipSuccess) e = prepare_ilu0_col<BICG_P>();
+  if (e == hipSuccess) e = prepare_ilu0_col<BICG_S>();
   return e;
 }
 
@@ -666,62 +878,88 @@ hipError_t launch_pc_setup(const OpDesc& op, int precond, const double* omega, i
   return hipGetLastError();
 }
 
+// K^-1 of X (b: X is first updated as MODE says)
+template <int MODE>
+static hipError_t pc_apply_run(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
+                               const double* Dinv, double* X, double* Y, const uint32_t* active,
+                               const uint32_t* skip, const BicgStep& b, hipStream_t s) {
+  const int nn = op.nx * op.ny;
+  const double2* D = (const double2*)Dinv;
+  double2 *x = (double2*)X, *y = (double2*)Y;
+  if (precond == RR_PRECOND_ILU0 && op.ny <= kIluColMax && op.n <= (1 << 26)) {
+    const int threads = (op.ny + 63) / 64 * 64;
+    // G = 8 while its places fit in LDS (128 KiB for 256 threads; 4 for 512)
+    const int G = threads <= 256 ? 8 : 4;
+    auto* kernel = threads == 64
+                       ? (adjoint ? k_pc_ilu0_apply_col<MODE, true, true, 8>
+                                  : k_pc_ilu0_apply_col<MODE, true, false, 8>)
+                   : G == 8 ? (adjoint ? k_pc_ilu0_apply_col<MODE, false, true, 8>
+                                       : k_pc_ilu0_apply_col<MODE, false, false, 8>)
+                            : (adjoint ? k_pc_ilu0_apply_col<MODE, false, true, 4>
+                                       : k_pc_ilu0_apply_col<MODE, false, false, 4>);
+    hipLaunchKernelGGL(kernel, dim3(k, n_omega), dim3(threads), ilu0_col_lds(G, threads), s, op.nx,
+                       op.ny, k, D, x, y, active, skip, b);
+  } else if (precond == RR_PRECOND_ILU0) {
+    if constexpr (MODE != BICG_NONE)
+      hipLaunchKernelGGL(k_bicg_update<MODE>, dim3(krylov_nchunk(op.n), k, n_omega),
+                         dim3(kKThreads), 0, s, op.n, k, x, b);
+    hipLaunchKernelGGL(k_pc_ilu0_apply, dim3(k, n_omega), dim3(kKThreads), ilu0_apply_lds(op.ny),
+                       s, op.nx, op.ny, k, adjoint, D, x, y, active, skip);
+  } else
+    hipLaunchKernelGGL(k_pc_jacobi_apply<MODE>, dim3((nn + 255) / 256, k, n_omega), dim3(256), 0,
+                       s, nn, k, adjoint, D, x, y, active, skip, b);
+  return hipGetLastError();
+}
+
 hipError_t launch_pc_apply(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
                            const double* Dinv, const double* X, double* Y,
                            const uint32_t* active, const uint32_t* skip, hipStream_t s) {
-  const int nn = op.nx * op.ny;
-  if (precond == RR_PRECOND_ILU0 && op.ny <= kIluColMax)
-    hipLaunchKernelGGL(k_pc_ilu0_apply_col, dim3(k, n_omega), dim3((op.ny + 63) / 64 * 64),
-                       ilu0_apply_lds(op.ny), s, op.nx, op.ny, k, adjoint, op.coef,
-                       (const double2*)Dinv, (const double2*)X, (double2*)Y, active, skip);
-  else if (precond == RR_PRECOND_ILU0)
-    hipLaunchKernelGGL(k_pc_ilu0_apply, dim3(k, n_omega), dim3(kKThreads), ilu0_apply_lds(op.ny),
-                       s, op.nx, op.ny, k, adjoint, op.coef, (const double2*)Dinv,
-                       (const double2*)X, (double2*)Y, active, skip);
-  else
-    hipLaunchKernelGGL(k_pc_jacobi_apply, dim3((nn + 255) / 256, k, n_omega), dim3(256), 0, s, nn,
-                       k, adjoint, (const double2*)Dinv, (const double2*)X, (double2*)Y, active,
-                       skip);
+  return pc_apply_run<BICG_NONE>(op, precond, n_omega, k, adjoint, Dinv, (double*)X, Y, active,
+                                 skip, BicgStep{}, s);
+}
+
+hipError_t launch_bicg_p(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
+                         const double* Dinv, double* p, double* y, const BicgStep& b,
+                         hipStream_t s) {
+  return pc_apply_run<BICG_P>(op, precond, n_omega, k, adjoint, Dinv, p, y, b.active, b.conv, b, s);
+}
+hipError_t launch_bicg_s(const OpDesc& op, int precond, int n_omega, int k, int adjoint,
+                         const double* Dinv, double* r, double* z, const BicgStep& b,
+                         hipStream_t s) {
+  return pc_apply_run<BICG_S>(op, precond, n_omega, k, adjoint, Dinv, r, z, b.active, b.conv, b, s);
+}
+hipError_t launch_bicg_xr(int64_t n, int n_omega, int k, const double* y, const double* z,
+                          const double* t, const double* rh, double* x, double* r,
+                          double* part_out, const BicgStep& b, hipStream_t s) {
+  hipLaunchKernelGGL(k_bicg_xr, dim3(krylov_nchunk(n), k, n_omega), dim3(kKThreads), 0, s, n, k,
+                     (const double2*)y, (const double2*)z, (const double2*)t, (const double2*)rh,
+                     (double2*)x, (double2*)r, (double2*)part_out, b.conv, b);
   return hipGetLastError();
 }
 
-hipError_t launch_kdot(int64_t n, int n_omega, int k, int npair, const double* A0,
-                       const double* B0, const double* A1, const double* B1, double* partial,
-                       const uint32_t* active, const uint32_t* skip, hipStream_t s) {
+hipError_t launch_kdot(int64_t n, int n_omega, int k, const double* A, const double* B,
+                       double* partial, const uint32_t* active, const uint32_t* skip,
+                       hipStream_t s) {
   const int nc = krylov_nchunk(n);
-  hipLaunchKernelGGL(k_kdot_partial, dim3(nc, k, n_omega), dim3(kKThreads), 0, s, n, k, npair,
-                     (const double2*)A0, (const double2*)B0, (const double2*)A1,
-                     (const double2*)B1, nc, (double2*)partial, active, skip);
+  hipLaunchKernelGGL(k_kdot_partial, dim3(nc, k, n_omega), dim3(kKThreads), 0, s, n, k,
+                     (const double2*)A, (const double2*)B, nc, (double2*)partial, active, skip);
   return hipGetLastError();
 }
 
-hipError_t launch_bicg_scalars(int N, int64_t n, int mode, int it, double tol, const double* partial,
-                               double* ks, double* bnorm2, uint32_t* active, uint32_t* conv,
-                               uint32_t* status, const uint32_t* skip, hipStream_t s) {
-  hipLaunchKernelGGL(k_bicg_scalars, dim3(1), dim3(kKThreads), 0, s, N, krylov_nchunk(n), mode,
-                     it, tol * tol, (const double2*)partial, (double2*)ks, bnorm2, active, conv,
+hipError_t launch_krylov_scalars(int N, int64_t n, int mode, double tol, const double* partial,
+                                 double* ks, double* bnorm2, uint32_t* active, uint32_t* live,
+                                 uint32_t* conv, uint32_t* status, const uint32_t* skip,
+                                 hipStream_t s) {
+  hipLaunchKernelGGL(k_krylov_scalars, dim3(1), dim3(kKThreads), 0, s, N, krylov_nchunk(n), mode,
+                     tol * tol, (const double2*)partial, (double2*)ks, bnorm2, active, live, conv,
                      status, skip);
   return hipGetLastError();
 }
 
-hipError_t launch_bicg_vec(int which, int64_t n, int n_omega, int k, const double* ks,
-                           const double* a, const double* b, const double* c, double* x,
-                           double* y, const uint32_t* active, const uint32_t* skip,
-                           hipStream_t s) {
-  dim3 grid((unsigned)((n + 255) / 256), k, n_omega);
-  if (which == 0)  // p = r + beta (p - omega v): a = r, b = v, y = p
-    hipLaunchKernelGGL(k_bicg_p, grid, dim3(256), 0, s, n, k, (const double2*)ks,
-                       (const double2*)a, (const double2*)b, (double2*)y, active, skip);
-  else if (which == 1)  // r -= alpha v: b = v, y = r
-    hipLaunchKernelGGL(k_bicg_s, grid, dim3(256), 0, s, n, k, (const double2*)ks,
-                       (const double2*)b, (double2*)y, active, skip);
-  else if (which == 2)  // x += alpha a + omega b, y(r) -= omega c
-    hipLaunchKernelGGL(k_bicg_xr, grid, dim3(256), 0, s, n, k, (const double2*)ks,
-                       (const double2*)a, (const double2*)b, (const double2*)c, (double2*)x,
-                       (double2*)y, active, skip);
-  else  // x += a
-    hipLaunchKernelGGL(k_kaxpy, grid, dim3(256), 0, s, n, k, (const double2*)a, (double2*)x,
-                       active, skip);
+hipError_t launch_kaxpy(int64_t n, int n_omega, int k, const double* d, double* x,
+                        const uint32_t* active, const uint32_t* skip, hipStream_t s) {
+  hipLaunchKernelGGL(k_kaxpy, dim3((unsigned)((n + 255) / 256), k, n_omega), dim3(256), 0, s, n, k,
+                     (const double2*)d, (double2*)x, active, skip);
   return hipGetLastError();
 }
 

@@ -72,14 +72,17 @@ hipError_t launch_burgers_coeffs(int nx, int ny, const double* U, double hx, dou
 // one XCD (workgroups are dealt to the eight in turn), whose L2 then serves
 // the lines that two strips share.  At n = 262144, 16 shifts, 20 columns: 0.85
 // ms with one thread per node and no strips, 0.54 ms now (2.7 GB).
+// DOTS: instead of Bm, D whose dot products with Y are taken on the way, one
+// pair of partial sums per workgroup and column: 1 <D, Y>, 2 <Y, D> and <Y, Y>.
 constexpr int kApplyLines = 4;
-template <typename OUT>
+template <typename OUT, int DOTS>
 __global__ __launch_bounds__(256) void k_apply(int nx, int ny, const double* __restrict__ coef,
                                                const double* __restrict__ omega, int k,
                                                int group, int chunks, int adjoint,
                                                const double2* __restrict__ X,
                                                const double2* __restrict__ Bm, int64_t bstride,
-                                               cplx<OUT>* __restrict__ Y, const uint32_t* skip) {
+                                               cplx<OUT>* __restrict__ Y, const uint32_t* skip,
+                                               double2* __restrict__ partial) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   constexpr int L = kApplyLines;
   const int chunk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
@@ -123,6 +126,7 @@ __global__ __launch_bounds__(256) void k_apply(int nx, int ny, const double* __r
   for (int col = blockIdx.z * group; col < j1; col++) {
     const int64_t off = ((int64_t)w * k + col) * n;
     const double2* x = X + off;
+    double2 s0 = make_double2(0, 0), s1 = make_double2(0, 0);
     const double2* bb = Bm ? Bm + (int64_t)w * bstride + (int64_t)col * n : nullptr;
     double2 v[L + 2], xn[L], xs[L], b[L];
 #pragma unroll
@@ -149,29 +153,63 @@ __global__ __launch_bounds__(256) void k_apply(int nx, int ny, const double* __r
       li += sv[t] * xs[t].y;
       double mr = sr * xc.x - si * xc.y - lr;
       double mi = sr * xc.y + si * xc.x - li;
-      if (bb) {
+      if (DOTS == 0 && bb) {
         mr = b[t].x - mr;
         mi = b[t].y - mi;
       }
-      if (live && i0 + t < nx) Y[off + at[t + 1]] = cplx<OUT>{(OUT)mr, (OUT)mi};
+      if (live && i0 + t < nx) {
+        Y[off + at[t + 1]] = cplx<OUT>{(OUT)mr, (OUT)mi};
+        if (DOTS) {
+          const double im = b[t].x * mi - b[t].y * mr;
+          s0.x += b[t].x * mr + b[t].y * mi;
+          s0.y += DOTS == 1 ? im : -im;
+          s1.x += mr * mr + mi * mi;
+        }
+      }
+    }
+    if (DOTS) {
+      for (int o = 32; o > 0; o >>= 1) {
+        s0.x += __shfl_down(s0.x, o, 64);
+        s0.y += __shfl_down(s0.y, o, 64);
+        s1.x += __shfl_down(s1.x, o, 64);
+      }
+      __shared__ double2 red[2][4];
+      __syncthreads();  // the column before has been read
+      if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = s0;
+        red[1][threadIdx.x >> 6] = s1;
+      }
+      __syncthreads();
+      if (threadIdx.x < 2) {
+        double2 sum = make_double2(0, 0);
+        for (int u = 0; u < 4; u++) {
+          sum.x += red[threadIdx.x][u].x;
+          sum.y += red[threadIdx.x][u].y;
+        }
+        partial[(((int64_t)w * k + col) * chunks + chunk) * 2 + threadIdx.x] = sum;
+      }
     }
   }
 }
 
-template <typename OUT>
+int apply_chunks(int nx, int ny) {
+  const int64_t items = (int64_t)((nx + kApplyLines - 1) / kApplyLines) * 2 * ny;
+  return (int)((items + 255) / 256);
+}
+
+template <typename OUT, int DOTS = 0>
 static hipError_t apply_run(const OpDesc& op, const double* omega, int n_omega, int k, int adjoint,
                             const double* X, const double* Bm, int64_t bstride, cplx<OUT>* Y,
-                            hipStream_t s, const uint32_t* skip) {
-  const int64_t items = (int64_t)((op.nx + kApplyLines - 1) / kApplyLines) * 2 * op.ny;
-  const int chunks = (int)((items + 255) / 256);
+                            hipStream_t s, const uint32_t* skip, double* partial = nullptr) {
+  const int chunks = apply_chunks(op.nx, op.ny);
   // columns in groups where the chunks alone leave the GPU idle (8 workgroups
   // a CU), two columns at least: each group reads the stencil again
   const int64_t wgs = (int64_t)chunks * n_omega;
   const int groups = (int)std::min<int64_t>((k + 1) / 2, std::max<int64_t>(1, 2048 / wgs));
   const int group = (k + groups - 1) / groups;
-  hipLaunchKernelGGL((k_apply<OUT>), dim3((chunks + 7) / 8 * 8, n_omega, (k + group - 1) / group),
+  hipLaunchKernelGGL((k_apply<OUT, DOTS>), dim3((chunks + 7) / 8 * 8, n_omega, (k + group - 1) / group),
                      dim3(256), 0, s, op.nx, op.ny, op.coef, omega, k, group, chunks, adjoint,
-                     (const double2*)X, (const double2*)Bm, bstride, Y, skip);
+                     (const double2*)X, (const double2*)Bm, bstride, Y, skip, (double2*)partial);
   return hipGetLastError();
 }
 
@@ -179,6 +217,13 @@ hipError_t launch_apply(const OpDesc& op, const double* omega, int n_omega, int 
                         const double* X, const double* Bm, int64_t bstride, double* Y,
                         hipStream_t s, const uint32_t* skip) {
   return apply_run(op, omega, n_omega, k, adjoint, X, Bm, bstride, (cplx<double>*)Y, s, skip);
+}
+hipError_t launch_apply_dots(const OpDesc& op, const double* omega, int n_omega, int k, int adjoint,
+                             const double* X, double* Y, const double* D, bool norm,
+                             double* partial, hipStream_t s, const uint32_t* skip) {
+  auto* run = norm ? apply_run<double, 2> : apply_run<double, 1>;
+  return run(op, omega, n_omega, k, adjoint, X, D, (int64_t)k * op.n, (cplx<double>*)Y, s, skip,
+             partial);
 }
 hipError_t launch_residual32(const OpDesc& op, const double* omega, int n_omega, int k, int adjoint,
                              const double* X, const double* Bm, int64_t bstride, float* Y,

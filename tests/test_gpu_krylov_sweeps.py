@@ -1,0 +1,71 @@
+"""The ILU(0) sweeps and the fused BiCGStab steps at the edges of their kernels:
+one wave or several to a grid line, groups of 8 or 4 neighbours, lines that fill
+neither, and lines past the column kernel's."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import operator as op
+from oracle import precond as opc
+from tests.gpu_util import oracle_problem, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def rr():
+    import paper_1902_01458_amd as m
+    return m
+
+
+def rand_block(shape, seed):
+    rng = np.random.Generator(np.random.PCG64(seed))
+    return rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+
+
+SHAPES = [(9, 7), (2, 64), (5, 65), (2, 250), (3, 257), (2, 512), (2, 513)]
+
+
+@pytest.mark.parametrize("nx,ny", SHAPES)
+def test_ilu0_sweeps_match_oracle(nx, ny):
+    w = W.small("kps", nx, ny, nu=2e-2)
+    U, coef, L, phi, hx, hy = oracle_problem(w)
+    prob = rr().BurgersProblem.from_workload(w)
+    oms = [1.3 + 0.1j]
+    f = rr().factor(prob, oms, "fp64", k_max=2, solver="bicgstab", precond="ilu0")
+    X = rand_block((1, 2, w.n), 6)
+    M = op.shifted(L, oms[0]).toarray()
+    K = opc.block_ilu0(M, opc.stencil_pattern(nx, ny))
+    for adjoint in (False, True):
+        Y = to_np(f.precond_apply(torch.tensor(X, device="cuda"), adjoint=adjoint))
+        ref = opc.apply_inverse(K, X[0].T, adjoint=adjoint).T
+        np.testing.assert_allclose(Y[0], ref, rtol=0, atol=1e-12 * np.abs(ref).max())
+    f.check()
+    f.free()
+
+
+# BiCGStab ends at ||b - M x|| <= 1e-11 ||b||; the error beside the exact
+# solution is that times ||M^-1|| ||b|| / ||x||, measured here from the residual
+# itself: 1e-10 leaves a factor of ten to the recurrence's residual.
+@pytest.mark.parametrize("nx,ny,precond", [(16, 64, "ilu0"), (9, 65, "ilu0"), (5, 257, "ilu0"),
+                                           (4, 513, "ilu0"), (11, 70, "jacobi")])
+@pytest.mark.parametrize("adjoint", [False, True])
+def test_bicgstab_residual(nx, ny, precond, adjoint):
+    w = W.small("kpb", nx, ny, nu=2e-2)
+    U, coef, L, phi, hx, hy = oracle_problem(w)
+    prob = rr().BurgersProblem.from_workload(w)
+    oms = [1.3 + 0.1j, 2.1 + 0.2j]
+    f = rr().factor(prob, oms, "fp64", k_max=3, solver="bicgstab", precond=precond,
+                    krylov_maxit=3000, krylov_tol=1e-11)
+    B = rand_block((2, 3, w.n), 7)
+    B[1, 2] = 0  # a system that has ended before the first iteration
+    Bt = torch.tensor(B, device="cuda")
+    X = to_np(f.adjoint_solve(Bt) if adjoint else f.solve(Bt))
+    f.check()
+    for i, om in enumerate(oms):
+        M = op.shifted(L, om)
+        M = M.conj().T if adjoint else M
+        R = B[i].T - M @ X[i].T
+        assert (np.linalg.norm(R, axis=0) <= 1e-10 * np.linalg.norm(B[i].T, axis=0)).all()
+    assert (X[1, 2] == 0).all()
+    f.free()
