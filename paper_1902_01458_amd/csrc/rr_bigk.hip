@@ -158,10 +158,8 @@ __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2
             s.x -= p.x;
             s.y -= p.y;
           }
-        for (int o = 1; o < 8; o <<= 1) {
-          s.x += __shfl_xor(s.x, o, 8);
-          s.y += __shfl_xor(s.y, o, 8);
-        }
+        s.x = sum8(s.x);
+        s.y = sum8(s.y);
         if (c < kBT && sub == 0) {
           if (a == c) s.x += 1.0;
           const double q = S0[a][a].x;
@@ -317,7 +315,9 @@ __global__ __launch_bounds__(256) void k_applyb(int64_t n, int k, const double2*
 // pair, so that a round of up to 64 pairs runs at once.  The rotation is the
 // narrow path's: with gamma = a_p^H a_q and e = gamma / |gamma|, the columns
 // [a_p, conj(e) a_q] are rotated by the real Jacobi angle of [[alpha,
-// |gamma|], [|gamma|, beta]].  Then sigma_c = ||a_c||, sorted descending
+// |gamma|], [|gamma|, beta]].  The columns start in descending order of their
+// norms, a rotation's larger column staying in front (8 sweeps against 10 where
+// the iteration has already sorted the spectrum).  Then sigma_c = ||a_c||, sorted descending
 // (ranks counted in parallel), Ut = A diag(1/sigma), W = J, both permuted;
 // Rinv W is formed by k_sgemm.
 //
@@ -329,13 +329,20 @@ __global__ __launch_bounds__(256) void k_applyb(int64_t n, int k, const double2*
 // than the rotations.  Beyond m = 100 A is in global scratch too (column c
 // contiguous) and one workgroup does everything.  At k = 100: 11.4 ms with A
 // in global scratch and a wave per pair, 5.1 ms with all of J in one
-// workgroup, 3.6 ms now.
+// workgroup, 3.85 with the sums by shuffles and the columns unsorted, 2.97 ms
+// now.
 constexpr int kJacobiLds = 100;  // largest m whose A fits the CU's LDS
 constexpr int kJacobiEl = (kJacobiLds + 15) / 16;
 constexpr int kJacobiParts = (kJacobiLds + 15) / 16;
-__device__ __forceinline__ double sum16(double v) {
-  for (int o = 1; o < 16; o <<= 1) v += __shfl_xor(v, o, 16);
-  return v;
+// The place of v[c] in the descending order (stable, NaNs first), each place once
+__device__ __forceinline__ int descending_rank(const double* v, int n, int c) {
+  int r = 0;
+  const bool cn = isnan(v[c]);
+  for (int d = 0; d < n; d++) {
+    const bool dn = isnan(v[d]);
+    r += (dn && !cn) || v[d] > v[c] || ((v[d] == v[c] || (dn && cn)) && d < c);
+  }
+  return r;
 }
 template <bool LDS>
 __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const double2* R, double2* A,
@@ -354,18 +361,34 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
   double2* Jw = Jm + (int64_t)w * m * m;
   double* svw = sv + (int64_t)w * m;
   int* rk = rank + (int64_t)w * m;
+  // every part has the same norms and ranks, in scratch of its own
+  svw += (int64_t)part * gridDim.x * m;
+  rk += (int64_t)part * gridDim.x * m;
+  const int group = threadIdx.x >> 4, lane = threadIdx.x & 15, ngroup = blockDim.x >> 4;
+  for (int c = group; c < m; c += ngroup) {
+    double s = 0;
+    for (int a = lane; a < k && c < k; a += 16) {
+      const double2 v = Rw[(int64_t)c * k + a];
+      s += v.x * v.x + v.y * v.y;
+    }
+    s = sum16(s);
+    if (lane == 0) svw[c] = c < k ? s : -1.0;  // the zero column comes last
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < m; c += blockDim.x) rk[c] = descending_rank(svw, m, c);
+  __syncthreads();
   for (int64_t e = threadIdx.x; e < (int64_t)m * m; e += blockDim.x) {
     const int c = (int)(e / m), a = (int)(e % m);  // column c, row a
+    const int64_t to = (int64_t)rk[c] * m + a;
     double2 v = make_double2(0, 0);
     if (a < k && c < k) {
       const double2 rc = Rw[(int64_t)c * k + a];  // A[a][c] = conj(R[c][a])
       v = make_double2(rc.x, -rc.y);
     }
-    Aw[e] = v;
-    if (a >= j0 && a < j1) Jw[e] = make_double2(a == c ? 1.0 : 0.0, 0.0);
+    Aw[to] = v;
+    if (a >= j0 && a < j1) Jw[to] = make_double2(a == c ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
-  const int group = threadIdx.x >> 4, lane = threadIdx.x & 15, ngroup = blockDim.x >> 4;
   const int npair = m / 2;
   int sweep = 0;
   for (; sweep < max_sweeps; sweep++) {
@@ -456,9 +479,6 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
     __syncthreads();
   }
   if (threadIdx.x == 0 && rotated && part == 0) latch(status, ST_SVD_NOT_CONVERGED);
-  // every part has the same norms and ranks, in scratch of its own
-  svw += (int64_t)part * gridDim.x * m;
-  rk += (int64_t)part * gridDim.x * m;
   for (int c = threadIdx.x; c < k; c += blockDim.x) {
     double s = 0;
     for (int a = 0; a < k; a++) {
@@ -469,11 +489,7 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
     if (!isfinite(svw[c])) latch(status, ST_NONFINITE);
   }
   __syncthreads();
-  for (int c = threadIdx.x; c < k; c += blockDim.x) {  // stable descending rank
-    int r = 0;
-    for (int d = 0; d < k; d++) r += (svw[d] > svw[c]) || (svw[d] == svw[c] && d < c);
-    rk[c] = r;
-  }
+  for (int c = threadIdx.x; c < k; c += blockDim.x) rk[c] = descending_rank(svw, k, c);
   __syncthreads();
   for (int64_t e = threadIdx.x; e < (int64_t)k * k; e += blockDim.x) {
     const int src = (int)(e / k), a = (int)(e % k);  // source column, row

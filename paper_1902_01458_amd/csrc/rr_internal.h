@@ -47,6 +47,29 @@ __device__ __forceinline__ double recip_newton(double x) {
   return fma(fma(-x, r, 1.0), r, r);
 }
 
+// The sum over a group of 8 or 16 lanes (aligned, all active), in every lane:
+// by lane moves within a row of 16, which take no turn in the LDS pipe that
+// shuffles share with the kernels' own data.
+template <int CTL>
+__device__ __forceinline__ double row_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double sum8(double v) {
+  v += row_move<0x141>(v);  // row_half_mirror: lane 7 - l
+  v += row_move<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  v += row_move<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  return v;
+}
+__device__ __forceinline__ double sum16(double v) {
+  v += row_move<0x128>(v);  // row_ror 8, 4, 2, 1
+  v += row_move<0x124>(v);
+  v += row_move<0x122>(v);
+  v += row_move<0x121>(v);
+  return v;
+}
+
 // The Jacobi rotation of two columns with Gram matrix [[al, g e], [., be]],
 // g e = gr + i gi: false when it is below the threshold |gr + i gi| <= 1e-15
 // sqrt(al be).  er + i ei = conj(e); the columns [x, (er + i ei) y] are rotated

@@ -280,10 +280,8 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
           s.x -= p.x;
           s.y -= p.y;
         }
-      for (int o = 1; o < 8; o <<= 1) {
-        s.x += __shfl_xor(s.x, o, 8);
-        s.y += __shfl_xor(s.y, o, 8);
-      }
+      s.x = sum8(s.x);
+      s.y = sum8(s.y);
       if (c < k && sub == 0) {
         if (a == c) s.x += 1.0;
         const double d = G[a][a].x;
@@ -479,12 +477,10 @@ __global__ __launch_bounds__(256) void k_jacobi_svd(int k, int kmax, const doubl
           gr += x.x * y.x + x.y * y.y;  // conj(x) y
           gi += x.x * y.y - x.y * y.x;
         }
-        for (int o = 1; o < 8; o <<= 1) {
-          al += __shfl_xor(al, o, 8);
-          be += __shfl_xor(be, o, 8);
-          gr += __shfl_xor(gr, o, 8);
-          gi += __shfl_xor(gi, o, 8);
-        }
+        al = sum8(al);
+        be = sum8(be);
+        gr = sum8(gr);
+        gi = sum8(gi);
         double er, ei, c, sn;
         if (jacobi_angle(al, be, gr, gi, er, ei, c, sn)) {  // rotate [a_p, e^{-i phi} a_q]
           for (int a = sub; a < m; a += 8) {
