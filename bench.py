@@ -3,7 +3,7 @@
 Workload: the 512 x 256 linearised Burgers operator (n = 262144, half-bandwidth
 512) swept over 16 shifts omega_i = 2^((i-6)/3) (0.25 .. 8, holding 2.0), sketch
 width k = 20, one subspace iteration, Phi-weighted complex Gaussian test matrix,
-seed 0.  One step = the whole path for the batch: 16 band factorisations, the
+seed 0.  One step = the whole path for the batch: 16 factorisations, the
 sketch, the forward / adjoint / subspace-iteration solves (with FP64-residual
 refinement in the mixed path), every Cholesky QR, the k x k SVDs, V and the
 response recovery of eq. (9).  Inputs (U, coefficients, Phi) are resident on the
@@ -237,6 +237,31 @@ TRAFFIC = os.path.join(ROOT, "profiles", "pmc_traffic.json")
 CSRC = os.path.join(ROOT, "paper_1902_01458_amd", "csrc")
 
 
+def nd_work(nx, ny):
+    """(real flops of the dissection's factorisation, complex factor entries read
+    by one solve) per shift: a front of p unknowns with a border of q takes the
+    inverse of its p x p block and the products with the p x q and q x p ones,
+    and a solve reads all three once (a leaf's border couplings are one stencil
+    coefficient each)."""
+    import ctypes
+
+    from paper_1902_01458_amd._lib import lib as load
+    lib = load()
+    count = lib.rr_nd_plan(nx, ny, 0, None, 0)
+    out = (ctypes.c_int64 * count)()
+    lib.rr_nd_plan(nx, ny, 0, out, count)
+    flops = entries = 0
+    for i in range(0, count, 17):
+        p, q, leaf = out[i], out[i + 1], out[i + 6] < 0
+        if leaf:
+            flops += 8 * p ** 3
+            entries += p * p
+        else:
+            flops += 8 * (p ** 3 + p * p * q + p * q * q)
+            entries += p * p + 2 * p * q
+    return float(flops), entries
+
+
 def traffic(kernel):
     """HBM bytes per launch of `kernel` from the calibrated FETCH_SIZE / WRITE_SIZE
     counters recorded in profiles/pmc_traffic.json, or None when none were taken
@@ -329,7 +354,14 @@ def main():
         else None
     b = 2 * w.ny
     n_om = len(w.omegas)
-    flops = 8.0 * w.n * b * b * n_om  # algorithmic band-LU flops per launch (all shifts)
+
+    def lu_work(res):
+        """(real flops of one factorisation, complex factor entries that one solve
+        reads, name) of the LU that a path was tuned to, all shifts."""
+        if res["tune"].get("superblock"):  # the band LU
+            return 8.0 * w.n * b * b * n_om, w.n * (2 * b + 1) * n_om, "band LU"
+        flops, entries = nd_work(w.nx, w.ny)
+        return flops * n_om, entries * n_om, "nested-dissection LU"
     auto = not args.no_autotune
     mixed = run_path(prob, w, "mixed", args.steps, args.warmup, args.tile, args.refine_iters,
                      auto, args.graph_reps, args.refine_tol)
@@ -342,13 +374,15 @@ def main():
         print(f"# fp64: {fp64['ms_per_step']:.1f} ms/step {fp64['calls_ms']}, tune "
               f"{fp64['tune']}", file=sys.stderr, flush=True)
     value = n_om / (mixed["ms_per_step"] * 1e-3)
+    flops, _, lu = lu_work(mixed)
     ach = flops / (mixed["factor_ms"] * 1e-3) / 1e12
-    fk = f"k_factor<float,{mixed['tune']['tile']}>"
-    # algorithmic bytes of one solve launch: the factor once (n (2b+1) entries
-    # per shift, FP32 or FP64), the right-hand sides in and the solutions out
-    # (FP64 complex, the caller's blocks)
+    band = lu == "band LU"
+    fk = (f"k_factor<float,{mixed['tune']['tile']}>" if band else "k_nd_*<float>")
+    # algorithmic bytes of one solve: the factor once (its entries in FP32 or
+    # FP64), the right-hand sides in and the solutions out (FP64 complex, the
+    # caller's blocks)
     def solve_roofline(res, esize, name):
-        byt = n_om * (w.n * (2 * b + 1) * esize + 2 * w.k * w.n * 16)
+        byt = lu_work(res)[1] * esize + n_om * 2 * w.k * w.n * 16
         bw = byt / (res["solve_ms"] * 1e-3) / 1e9
         np_ = 16 * ((w.k + 15) // 16)
         T = res["tune"]["tile"]
@@ -357,12 +391,13 @@ def main():
         # of the k columns
         short = (b + T - 1) // T <= 8
         tail = short and w.k - (np_ - 16) <= 8
-        kname = (f"k_solve2<{name},{T},16,false>" if (res["tune"].get("superblock") or 0) < 0
-                 else f"k_ssolve<{name},{T},{np_},false,{str(short).lower()},{str(tail).lower()}>")
+        sb = res["tune"].get("superblock") or 0
+        kname = (f"k_nd_*<{name}>" if sb == 0 else
+                 f"k_solve2<{name},{T},16,false>" if sb < 0 else f"k_ssolve<{name},{T},{np_},false,{str(short).lower()},{str(tail).lower()}>")
         return {"bound": "hbm", "achieved": bw, "peak": 8000.0, "unit": "GB/s",
                 "frac": bw / 8000.0, "bytes_per_launch": byt, "traffic": traffic(kname),
                 "kernel": f"{kname} (forward solve of the eq. 9 recovery, all {n_om} shifts x "
-                          f"{w.k} columns, one launch)",
+                          f"{w.k} columns)",
                 "launch_ms": res["solve_ms"]}
     line = {
         "metric": METRIC, "value": value, "unit": "ω-solves/s", "n_gpus": 1,
@@ -383,12 +418,12 @@ def main():
         "graph_ms_per_step": mixed.get("graph_ms_per_step"),
         "roofline": {"bound": "mfma", "achieved": ach, "peak": PEAK["mixed"], "unit": "TFLOP/s",
                      "frac": ach / PEAK["mixed"], "traffic": traffic(fk),
-                     "kernel": f"{fk} (band LU of all {n_om} shifts, one launch)",
+                     "kernel": f"{fk} ({lu} of all {n_om} shifts)",
                      "launch_ms": mixed["factor_ms"]},
         "roofline_solve_fp32": solve_roofline(mixed, 8, "float"),
     }
     if fp64 is not None:
-        a64 = flops / (fp64["factor_ms"] * 1e-3) / 1e12
+        a64 = lu_work(fp64)[0] / (fp64["factor_ms"] * 1e-3) / 1e12
         line["fp64"] = {"value": n_om / (fp64["ms_per_step"] * 1e-3),
                         "ms_per_step": fp64["ms_per_step"], "calls_ms": fp64["calls_ms"],
                         "optional_svd_ms": fp64["optional_svd_ms"],

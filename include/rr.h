@@ -70,7 +70,7 @@ extern "C" {
 typedef enum {
   RR_OK = 0,
   RR_ERR_INVALID = 1,        /* bad argument (size, pointer, option)          */
-  RR_ERR_SINGULAR = 2,       /* zero or non-finite pivot in the band LU       */
+  RR_ERR_SINGULAR = 2,       /* zero or non-finite pivot in the LU            */
   RR_ERR_NOT_CONVERGED = 3,  /* mixed-precision refinement missed tolerance   */
   RR_ERR_BREAKDOWN = 4,      /* Gram matrix not positive definite (CholQR)    */
   RR_ERR_NONFINITE = 5,      /* NaN/Inf in inputs or results                  */

@@ -117,7 +117,7 @@ class BurgersProblem:
 
 
 class Factors:
-    """One band LU per shift (M(omega) = i omega I - L), owned by the library.
+    """One LU per shift (M(omega) = i omega I - L), owned by the library.
     With discount = beta > 0 the shifts become omega - i beta: the discounted
     resolvent of Section 2.1, the growth rates of L lowered by beta (the
     paper's complex frequency omega + i beta in its e^{-i omega t} convention).

@@ -830,7 +830,7 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     f->has_burgers = true;
   }
   {
-    hipError_t e = krylov ? prepare_krylov(p->ny)
+    hipError_t e = krylov ? prepare_krylov(f->precond, p->ny)
                    : f->nd ? nd_prepare()
                            : prepare_factor(T, prec == RR_MIXED);
     if (e == hipSuccess && !krylov && !f->nd) e = prepare_solve(T, prec == RR_MIXED);

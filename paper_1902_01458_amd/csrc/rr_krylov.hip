@@ -1,7 +1,7 @@
 // LU-free solves of the shifted systems M(omega) X = B and M^H X = B: the
 // paper notes (Section 3.2, after Fig. 7) that BiCGStab or GMRES with an
 // incomplete-LU or Jacobi preconditioner can stand in for the direct solves;
-// that is what lets Algorithm 1 run where the band LU no longer fits in
+// that is what lets Algorithm 1 run where the LU no longer fits in
 // memory.  Everything here is FP64 and batched: every (shift, column) pair is
 // its own linear system, M is applied from the stencil (k_apply).
 //
@@ -838,31 +838,36 @@ size_t ilu0_apply_lds(int ny) { return (size_t)2 * ny * 2 * sizeof(double2); }
 
 size_t ilu0_col_lds(int G, int threads) { return (size_t)4 * G * threads * sizeof(double2); }
 
-template <int MODE>
-static hipError_t prepare_ilu0_col() {
-  auto lds = [](const void* fn, size_t bytes) {
-    return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  };
+template <int MODE, int G>
+static hipError_t prepare_ilu0_col(int threads) {
   hipError_t e = hipSuccess;
-  for (const void* fn : {(const void*)k_pc_ilu0_apply_col<MODE, false, true, 8>,
-                         (const void*)k_pc_ilu0_apply_col<MODE, false, false, 8>})
-    if (e == hipSuccess) e = lds(fn, ilu0_col_lds(8, 256));
-  for (const void* fn : {(const void*)k_pc_ilu0_apply_col<MODE, false, true, 4>,
-                         (const void*)k_pc_ilu0_apply_col<MODE, false, false, 4>})
-    if (e == hipSuccess) e = lds(fn, ilu0_col_lds(4, kIluColMax));
+  for (const void* fn : {(const void*)k_pc_ilu0_apply_col<MODE, false, true, G>,
+                         (const void*)k_pc_ilu0_apply_col<MODE, false, false, G>})
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)ilu0_col_lds(G, threads));
+  return e;
+}
+template <int G>
+static hipError_t prepare_ilu0_cols(int threads) {
+  hipError_t e = prepare_ilu0_col<BICG_NONE, G>(threads);
+  if (e == hipSuccess) e = prepare_ilu0_col<BICG_P, G>(threads);
+  if (e == hipSuccess) e = prepare_ilu0_col<BICG_S, G>(threads);
   return e;
 }
 
-hipError_t prepare_krylov(int ny) {
+// Allows the LDS that this grid's kernels ask for beyond the default: a kernel's
+// first mention loads it, about 0.2 ms each, so only those.
+hipError_t prepare_krylov(int precond, int ny) {
+  if (precond != RR_PRECOND_ILU0) return hipSuccess;
   hipError_t e = hipFuncSetAttribute((const void*)k_pc_ilu0,
                                      hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)ilu0_lds(ny));
   if (e == hipSuccess)
     e = hipFuncSetAttribute((const void*)k_pc_ilu0_apply,
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)ilu0_apply_lds(ny));
-  if (e == hipSuccess) e = prepare_ilu0_col<BICG_NONE>();
-  if (e == hipSuccess) e = prepare_ilu0_col<BICG_P>();
-  if (e == hipSuccess) e = prepare_ilu0_col<BICG_S>();
+  if (e == hipSuccess && ny > 64 && ny <= 256) e = prepare_ilu0_cols<8>(256);
+  if (e == hipSuccess && ny > 256 && ny <= kIluColMax) e = prepare_ilu0_cols<4>(kIluColMax);
   return e;
 }
 
