@@ -56,7 +56,7 @@ rr_free_fn g_dealloc = nullptr;
 void* g_alloc_ctx = nullptr;
 
 // Blocks of freed handles (default allocator, 1 MiB and more), kept for the
-// next handle.  Freshly mapped device memory has to be cleared by the driver:
+// next handle.  Freshly mapped device memory is cleared before its first use:
 // a program that makes and frees a 23 GB handle per sweep of 64 shifts at 256
 // x 128 spent 600 ms a sweep waiting for that once the card's cleared memory
 // was used up, against 56 ms of work.  Bounded at 1/32 of the device's memory

@@ -18,7 +18,7 @@
 // shifted CholeskyQR3).
 #include <algorithm>
 
-#include "rr_internal.h"
+#include "rr_mfma.h"
 
 namespace rr {
 
@@ -92,6 +92,37 @@ __global__ void k_gramb_reduce(int k, int nchunk, const double2* part, int64_t s
   G[w * sG + idx] = up ? s : make_double2(s.x, -s.y);
 }
 
+// A 32 x 32 complex product of blocks in LDS on the FP64 matrix cores: waves 0
+// to 7 of the workgroup take a 16 x 16 tile's real or imaginary part each (the
+// others wait).  CT: X^H Y, else X Y.
+typedef Mf<double>::v4 BlockAcc;
+typedef double2 Block[kBT][kBT + 1];
+template <bool CT>
+__device__ __forceinline__ void block_mul(BlockAcc& acc, const Block& X, const Block& Y) {
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
+  if (wave >= 8) return;
+  const bool im = wave & 1;
+  const int r0 = 16 * (wave >> 2), c0 = 16 * ((wave >> 1) & 1);
+#pragma unroll
+  for (int s = 0; s < kBT / 4; s++) {
+    const int kk = 4 * s + g;
+    const double2 x = CT ? X[kk][r0 + i] : X[r0 + i][kk], y = Y[kk][c0 + i];
+    acc = Mf<double>::op(x.x, im ? y.y : y.x, acc);
+    acc = Mf<double>::op(im != CT ? x.y : -x.y, im ? y.x : y.y, acc);
+  }
+}
+__device__ __forceinline__ void block_store(const BlockAcc& acc, Block& Z) {
+  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
+  if (wave >= 8) return;
+  const int r0 = 16 * (wave >> 2), c = 16 * ((wave >> 1) & 1) + (l & 15);
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    double2& z = Z[r0 + Mf<double>::row(l, e)][c];
+    if (wave & 1) z.y = acc[e];
+    else z.x = acc[e];
+  }
+}
+
 // G = R^H R (R upper, real positive diagonal) and R^-1, one workgroup per
 // shift, in 32 x 32 blocks: a diagonal block is factored and inverted in LDS
 // (one barrier per step, as in the narrow path), its block row multiplied by
@@ -99,11 +130,13 @@ __global__ void k_gramb_reduce(int k, int nchunk, const double2* part, int64_t s
 // with the diagonal inverses.  A thread holds one element of a block.  The
 // chain is k short steps in LDS and (k / 32)^3 / 3 block products, where the
 // unblocked form took k steps through global memory and one thread per column
-// of R^-1: 957 us at k = 100.  A pivot that is not positive latches
+// of R^-1: 957 us at k = 100; 211 with the products by one thread an element,
+// which wait for LDS, and a barrier for
+// each step of the inverses, 154 now.  A pivot that is not positive latches
 // ST_BREAKDOWN and is taken as 1 (the results stay finite).
 __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2* G, double2* R,
                                                 double2* Rinv, uint32_t* status) {
-  __shared__ double2 S0[kBT][kBT + 1], S1[kBT][kBT + 1], S2[kBT][kBT + 1];
+  __shared__ Block S0, S1, S2;
   const int w = blockIdx.x, t = threadIdx.x, ti = t >> 5, tj = t & 31;
   const int nt = (k + kBT - 1) / kBT;
   const double2* Gw = G + w * sM;
@@ -148,37 +181,18 @@ __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2
     S0[ti][tj] = v;
     put(Rw, j0 + ti, j0 + tj, v);
     __syncthreads();
-    {  // S1 = S0^-1 from the last row up, eight threads per column
-      const int c = t >> 3, sub = t & 7;
-      for (int a = kBT - 1; a >= 0; a--) {
-        double2 s = none;
-        if (c < kBT)
-          for (int x = a + 1 + sub; x <= c; x += 8) {
-            const double2 p = bmul(S0[a][x], S1[x][c]);
-            s.x -= p.x;
-            s.y -= p.y;
-          }
-        s.x = sum8(s.x);
-        s.y = sum8(s.y);
-        if (c < kBT && sub == 0) {
-          if (a == c) s.x += 1.0;
-          const double q = S0[a][a].x;
-          S1[a][c] = c >= a ? make_double2(s.x / q, s.y / q) : none;
-        }
-        __syncthreads();
-      }
-    }
+    invert_upper(S0, S1, kBT);
+    __syncthreads();
     put(Xw, j0 + ti, j0 + tj, S1[ti][tj]);
     for (int C = J + 1; C < nt; C++) {  // block row J: R_JC = S1^H G_JC
       S2[ti][tj] = get(Rw, j0 + ti, kBT * C + tj);
       __syncthreads();
-      double2 s = none;
-      for (int l = 0; l <= ti; l++) {
-        const double2 p = bmulc(S1[l][ti], S2[l][tj]);
-        s.x += p.x;
-        s.y += p.y;
-      }
-      put(Rw, j0 + ti, kBT * C + tj, s);
+      BlockAcc acc = {};
+      block_mul<true>(acc, S1, S2);
+      __syncthreads();
+      block_store(acc, S2);
+      __syncthreads();
+      put(Rw, j0 + ti, kBT * C + tj, S2[ti][tj]);
       __syncthreads();
     }
     for (int B = J + 1; B < nt; B++) {  // G_BC -= R_JB^H R_JC, C >= B
@@ -187,13 +201,12 @@ __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2
         S2[ti][tj] = get(Rw, j0 + ti, kBT * C + tj);
         const double2 g = get(Rw, kBT * B + ti, kBT * C + tj);
         __syncthreads();
-        double2 s = none;
-#pragma unroll 8
-        for (int l = 0; l < kBT; l++) {
-          const double2 p = bmulc(S0[l][ti], S2[l][tj]);
-          s.x += p.x;
-          s.y += p.y;
-        }
+        BlockAcc acc = {};
+        block_mul<true>(acc, S0, S2);
+        __syncthreads();
+        block_store(acc, S2);
+        __syncthreads();
+        const double2 s = S2[ti][tj];
         put(Rw, kBT * B + ti, kBT * C + tj,
             C > B || tj >= ti ? make_double2(g.x - s.x, g.y - s.y) : none);
         __syncthreads();
@@ -202,29 +215,23 @@ __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2
   }
   for (int J = 1; J < nt; J++)
     for (int I = J - 1; I >= 0; I--) {  // X_IJ = -X_II sum_L R_IL X_LJ
-      double2 s = none;
+      BlockAcc acc = {};
       for (int L = I + 1; L <= J; L++) {
         S0[ti][tj] = get(Rw, kBT * I + ti, kBT * L + tj);
         S1[ti][tj] = get(Xw, kBT * L + ti, kBT * J + tj);
         __syncthreads();
-#pragma unroll 8
-        for (int l = 0; l < kBT; l++) {
-          const double2 p = bmul(S0[ti][l], S1[l][tj]);
-          s.x += p.x;
-          s.y += p.y;
-        }
+        block_mul<false>(acc, S0, S1);
         __syncthreads();
       }
-      S2[ti][tj] = s;
+      block_store(acc, S2);
       S0[ti][tj] = get(Xw, kBT * I + ti, kBT * I + tj);
       __syncthreads();
-      double2 x = none;
-      for (int l = ti; l < kBT; l++) {
-        const double2 p = bmul(S0[ti][l], S2[l][tj]);
-        x.x -= p.x;
-        x.y -= p.y;
-      }
-      put(Xw, kBT * I + ti, kBT * J + tj, x);
+      acc = {};
+      block_mul<false>(acc, S0, S2);
+      block_store(acc, S1);
+      __syncthreads();
+      const double2 x = S1[ti][tj];
+      put(Xw, kBT * I + ti, kBT * J + tj, make_double2(-x.x, -x.y));
       __syncthreads();
     }
   if (t == 0 && bad) latch(status, ST_BREAKDOWN);

@@ -70,6 +70,47 @@ __device__ __forceinline__ double sum16(double v) {
   return v;
 }
 
+// Orders a wave's LDS accesses before and after it: its lanes see each other's
+// stores (the wave's LDS instructions run in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// X = R^-1 of an upper triangular R with real diagonal, both in LDS, k <= 32
+// rows: column c by the eight threads 8c .. 8c + 7, which lie in one wave and
+// read no other column of X, so that the k steps from the last row up take no
+// barrier.  A step is a chain of LDS reads, the sum, a division and a store;
+// its four reads a thread go out together.
+template <int LD>
+__device__ __forceinline__ void invert_upper(const double2 (*R)[LD], double2 (*X)[LD], int k) {
+  const int c = threadIdx.x >> 3, sub = threadIdx.x & 7;
+  if (c >= k) return;
+  for (int a = k - 1; a >= 0; a--) {
+    double2 r[4], x[4], s = make_double2(0, 0);
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int e = min(a + 1 + sub + 8 * u, k - 1);
+      r[u] = R[a][e];
+      x[u] = X[e][c];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      if (a + 1 + sub + 8 * u <= c) {
+        s.x -= r[u].x * x[u].x - r[u].y * x[u].y;
+        s.y -= r[u].x * x[u].y + r[u].y * x[u].x;
+      }
+    s.x = sum8(s.x);
+    s.y = sum8(s.y);
+    if (sub == 0) {
+      if (a == c) s.x += 1.0;
+      const double d = R[a][a].x;
+      X[a][c] = c >= a ? make_double2(s.x / d, s.y / d) : make_double2(0, 0);
+    }
+    wave_sync();
+  }
+}
+
 // The Jacobi rotation of two columns with Gram matrix [[al, g e], [., be]],
 // g e = gr + i gi: false when it is below the threshold |gr + i gi| <= 1e-15
 // sqrt(al be).  er + i ei = conj(e); the columns [x, (er + i ei) y] are rotated

@@ -270,26 +270,8 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
     if (e < k * k) G[e / k][e % k] = v[q];  // R
   }
   __syncthreads();
-  {  // R X = I from the last row up: eight threads per column
-    const int c = t >> 3, sub = t & 7;
-    for (int a = k - 1; a >= 0; a--) {
-      double2 s = make_double2(0, 0);
-      if (c < k)
-        for (int x = a + 1 + sub; x <= c; x += 8) {
-          const double2 p = cmul(G[a][x], Ri[x][c]);
-          s.x -= p.x;
-          s.y -= p.y;
-        }
-      s.x = sum8(s.x);
-      s.y = sum8(s.y);
-      if (c < k && sub == 0) {
-        if (a == c) s.x += 1.0;
-        const double d = G[a][a].x;
-        Ri[a][c] = c >= a ? make_double2(s.x / d, s.y / d) : make_double2(0, 0);
-      }
-      __syncthreads();
-    }
-  }
+  invert_upper(G, Ri, k);  // R X = I
+  __syncthreads();
   if (pass > 0) {
     // R <- R Rold ; Rinv <- Riold Ri
     double2 ni[4];
