@@ -131,9 +131,9 @@ __device__ __forceinline__ void block_store(const BlockAcc& acc, Block& Z) {
 // chain is k short steps in LDS and (k / 32)^3 / 3 block products, where the
 // unblocked form took k steps through global memory and one thread per column
 // of R^-1: 957 us at k = 100; 211 with the products by one thread an element,
-// which wait for LDS, and a barrier for
-// each step of the inverses, 154 now.  A pivot that is not positive latches
-// ST_BREAKDOWN and is taken as 1 (the results stay finite).
+// which wait for LDS, and a barrier for each step of the inverses, 154 now.  A
+// pivot that is not positive latches ST_BREAKDOWN and is taken as 1 (the results
+// stay finite).
 __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2* G, double2* R,
                                                 double2* Rinv, uint32_t* status) {
   __shared__ Block S0, S1, S2;
@@ -324,9 +324,9 @@ __global__ __launch_bounds__(256) void k_applyb(int64_t n, int k, const double2*
 // [a_p, conj(e) a_q] are rotated by the real Jacobi angle of [[alpha,
 // |gamma|], [|gamma|, beta]].  The columns start in descending order of their
 // norms, a rotation's larger column staying in front (8 sweeps against 10 where
-// the iteration has already sorted the spectrum).  Then sigma_c = ||a_c||, sorted descending
-// (ranks counted in parallel), Ut = A diag(1/sigma), W = J, both permuted;
-// Rinv W is formed by k_sgemm.
+// the iteration has already sorted the spectrum).  Then sigma_c = ||a_c||, sorted
+// descending (ranks counted in parallel), Ut = A diag(1/sigma), W = J, both
+// permuted; Rinv W is formed by k_sgemm.
 //
 // Bound by the latency of its rounds (m - 1 a sweep).  In LDS mode (m <= 100:
 // 160 KB) A stays in LDS, a pair's columns in registers for the round, and
