@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void k_gram_sum(int k, int kmax, int nchunk,
 //
 // Bound by latency (k dependent steps, one workgroup per shift): one barrier
 // per step of the factorisation, which leaves the rows' scaling by the roots
-// of the pivots to the end, and one per row of the inverse, eight threads
+// of the pivots to the end, and none in the inverse, eight threads of a wave
 // sharing each of its elements' sums.
 __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
                                               const double2* __restrict__ Gg,
@@ -229,11 +229,6 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
       if (pass > 0) Ro[a][c] = Rw[e];
     }
     __syncthreads();
-    if (attempt == 0) {
-      double tr = 0;
-      for (int j = 0; j < k; j++) tr += G[j][j].x;
-      shift = 11.0 * ((double)(m + 2) * k + (double)k * (k + 1)) * 0x1p-53 * tr;
-    }
     bad = false;
     for (int j = 0; j < k; j++) {  // rows j of sqrt(pivot) R; `bad` is block-uniform
       const double d = G[j][j].x;
@@ -251,6 +246,11 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
       __syncthreads();
     }
     if (!(bad && pass == 0 && attempt == 0)) break;
+    // the trace from memory: every thread needs it, and the steps above have
+    // overwritten the diagonal in LDS
+    double tr = 0;
+    for (int j = 0; j < k; j++) tr += Gg[at + j * (k + 1)].x;
+    shift = 11.0 * ((double)(m + 2) * k + (double)k * (k + 1)) * 0x1p-53 * tr;
   }
   if (pass == 0 && t == 0) shifted[w] = attempt;
   double2 v[4];

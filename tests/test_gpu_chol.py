@@ -1,0 +1,47 @@
+"""The k x k Cholesky factors: the shifted retry of a Gram matrix that is not
+numerically positive definite, and blocks whose squares are near the ends of
+FP64's range."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests.gpu_util import gain_errors, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+def rr():
+    import paper_1902_01458_amd as m
+    return m
+
+
+@pytest.mark.parametrize("k", [17, 32])
+def test_shift_is_the_same_for_every_row_and_run(k):
+    """Columns that are one direction and 1e-10 of noise: elimination step 0
+    takes almost all of the Gram matrix's diagonal away, so a shift from a
+    trace summed meanwhile would be wrong, and depend on the waves' timing.
+
+    The gains carry u sigma_1 from the product Q R: 1e-12 relative to sigma_1
+    (a basis formed through the composed inverse is orthonormal to u cond(Y)
+    only, which says nothing about the shift)."""
+    copies = 32
+    w = W.small("sh", 48, 20, nu=1e-2)
+    prob = rr().BurgersProblem.from_workload(w)
+    f = rr().factor(prob, [1.3] * copies, "fp64", k_max=k)
+    rng = np.random.Generator(np.random.PCG64(5))
+    one = rng.standard_normal(w.n) + 1j * rng.standard_normal(w.n)
+    Y = one + 1e-10 * (rng.standard_normal((k, w.n)) + 1j * rng.standard_normal((k, w.n)))
+    Us = torch.tensor(Y, device="cuda").expand(copies, -1, -1).contiguous()
+    V = torch.tensor(np.eye(k, w.n) + 0j, device="cuda").expand(copies, -1, -1).contiguous()
+    first = None
+    for _ in range(3):
+        out = {key: to_np(v) for key, v in f.resvd(Us, V).items()}
+        f.check()
+        first = first or out
+        for key in ("sigma_svd", "U_svd", "V_svd"):
+            for i in range(copies):
+                np.testing.assert_array_equal(out[key][i], first[key][0])
+    ref = np.linalg.svd(Y.T, compute_uv=False)
+    assert gain_errors(first["sigma_svd"][0], ref).max() <= 1e-12
+    f.free()
