@@ -167,9 +167,11 @@ __global__ __launch_bounds__(1024) void k_cholb(int k, int64_t sM, const double2
       bad |= no;
       const double rd = no ? 1.0 : 1.0 / d;
       if (ti > j && tj >= ti) {
-        const double2 p = bmulc(S0[j][ti], S0[j][tj]);
-        S0[ti][tj].x -= p.x * rd;
-        S0[ti][tj].y -= p.y * rd;
+        // (scaled before the product, as in the narrow path)
+        const double2 gc = S0[j][tj];
+        const double2 p = bmulc(S0[j][ti], make_double2(gc.x * rd, gc.y * rd));
+        S0[ti][tj].x -= p.x;
+        S0[ti][tj].y -= p.y;
       }
       __syncthreads();
     }

@@ -239,9 +239,12 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
       for (int e = t; e < wd * wd; e += 256) {
         const int a = j + 1 + e / wd, c = j + 1 + e % wd;
         if (c < a) continue;
-        const double2 p = cmulc(G[j][a], G[j][c]);
-        G[a][c].x -= p.x * rd;
-        G[a][c].y -= p.y * rd;
+        // (scaled before the product: entries of G are squares already, and
+        // their products leave FP64's range from |Y| ~ 1e77 on)
+        const double2 gc = G[j][c];
+        const double2 p = cmulc(G[j][a], make_double2(gc.x * rd, gc.y * rd));
+        G[a][c].x -= p.x;
+        G[a][c].y -= p.y;
       }
       __syncthreads();
     }

@@ -45,3 +45,26 @@ def test_shift_is_the_same_for_every_row_and_run(k):
     ref = np.linalg.svd(Y.T, compute_uv=False)
     assert gain_errors(first["sigma_svd"][0], ref).max() <= 1e-12
     f.free()
+
+
+@pytest.mark.parametrize("k", [9, 40])
+@pytest.mark.parametrize("power", [-400, 400])
+def test_basis_of_a_scaled_operator(k, power):
+    """L and the shift times 2^power: every step of the sketch scales exactly,
+    with entries of the Gram matrix near 2^(-2 power), whose products leave
+    FP64's range.  The basis is that of the unscaled operator but for sums
+    that round otherwise where a term is subnormal: 1e-12."""
+    rng = np.random.Generator(np.random.PCG64(8))
+    coef = rng.standard_normal((12, 9, 12))
+    coef[..., 0] -= 8.0
+    coef[..., 6] -= 8.0
+    got = []
+    for scale in (1.0, 2.0 ** power):
+        f = rr().factor(rr().BurgersProblem.from_coefficients(coef * scale), [0.7 * scale],
+                        "fp64", k_max=k)
+        Q = to_np(f.sketch_solve(k, 3, 1))[0].T
+        f.check()
+        f.free()
+        assert np.linalg.norm(Q.conj().T @ Q - np.eye(k), 2) <= 1e-12
+        got.append(Q)
+    assert np.linalg.norm(got[1] - got[0], 2) <= 1e-12
