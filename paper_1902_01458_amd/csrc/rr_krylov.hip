@@ -121,7 +121,8 @@ __global__ void k_pc_jacobi(int nn, const double* __restrict__ coef,
 //   8, 9  backward, K:  (c3, c9) of p, (c1, c7) of p
 //   10,11 backward, K^H:(c4, c10) of p+1, (c2, c8) of p+ny
 // (the stencil coefficients themselves; the blocks are minus them, and
-// neighbours outside the grid hold zeros).  In the natural node order every
+// neighbours outside the grid hold zeros, whatever the caller's array has
+// there: the column sweep multiplies them by the zeros of missing nodes).  In the natural node order every
 // operand load of a sweep step touches one cache line per thread, which
 // bounds the sweep (measured: 10 ms per apply at 1024 x 512 against 3.9 ms
 // with the operands read coalesced).
@@ -188,12 +189,12 @@ __global__ __launch_bounds__(kKThreads) void k_pc_ilu0(int nx, int ny,
       const double* cr = coef + 12 * (int64_t)(j < ny - 1 ? p + 1 : p);
       const double* cd = coef + 12 * (int64_t)(i < nx - 1 ? p + ny : p);
       const bool hl = j > 0, hu = i > 0, hr = j < ny - 1, hd = i < nx - 1;
-      Fw[4 * ns + sl] = make_double2(c[4], c[10]);
-      Fw[5 * ns + sl] = make_double2(c[2], c[8]);
+      Fw[4 * ns + sl] = hl ? make_double2(c[4], c[10]) : make_double2(0, 0);
+      Fw[5 * ns + sl] = hu ? make_double2(c[2], c[8]) : make_double2(0, 0);
       Fw[6 * ns + sl] = hl ? make_double2(cl[3], cl[9]) : make_double2(0, 0);
       Fw[7 * ns + sl] = hu ? make_double2(cu[1], cu[7]) : make_double2(0, 0);
-      Fw[8 * ns + sl] = make_double2(c[3], c[9]);
-      Fw[9 * ns + sl] = make_double2(c[1], c[7]);
+      Fw[8 * ns + sl] = hr ? make_double2(c[3], c[9]) : make_double2(0, 0);
+      Fw[9 * ns + sl] = hd ? make_double2(c[1], c[7]) : make_double2(0, 0);
       Fw[10 * ns + sl] = hr ? make_double2(cr[4], cr[10]) : make_double2(0, 0);
       Fw[11 * ns + sl] = hd ? make_double2(cd[2], cd[8]) : make_double2(0, 0);
     }

@@ -69,3 +69,35 @@ def test_bicgstab_residual(nx, ny, precond, adjoint):
         assert (np.linalg.norm(R, axis=0) <= 1e-10 * np.linalg.norm(B[i].T, axis=0)).all()
     assert (X[1, 2] == 0).all()
     f.free()
+
+
+@pytest.mark.parametrize("nx,ny", [(9, 7), (6, 70), (3, 257), (2, 513)])
+@pytest.mark.parametrize("edge", [np.nan, np.inf, 1e300])
+def test_coefficients_towards_missing_neighbours_are_not_used(nx, ny, edge):
+    """Neighbours outside the grid contribute nothing, whatever the coefficient
+    array holds for them: the same bits as with zeros there."""
+    rng = np.random.Generator(np.random.PCG64(21))
+    coef = rng.standard_normal((nx, ny, 12))
+    coef[..., 0] -= 8.0
+    coef[..., 6] -= 8.0
+    X = torch.tensor(rand_block((1, 2, 2 * nx * ny), 22), device="cuda")
+    got = []
+    for v in (0.0, edge):
+        c = coef.copy()
+        for off in (0, 6):
+            c[-1, :, off + 1] = c[0, :, off + 2] = v  # east, west
+            c[:, -1, off + 3] = c[:, 0, off + 4] = v  # north, south
+        prob = rr().BurgersProblem.from_coefficients(c)
+        f = rr().factor(prob, [0.9], "fp64", k_max=2, solver="bicgstab", precond="ilu0",
+                        krylov_maxit=300)
+        got.append([to_np(f.precond_apply(X)), to_np(f.precond_apply(X, adjoint=True)),
+                    to_np(f.solve(X)), to_np(prob.apply([0.9], X))])
+        f.check()
+        f.free()
+        f = rr().factor(prob, [0.9], "fp64", k_max=2)
+        got[-1] += [to_np(f.solve(X)), to_np(f.adjoint_solve(X))]
+        f.check()
+        f.free()
+    assert np.isfinite(got[0][0]).all()
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
