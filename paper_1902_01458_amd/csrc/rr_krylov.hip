@@ -293,6 +293,16 @@ __device__ __forceinline__ bool bicg_step(const BicgStep& b, int64_t q, bool own
   return true;
 }
 
+// Whether system q still runs, the same for every thread of the workgroup.
+// Where several workgroups take a system's step, its owner may end the system
+// and with it the solve while they start: their waves then see either state,
+// and no thread may leave before the vote, as the step has barriers.  A
+// workgroup that goes on comes to the owner's decision, from the same sums.
+__device__ __forceinline__ bool system_runs(const BicgStep& b, int64_t q) {
+  const bool done = __hip_atomic_load(b.conv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __syncthreads_or(!done && b.active[q] != 0);
+}
+
 // r, p, v of one unknown to the updated vector's value
 template <int MODE>
 __device__ __forceinline__ double2 bicg_update(double2 r, double2 p, double2 v, double2 c0,
@@ -305,12 +315,10 @@ __device__ __forceinline__ double2 bicg_update(double2 r, double2 p, double2 v, 
 template <int MODE>
 __global__ __launch_bounds__(kKThreads) void k_bicg_update(int64_t n, int k, double2* X,
                                                            BicgStep b) {
-  if (__hip_atomic_load(b.conv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   __shared__ double2 red[2 * kKThreads / 64];
   const int64_t q = (int64_t)blockIdx.z * k + blockIdx.y;
   double2 c0, c1;
-  // (a workgroup that sees the owner's store ends as the others do)
-  if (!__syncthreads_or(b.active[q] != 0)) return;
+  if (!system_runs(b, q)) return;
   if (!bicg_step<MODE>(b, q, blockIdx.x == 0, red, c0, c1)) return;
   const int64_t e0 = (int64_t)blockIdx.x * kKChunk;
   const int rows = (int)min((int64_t)kKChunk, n - e0);
@@ -329,14 +337,15 @@ __global__ __launch_bounds__(256) void k_pc_jacobi_apply(int nn, int k, int adjo
                                                          double2* X, double2* Y,
                                                          const uint32_t* active,
                                                          const uint32_t* skip, BicgStep b) {
-  if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   __shared__ double2 red[8];
   const int p = blockIdx.x * blockDim.x + threadIdx.x, c = blockIdx.y, w = blockIdx.z;
   const int64_t q = (int64_t)w * k + c;
-  if (MODE == BICG_NONE && active && !active[q]) return;
   double2 c0, c1;
-  if (MODE != BICG_NONE) {  // (a workgroup that sees the owner's store ends as the others do)
-    if (!__syncthreads_or(active[q] != 0)) return;
+  if (MODE == BICG_NONE) {
+    if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    if (active && !active[q]) return;
+  } else {
+    if (!system_runs(b, q)) return;
     if (!bicg_step<MODE>(b, q, blockIdx.x == 0, red, c0, c1)) return;
   }
   if (p >= nn) return;

@@ -101,3 +101,35 @@ def test_coefficients_towards_missing_neighbours_are_not_used(nx, ny, edge):
     assert np.isfinite(got[0][0]).all()
     for a, b in zip(*got):
         np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("nx,ny,precond", [(40, 30, "jacobi"), (4, 530, "ilu0")])
+def test_systems_end_alike_in_every_workgroup(nx, ny, precond):
+    """A system's step is taken by several workgroups, the one that owns it
+    ending the system, and the last system the solve, while the others start.
+    Systems that end at different iterations, every one in turn the last: each
+    reaches the tolerance, a system's result does not depend on the others',
+    and runs repeat bit for bit."""
+    w = W.small("kpe", nx, ny, nu=2e-2)
+    prob = rr().BurgersProblem.from_workload(w)
+    f = rr().factor(prob, [1.3 + 0.1j, 9.0 + 4.0j], "fp64", k_max=3, solver="bicgstab",
+                    precond=precond, krylov_maxit=3000, krylov_tol=1e-11)
+    B = rand_block((2, 3, w.n), 23)
+    B[:, 1] *= np.linspace(0.0, 1.0, w.n) ** 8
+    ref = None
+    for gone in [None, None, (0, 0), (0, 1), (0, 2), (1, 0), (1, 1), (1, 2), None]:
+        C = B.copy()
+        if gone:
+            C[gone] = 0
+        X = to_np(f.solve(torch.tensor(C, device="cuda")))
+        f.check()
+        ref = X if ref is None else ref
+        want = ref.copy()
+        if gone:
+            want[gone] = 0
+        np.testing.assert_array_equal(X, want)
+    U, coef, L, phi, hx, hy = oracle_problem(w)
+    for i, om in enumerate([1.3 + 0.1j, 9.0 + 4.0j]):
+        R = B[i].T - op.shifted(L, om) @ ref[i].T
+        assert (np.linalg.norm(R, axis=0) <= 1e-10 * np.linalg.norm(B[i].T, axis=0)).all()
+    f.free()
