@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <new>
 #include <string>
 
 #include "rr_internal.h"
@@ -499,12 +500,13 @@ Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T,
   pl.omega = 2 * (size_t)n_omega * sizeof(double);
   const int kn = std::min(k_max, kNarrowK);  // widest solve launch
   if (nd) {
-    nd_make_plan(nx, ny, nd_tables, &pl.nd);
+    if (nd_tables) nd_make_plan(nx, ny, &pl.nd);
+    else nd_sizes(nx, ny, &pl.nd);
     const NdPlan& d = pl.nd;
     const size_t w = n_omega;
     // a mixed solve runs the probes' columns too
     const int ks = prec == RR_MIXED && probes ? kn + probe_cols(kn, solve_np(kn)) : kn;
-    pl.nd_fronts = d.fronts.size() * sizeof(NdFront);
+    pl.nd_fronts = (size_t)d.nfronts * sizeof(NdFront);
     pl.nd_tasks = (size_t)d.ntasks * sizeof(NdTask);
     pl.nd_rows = (size_t)d.allrows * sizeof(int);
     pl.nd_border = (size_t)d.border * sizeof(int);
@@ -1186,7 +1188,12 @@ size_t rr_factor_bytes(int32_t nx, int32_t ny, int32_t n_omega, int32_t k_max, r
   if (k_max > (prec == RR_FP64 ? kMaxWideK : kNarrowK)) return 0;
   const int T = tile ? tile : 64;
   if (T != 32 && T != 64) return 0;
-  return make_plan(nx, ny, n_omega, k_max, prec, T, true, true, 0, true, tile == 0, false).total();
+  if (2 * (int64_t)nx * ny > (1ll << 40)) return SIZE_MAX;
+  try {
+    return make_plan(nx, ny, n_omega, k_max, prec, T, true, true, 0, true, tile == 0, false).total();
+  } catch (const std::bad_alloc&) {
+    return 0;
+  }
 }
 
 // ---------------------------------------------------------------------------

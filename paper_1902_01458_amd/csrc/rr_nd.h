@@ -70,6 +70,7 @@ struct NdPlan {
   // leaf's: the position of its one neighbour among the leaf's unknowns
   std::vector<int> bmap;
   std::vector<int> grow;   // border entry -> row (padding: the zero row)
+  int64_t nfronts = 0;
   int64_t rows = 0;        // rows of the separators; row `rows` of the workspaces is zero
   int64_t allrows = 0;     // with the leaves'
   int64_t border = 0;
@@ -79,8 +80,10 @@ struct NdPlan {
   int64_t urows[2] = {};   // rows of the update arenas
   int64_t ntasks = 0;
 };
-// sizes only when `tables` is false (no index tables, no tasks but their number)
-void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan);
+// the counts and sizes alone (nfronts and below), from the distinct blocks
+void nd_sizes(int nx, int ny, NdPlan* plan);
+// the whole plan
+void nd_make_plan(int nx, int ny, NdPlan* plan);
 
 struct NdDevice {  // device pointers of a handle
   NdFront* fronts = nullptr;

@@ -13,6 +13,9 @@
 // is made of runs of its halves' borders; the node at a separator's own end
 // belongs to neither half's.
 #include <algorithm>
+#include <map>
+#include <new>
+#include <tuple>
 
 #include "rr_internal.h"
 
@@ -33,15 +36,75 @@ void set_border(Block& b, int nx, int ny) {
   for (int s = 0; s < 4; s++) b.off[s + 1] = b.off[s] + 2 * len[s];
 }
 
-int up16(int v) { return (v + 15) & ~15; }
+int64_t up16(int64_t v) { return (v + 15) & ~int64_t(15); }
+int64_t tiles(int64_t v) { return (v + kNdTile - 1) / kNdTile; }
+// Temporaries of a front past one tile: T12, the pivot block's row and column,
+// two copies of the pivot inverse in either order.
+int64_t temp_size(int64_t P, int64_t Q) {
+  return P > kNdTile ? P * Q + 2 * kNdTile * P + 4 * kNdTile * kNdTile : 0;
+}
 
 }  // namespace
 
-void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
+// Counted by distinct blocks: at one depth they differ by a node or so a side
+// and by which sides border on a separator, a few dozen where a front each
+// would be n / 32 (16384 x 8192: 4 s and 1.6 GB on the host).
+void nd_sizes(int nx, int ny, NdPlan* plan) {
   NdPlan& pl = *plan;
   pl = NdPlan{};
   pl.nx = nx;
   pl.ny = ny;
+  typedef std::tuple<int, int, bool, bool, bool, bool> Shape;  // nodes; left, right, low, high
+  std::map<Shape, int64_t> level;
+  level[Shape{nx, ny, false, false, false, false}] = 1;
+  for (int d = 0; !level.empty(); d++) {
+    std::map<Shape, int64_t> next;
+    int64_t s = 0, u = 0, t = 0;
+    for (const auto& [shape, count] : level) {
+      const auto [a, c, left, right, low, high] = shape;
+      const bool leaf = (int64_t)a * c <= kNdLeafNodes, across_x = a >= c;
+      const int64_t P = up16(2 * (leaf ? (int64_t)a * c : across_x ? c : a));
+      const int64_t Q = up16(2 * ((int64_t)c * (left + right) + (int64_t)a * (low + high)));
+      pl.nfronts += count;
+      pl.allrows += count * P;
+      pl.border += count * Q;
+      pl.factor += count * P * P;
+      s += count * Q * Q;
+      u += count * Q;
+      t += count * temp_size(P, Q);
+      if (leaf) {
+        pl.ntasks += count;
+        continue;
+      }
+      pl.rows += count * P;
+      pl.factor += count * 2 * P * Q;
+      const int64_t np = tiles(P), nq = tiles(Q);
+      int64_t tasks = nq * nq;                      // schur
+      tasks += P <= kNdDownP ? 1 : P / 16;          // down, rowsX
+      if (P <= kNdTile)
+        tasks++;
+      else  // assemble, panel, update, border, gather, rowsP, rowsQ
+        tasks += np * np + 2 * np * nq + 2 * np * (np - 1) + np * np * np + np * nq + np + P / 16 +
+                 Q / 16;
+      pl.ntasks += count * tasks;
+      if (across_x) {
+        next[Shape{(a - 1) / 2, c, left, true, low, high}] += count;
+        next[Shape{a - 1 - (a - 1) / 2, c, true, right, low, high}] += count;
+      } else {
+        next[Shape{a, (c - 1) / 2, left, right, low, true}] += count;
+        next[Shape{a, c - 1 - (c - 1) / 2, left, right, true, high}] += count;
+      }
+    }
+    pl.schur[d & 1] = std::max(pl.schur[d & 1], s);
+    pl.urows[d & 1] = std::max(pl.urows[d & 1], u);
+    pl.temp = std::max(pl.temp, t);
+    level.swap(next);
+  }
+}
+
+void nd_make_plan(int nx, int ny, NdPlan* plan) {
+  nd_sizes(nx, ny, plan);
+  NdPlan& pl = *plan;
   std::vector<Block> blocks(1, Block{0, nx, 0, ny, false, false, 0, {}});
   std::vector<int> first(1, 0);  // first front of every depth
   for (size_t lo = 0; lo < blocks.size();) {
@@ -58,8 +121,8 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
       fr.childA = fr.childB = -1;
       fr.p = 2 * (b.leaf ? a * c : b.across_x ? c : a);
       fr.q = b.off[4];
-      fr.P = up16(fr.p);
-      fr.Q = up16(fr.q);
+      fr.P = (int)up16(fr.p);
+      fr.Q = (int)up16(fr.q);
       if (!b.leaf) {
         fr.childA = (int)blocks.size();
         fr.childB = fr.childA + 1;
@@ -86,58 +149,29 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
   pl.levels.resize(depth);
   // offsets: factors by front; Schur complements and updates in an arena per
   // parity of the depth (only the level above reads them); temporaries per level
+  int64_t rows = 0, leaf_rows = pl.rows, border = 0, factor = 0;
   for (int d = 0; d < depth; d++) {
     int64_t s = 0, u = 0, t = 0;
     for (int f = first[d]; f < first[d + 1]; f++) {
       NdFront& fr = pl.fronts[f];
       const int64_t P = fr.P, Q = fr.Q;
       const bool leaf = fr.childA < 0;
-      if (!leaf) {
-        fr.row = (int)pl.rows;
-        pl.rows += P;
-      }
-      fr.bor = (int)pl.border;
-      pl.border += Q;
-      fr.a = pl.factor;
+      fr.row = (int)(leaf ? leaf_rows : rows);
+      (leaf ? leaf_rows : rows) += P;
+      fr.bor = (int)border;
+      border += Q;
+      fr.a = factor;
       fr.b12 = fr.a + P * P;
       fr.f21 = fr.b12 + (leaf ? 0 : P * Q);
-      pl.factor = fr.f21 + (leaf ? 0 : P * Q);
+      factor = fr.f21 + (leaf ? 0 : P * Q);
       fr.s = s;
       s += Q * Q;
       fr.urow = (int)u;
       u += Q;
-      if (P > kNdTile) {
-        fr.t = t;
-        t += P * Q + 2 * kNdTile * P + 4 * kNdTile * kNdTile;
-      }
-    }
-    pl.schur[d & 1] = std::max(pl.schur[d & 1], s);
-    pl.urows[d & 1] = std::max(pl.urows[d & 1], u);
-    pl.temp = std::max(pl.temp, t);
-  }
-  pl.allrows = pl.rows;
-  for (NdFront& fr : pl.fronts)
-    if (fr.childA < 0) {
-      fr.row = (int)pl.allrows;
-      pl.allrows += fr.P;
-    }
-  auto tiles = [](int v) { return (v + kNdTile - 1) / kNdTile; };
-  for (const NdFront& fr : pl.fronts) {
-    const int64_t np = tiles(fr.P), nq = tiles(fr.Q);
-    if (fr.childA < 0) {
-      pl.ntasks++;
-      continue;
-    }
-    pl.ntasks += nq * nq;  // schur
-    pl.ntasks += fr.P <= kNdDownP ? 1 : fr.P / 16;  // down, rowsX
-    if (fr.P <= kNdTile) {
-      pl.ntasks++;
-    } else {  // assemble, panel, update, border, gather, rowsP, rowsQ
-      pl.ntasks += np * np + 2 * np * nq + 2 * np * (np - 1) + np * np * np + np * nq + np +
-                   fr.P / 16 + fr.Q / 16;
+      if (P > kNdTile) fr.t = t;
+      t += temp_size(P, Q);
     }
   }
-  if (!tables) return;
 
   std::vector<int> row_of((size_t)nx * ny);
   pl.pdof.assign(pl.allrows, -1);
@@ -239,7 +273,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     });
     int steps = 0;
     each(lv.assemble, false, true, [&](int f, const NdFront& fr) {
-      const int np = tiles(fr.P), nq = tiles(fr.Q);
+      const int np = (int)tiles(fr.P), nq = (int)tiles(fr.Q);
       lv.largeP = std::max(lv.largeP, fr.P);
       steps = std::max(steps, np);
       for (int i = 0; i < np; i++)
@@ -254,7 +288,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
     lv.update.resize(steps);
     for (int k = 0; k < steps; k++) {
       each(lv.panel[k], false, true, [&](int f, const NdFront& fr) {
-        const int np = tiles(fr.P);
+        const int np = (int)tiles(fr.P);
         for (int j = 0; j < np && k < np; j++)
           if (j != k) {
             pl.tasks.push_back({f, j, k, 0});
@@ -262,7 +296,7 @@ void nd_make_plan(int nx, int ny, bool tables, NdPlan* plan) {
           }
       });
       each(lv.update[k], false, true, [&](int f, const NdFront& fr) {
-        const int np = tiles(fr.P);
+        const int np = (int)tiles(fr.P);
         if (k >= np) return;
         if (k + 1 < np) pl.tasks.push_back({f, k + 1, k + 1, k});  // the next pivot tile first
         for (int i = 0; i < np; i++)
@@ -305,7 +339,12 @@ extern "C" int64_t rr_nd_plan(int32_t nx, int32_t ny, int32_t what, int64_t* out
       (cap > 0 && !out))
     return -1;
   rr::NdPlan pl;
-  rr::nd_make_plan(nx, ny, what != 5, &pl);
+  try {
+    if (what == 5) rr::nd_sizes(nx, ny, &pl);
+    else rr::nd_make_plan(nx, ny, &pl);
+  } catch (const std::bad_alloc&) {
+    return -1;
+  }
   int64_t count = 0;
   auto put = [&](int64_t v) {
     if (count < cap) out[count] = v;

@@ -6,6 +6,8 @@ and its launches cover every tile once.
 Tolerance of the solves: n u kappa for these well-conditioned systems is far
 below 1e-11 relative (FP64 products of at most 200 x 200 blocks)."""
 import ctypes
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -196,3 +198,40 @@ def test_nested_dissection_needs_no_more_memory_than_the_band(nx, ny, prec):
     for nw in (1, 7):
         assert 0 < L.rr_factor_bytes(nx, ny, nw, 8, prec, 0) <= L.rr_factor_bytes(nx, ny, nw, 8,
                                                                                    prec, 64)
+
+
+@pytest.mark.parametrize("nx,ny", GRIDS + [(300, 200), (20, 400), (5, 1200), (129, 127)])
+def test_sizes_counted_by_blocks_are_the_plans(nx, ny):
+    fronts, pdof, bmap, grow, tasks, totals = plan(nx, ny)
+    tree = [x for x in fronts if x["childA"] >= 0]
+    depth = max(x["depth"] for x in fronts) + 1
+
+    def per_level(size, parity):
+        return max([sum(size(x) for x in fronts if x["depth"] == d)
+                    for d in range(depth) if d % 2 == parity], default=0)
+
+    def temp(x):
+        return x["P"] * x["Q"] + 2 * TILE * x["P"] + 4 * TILE * TILE if x["P"] > TILE else 0
+
+    want = [sum(x["P"] for x in tree), sum(x["P"] for x in fronts), sum(x["Q"] for x in fronts),
+            sum(x["P"] ** 2 for x in fronts) + sum(2 * x["P"] * x["Q"] for x in tree),
+            per_level(lambda x: x["Q"] ** 2, 0), per_level(lambda x: x["Q"] ** 2, 1),
+            max(per_level(temp, 0), per_level(temp, 1)),
+            per_level(lambda x: x["Q"], 0), per_level(lambda x: x["Q"], 1), len(tasks)]
+    assert totals.tolist() == want
+
+
+@pytest.mark.parametrize("nx,ny", [(16384, 8192), (40000, 40000), (2 ** 31 - 1, 1),
+                                   (2 ** 20, 2 ** 20), (2 ** 31 - 1, 2 ** 31 - 1)])
+def test_the_size_of_a_grid_of_any_size_is_answered_at_once(nx, ny):
+    """In a process of its own: an exception through the C entry ends it."""
+    code = ("import time\n"
+            "from paper_1902_01458_amd import _lib\n"
+            "L = _lib.lib()\n"
+            f"t = time.perf_counter(); b = L.rr_factor_bytes({nx}, {ny}, 1, 8, 0, 0)\n"
+            "print(b, time.perf_counter() - t)\n")
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=110)
+    assert out.returncode == 0, out.stderr[-500:]
+    size, seconds = out.stdout.split()
+    assert int(size) >= min(2 * nx * ny * 16 * 16, 2 ** 64 - 1)  # 16 entries a row at least
+    assert float(seconds) < 0.1
