@@ -451,7 +451,7 @@ struct Plan {
   BandGeom geom;
   size_t coef, phi, U, omega, tiles, xs, cbuf, flags, ctrl, theta, vec, work3, partial, kk2, rho,
       shifted, grad, big = 0, wide = 0, probe_blk = 0, probe_z = 0;
-  NdPlan nd;  // the nested-dissection LU's (no band LU then)
+  NdPlan nd;  // the nested-dissection LU's sizes (no band LU then)
   size_t nd_fronts = 0, nd_tasks = 0, nd_rows = 0, nd_border = 0, nd_factor = 0, nd_schur[2] = {},
          nd_temp = 0, nd_vec = 0, nd_u[2] = {};
   int nchunk, grad_nchunk, probe_np = 0, probe_p = 0;
@@ -485,7 +485,7 @@ bool use_nd(bool krylov, bool gmres_ir, int superblock) {
 }
 
 Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T, bool has_phi,
-               bool has_U, int sb, bool probes, bool nd, bool nd_tables) {
+               bool has_U, int sb, bool probes, bool nd) {
   Plan pl{};
   const int64_t n = 2 * (int64_t)nx * ny;
   const size_t nn = (size_t)nx * ny;
@@ -500,8 +500,7 @@ Plan make_plan(int nx, int ny, int n_omega, int k_max, rr_precision prec, int T,
   pl.omega = 2 * (size_t)n_omega * sizeof(double);
   const int kn = std::min(k_max, kNarrowK);  // widest solve launch
   if (nd) {
-    if (nd_tables) nd_make_plan(nx, ny, &pl.nd);
-    else nd_sizes(nx, ny, &pl.nd);
+    nd_sizes(nx, ny, &pl.nd);
     const NdPlan& d = pl.nd;
     const size_t w = n_omega;
     // a mixed solve runs the probes' columns too
@@ -694,17 +693,8 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
   const size_t nn = (size_t)p->nx * p->ny;
   const bool gmres_ir = prec == RR_MIXED && tune && tune->refine_method == RR_REFINE_GMRES;
   f->nd = use_nd(krylov, gmres_ir, tune ? tune->superblock : 0);
-  if (f->nd) {  // a plan is made on the host: not for what no device holds (16 entries a row at least)
-    size_t free_b = 0, total_b = 0;
-    const double need = 16.0 * n64 * n_omega * (prec == RR_MIXED ? 8 : 16);
-    if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && need > (double)total_b) {
-      delete f;
-      return fail(RR_ERR_NOMEM, "the LU does not fit in device memory");
-    }
-  }
-  Plan pl = make_plan(p->nx, p->ny, n_omega, k_max, prec, T, p->phi != nullptr, p->U != nullptr,
-                      tune ? tune->superblock : 0, !krylov && !gmres_ir, f->nd, true);
-  f->ndp = std::move(pl.nd);
+  const Plan pl = make_plan(p->nx, p->ny, n_omega, k_max, prec, T, p->phi != nullptr, p->U != nullptr,
+                      tune ? tune->superblock : 0, !krylov && !gmres_ir, f->nd);
   f->tile_bytes = pl.tiles;
   rr_status st = RR_OK;
 #define ALLOC(ptr, bytes)                      \
@@ -790,6 +780,14 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
     ALLOC(f->gm.partial, cols * gmres_nchunk(n64) * (m + 1) * cplx);
   }
 #undef ALLOC
+  if (f->nd) {  // the tables on the host, once the device memory is there
+    try {
+      nd_make_plan(p->nx, p->ny, &f->ndp);
+    } catch (const std::bad_alloc&) {
+      st = fail(RR_ERR_NOMEM, "no host memory for the plan of the LU");
+      goto fail_free;
+    }
+  }
   {
     hipError_t e = hipMemcpyAsync(f->coef, p->coef, nn * 12 * sizeof(double),
                                   hipMemcpyDeviceToDevice, s);
@@ -1190,7 +1188,7 @@ size_t rr_factor_bytes(int32_t nx, int32_t ny, int32_t n_omega, int32_t k_max, r
   if (T != 32 && T != 64) return 0;
   if (2 * (int64_t)nx * ny > (1ll << 40)) return SIZE_MAX;
   try {
-    return make_plan(nx, ny, n_omega, k_max, prec, T, true, true, 0, true, tile == 0, false).total();
+    return make_plan(nx, ny, n_omega, k_max, prec, T, true, true, 0, true, tile == 0).total();
   } catch (const std::bad_alloc&) {
     return 0;
   }
