@@ -51,6 +51,19 @@ __device__ __forceinline__ void zero(CAcc<R>& a) {
   a.im = typename Mf<R>::v4{0, 0, 0, 0};
 }
 
+template <typename R>
+__device__ __forceinline__ cplx<R> narrow(zc v) {
+  return cplx<R>{(R)v.re, (R)v.im};
+}
+// An inverse's element as it is kept; one that FP32 does not hold counts as a
+// bad pivot.
+template <typename R>
+__device__ __forceinline__ cplx<R> kept(zc v, bool& bad) {
+  const cplx<R> k = narrow<R>(v);
+  if constexpr (sizeof(R) < sizeof(double)) bad |= !(isfinite(k.re) && isfinite(k.im));
+  return k;
+}
+
 // M(omega) between unknowns dr (row) and dc: i omega - L.
 template <typename R>
 __device__ __forceinline__ cplx<R> entry(const OpDesc& op, double om_r, double om_i, int dr,
@@ -94,24 +107,25 @@ __device__ __forceinline__ void add(cplx<R>& a, cplx<R> b) {
 // update the rest (the pivot row's wave, which has no row to update, takes
 // that wave's row).  A zero or non-finite pivot latches ST_SINGULAR and is
 // replaced by 1.
+//
+// In FP64 for FP32 factors too: without pivoting the inverse of a front's block
+// grows now and then, and the FP32 one then loses the digits that refinement
+// next to an eigenvalue of L needs.  Over 80 grids at 1e-5 |lambda| (emulated), 30
+// solves missed 1e-10 within six corrections with FP32 inverses, 14 of them
+// solves that the band LU finishes; 15 and 4 with FP64 ones (or pivoted ones: it
+// is the growth).  The band LU misses 28.  The price is the tile's 75 KB of LDS,
+// two workgroups a CU instead of four: 512 x 256, 16 shifts, FP32, k_nd_leaf
+// 1.69 -> 3.96 ms, the factor 18.7 -> 23.2 ms.
 // ---------------------------------------------------------------------------
-template <int S>
-__device__ __forceinline__ float row_bcast(float v) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + S, 0xf, 0xf, true));
-}
 template <int S>
 __device__ __forceinline__ double row_bcast(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + S, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + S, 0xf, 0xf, true);
   return __hiloint2double(hi, lo);
 }
-template <int S, typename R>
-__device__ __forceinline__ cplx<R> row_bcast(cplx<R> v) {
-  return cplx<R>{row_bcast<S>(v.re), row_bcast<S>(v.im)};
-}
-__device__ __forceinline__ float lane_value(float v, int lane) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+template <int S>
+__device__ __forceinline__ zc row_bcast(zc v) {
+  return zc{row_bcast<S>(v.re), row_bcast<S>(v.im)};
 }
 __device__ __forceinline__ double lane_value(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
@@ -122,39 +136,38 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 __device__ __forceinline__ double recip(double x) {
   return x > 1e-290 && x < 1e290 ? recip_newton(x) : 1.0 / x;
 }
-__device__ __forceinline__ float recip(float x) { return 1.0f / x; }
 
-template <typename R, int S>
+template <int S>
 struct Inv16 {
-  static __device__ __forceinline__ void run(cplx<R> (&a)[4], bool& bad) {
+  static __device__ __forceinline__ void run(zc (&a)[4], bool& bad) {
     if constexpr (S < 16) {
       constexpr int G = S >> 2, C = S & 3;
       const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
       const int src = 16 * G + i;
-      const cplx<R> f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
-      cplx<R> d{lane_value(a[C].re, 16 * G + S), lane_value(a[C].im, 16 * G + S)};
-      const R mag = d.re * d.re + d.im * d.im;
-      R rm = recip(mag);
-      if (!(mag > (R)0) || !isfinite(mag)) {
+      const zc f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
+      zc d{lane_value(a[C].re, 16 * G + S), lane_value(a[C].im, 16 * G + S)};
+      const double mag = d.re * d.re + d.im * d.im;
+      double rm = recip(mag);
+      if (!(mag > 0.0) || !isfinite(mag)) {
         bad = true;
-        d = cplx<R>{(R)1, (R)0};
-        rm = (R)1;
+        d = zc{1.0, 0.0};
+        rm = 1.0;
       }
-      const cplx<R> inv{d.re * rm, -d.im * rm};
-      cplx<R> m = cmul(f, inv);
+      const zc inv{d.re * rm, -d.im * rm};
+      zc m = cmul(f, inv);
       const bool piv = i == S;
-      if (piv) m = cplx<R>{-inv.re, -inv.im};
+      if (piv) m = zc{-inv.re, -inv.im};
 #pragma unroll
       for (int c = 0; c < 4; c++) {
-        const cplx<R> v = row_bcast<S>(a[c]);
-        cplx<R> b = a[c];
-        if (piv) b = cplx<R>{(R)0, (R)0};
+        const zc v = row_bcast<S>(a[c]);
+        zc b = a[c];
+        if (piv) b = zc{0.0, 0.0};
         b.re -= m.re * v.re - m.im * v.im;
         b.im -= m.re * v.im + m.im * v.re;
         a[c] = b;
       }
-      if (g == G) a[C] = cplx<R>{-m.re, -m.im};
-      Inv16<R, S + 1>::run(a, bad);
+      if (g == G) a[C] = zc{-m.re, -m.im};
+      Inv16<S + 1>::run(a, bad);
     }
   }
 };
@@ -164,42 +177,41 @@ constexpr int kPvSize = 2 * 16 * kPv;  // two of them, by pivot parity
 
 // (inlined: as a function it would take its LDS operands through generic
 // pointers, i.e. flat instead of LDS instructions)
-template <typename R>
-__device__ __forceinline__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pvs, uint32_t* status) {
+__device__ __forceinline__ void invert_tile(zc* F, int ld, int T, zc* pvs, uint32_t* status) {
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
   const int nb = T >> 4;
   // invert pivot block kb from LDS into its pv
   auto pivot = [&](int kb) __attribute__((always_inline)) {
-    cplx<R> a[4];
+    zc a[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) a[c] = F[(16 * kb + 4 * g + c) * ld + 16 * kb + i];
     bool bad = false;
-    Inv16<R, 0>::run(a, bad);
+    Inv16<0>::run(a, bad);
     if (bad && l == 0) latch(status, ST_SINGULAR);
 #pragma unroll
     for (int c = 0; c < 4; c++) pvs[(kb & 1) * 16 * kPv + i * kPv + 4 * g + c] = a[c];
   };
-  auto put = [&](int rb, int j, const CAcc<R>& acc) {
+  auto put = [&](int rb, int j, const CAcc<double>& acc) {
 #pragma unroll
     for (int e = 0; e < 4; e++)
-      F[(16 * j + i) * ld + 16 * rb + Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
+      F[(16 * j + i) * ld + 16 * rb + Mf<double>::row(l, e)] = zc{acc.re[e], acc.im[e]};
   };
   // (one place calls pivot: a second would make it a function, its operands in
   // scratch memory)
   for (int kb = -1;; kb++) {
-    const cplx<R>* pv = pvs + (kb & 1) * 16 * kPv;
+    const zc* pv = pvs + (kb & 1) * 16 * kPv;
     const int nx = kb + 1;
-    CAcc<R> held;
+    CAcc<double> held;
     int rb = wave;
     bool rows = false;
     if (kb >= 0) {
       if (wave != kb && wave < nb) {  // block row kb: R_j = pv F(kb, j), j = wave
-        CAcc<R> acc;
+        CAcc<double> acc;
         zero(acc);
-        const cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
+        const zc* col = F + (16 * wave + i) * ld + 16 * kb;
 #pragma unroll
         for (int s = 0; s < 4; s++)
-          cmfma<R, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
+          cmfma<double, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
         put(kb, wave, acc);
       }
       __syncthreads();
@@ -208,29 +220,29 @@ __device__ __forceinline__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* 
       if (wave == kb) rb = nx;         // (nx < nb) the next pivot's row, for its wave
       rows = wave < nb && rb < nb && (wave == kb || wave != nx);
       if (wave < nb && (rows || wave == nx)) {
-        cplx<R> cf[4];
+        zc cf[4];
 #pragma unroll
         for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * rb + i];
         for (int j = 0; j < nb; j++) {
           if (j == kb || (wave == nx ? j != nx : (rb == nx && j == nx))) continue;
-          CAcc<R> acc;
-          const cplx<R>* col = F + (16 * j + i) * ld;
+          CAcc<double> acc;
+          const zc* col = F + (16 * j + i) * ld;
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            const cplx<R> v = col[16 * rb + Mf<R>::row(l, e)];
+            const zc v = col[16 * rb + Mf<double>::row(l, e)];
             acc.re[e] = v.re;
             acc.im[e] = v.im;
           }
 #pragma unroll
           for (int s = 0; s < 4; s++)
-            cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
+            cmfma<double, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
           put(rb, j, acc);
         }
         if (rows) {
           zero(held);
 #pragma unroll
           for (int s = 0; s < 4; s++)
-            cmfma<R, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
+            cmfma<double, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
         }
       }
     }
@@ -277,13 +289,18 @@ struct FactorArgs {
 };
 
 constexpr int kLd = kNdTile + 1;  // pitch of a tile in LDS
+constexpr size_t kTileLds = (size_t)(kNdTile * kLd + kPvSize) * sizeof(zc);
+// A P x P tile with its pivot inverses; k_nd_front (R: the factor's type) keeps
+// 4 x 16 rows of P + 1 for F21 in the tile's place.
 template <typename R>
-constexpr size_t tile_lds() {
-  return (size_t)(kNdTile * kLd + kPvSize) * sizeof(cplx<R>);
+__host__ __device__ constexpr int front_tile(int P) {  // in elements of zc
+  const int rows = (int)(kNdTile * sizeof(cplx<R>) / sizeof(zc));
+  return (P > rows ? P : rows) * (P + 1);
 }
+size_t leaf_lds(int P) { return (size_t)(P * (P + 1) + kPvSize) * sizeof(zc); }
 template <typename R>
-size_t front_lds(int P, bool leaf) {  // k_nd_front keeps 4 x 16 rows of P + 1 for F21
-  return (size_t)((leaf ? P : kNdTile) * (P + 1) + kPvSize) * sizeof(cplx<R>);
+size_t front_lds(int P) {
+  return (size_t)(front_tile<R>(P) + kPvSize) * sizeof(zc);
 }
 
 // A leaf's border: its unknowns' positions in the leaf and their real
@@ -316,41 +333,66 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
   const NdFront fr = g.fronts[g.tasks[blockIdx.x].front];
   const double om_r = g.omega[2 * w], om_i = g.omega[2 * w + 1];
   const int p = fr.p, P = fr.P, Q = fr.Q, ld = P + 1;
-  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
-  cplx<R>* pv = F + P * ld;
+  zc* F = reinterpret_cast<zc*>(smem_raw);
+  zc* pv = F + P * ld;
   const int* pd = g.pdof + fr.row;
   leaf_border<R>(lb, g.op, fr, g.pdof, g.bmap, g.grow);
-  for (int e = threadIdx.x; e < P * ld; e += 256) F[e] = cplx<R>{(R)0, (R)0};
+  for (int e = threadIdx.x; e < P * ld; e += 256) F[e] = zc{0.0, 0.0};
   __syncthreads();
   if (threadIdx.x < P) {  // one thread a row: its at most six entries in the leaf
     const int r = threadIdx.x;
     if (r < p) {
       const int dof = pd[r], across = fr.across, m = (r >> 1) % across;
       const double* cf = g.op.coef + 12 * (int64_t)(dof >> 1) + 6 * (r & 1);
-      F[r * ld + r] = cplx<R>{(R)(-cf[0] - om_i), (R)om_r};
-      F[(r ^ 1) * ld + r] = cplx<R>{(R)-cf[5], (R)0};
-      if (r + 2 * across < p) F[(r + 2 * across) * ld + r] = cplx<R>{(R)-cf[1], (R)0};
-      if (r - 2 * across >= 0) F[(r - 2 * across) * ld + r] = cplx<R>{(R)-cf[2], (R)0};
-      if (m < across - 1) F[(r + 2) * ld + r] = cplx<R>{(R)-cf[3], (R)0};
-      if (m > 0) F[(r - 2) * ld + r] = cplx<R>{(R)-cf[4], (R)0};
+      F[r * ld + r] = zc{-cf[0] - om_i, om_r};
+      F[(r ^ 1) * ld + r] = zc{-cf[5], 0.0};
+      if (r + 2 * across < p) F[(r + 2 * across) * ld + r] = zc{-cf[1], 0.0};
+      if (r - 2 * across >= 0) F[(r - 2 * across) * ld + r] = zc{-cf[2], 0.0};
+      if (m < across - 1) F[(r + 2) * ld + r] = zc{-cf[3], 0.0};
+      if (m > 0) F[(r - 2) * ld + r] = zc{-cf[4], 0.0};
     } else {
-      F[r * ld + r] = cplx<R>{(R)1, (R)0};
+      F[r * ld + r] = zc{1.0, 0.0};
     }
   }
   __syncthreads();
-  invert_tile<R>(F, ld, P, pv, g.status);
+  invert_tile(F, ld, P, pv, g.status);
   cplx<R>* A = g.factor + w * g.nfactor + fr.a;
+  bool bad = false;
   for (int e = threadIdx.x; e < P * P; e += 256) {
     const int c = e / P, r = e - c * P;
-    A[e] = F[c * ld + r];
+    A[e] = kept<R>(F[c * ld + r], bad);
   }
+  if (bad) latch(g.status, ST_SINGULAR);
   cplx<R>* S = g.schur_out + w * g.nout + fr.s;
   for (int e = threadIdx.x; e < Q * Q; e += 256) {
     const int r = e / Q, c = e - r * Q;
-    const cplx<R> v = F[lb.at[c] * ld + lb.at[r]];
-    const R f = -lb.f21[r], h = lb.f12[c];
-    S[e] = cplx<R>{f * v.re * h, f * v.im * h};
+    const zc v = F[lb.at[c] * ld + lb.at[r]];
+    const double f = -lb.f21[r], h = lb.f12[c];
+    S[e] = narrow<R>(zc{f * v.re * h, f * v.im * h});
   }
+}
+
+// A T x T tile in LDS (T <= TM) from one type to the other in the same place:
+// every thread holds its elements over a barrier.
+template <int TM, typename TO, typename FROM>
+__device__ __forceinline__ void tile_convert(const cplx<FROM>* from, cplx<TO>* to, int ld, int T,
+                                             bool& bad) {
+  constexpr int N = (TM * TM + 255) / 256;
+  cplx<TO> v[N];
+#pragma unroll
+  for (int u = 0; u < N; u++) {
+    const int e = threadIdx.x + 256 * u, c = e / T, r = e - c * T;
+    if (e >= T * T) continue;
+    const cplx<FROM> x = from[c * ld + r];
+    v[u] = kept<TO>(zc{x.re, x.im}, bad);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < N; u++) {
+    const int e = threadIdx.x + 256 * u, c = e / T, r = e - c * T;
+    if (e < T * T) to[c * ld + r] = v[u];
+  }
+  __syncthreads();
 }
 
 // A front with halves and P <= 64, one workgroup (blockIdx.z > 0: further ones
@@ -366,12 +408,13 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
 template <typename R, int PM>
 __global__ __launch_bounds__(256, PM <= 16 ? 4 : PM <= 32 ? 3 : 2) void k_nd_front(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
-  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
+  zc* D = reinterpret_cast<zc*>(smem_raw);            // F11 and its inverse
+  cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);  // the inverse as it is kept
   const int w = g.w0 + blockIdx.y;
   const NdFront fr = g.fronts[g.tasks[blockIdx.x].front];
   const double om_r = g.omega[2 * w], om_i = g.omega[2 * w + 1];
   const int p = fr.p, P = fr.P, Q = fr.Q, ld = P + 1;
-  cplx<R>* pv = F + kNdTile * ld;
+  zc* pv = D + front_tile<R>(P);
   const int* pd = g.pdof + fr.row;
   const int* bm = g.bmap + fr.bor;
   const int* gr = g.grow + fr.bor;
@@ -400,20 +443,23 @@ __global__ __launch_bounds__(256, PM <= 16 ? 4 : PM <= 32 ? 3 : 2) void k_nd_fro
       for (int u = 0; u < 4; u++) {
         const int r = r0 + 4 * u;
         if (r >= P || c >= P) continue;
-        cplx<R> v{(R)(r == c ? 1 : 0), (R)0};
+        zc v{r == c ? 1.0 : 0.0, 0.0};
         if (r < p && c < p) {
-          v = cplx<R>{(R)0, (R)0};
+          v = zc{0.0, 0.0};
           const int d = (r >> 1) - (c >> 1);
-          if (d >= -1 && d <= 1) v = entry<R>(g.op, om_r, om_i, pd[r], pd[c]);
-          add(v, x[u]);
-          add(v, y[u]);
+          if (d >= -1 && d <= 1) v = entry<double>(g.op, om_r, om_i, pd[r], pd[c]);
+          v.re += (double)x[u].re + (double)y[u].re;
+          v.im += (double)x[u].im + (double)y[u].im;
         }
-        F[c * ld + r] = v;
+        D[c * ld + r] = v;
       }
     }
   }
   __syncthreads();
-  invert_tile<R>(F, ld, P, pv, g.status);
+  invert_tile(D, ld, P, pv, g.status);
+  bool bad = false;
+  if constexpr (sizeof(R) < sizeof(double)) tile_convert<PM>(D, F, ld, P, bad);
+  if (bad) latch(g.status, ST_SINGULAR);
   if (blockIdx.z == 0)
     for (int e = threadIdx.x; e < P * P; e += 256) {
       const int c = e / P, r = e - c * P;
@@ -643,19 +689,24 @@ __device__ __forceinline__ int64_t t_piv(const NdFront& f, int k, int rowmajor) 
 }
 __device__ __forceinline__ int tile_width(int P, int k) { return min(kNdTile, P - kNdTile * k); }
 
-// Invert the T x T tile in LDS and write it as pivot inverse k.
+// Invert the T x T tile in LDS and write it as pivot inverse k (pv: behind a
+// tile of zc).
 template <typename R>
-__device__ __forceinline__ void pivot_out(cplx<R>* F, cplx<R>* pv, int T, const NdFront& fr, int k,
-                          cplx<R>* temp, uint32_t* status) {
+__device__ __forceinline__ void pivot_out(cplx<R>* F, zc* pv, int T, const NdFront& fr, int k,
+                                          cplx<R>* temp, uint32_t* status) {
+  zc* D = reinterpret_cast<zc*>(F);
   __syncthreads();
-  invert_tile<R>(F, kLd, T, pv, status);
+  bool bad = false;
+  if constexpr (sizeof(R) < sizeof(double)) tile_convert<kNdTile>(F, D, kLd, T, bad);
+  invert_tile(D, kLd, T, pv, status);
   cplx<R>* pc = temp + t_piv(fr, k, 0);
   cplx<R>* pr = temp + t_piv(fr, k, 1);
   for (int e = threadIdx.x; e < T * T; e += 256) {
     const int c = e / T, r = e - c * T;
-    pc[c * kNdTile + r] = F[c * kLd + r];
-    pr[c * kNdTile + r] = F[r * kLd + c];
+    pc[c * kNdTile + r] = kept<R>(D[c * kLd + r], bad);
+    pr[c * kNdTile + r] = narrow<R>(D[r * kLd + c]);
   }
+  if (bad) latch(status, ST_SINGULAR);
 }
 
 // A 64 x 64 tile of F11 (kind 0, into A), F12 (1, into T12) or F21 (2).
@@ -664,7 +715,7 @@ template <typename R>
 __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
   cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
-  cplx<R>* pv = F + kNdTile * kLd;
+  zc* pv = reinterpret_cast<zc*>(smem_raw) + kNdTile * kLd;
   const int w = g.w0 + blockIdx.y;
   const NdTask t = g.tasks[xcd_task()];
   const NdFront fr = g.fronts[t.front];
@@ -811,7 +862,7 @@ template <typename R>
 __global__ __launch_bounds__(256, 2) void k_nd_update(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
   cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
-  cplx<R>* pv = F + kNdTile * kLd;
+  zc* pv = reinterpret_cast<zc*>(smem_raw) + kNdTile * kLd;
   const int w = g.w0 + blockIdx.y;
   const NdTask t = g.tasks[xcd_task()];
   const NdFront fr = g.fronts[t.front];
@@ -1437,7 +1488,7 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
   a.nfactor = pl.factor;
   a.ntemp = pl.temp;
   a.status = status;
-  const size_t lds = tile_lds<R>();
+  const size_t lds = kTileLds;
   for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
     const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
     a.w0 = w0;
@@ -1452,14 +1503,14 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
       a.schur_in = (cplx<R>*)d.schur[~dep & 1];
       a.nout = pl.schur[dep & 1];
       a.nin = pl.schur[~dep & 1];
-      run(k_nd_leaf<R>, lv.leaf, front_lds<R>(lv.leafP, true));
-      const size_t fl = front_lds<R>(lv.maxP, false);
+      run(k_nd_leaf<R>, lv.leaf, leaf_lds(lv.leafP));
+      const size_t fl = front_lds<R>(lv.maxP);
       if (lv.maxP <= 16) run(k_nd_front<R, 16>, lv.small, fl, shares(lv, nw));
       else if (lv.maxP <= 32) run(k_nd_front<R, 32>, lv.small, fl, shares(lv, nw));
       else run(k_nd_front<R, 64>, lv.small, fl, shares(lv, nw));
       run(k_nd_assemble<R>, lv.assemble, lds);
       for (size_t k = 0; k < lv.panel.size(); k++) {
-        run(k_nd_panel<R>, lv.panel[k], lds);
+        run(k_nd_panel<R>, lv.panel[k], (size_t)kNdTile * kLd * sizeof(cplx<R>));
         run(k_nd_update<R>, lv.update[k], lds);
       }
       run(k_nd_border<R>, lv.border, 0);
@@ -1555,11 +1606,11 @@ hipError_t prepare_r() {
     if (e == hipSuccess && bytes > 64 * 1024)
       e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   };
-  lds((const void*)k_nd_leaf<R>, tile_lds<R>());
-  lds((const void*)k_nd_front<R, 64>, tile_lds<R>());
-  lds((const void*)k_nd_assemble<R>, tile_lds<R>());
-  lds((const void*)k_nd_panel<R>, tile_lds<R>());
-  lds((const void*)k_nd_update<R>, tile_lds<R>());
+  lds((const void*)k_nd_leaf<R>, kTileLds);
+  lds((const void*)k_nd_front<R, 64>, kTileLds);
+  lds((const void*)k_nd_assemble<R>, kTileLds);
+  lds((const void*)k_nd_panel<R>, kTileLds);
+  lds((const void*)k_nd_update<R>, kTileLds);
   return e;
 }
 

@@ -85,3 +85,21 @@ def test_zero_pivot_is_reported():
         f.check()
     assert e.value.status == 2
     f.free()
+
+
+@pytest.mark.parametrize("scale", [1e42, 1e-42])
+def test_factors_that_fp32_does_not_hold_are_reported(scale):
+    """A mixed handle without refinement: the inverses are formed in FP64, and
+    an element beyond FP32's range counts as a bad pivot, not as an infinity
+    in the results.  (L scaled by 1e42 has inverses that FP32 rounds to zero
+    or, with the couplings, overflows on.)"""
+    rng = np.random.Generator(np.random.PCG64(8))
+    coef = rng.standard_normal((33, 17, 12))
+    coef[..., 0] -= 8.0
+    coef[..., 6] -= 8.0
+    prob = rr().BurgersProblem.from_coefficients(coef * scale)
+    f = rr().factor(prob, [0.7 * scale], "mixed", k_max=2, refine_tol=1.0)
+    with pytest.raises(rr().RRError) as e:
+        f.check()
+    assert e.value.status == 2
+    f.free()
