@@ -1263,8 +1263,11 @@ rr_status rr_graph_launch(rr_graph* g, void* stream) {
 namespace {
 
 // Cache of autotuner picks: a JSON object, one entry per line,
-//   "gfx950|512x256|w16|k20|mixed": {"tile": 64, "grid": 512, "superblock": 4, "ms": 812.5},
-// at the path named by RR_AUTOTUNE_CACHE (no cache when unset).
+//   "gfx950|lu2|512x256|w16|k20|mixed": {"tile": 64, "grid": 512, "superblock": 0, "ms": 62.5},
+// at the path named by RR_AUTOTUNE_CACHE (no cache when unset).  "lu2" names
+// the candidates tried (the dissection LU and the band LU): a pick from among
+// others, e.g. from a file without the name, written when the band LU was the
+// only one, is not taken.
 std::string tune_key(const rr_problem* p, int nw, int k, rr_precision prec) {
   std::string arch = "gpu";
   int dev = 0;
@@ -1276,7 +1279,7 @@ std::string tune_key(const rr_problem* p, int nw, int k, rr_precision prec) {
   } else {
     (void)hipGetLastError();
   }
-  return arch + "|" + std::to_string(p->nx) + "x" + std::to_string(p->ny) + "|w" +
+  return arch + "|lu2|" + std::to_string(p->nx) + "x" + std::to_string(p->ny) + "|w" +
          std::to_string(nw) + "|k" + std::to_string(k) + "|" + (prec == RR_MIXED ? "mixed" : "fp64");
 }
 
