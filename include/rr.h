@@ -393,9 +393,10 @@ rr_status rr_set_allocator(rr_alloc_fn alloc, rr_free_fn dealloc, void* ctx);
 
 /* Device bytes rr_factor would allocate for these sizes (with phi and U),
  * 0 for invalid sizes; tile 0 means the default LU (nested dissection), a
- * tile the band LU with that tile and 256 rows per solve step.  Past 2^40
- * unknowns the dissection's answer is SIZE_MAX.  A sweep too large for the
- * device is split into chunks of shifts sized with it. */
+ * tile the band LU with that tile and 256 rows per solve step (pass it, 64 by
+ * default, for a handle that takes the band LU: superblock != 0 or GMRES-IR).
+ * Past 2^40 unknowns the dissection's answer is SIZE_MAX.  A sweep too large
+ * for the device is split into chunks of shifts sized with it. */
 size_t rr_factor_bytes(int32_t nx, int32_t ny, int32_t n_omega, int32_t k_max, rr_precision prec,
                        int32_t tile);
 

@@ -392,8 +392,14 @@ def autotune(prob: BurgersProblem, omegas, k: int, precision: str = "fp64",
 _SWEEP_BYTES = 8 << 30
 
 
+def _lu_tile(tile, superblock):
+    """factor_bytes' tile for the LU that a handle of these options takes: 0 for
+    the dissection's, for the band LU's the tile or its default."""
+    return (tile or 64) if superblock else 0
+
+
 def _sweep_chunk(prob, om, k, seed, q, precision, tile, grid, superblock=0):
-    per = factor_bytes(prob.nx, prob.ny, 1, k, precision, tile if superblock else 0)
+    per = factor_bytes(prob.nx, prob.ny, 1, k, precision, _lu_tile(tile, superblock))
     parts = max(1, min(om.size, -(-om.size * per // _SWEEP_BYTES)))
     sB, sAV = [], []
     for part in np.array_split(om, parts):
@@ -422,8 +428,9 @@ def sweep(prob: BurgersProblem, omegas, k: int, q: int = 0, seed: int = 0,
           precision: str = "fp64", tune: Optional[dict] = None, chunk: int = 0,
           memory_fraction: float = 0.8, on_failure: str = "raise") -> dict:
     """Frequency sweep sharing one L: the shifts are processed in chunks that
-    fit in device memory (rr_factor_bytes), each chunk as one captured graph
-    (factorisation, sketch, subspace iteration, adjoint solve, SVD, eq. 9).
+    fit in device memory (rr_factor_bytes), each chunk in parts whose handles
+    take at most 8 GiB, and each part as a factorisation and one captured graph
+    (sketch, subspace iteration, adjoint solve, SVD, eq. 9).
     With on_failure="fp64", a mixed-precision chunk that reports a numerical
     failure is refactored and run again in FP64 (in sub-chunks sized for the
     FP64 factors). Returns sigma_B, sigma_AV (n_omega, k) on the GPU, the chunk
@@ -434,8 +441,8 @@ def sweep(prob: BurgersProblem, omegas, k: int, q: int = 0, seed: int = 0,
     tile = int(tune["tile"]) if tune else 0
     grid = int(tune["grid"]) if tune else 0
     sb = int(tune.get("superblock", 0)) if tune else 0
-    if chunk <= 0:  # rr_factor_bytes: tile 0 is the default LU's size, a tile the band LU's
-        chunk = _chunk_size(prob, k, precision, tile if sb else 0, memory_fraction, om.size)
+    if chunk <= 0:
+        chunk = _chunk_size(prob, k, precision, _lu_tile(tile, sb), memory_fraction, om.size)
     sB = torch.empty((om.size, k), dtype=torch.float64, device="cuda")
     sAV = torch.empty((om.size, k), dtype=torch.float64, device="cuda")
     redone = []
