@@ -374,11 +374,21 @@ rr_status rr_set_timing_events(rr_factors* f, void* factor_begin, void* factor_e
  * report is tested. */
 rr_status rr_set_jacobi_sweeps(rr_factors* f, int32_t sweeps);
 
-/* Device bytes held by the handle. */
+/* Device bytes the handle asked for.  A block left by a freed handle (below)
+ * may be up to 1/8 larger than what was asked for. */
 size_t rr_bytes(const rr_factors* f);
 
-/* Free a handle (NULL-safe). Synchronises the device first. */
+/* Free a handle (NULL-safe). Synchronises the device first.  Without a
+ * registered allocator, its blocks of 1 MiB and more are kept for later
+ * handles: at most 1/32 of the device's memory in all, and none that eight
+ * further rr_factor calls did not use; an allocation of this library that
+ * fails gives them back and is tried again.  Other allocators of the process
+ * do not see them as free until rr_release_memory. */
 void rr_factors_free(rr_factors* f);
+
+/* Give the blocks that freed handles left back to the device.  Live handles
+ * keep theirs.  May synchronise the device (hipFree does). */
+void rr_release_memory(void);
 
 /* Device allocator for the handles created after this call (process-wide):
  * alloc(bytes, stream, ctx) returns device memory or NULL, dealloc(ptr, ctx)

@@ -21,7 +21,7 @@ PRECONDS = {"jacobi": 0, "ilu0": 1}
 # every symbol include/rr.h declares (the last three are test hooks)
 EXPORTS = ("rr_burgers_coeffs", "rr_apply", "rr_factor", "rr_refactor", "rr_sketch_solve",
            "rr_adjoint_solve", "rr_solve", "rr_gains", "rr_resvd", "rr_grad", "rr_check", "rr_refine_count",
-           "rr_bytes", "rr_factors_free", "rr_set_allocator", "rr_factor_bytes", "rr_graph_capture",
+           "rr_bytes", "rr_factors_free", "rr_release_memory", "rr_set_allocator", "rr_factor_bytes", "rr_graph_capture",
            "rr_graph_launch", "rr_graph_free", "rr_autotune", "rr_last_error", "rr_philox_raw",
            "rr_sketch", "rr_factor_schedule", "rr_set_test_matrix", "rr_set_jacobi_sweeps",
            "rr_grad_noalloc", "rr_set_timing_events", "rr_precond_apply")
@@ -85,6 +85,7 @@ def lib() -> ctypes.CDLL:
         "rr_refine_count": [vp],
         "rr_bytes": [vp],
         "rr_factors_free": [vp],
+        "rr_release_memory": [],
         "rr_last_error": [],
         "rr_philox_raw": [vp, i64, ctypes.c_uint32, ctypes.c_uint32, ctypes.c_uint32,
                           ctypes.c_uint32, vp],
@@ -111,6 +112,7 @@ def lib() -> ctypes.CDLL:
     L.rr_last_error.restype = ctypes.c_char_p
     L.rr_bytes.restype = ctypes.c_size_t
     L.rr_factors_free.restype = None
+    L.rr_release_memory.restype = None
     L.rr_factor_bytes.restype = ctypes.c_size_t
     L.rr_graph_free.restype = None
     L.rr_refine_count.restype = ctypes.c_int32

@@ -363,6 +363,13 @@ def use_torch_allocator(enable: bool = True):
     _ALLOCATOR = cbs
 
 
+def release_memory():
+    """Give the device memory that freed handles left for the next ones back to
+    the device (rr_release_memory), e.g. before another library's large
+    allocation; PyTorch's allocator does not see it as free until then."""
+    lib().rr_release_memory()
+
+
 def factor_bytes(nx: int, ny: int, n_omega: int, k_max: int, precision: str = "fp64",
                  tile: int = 0) -> int:
     return int(lib().rr_factor_bytes(nx, ny, n_omega, k_max, PRECISIONS[precision], tile))

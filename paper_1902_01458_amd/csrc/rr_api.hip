@@ -62,9 +62,9 @@ void* g_alloc_ctx = nullptr;
 // x 128 spent 600 ms a sweep waiting for that once the card's cleared memory
 // was used up, against 56 ms of work.  Bounded at 1/32 of the device's memory
 // (9 GB); a block that eight further handles did not use is given back, and
-// all of a device's are when an allocation fails or the allocator changes.
-// Blocks enter idle (the device is synchronised first), so any stream may
-// take one.
+// all are when an allocation fails, the allocator changes or the program asks
+// for it (rr_release_memory).  Blocks enter idle (the device is synchronised
+// first; where that fails they are freed instead), so any stream may take one.
 class BlockPool {
  public:
   static constexpr size_t kMin = size_t(1) << 20;
@@ -161,11 +161,11 @@ rr_status dalloc(rr_factors* f, T** p, size_t bytes) {
   return RR_OK;
 }
 
-// The handle's device is idle.
-void free_all(rr_factors* f) {
+// idle: nothing on the device uses the handle's blocks any more.
+void free_all(rr_factors* f, bool idle) {
   for (const auto& b : f->blocks) {
     if (f->dealloc) f->dealloc(b.first, f->alloc_ctx);
-    else if (!pool().give(f->device, b.first, b.second)) (void)hipFree(b.first);
+    else if (!idle || !pool().give(f->device, b.first, b.second)) (void)hipFree(b.first);
   }
 }
 
@@ -861,8 +861,7 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
   *out = f;
   return RR_OK;
 fail_free:
-  (void)hipStreamSynchronize(s);
-  free_all(f);
+  free_all(f, hipStreamSynchronize(s) == hipSuccess);
   delete f;
   return st;
 }
@@ -1164,11 +1163,12 @@ void rr_factors_free(rr_factors* f) {
   int dev = f->device;
   (void)hipGetDevice(&dev);
   if (dev != f->device) (void)hipSetDevice(f->device);
-  (void)hipDeviceSynchronize();
-  free_all(f);
+  free_all(f, hipDeviceSynchronize() == hipSuccess);
   if (dev != f->device) (void)hipSetDevice(dev);
   delete f;
 }
+
+void rr_release_memory(void) { pool().trim(); }
 
 rr_status rr_set_allocator(rr_alloc_fn alloc, rr_free_fn dealloc, void* ctx) {
   if ((alloc == nullptr) != (dealloc == nullptr))

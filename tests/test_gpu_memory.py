@@ -73,3 +73,27 @@ def test_what_no_device_holds_is_out_of_memory():
     f = rr().factor(prob, [1.0], "fp64", k_max=2)
     f.check()
     f.free()
+
+
+def test_blocks_of_freed_handles_are_given_back_on_request():
+    w = W.small("rm", 128, 64, nu=1e-2)
+    prob = rr().BurgersProblem.from_workload(w)
+    rr().release_memory()
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    f = rr().factor(prob, [0.5, 1.0, 2.0, 3.0], "fp64", k_max=16)
+    f.check()
+    held = f.nbytes()
+    f.free()
+    assert before - torch.cuda.mem_get_info()[0] > held // 2 > 50 << 20  # kept for the next handle
+    live = rr().factor(prob, [0.5], "fp64", k_max=16)
+    B = torch.randn((1, 16, w.n), dtype=torch.complex128, device="cuda")
+    X = live.solve(B)
+    rr().release_memory()  # a live handle's blocks stay
+    assert torch.equal(live.solve(B), X)
+    live.check()
+    live.free()
+    rr().release_memory()
+    del B, X
+    torch.cuda.empty_cache()
+    assert before - torch.cuda.mem_get_info()[0] <= 16 << 20
