@@ -9,8 +9,9 @@
 //   * Cholesky G = R^H R and R^-1 in 32 x 32 blocks, one workgroup per shift;
 //   * k x k products (composing the two CholQR passes, R^-1 W) in 32 x 32 tiles;
 //   * tall products Y S (n x k by k x k) in 64 x 32 output tiles;
-//   * the one-sided Jacobi SVD of R^H, one workgroup per shift, 16 lanes per
-//     column pair of the round-robin order (in LDS up to k = 100);
+//   * the one-sided Jacobi SVD of R^H, one workgroup per shift, 16 lanes (from
+//     k = 361 on 64) per column pair of the round-robin order (in LDS up to k =
+//     100);
 //   * column norms for eq. (9)'s sigma_j = ||M^-1 v_j||.
 // Same steps and outputs as the narrow path (CholQR2, then the SVD of the
 // k x k factor), with one difference: a Gram matrix that is not numerically
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(256) void k_applyb(int64_t n, int k, const double2*
 
 // One-sided (Hestenes) Jacobi SVD of A = R^H (k x k) per shift, one
 // workgroup: the pairs of each round follow the round-robin order, 16 lanes a
-// pair, so that a round of up to 64 pairs runs at once.  The rotation is the
+// pair (LN), so that a round of up to 64 pairs runs at once.  The rotation is the
 // narrow path's: with gamma = a_p^H a_q and e = gamma / |gamma|, the columns
 // [a_p, conj(e) a_q] are rotated by the real Jacobi angle of [[alpha,
 // |gamma|], [|gamma|, beta]].  The columns start in descending order of their
@@ -339,8 +340,14 @@ __global__ __launch_bounds__(256) void k_applyb(int64_t n, int k, const double2*
 // contiguous) and one workgroup does everything.  At k = 100: 11.4 ms with A
 // in global scratch and a wave per pair, 5.1 ms with all of J in one
 // workgroup, 3.85 with the sums by shuffles and the columns unsorted, 2.97 ms
-// now.
+// now; at k = 102, with A in global scratch, 6.9 ms, at 128 11.2.
+//
+// In global scratch a pair takes 16 lanes up to m = 360 and a wave beyond, where
+// the columns no longer stay in the caches near the CU and the longer runs of
+// whole lines win (gains of one shift, 16 / 64 lanes: k = 300 165 / 174 ms, 360
+// 289 / 307, 372 423 / 369, 450 847 / 723, 500 1146 / 950).
 constexpr int kJacobiLds = 100;  // largest m whose A fits the CU's LDS
+constexpr int kJacobiNarrow = 360;
 constexpr int kJacobiEl = (kJacobiLds + 15) / 16;
 constexpr int kJacobiParts = (kJacobiLds + 15) / 16;
 // The place of v[c] in the descending order (stable, NaNs first), each place once
@@ -353,7 +360,17 @@ __device__ __forceinline__ int descending_rank(const double* v, int n, int c) {
   }
   return r;
 }
-template <bool LDS>
+// The sum over a pair's LN lanes, in every lane.
+template <int LN>
+__device__ __forceinline__ double pair_sum(double v) {
+  v = sum16(v);
+  if constexpr (LN == 64) {
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+  }
+  return v;
+}
+template <bool LDS, int LN>
 __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const double2* R, double2* A,
                                                   double2* Jm, double* sigma, double2* Ut,
                                                   double2* W, double* sv, int* rank,
@@ -373,14 +390,14 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
   // every part has the same norms and ranks, in scratch of its own
   svw += (int64_t)part * gridDim.x * m;
   rk += (int64_t)part * gridDim.x * m;
-  const int group = threadIdx.x >> 4, lane = threadIdx.x & 15, ngroup = blockDim.x >> 4;
+  const int group = threadIdx.x / LN, lane = threadIdx.x % LN, ngroup = blockDim.x / LN;
   for (int c = group; c < m; c += ngroup) {
     double s = 0;
-    for (int a = lane; a < k && c < k; a += 16) {
+    for (int a = lane; a < k && c < k; a += LN) {
       const double2 v = Rw[(int64_t)c * k + a];
       s += v.x * v.x + v.y * v.y;
     }
-    s = sum16(s);
+    s = pair_sum<LN>(s);
     if (lane == 0) svw[c] = c < k ? s : -1.0;  // the zero column comes last
   }
   __syncthreads();
@@ -438,12 +455,12 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
             gram(ax[u], ay[u]);
           }
         } else {
-          for (int r = lane; r < m; r += 16) gram(ap[r], aq[r]);
+          for (int r = lane; r < m; r += LN) gram(ap[r], aq[r]);
         }
-        al = sum16(al);
-        be = sum16(be);
-        gr = sum16(gr);
-        gi = sum16(gi);
+        al = pair_sum<LN>(al);
+        be = pair_sum<LN>(be);
+        gr = pair_sum<LN>(gr);
+        gi = pair_sum<LN>(gi);
         double er, ei, c, sn;
         if (jacobi_angle(al, be, gr, gi, er, ei, c, sn)) {
           auto rotate = [&](double2& x, double2& y) {
@@ -467,7 +484,7 @@ __global__ __launch_bounds__(1024) void k_jacobib(int k, int64_t sM, const doubl
               jq[j0 + lane] = jy;
             }
           } else {
-            for (int r = lane; r < m; r += 16) {
+            for (int r = lane; r < m; r += LN) {
               double2 x = ap[r], y = aq[r];
               rotate(x, y);
               ap[r] = x;
@@ -571,7 +588,7 @@ size_t gramb_partial(int64_t n, int k_max) {
 }
 // dynamic LDS of the wide kernels, set when a handle is created
 hipError_t prepare_big() {
-  return hipFuncSetAttribute((const void*)k_jacobib<true>,
+  return hipFuncSetAttribute((const void*)k_jacobib<true, 16>,
                              hipFuncAttributeMaxDynamicSharedMemorySize,
                              kJacobiLds * kJacobiLds * (int)sizeof(double2));
 }
@@ -649,8 +666,9 @@ hipError_t launch_small_svd_big(int64_t n, int n_omega, int k, const double* Z, 
                        (const double2*)ws.R, (double2*)ws.big1, (double2*)ws.big2, sigma,
                        (double2*)ws.Ut, (double2*)ws.W, sv, rank, status, ws.jacobi_sweeps);
   };
-  if (m <= kJacobiLds) jacobi(k_jacobib<true>, (size_t)m * m * sizeof(double2));
-  else jacobi(k_jacobib<false>, 0);
+  if (m <= kJacobiLds) jacobi(k_jacobib<true, 16>, (size_t)m * m * sizeof(double2));
+  else if (m <= kJacobiNarrow) jacobi(k_jacobib<false, 16>, 0);
+  else jacobi(k_jacobib<false, 64>, 0);
   sgemm(n_omega, k, sM, ws.Rinv, ws.W, ws.G, s);  // Tv = R^-1 W
   applyb(n, n_omega, k, Z, sM, ws.G, V, s);        // V = Z Tv
   if (Uqu) applyb(n, n_omega, k, Q, sM, ws.Ut, Uqu, s);
