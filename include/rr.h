@@ -238,8 +238,8 @@ rr_status rr_apply(const rr_problem* p, const double* omega_re, const double* om
  * takes private copies of coef, phi and U.  k_max bounds the sketch width of
  * later calls (workspaces are sized for it): 1 .. 32 in mixed precision,
  * 1 .. 512 in FP64, where widths above 32 (the k study of Section 3.2,
- * Fig. 7) take global-memory k x k kernels and band solves of 32 columns at
- * a time, and a Gram matrix that is not numerically positive definite is
+ * Fig. 7) take global-memory k x k kernels and solves of 32 columns at a
+ * time, and a Gram matrix that is not numerically positive definite is
  * reported as RR_ERR_BREAKDOWN instead of taking shifted CholeskyQR3.
  * rr_resvd takes the same widths.  omega_re / omega_im: host arrays
  * of n_omega doubles (omega_im may be NULL: real shifts).  On success *out is

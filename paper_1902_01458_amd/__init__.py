@@ -1,8 +1,8 @@
 """Randomized resolvent analysis on the MI355X (gfx950).
 
 The hot path of Ribeiro, Yeh & Taira, "Randomized resolvent analysis"
-(arXiv:1902.01458), Algorithm 1: a physics-weighted Gaussian sketch, one band
-LU of i*omega*I - L per frequency, forward and adjoint multi-RHS solves,
+(arXiv:1902.01458), Algorithm 1: a physics-weighted Gaussian sketch, one LU
+of i*omega*I - L per frequency, forward and adjoint multi-RHS solves,
 Cholesky-QR orthonormalisation, the reduced SVD and the recovery of gains and
 modes through eq. (9); plus mixed-precision refinement, batched frequency
 sweeps and the gradient of the leading gain.  All numerical work runs in the

@@ -18,13 +18,13 @@ REFINE_METHODS = {"plain": 0, "gmres": 1}
 SOLVERS = {"lu": 0, "bicgstab": 1, "gmres": 2}
 PRECONDS = {"jacobi": 0, "ilu0": 1}
 
-# every symbol include/rr.h declares (the last three are test hooks)
+# every symbol include/rr.h declares
 EXPORTS = ("rr_burgers_coeffs", "rr_apply", "rr_factor", "rr_refactor", "rr_sketch_solve",
            "rr_adjoint_solve", "rr_solve", "rr_gains", "rr_resvd", "rr_grad", "rr_check", "rr_refine_count",
            "rr_bytes", "rr_factors_free", "rr_release_memory", "rr_set_allocator", "rr_factor_bytes", "rr_graph_capture",
            "rr_graph_launch", "rr_graph_free", "rr_autotune", "rr_last_error", "rr_philox_raw",
            "rr_sketch", "rr_factor_schedule", "rr_set_test_matrix", "rr_set_jacobi_sweeps",
-           "rr_grad_noalloc", "rr_set_timing_events", "rr_precond_apply")
+           "rr_grad_noalloc", "rr_set_timing_events", "rr_precond_apply", "rr_nd_plan")
 
 
 class RRError(RuntimeError):

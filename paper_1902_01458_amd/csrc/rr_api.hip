@@ -182,7 +182,7 @@ uint32_t* live_word(rr_factors* f) { return f->ctrl + 22; }
 // ctrl[4 + it]: unconverged columns after correction it (mixed solves)
 constexpr int kMaxRefine = 16;
 // Sketch widths above this take the wide k x k kernels (rr_bigk.hip) and
-// band solves in groups of this many columns (FP64 only).
+// solves in groups of this many columns (FP64 only).
 constexpr int kNarrowK = 32;
 
 // Refinement probes: the columns a solve of k columns has spare (the solve
@@ -345,7 +345,7 @@ rr_status krylov_solve(rr_factors* f, int k, int adjoint, const double* Bm, int6
   return RR_OK;
 }
 
-// X = M^-1 Bm (or M^-H): one FP64 band solve, or FP32 solves with FP64
+// X = M^-1 Bm (or M^-H): one FP64 solve, or FP32 solves with FP64
 // residual refinement to `tol`.  Bm's blocks are bstride apart (0 = shared by
 // all shifts).  The mixed loop has a fixed number of launches; once every
 // column of every shift has converged the remaining ones return at once.

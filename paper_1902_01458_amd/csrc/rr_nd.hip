@@ -28,7 +28,7 @@
 // repeatable.
 //
 // Against the band LU in the natural order (half-band 2 ny): at 512 x 256 a
-// shift takes 6.9e10 real flops and 6.5e7 factor entries instead of 5.5e11 and
+// shift takes 5.8e10 real flops and 4.1e7 factor entries instead of 5.5e11 and
 // 2.7e8, and the longest chain of dependent eliminations is about 2.5e3
 // unknowns (the separators on one path of the tree) instead of 262144.
 #include <algorithm>
@@ -1210,7 +1210,7 @@ __device__ __forceinline__ void block_mul(v4<R> (&acc)[NB], const OperandBlock<R
 // A front with P <= 64, sweep up: one workgroup per front (and share of its
 // border rows, blockIdx.z).  A chain of short products: each one's operands are
 // on their way before the one ahead of it is done, and the halves' updates
-// while it runs (8 shifts, the 2048 x 1024 grid's solve 4.14 -> 4.00 ms).
+// while it runs (8 shifts, 512 x 256, a solve 4.14 -> 4.00 ms).
 // PM: the level's largest P, 16, 32 or 64 (the operands held in registers)
 template <typename R, typename IO, int NB, bool ADJ, int PM>
 __global__ __launch_bounds__(256, 2) void k_nd_up(SolveArgs<R, IO> a) {
@@ -1329,7 +1329,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_down(SolveArgs<R, IO> a) {
   const cplx<R>* z = a.z + w * a.nw + (int64_t)fr.row * k;
   cplx<R>* x = W + (int64_t)fr.row * k;
   const int* gr = a.grow + fr.bor;
-  const int nrb = P / 16, nsplit = 4 / nrb;  // nrb <= 4
+  const int nrb = P / 16, nsplit = 4 / nrb;  // nrb <= 2 (kNdDownP)
   const int rb = wave % nrb, ks = wave / nrb;
   int col[NB];
 #pragma unroll
