@@ -74,7 +74,11 @@ hipError_t launch_burgers_coeffs(int nx, int ny, const double* U, double hx, dou
 // ms with one thread per node and no strips, 0.54 ms now (2.7 GB).
 // DOTS: instead of Bm, D whose dot products with Y are taken on the way, one
 // pair of partial sums per workgroup and column: 1 <D, Y>, 2 <Y, D> and <Y, Y>.
+// Below kApplyDealt workgroups a shift the strips go out in turn: filling the
+// eighths up would start up to seven idle workgroups a shift (16 x 8 nodes, 1000
+// shifts: 191 us a call instead of 59).
 constexpr int kApplyLines = 4;
+constexpr int kApplyDealt = 64;
 template <typename OUT, int DOTS>
 __global__ __launch_bounds__(256) void k_apply(int nx, int ny, const double* __restrict__ coef,
                                                const double* __restrict__ omega, int k,
@@ -85,12 +89,15 @@ __global__ __launch_bounds__(256) void k_apply(int nx, int ny, const double* __r
                                                double2* __restrict__ partial) {
   if (skip && __hip_atomic_load(skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
   constexpr int L = kApplyLines;
-  const int chunk = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const int chunk = chunks < kApplyDealt
+                        ? blockIdx.x
+                        : (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
   if (chunk >= chunks) return;
   const int w = blockIdx.y, ld = 2 * ny, strips = (nx + L - 1) / L;
   const int64_t n = (int64_t)nx * ld;
   const int64_t item = chunk * (int64_t)256 + threadIdx.x;
   const bool live = item < (int64_t)strips * ld;
+  if (DOTS == 0 && (item & ~int64_t(63)) >= (int64_t)strips * ld) return;  // a wave without work
   const int strip = live ? (int)(item / ld) : strips - 1;
   const int r = live ? (int)(item % ld) : (int)(threadIdx.x & 1);  // unknown within a line
   const int c = r & 1, j = r >> 1, i0 = L * strip;
@@ -207,7 +214,8 @@ static hipError_t apply_run(const OpDesc& op, const double* omega, int n_omega, 
   const int64_t wgs = (int64_t)chunks * n_omega;
   const int groups = (int)std::min<int64_t>((k + 1) / 2, std::max<int64_t>(1, 2048 / wgs));
   const int group = (k + groups - 1) / groups;
-  hipLaunchKernelGGL((k_apply<OUT, DOTS>), dim3((chunks + 7) / 8 * 8, n_omega, (k + group - 1) / group),
+  const int dealt = chunks < kApplyDealt ? chunks : (chunks + 7) / 8 * 8;
+  hipLaunchKernelGGL((k_apply<OUT, DOTS>), dim3(dealt, n_omega, (k + group - 1) / group),
                      dim3(256), 0, s, op.nx, op.ny, op.coef, omega, k, group, chunks, adjoint,
                      (const double2*)X, (const double2*)Bm, bstride, Y, skip, (double2*)partial);
   return hipGetLastError();
