@@ -810,6 +810,11 @@ rr_status rr_factor(const rr_problem* p, const double* omega_re, const double* o
       upload(f->ndd.grow, f->ndp.grow.data(), pl.nd_border);
     }
     if (e == hipSuccess) e = launch_fill_u32(f->ctrl, 0u, 64, s);
+    // the preconditioner's setup writes the slots of nodes alone, its sweeps
+    // read the others as zeros
+    if (e == hipSuccess && f->pc_dinv)
+      e = launch_fill_u32((uint32_t*)f->pc_dinv, 0u,
+                          (int64_t)(pc_bytes(f->precond, p->nx, p->ny, n_omega) / 4), s);
     // the Krylov blocks start finite (their norms are taken on every cycle,
     // also the ones that skip their other work)
     if (e == hipSuccess && f->gm.V)

@@ -111,7 +111,9 @@ __global__ void k_pc_jacobi(int nn, const double* __restrict__ coef,
 }
 
 // Block ILU(0) data of a shift, stored by anti-diagonal: slot (d, j) = d ny +
-// j holds node (i, j) = (d - j, j) (slots with i outside 0 .. nx-1 hold zeros),
+// j holds node (i, j) = (d - j, j) (slots with i outside 0 .. nx-1 hold the zeros
+// that the handle's creation put there: filling them at each setup took as long
+// again as the recurrence where ny is well past nx),
 // as kIluFields arrays of slots double2 (structure of arrays), so that the
 // sweeps, whose threads take consecutive j on one anti-diagonal, read
 // consecutive words:
@@ -148,13 +150,11 @@ __global__ __launch_bounds__(kKThreads) void k_pc_ilu0(int nx, int ny,
     C2* cur = ring + (d & 1) * ny;
     const C2* prev = ring + ((d + 1) & 1) * ny;
     const int j0 = max(0, d - nx + 1), j1 = min(ny - 1, d);
-    for (int j = threadIdx.x; j < ny; j += blockDim.x) {  // unused slots: zeros
-      if (j < j0 || j > j1)
-        for (int e = 0; e < kIluFields; e++) Fw[e * ns + (int64_t)d * ny + j] = make_double2(0, 0);
-    }
     for (int j = j0 + threadIdx.x; j <= j1; j += blockDim.x) {
       const int i = d - j, p = j + ny * i;
-      const double* c = coef + 12 * (int64_t)p;
+      double c[12];  // (loaded at once, also where a border's masks drop some)
+#pragma unroll
+      for (int e = 0; e < 12; e++) c[e] = coef[12 * (int64_t)p + e];
       C2 D = node_block(c, om_r, om_i);
       if (j > 0) {  // - M_p,p-1 D_p-1^-1 M_p-1,p: diag(-c4, -c10) E diag(-c3', -c9')
         const double* cq = coef + 12 * (int64_t)(p - 1);

@@ -133,3 +133,35 @@ def test_systems_end_alike_in_every_workgroup(nx, ny, precond):
         R = B[i].T - op.shifted(L, om) @ ref[i].T
         assert (np.linalg.norm(R, axis=0) <= 1e-10 * np.linalg.norm(B[i].T, axis=0)).all()
     f.free()
+
+
+def test_the_unused_slots_are_zeros_in_reused_memory():
+    """The sweeps read the slots beside the grid as zeros, in a block that
+    another handle has used too, and after every setup."""
+    def solves():
+        w = W.small("kpz", 130, 60, nu=2e-2)
+        prob = rr().BurgersProblem.from_workload(w)
+        f = rr().factor(prob, [1.3 + 0.1j, 0.7], "fp64", k_max=2, solver="bicgstab",
+                        precond="ilu0", krylov_maxit=400)
+        B = torch.tensor(rand_block((2, 2, w.n), 31), device="cuda")
+        out = []
+        for _ in range(2):
+            out += [to_np(f.precond_apply(B)), to_np(f.precond_apply(B, adjoint=True)),
+                    to_np(f.solve(B))]
+            f.refactor()
+        f.check()
+        f.free()
+        return out
+
+    rr().release_memory()
+    ref = solves()
+    rr().release_memory()
+    w = W.small("kpz", 60, 130, nu=2e-2)  # its block is 1.08 times the other's
+    f = rr().factor(rr().BurgersProblem.from_workload(w), [1.3], "fp64", k_max=1,
+                    solver="bicgstab", precond="ilu0")
+    f.check()
+    f.free()
+    for a, b in zip(ref, solves()):
+        np.testing.assert_array_equal(a, b)
+    for a, b in zip(ref[:3], ref[3:]):
+        np.testing.assert_array_equal(a, b)
