@@ -204,7 +204,13 @@ __global__ __launch_bounds__(256) void k_gram_sum(int k, int kmax, int nchunk,
 // per step of the factorisation, which leaves the rows' scaling by the roots
 // of the pivots to the end, and none in the inverse, eight threads of a wave
 // sharing each of its elements' sums.
-__global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
+//
+// Gg: nparts partial sums of G a shift, sG elements apart from shift to shift
+// (up to kCholParts straight from k_gram, added in k_gram_sum's order: a launch
+// of 4 us less; else k_gram_sum's total, as eight sums of k = 32 already cost 3 us
+// more here).
+constexpr int kCholParts = 4;
+__global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m, int nparts, int64_t sG,
                                               const double2* __restrict__ Gg,
                                               double2* __restrict__ Rg, double2* __restrict__ Rinvg,
                                               int pass, uint32_t* __restrict__ shifted,
@@ -217,13 +223,25 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
   const int64_t at = (int64_t)w * kmax * kmax;
   double2* Rw = Rg + at;
   double2* Riw = Rinvg + at;
+  const double2* Gw = Gg + w * sG;
+  auto total = [&](int e) {
+    double2 s = Gw[e];
+#pragma unroll
+    for (int c = 1; c < kCholParts; c++)
+      if (c < nparts) {
+        const double2 v = Gw[c * k * k + e];
+        s.x += v.x;
+        s.y += v.y;
+      }
+    return s;
+  };
   bool bad = false;
   int attempt = 0;
   double shift = 0.0;
   for (;; attempt++) {
     for (int e = t; e < k * k; e += 256) {
       const int a = e / k, c = e % k;
-      double2 v = c >= a ? Gg[at + e] : make_double2(0, 0);
+      double2 v = c >= a ? total(e) : make_double2(0, 0);
       if (a == c) v.x += shift;
       G[a][c] = v;
       if (pass > 0) Ro[a][c] = Rw[e];
@@ -252,7 +270,7 @@ __global__ __launch_bounds__(256) void k_chol(int k, int kmax, int64_t m,
     // the trace from memory: every thread needs it, and the steps above have
     // overwritten the diagonal in LDS
     double tr = 0;
-    for (int j = 0; j < k; j++) tr += Gg[at + j * (k + 1)].x;
+    for (int j = 0; j < k; j++) tr += total(j * (k + 1)).x;
     shift = 11.0 * ((double)(m + 2) * k + (double)k * (k + 1)) * 0x1p-53 * tr;
   }
   if (pass == 0 && t == 0) shifted[w] = attempt;
@@ -385,11 +403,14 @@ static void chol_passes(int n, int n_omega, int k, double* Y, bool explicit_q, S
     else if (k <= 16) gram(std::integral_constant<int, 2>{});
     else if (k <= 24) gram(std::integral_constant<int, 3>{});
     else gram(std::integral_constant<int, 4>{});
-    hipLaunchKernelGGL(k_gram_sum, dim3((k * k + 15) / 16, n_omega), dim3(256), 0, s, k, ws.kmax,
-                       nc, (const double2*)part, (double2*)ws.G, only);
+    const bool direct = nc <= kCholParts;
+    if (!direct)
+      hipLaunchKernelGGL(k_gram_sum, dim3((k * k + 15) / 16, n_omega), dim3(256), 0, s, k, ws.kmax,
+                         nc, (const double2*)part, (double2*)ws.G, only);
     hipLaunchKernelGGL(k_chol, dim3(n_omega), dim3(256), 0, s, k, ws.kmax, (int64_t)n,
-                       (const double2*)ws.G, (double2*)ws.R, (double2*)ws.Rinv, pass, ws.shifted,
-                       status);
+                       direct ? nc : 1, (int64_t)(direct ? nc * k * k : ws.kmax * ws.kmax),
+                       (const double2*)(direct ? ws.partial : ws.G), (double2*)ws.R,
+                       (double2*)ws.Rinv, pass, ws.shifted, status);
     if (pass == 0 && explicit_q) {
       hipLaunchKernelGGL(k_apply_small, dim3((n + 255) / 256, n_omega), dim3(256), 0, s,
                          (int64_t)n, k, (const double2*)Y, (const double2*)ws.Rinv, ws.kmax,

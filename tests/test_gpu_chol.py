@@ -68,3 +68,23 @@ def test_basis_of_a_scaled_operator(k, power):
         assert np.linalg.norm(Q.conj().T @ Q - np.eye(k), 2) <= 1e-12
         got.append(Q)
     assert np.linalg.norm(got[1] - got[0], 2) <= 1e-12
+
+
+@pytest.mark.parametrize("nx,ny", [(16, 8), (43, 6), (32, 16), (33, 16)])
+@pytest.mark.parametrize("k", [3, 32])
+def test_basis_from_few_partial_sums(nx, ny, k):
+    """One, three, four and five partial sums of the Gram matrix: up to four the
+    Cholesky adds them itself.  CholQR2 against numpy's QR: u cond(Y), cond(Y)
+    <= 1e2, 1e-12; k_max above k, and three shifts, so that strides count."""
+    w = W.small("o", nx, ny, nu=5e-2)
+    prob = rr().BurgersProblem.from_workload(w)
+    f = rr().factor(prob, [0.7, 2.0, 1.1], "fp64", k_max=32)
+    Q = to_np(f.sketch_solve(k, 3, 0))
+    Y = to_np(f.solve(rr().sketch(prob, k, 3).expand(3, -1, -1).contiguous()))
+    f.check()
+    f.free()
+    for i in range(3):
+        assert np.linalg.cond(Y[i]) < 1e2
+        q, r = np.linalg.qr(Y[i].T)
+        q = q * (np.diag(r) / np.abs(np.diag(r)))
+        assert np.linalg.norm(Q[i].T - q, 2) <= 1e-12
