@@ -155,8 +155,7 @@ typedef struct {
                             FP32 solves and holds gmres_restart + 2 more
                             blocks of n_omega*k_max*n complex FP64 (not
                             counted by rr_factor_bytes).  The FP32 LU is then
-                            the band LU: as a preconditioner at such shifts it
-                            has to be backward stable                          */
+                            the band LU                                        */
   int32_t gmres_restart; /* steps per GMRES-IR correction, 1 .. 16 (default 8) */
   int32_t superblock;    /* 0 = the LU in nested-dissection order (for a
                             GMRES-IR handle the band LU with 256 rows per

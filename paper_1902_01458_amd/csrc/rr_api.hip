@@ -476,10 +476,11 @@ int superblock_tiles(int want, int T, int B) {
 // Which LU a handle takes: the nested-dissection one, unless the caller asks
 // for a superblock (or, < 0, the tile-by-tile solve), which only the band LU
 // has, or for GMRES-IR.  GMRES-IR serves shifts with kappa(M) eps_32 >> 1,
-// where the FP32 factors are only a preconditioner: there the fronts' explicit
-// inverses are too far from a backward stable LU (at 1e-7 |lambda| from an
-// eigenvalue of a 32 x 16 operator it left 7 of 8 columns unconverged after
-// six corrections; with the band LU two suffice).
+// where the FP32 factors are only a preconditioner.  With tile inverses formed in
+// FP32 the dissection left 7 of 8 columns unconverged after six corrections at
+// 1e-7 |lambda| from an eigenvalue of a 32 x 16 operator, where two suffice with
+// the band LU.  With the FP64 ones of now the tested cases converge on either;
+// the band stays until the dissection has been measured beside it over the range.
 bool use_nd(bool krylov, bool gmres_ir, int superblock) {
   return !krylov && !gmres_ir && superblock == 0;
 }
