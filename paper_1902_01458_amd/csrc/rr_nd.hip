@@ -108,24 +108,34 @@ __device__ __forceinline__ void add(cplx<R>& a, cplx<R> b) {
 // that wave's row).  A zero or non-finite pivot latches ST_SINGULAR and is
 // replaced by 1.
 //
-// In FP64 for FP32 factors too: without pivoting the inverse of a front's block
-// grows now and then, and the FP32 one then loses the digits that refinement
-// next to an eigenvalue of L needs.  Over 80 grids at 1e-5 |lambda| (emulated), 30
-// solves missed 1e-10 within six corrections with FP32 inverses, 14 of them
-// solves that the band LU finishes; 15 and 4 with FP64 ones (or pivoted ones: it
-// is the growth).  The band LU misses 28.  The price is the tile's 75 KB of LDS,
-// two workgroups a CU instead of four: 512 x 256, 16 shifts, FP32, k_nd_leaf
-// 1.69 -> 3.96 ms, the factor 18.7 -> 23.2 ms.
+// In FP64 for FP32 factors too where P <= 64: without pivoting the inverse of a
+// leaf's or a small front's block grows now and then, and the FP32 one then loses
+// the digits that refinement next to an eigenvalue of L needs.  Over 80 grids at
+// 1e-5 |lambda| (emulated), 30 solves missed 1e-10 within six corrections with
+// FP32 inverses, 14 of them solves that the band LU finishes; 15 and 4 with FP64
+// ones (or pivoted ones: it is the growth).  The band LU misses 28.  The pivot
+// tiles of larger fronts are inverted in the factor's type: over 48 grids up to
+// 80 x 70 FP64 ones there made no difference (5 misses, 4 without).  The price is
+// the FP64 tile's 75 KB of LDS, two workgroups a CU instead of four: 512 x 256, 16
+// shifts, FP32, k_nd_leaf 1.69 -> 3.96 ms.
 // ---------------------------------------------------------------------------
+template <int S>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + S, 0xf, 0xf, true));
+}
 template <int S>
 __device__ __forceinline__ double row_bcast(double v) {
   const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + S, 0xf, 0xf, true);
   const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + S, 0xf, 0xf, true);
   return __hiloint2double(hi, lo);
 }
-template <int S>
-__device__ __forceinline__ zc row_bcast(zc v) {
-  return zc{row_bcast<S>(v.re), row_bcast<S>(v.im)};
+template <int S, typename R>
+__device__ __forceinline__ cplx<R> row_bcast(cplx<R> v) {
+  return cplx<R>{row_bcast<S>(v.re), row_bcast<S>(v.im)};
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 __device__ __forceinline__ double lane_value(double v, int lane) {
   return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
@@ -136,38 +146,39 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 __device__ __forceinline__ double recip(double x) {
   return x > 1e-290 && x < 1e290 ? recip_newton(x) : 1.0 / x;
 }
+__device__ __forceinline__ float recip(float x) { return 1.0f / x; }
 
-template <int S>
+template <typename R, int S>
 struct Inv16 {
-  static __device__ __forceinline__ void run(zc (&a)[4], bool& bad) {
+  static __device__ __forceinline__ void run(cplx<R> (&a)[4], bool& bad) {
     if constexpr (S < 16) {
       constexpr int G = S >> 2, C = S & 3;
       const int l = threadIdx.x & 63, i = l & 15, g = l >> 4;
       const int src = 16 * G + i;
-      const zc f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
-      zc d{lane_value(a[C].re, 16 * G + S), lane_value(a[C].im, 16 * G + S)};
-      const double mag = d.re * d.re + d.im * d.im;
-      double rm = recip(mag);
-      if (!(mag > 0.0) || !isfinite(mag)) {
+      const cplx<R> f{__shfl(a[C].re, src), __shfl(a[C].im, src)};  // a(i, S)
+      cplx<R> d{lane_value(a[C].re, 16 * G + S), lane_value(a[C].im, 16 * G + S)};
+      const R mag = d.re * d.re + d.im * d.im;
+      R rm = recip(mag);
+      if (!(mag > (R)0) || !isfinite(mag)) {
         bad = true;
-        d = zc{1.0, 0.0};
-        rm = 1.0;
+        d = cplx<R>{(R)1, (R)0};
+        rm = (R)1;
       }
-      const zc inv{d.re * rm, -d.im * rm};
-      zc m = cmul(f, inv);
+      const cplx<R> inv{d.re * rm, -d.im * rm};
+      cplx<R> m = cmul(f, inv);
       const bool piv = i == S;
-      if (piv) m = zc{-inv.re, -inv.im};
+      if (piv) m = cplx<R>{-inv.re, -inv.im};
 #pragma unroll
       for (int c = 0; c < 4; c++) {
-        const zc v = row_bcast<S>(a[c]);
-        zc b = a[c];
-        if (piv) b = zc{0.0, 0.0};
+        const cplx<R> v = row_bcast<S>(a[c]);
+        cplx<R> b = a[c];
+        if (piv) b = cplx<R>{(R)0, (R)0};
         b.re -= m.re * v.re - m.im * v.im;
         b.im -= m.re * v.im + m.im * v.re;
         a[c] = b;
       }
-      if (g == G) a[C] = zc{-m.re, -m.im};
-      Inv16<S + 1>::run(a, bad);
+      if (g == G) a[C] = cplx<R>{-m.re, -m.im};
+      Inv16<R, S + 1>::run(a, bad);
     }
   }
 };
@@ -177,41 +188,42 @@ constexpr int kPvSize = 2 * 16 * kPv;  // two of them, by pivot parity
 
 // (inlined: as a function it would take its LDS operands through generic
 // pointers, i.e. flat instead of LDS instructions)
-__device__ __forceinline__ void invert_tile(zc* F, int ld, int T, zc* pvs, uint32_t* status) {
+template <typename R>
+__device__ __forceinline__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* pvs, uint32_t* status) {
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, i = l & 15, g = l >> 4;
   const int nb = T >> 4;
   // invert pivot block kb from LDS into its pv
   auto pivot = [&](int kb) __attribute__((always_inline)) {
-    zc a[4];
+    cplx<R> a[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) a[c] = F[(16 * kb + 4 * g + c) * ld + 16 * kb + i];
     bool bad = false;
-    Inv16<0>::run(a, bad);
+    Inv16<R, 0>::run(a, bad);
     if (bad && l == 0) latch(status, ST_SINGULAR);
 #pragma unroll
     for (int c = 0; c < 4; c++) pvs[(kb & 1) * 16 * kPv + i * kPv + 4 * g + c] = a[c];
   };
-  auto put = [&](int rb, int j, const CAcc<double>& acc) {
+  auto put = [&](int rb, int j, const CAcc<R>& acc) {
 #pragma unroll
     for (int e = 0; e < 4; e++)
-      F[(16 * j + i) * ld + 16 * rb + Mf<double>::row(l, e)] = zc{acc.re[e], acc.im[e]};
+      F[(16 * j + i) * ld + 16 * rb + Mf<R>::row(l, e)] = cplx<R>{acc.re[e], acc.im[e]};
   };
   // (one place calls pivot: a second would make it a function, its operands in
   // scratch memory)
   for (int kb = -1;; kb++) {
-    const zc* pv = pvs + (kb & 1) * 16 * kPv;
+    const cplx<R>* pv = pvs + (kb & 1) * 16 * kPv;
     const int nx = kb + 1;
-    CAcc<double> held;
+    CAcc<R> held;
     int rb = wave;
     bool rows = false;
     if (kb >= 0) {
       if (wave != kb && wave < nb) {  // block row kb: R_j = pv F(kb, j), j = wave
-        CAcc<double> acc;
+        CAcc<R> acc;
         zero(acc);
-        const zc* col = F + (16 * wave + i) * ld + 16 * kb;
+        const cplx<R>* col = F + (16 * wave + i) * ld + 16 * kb;
 #pragma unroll
         for (int s = 0; s < 4; s++)
-          cmfma<double, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
+          cmfma<R, false, false>(acc.re, acc.im, pv[i * kPv + 4 * s + g], col[4 * s + g]);
         put(kb, wave, acc);
       }
       __syncthreads();
@@ -220,29 +232,29 @@ __device__ __forceinline__ void invert_tile(zc* F, int ld, int T, zc* pvs, uint3
       if (wave == kb) rb = nx;         // (nx < nb) the next pivot's row, for its wave
       rows = wave < nb && rb < nb && (wave == kb || wave != nx);
       if (wave < nb && (rows || wave == nx)) {
-        zc cf[4];
+        cplx<R> cf[4];
 #pragma unroll
         for (int s = 0; s < 4; s++) cf[s] = F[(16 * kb + 4 * s + g) * ld + 16 * rb + i];
         for (int j = 0; j < nb; j++) {
           if (j == kb || (wave == nx ? j != nx : (rb == nx && j == nx))) continue;
-          CAcc<double> acc;
-          const zc* col = F + (16 * j + i) * ld;
+          CAcc<R> acc;
+          const cplx<R>* col = F + (16 * j + i) * ld;
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            const zc v = col[16 * rb + Mf<double>::row(l, e)];
+            const cplx<R> v = col[16 * rb + Mf<R>::row(l, e)];
             acc.re[e] = v.re;
             acc.im[e] = v.im;
           }
 #pragma unroll
           for (int s = 0; s < 4; s++)
-            cmfma<double, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
+            cmfma<R, false, true>(acc.re, acc.im, cf[s], col[16 * kb + 4 * s + g]);
           put(rb, j, acc);
         }
         if (rows) {
           zero(held);
 #pragma unroll
           for (int s = 0; s < 4; s++)
-            cmfma<double, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
+            cmfma<R, false, true>(held.re, held.im, cf[s], pv[(4 * s + g) * kPv + i]);
         }
       }
     }
@@ -289,7 +301,10 @@ struct FactorArgs {
 };
 
 constexpr int kLd = kNdTile + 1;  // pitch of a tile in LDS
-constexpr size_t kTileLds = (size_t)(kNdTile * kLd + kPvSize) * sizeof(zc);
+template <typename R>
+constexpr size_t tile_lds() {
+  return (size_t)(kNdTile * kLd + kPvSize) * sizeof(cplx<R>);
+}
 // A P x P tile with its pivot inverses; k_nd_front (R: the factor's type) keeps
 // 4 x 16 rows of P + 1 for F21 in the tile's place.
 template <typename R>
@@ -355,7 +370,7 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
     }
   }
   __syncthreads();
-  invert_tile(F, ld, P, pv, g.status);
+  invert_tile<double>(F, ld, P, pv, g.status);
   cplx<R>* A = g.factor + w * g.nfactor + fr.a;
   bool bad = false;
   for (int e = threadIdx.x; e < P * P; e += 256) {
@@ -372,19 +387,16 @@ __global__ __launch_bounds__(256, 2) void k_nd_leaf(FactorArgs<R> g) {
   }
 }
 
-// A T x T tile in LDS (T <= TM) from one type to the other in the same place:
-// every thread holds its elements over a barrier.
-template <int TM, typename TO, typename FROM>
-__device__ __forceinline__ void tile_convert(const cplx<FROM>* from, cplx<TO>* to, int ld, int T,
-                                             bool& bad) {
+// A T x T tile in LDS (T <= TM) to the factor's type in the same place: every
+// thread holds its elements over a barrier.
+template <int TM, typename R>
+__device__ __forceinline__ void tile_narrow(const zc* from, cplx<R>* to, int ld, int T, bool& bad) {
   constexpr int N = (TM * TM + 255) / 256;
-  cplx<TO> v[N];
+  cplx<R> v[N];
 #pragma unroll
   for (int u = 0; u < N; u++) {
     const int e = threadIdx.x + 256 * u, c = e / T, r = e - c * T;
-    if (e >= T * T) continue;
-    const cplx<FROM> x = from[c * ld + r];
-    v[u] = kept<TO>(zc{x.re, x.im}, bad);
+    if (e < T * T) v[u] = kept<R>(from[c * ld + r], bad);
   }
   __syncthreads();
 #pragma unroll
@@ -456,9 +468,9 @@ __global__ __launch_bounds__(256, PM <= 16 ? 4 : PM <= 32 ? 3 : 2) void k_nd_fro
     }
   }
   __syncthreads();
-  invert_tile(D, ld, P, pv, g.status);
+  invert_tile<double>(D, ld, P, pv, g.status);
   bool bad = false;
-  if constexpr (sizeof(R) < sizeof(double)) tile_convert<PM>(D, F, ld, P, bad);
+  if constexpr (sizeof(R) < sizeof(double)) tile_narrow<PM>(D, F, ld, P, bad);
   if (bad) latch(g.status, ST_SINGULAR);
   if (blockIdx.z == 0)
     for (int e = threadIdx.x; e < P * P; e += 256) {
@@ -689,24 +701,19 @@ __device__ __forceinline__ int64_t t_piv(const NdFront& f, int k, int rowmajor) 
 }
 __device__ __forceinline__ int tile_width(int P, int k) { return min(kNdTile, P - kNdTile * k); }
 
-// Invert the T x T tile in LDS and write it as pivot inverse k (pv: behind a
-// tile of zc).
+// Invert the T x T tile in LDS and write it as pivot inverse k.
 template <typename R>
-__device__ __forceinline__ void pivot_out(cplx<R>* F, zc* pv, int T, const NdFront& fr, int k,
-                                          cplx<R>* temp, uint32_t* status) {
-  zc* D = reinterpret_cast<zc*>(F);
+__device__ __forceinline__ void pivot_out(cplx<R>* F, cplx<R>* pv, int T, const NdFront& fr, int k,
+                          cplx<R>* temp, uint32_t* status) {
   __syncthreads();
-  bool bad = false;
-  if constexpr (sizeof(R) < sizeof(double)) tile_convert<kNdTile>(F, D, kLd, T, bad);
-  invert_tile(D, kLd, T, pv, status);
+  invert_tile<R>(F, kLd, T, pv, status);
   cplx<R>* pc = temp + t_piv(fr, k, 0);
   cplx<R>* pr = temp + t_piv(fr, k, 1);
   for (int e = threadIdx.x; e < T * T; e += 256) {
     const int c = e / T, r = e - c * T;
-    pc[c * kNdTile + r] = kept<R>(D[c * kLd + r], bad);
-    pr[c * kNdTile + r] = narrow<R>(D[r * kLd + c]);
+    pc[c * kNdTile + r] = F[c * kLd + r];
+    pr[c * kNdTile + r] = F[r * kLd + c];
   }
-  if (bad) latch(status, ST_SINGULAR);
 }
 
 // A 64 x 64 tile of F11 (kind 0, into A), F12 (1, into T12) or F21 (2).
@@ -715,7 +722,7 @@ template <typename R>
 __global__ __launch_bounds__(256, 2) void k_nd_assemble(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
   cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
-  zc* pv = reinterpret_cast<zc*>(smem_raw) + kNdTile * kLd;
+  cplx<R>* pv = F + kNdTile * kLd;
   const int w = g.w0 + blockIdx.y;
   const NdTask t = g.tasks[xcd_task()];
   const NdFront fr = g.fronts[t.front];
@@ -862,7 +869,7 @@ template <typename R>
 __global__ __launch_bounds__(256, 2) void k_nd_update(FactorArgs<R> g) {
   extern __shared__ __align__(16) char smem_raw[];
   cplx<R>* F = reinterpret_cast<cplx<R>*>(smem_raw);
-  zc* pv = reinterpret_cast<zc*>(smem_raw) + kNdTile * kLd;
+  cplx<R>* pv = F + kNdTile * kLd;
   const int w = g.w0 + blockIdx.y;
   const NdTask t = g.tasks[xcd_task()];
   const NdFront fr = g.fronts[t.front];
@@ -1488,7 +1495,7 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
   a.nfactor = pl.factor;
   a.ntemp = pl.temp;
   a.status = status;
-  const size_t lds = kTileLds;
+  const size_t lds = tile_lds<R>();
   for (int w0 = 0; w0 < n_omega; w0 += kMaxY) {
     const unsigned nw = (unsigned)std::min(kMaxY, n_omega - w0);
     a.w0 = w0;
@@ -1606,11 +1613,11 @@ hipError_t prepare_r() {
     if (e == hipSuccess && bytes > 64 * 1024)
       e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   };
-  lds((const void*)k_nd_leaf<R>, kTileLds);
-  lds((const void*)k_nd_front<R, 64>, kTileLds);
-  lds((const void*)k_nd_assemble<R>, kTileLds);
-  lds((const void*)k_nd_panel<R>, kTileLds);
-  lds((const void*)k_nd_update<R>, kTileLds);
+  lds((const void*)k_nd_leaf<R>, tile_lds<double>());
+  lds((const void*)k_nd_front<R, 64>, tile_lds<double>());
+  lds((const void*)k_nd_assemble<R>, tile_lds<R>());
+  lds((const void*)k_nd_panel<R>, tile_lds<R>());
+  lds((const void*)k_nd_update<R>, tile_lds<R>());
   return e;
 }
 
