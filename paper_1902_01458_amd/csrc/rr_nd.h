@@ -38,13 +38,20 @@ constexpr int kNdTile = 64;       // product tile edge, and the widest one-launc
 // walking all of it (P = 64, Q = 376: 48 / 79 us forward / adjoint a level for
 // one shift against 20 / 28; level by level about equal for 16).
 constexpr int kNdDownP = 32;
+// From kNdLeafApart narrow leaves (all shifts') on, the factor launches leaves up
+// to kNdLeafP apart from the wider ones, whose FP64 tile takes 75 KB of LDS:
+// three workgroups a CU then, not two.  At 512 x 256 4001 of 4096 leaves have 48
+// rows; 16 shifts, the factor 31.9 -> 30.8 ms FP64, 21.6 -> 20.4 FP32; with 977
+// (256 x 128, one shift) the second launch costs 20 us more than it gives.
+constexpr int kNdLeafP = 48, kNdLeafApart = 3072;
 constexpr int kNdLeafNodes = 32;  // blocks of at most this many nodes are leaves
 
 struct NdTask { int front, i, j, kind; };
 struct NdSpan { int first = 0, count = 0; };  // a range of the task list
 
 struct NdLevel {  // fronts at one depth of the tree
-  NdSpan leaf;       // one task a leaf
+  NdSpan leaf;       // one task a leaf, those of P <= kNdLeafP first:
+  NdSpan leafs[2];   // the two widths apart, for the factor
   NdSpan small;      // one task a front with halves, P <= kNdTile
   NdSpan assemble;   // P > kNdTile: tiles of A, T12 and F21
   std::vector<NdSpan> panel, update;  // per pivot tile

@@ -1510,7 +1510,12 @@ hipError_t factor_run(const OpDesc& op, const NdPlan& pl, const NdDevice& d, con
       a.schur_in = (cplx<R>*)d.schur[~dep & 1];
       a.nout = pl.schur[dep & 1];
       a.nin = pl.schur[~dep & 1];
-      run(k_nd_leaf<R>, lv.leaf, leaf_lds(lv.leafP));
+      if ((int64_t)lv.leafs[0].count * nw >= kNdLeafApart) {
+        run(k_nd_leaf<R>, lv.leafs[0], leaf_lds(kNdLeafP));
+        run(k_nd_leaf<R>, lv.leafs[1], leaf_lds(lv.leafP));
+      } else {
+        run(k_nd_leaf<R>, lv.leaf, leaf_lds(lv.leafP));
+      }
       const size_t fl = front_lds<R>(lv.maxP);
       if (lv.maxP <= 16) run(k_nd_front<R, 16>, lv.small, fl, shares(lv, nw));
       else if (lv.maxP <= 32) run(k_nd_front<R, 32>, lv.small, fl, shares(lv, nw));

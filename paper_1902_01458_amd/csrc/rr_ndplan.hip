@@ -252,11 +252,15 @@ void nd_make_plan(int nx, int ny, NdPlan* plan) {
     const int f0 = first[d], f1 = first[d + 1];
     lv.front = f0;
     open(lv.leaf);
-    for (int f = f0; f < f1; f++)
-      if (pl.fronts[f].childA < 0) {
-        pl.tasks.push_back({f, 0, 0, 0});
-        lv.leafP = std::max(lv.leafP, pl.fronts[f].P);
-      }
+    for (int wide = 0; wide < 2; wide++) {
+      open(lv.leafs[wide]);
+      for (int f = f0; f < f1; f++)
+        if (pl.fronts[f].childA < 0 && (pl.fronts[f].P > kNdLeafP) == (wide == 1)) {
+          pl.tasks.push_back({f, 0, 0, 0});
+          lv.leafP = std::max(lv.leafP, pl.fronts[f].P);
+        }
+      close(lv.leafs[wide]);
+    }
     close(lv.leaf);
     // calls emit(front) for the fronts of one kind, collecting a span
     auto each = [&](NdSpan& sp, bool small, bool large, auto emit) {

@@ -103,3 +103,25 @@ def test_factors_that_fp32_does_not_hold_are_reported(scale):
         f.check()
     assert e.value.status == 2
     f.free()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+def test_many_shifts_take_the_leaves_by_width(prec):
+    """160 shifts of 20 narrow and 12 wide leaves run them in two launches: the same
+    bits as the same shifts a few at a time, which do not."""
+    w = W.small("nd", 37, 29, nu=1e-2)
+    prob = rr().BurgersProblem.from_workload(w)
+    oms = [0.3 + 0.05 * i for i in range(160)]
+    g = torch.Generator(device="cuda").manual_seed(4)
+    B = torch.randn((len(oms), 3, w.n), dtype=torch.complex128, device="cuda", generator=g)
+    f = rr().factor(prob, oms, prec, k_max=3, refine_tol=1.0)
+    X, Z = to_np(f.solve(B)), to_np(f.adjoint_solve(B))
+    f.check()
+    f.free()
+    for i0 in (0, 77, 155):
+        f = rr().factor(prob, oms[i0:i0 + 5], prec, k_max=3, refine_tol=1.0)
+        part = B[i0:i0 + 5].contiguous()
+        np.testing.assert_array_equal(to_np(f.solve(part)), X[i0:i0 + 5])
+        np.testing.assert_array_equal(to_np(f.adjoint_solve(part)), Z[i0:i0 + 5])
+        f.check()
+        f.free()
