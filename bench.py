@@ -263,7 +263,8 @@ def nd_work(nx, ny):
 
 
 def traffic(kernel):
-    """HBM bytes per launch of `kernel` from the calibrated FETCH_SIZE / WRITE_SIZE
+    """HBM bytes per launch of `kernel` (of the dissection: of all launches of an
+    nd_factor or nd_solve) from the calibrated FETCH_SIZE / WRITE_SIZE
     counters recorded in profiles/pmc_traffic.json, or None when none were taken
     or the kernel sources changed since (the file keeps their SHA-256)."""
     import hashlib
@@ -395,7 +396,8 @@ def main():
         kname = (f"k_nd_*<{name}>" if sb == 0 else
                  f"k_solve2<{name},{T},16,false>" if sb < 0 else f"k_ssolve<{name},{T},{np_},false,{str(short).lower()},{str(tail).lower()}>")
         return {"bound": "hbm", "achieved": bw, "peak": 8000.0, "unit": "GB/s",
-                "frac": bw / 8000.0, "bytes_per_launch": byt, "traffic": traffic(kname),
+                "frac": bw / 8000.0, "bytes_per_launch": byt,
+                "traffic": traffic(f"nd_solve<{name}>" if sb == 0 else kname),
                 "kernel": f"{kname} (forward solve of the eq. 9 recovery, all {n_om} shifts x "
                           f"{w.k} columns)",
                 "launch_ms": res["solve_ms"]}
@@ -417,7 +419,8 @@ def main():
         "optional_svd_ms": mixed["optional_svd_ms"],
         "graph_ms_per_step": mixed.get("graph_ms_per_step"),
         "roofline": {"bound": "mfma", "achieved": ach, "peak": PEAK["mixed"], "unit": "TFLOP/s",
-                     "frac": ach / PEAK["mixed"], "traffic": traffic(fk),
+                     "frac": ach / PEAK["mixed"],
+                     "traffic": traffic(fk if band else "nd_factor<float>"),
                      "kernel": f"{fk} ({lu} of all {n_om} shifts)",
                      "launch_ms": mixed["factor_ms"]},
         "roofline_solve_fp32": solve_roofline(mixed, 8, "float"),

@@ -117,7 +117,7 @@ __device__ __forceinline__ void add(cplx<R>& a, cplx<R> b) {
 // tiles of larger fronts are inverted in the factor's type: over 48 grids up to
 // 80 x 70 FP64 ones there made no difference (5 misses, 4 without).  The price is
 // the FP64 tile's 75 KB of LDS, two workgroups a CU instead of four: 512 x 256, 16
-// shifts, FP32, k_nd_leaf 1.69 -> 3.96 ms.
+// shifts, FP32, k_nd_leaf 1.69 -> 3.96 ms, 2.87 with narrow leaves apart.
 // ---------------------------------------------------------------------------
 template <int S>
 __device__ __forceinline__ float row_bcast(float v) {
@@ -275,7 +275,7 @@ __device__ __forceinline__ void invert_tile(cplx<R>* F, int ld, int T, cplx<R>* 
 // The task of a workgroup: workgroups are dealt to the eight XCDs in turn, so
 // every eighth one takes consecutive tasks.  A front's tiles then share one L2,
 // which reads their common operands once: 512 x 256, 16 shifts, FP64, k_nd_schur
-// 55 -> 28 GB read, the factor 32.5 -> 32.0 ms; one FP32 shift 3.04 -> 2.88 ms.
+// 42 -> 21 GB read, the factor 32.5 -> 32.0 ms; one FP32 shift 3.04 -> 2.88 ms.
 __device__ __forceinline__ int xcd_task() {
   const int n = gridDim.x, c = blockIdx.x & 7;
   return c * (n >> 3) + min(c, n & 7) + (blockIdx.x >> 3);
